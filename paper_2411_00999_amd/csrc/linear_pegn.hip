@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/lnpegn.h"
 #include "lnpegn_device.h"
 
@@ -33,10 +35,6 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 // c ^ 4*(r & 3); a direct-to-LDS load writes a wave's 64 chunks contiguously, so the swizzle is applied
 // by choosing which chunk of memory each lane fetches.
 constexpr int kBufs = 3, kMaxSplit = 64;
-#define LIN_STR2(x) #x
-#define LIN_STR(x) LIN_STR2(x)
-#define LIN_XROW 512   // bytes per LDS row of x and of g, as literals for the assembly below
-#define LIN_GROW 256
 
 // kElem: bytes per element (2: bf16, 4: fp32).  A stage is 64 positions of bf16 or 32 of fp32: the same
 // 48 KiB either way.
@@ -48,18 +46,15 @@ struct LinCfg {
     static constexpr int kXRow = kTileK * kElem, kGRow = kTileL * kElem;  // bytes per LDS row
     static constexpr int kXBytes = kStageT * kXRow, kGBytes = kStageT * kGRow;
     static constexpr int kStageBytes = kXBytes + kGBytes;
-    static constexpr int kXLoads = kXBytes / 1024, kLoads = kStageBytes / 1024;   // direct loads of 1 KiB
-    static constexpr int kLoadsPerWave = kLoads / kWaves;
-    static_assert(kLoads % kWaves == 0, "loads must divide evenly over the waves");
+    static constexpr int kXLoadsPerWave = kXBytes / 1024 / kWaves, kGLoadsPerWave = kGBytes / 1024 / kWaves;   // loads of 1 KiB
+    static_assert(kXBytes % (1024 * kWaves) == 0 && kGBytes % (1024 * kWaves) == 0, "loads must divide evenly over the waves");
     static_assert(kXRow >= 256 && kGRow >= 256 && kXRow <= 1024 && kGRow <= 1024, "row of 16..64 chunks");
     static_assert(kBufs * kStageBytes <= 160 * 1024, "three stages must fit in LDS");
 };
 // 8 waves (two per SIMD, so one can issue MFMAs while the other waits for LDS), each 64 x 64: 256 x 128
 // per workgroup.  Measured against 4 waves of 128 x 64 (one per SIMD, fewer LDS reads per MFMA): the
 // lone wave cannot cover its own LDS latency and is 30 % slower.
-#define LIN_CFG 4, 2, 2, 2
-typedef LinCfg<LIN_CFG, 2> Cfg;          // tile shape and wave count are the same for both element types
-typedef LinCfg<LIN_CFG, 4> CfgF32;
+typedef LinCfg<4, 2, 2, 2, 2> Cfg;       // tile shape and wave count are the same for both element types
 
 struct LinArgs {
     const char *x;          // [B,T,K] bf16 or fp32
@@ -91,15 +86,66 @@ __device__ __forceinline__ void load_to_lds(uint32_t lds_addr, uint32_t voff, co
                  : "memory");
 }
 
-template <typename C, int WM, int WN, int MI, int NI, int kElem>
+// The same for lanes that each have an address of their own.
+__device__ __forceinline__ void load_to_lds_lane(uint32_t lds_addr, const void *lane_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"(lds_addr), "v"(lane_addr)
+                 : "memory");
+}
+
+// The same as an instruction that the compiler counts, for kernels that load into registers besides: it waits for
+// those by the number of loads behind them that it knows of, and with the direct loads hidden from it waits for
+// most of them too.  (A buffer load: the global form it takes for one that completes out of order.)  A lane without
+// data asks for an offset outside the buffer, and zeros are written.
+constexpr int kTrackedBytes = 0x7ffffff0, kTrackedNone = INT32_MIN;
+__device__ __forceinline__ void load_to_lds_tracked(uint32_t lds_addr, int voff, const void *base)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base, kTrackedBytes),
+                                             (__attribute__((address_space(3))) void *)(uintptr_t)lds_addr, 16, voff, 0, 0, 0);
+}
+
+// What a lane reads whose chunk lies outside the matrix or behind the end of an example.
+__device__ __constant__ uint32_t kZeroChunk[4] __attribute__((aligned(16))) = {0u, 0u, 0u, 0u};
+
+// Sixteen bytes from an address that is only aligned to an element.
+typedef u32x4_t u32x4_at2_t __attribute__((aligned(2)));
+typedef u32x4_t u32x4_at4_t __attribute__((aligned(4)));
+template <int kElem>
+__device__ __forceinline__ u32x4_t load_chunk(const void *p)
+{
+    // (named as global memory: the waits behind a flat load are for everything under way)
+    if constexpr (kElem == 2) return *(const __attribute__((address_space(1))) u32x4_at2_t *)p;
+    else return *(const __attribute__((address_space(1))) u32x4_at4_t *)p;
+}
+
+// v shifted towards its low end by `bytes` (0..15); zeros come in behind.
+__device__ __forceinline__ u32x4_t shift_down(u32x4_t v, int bytes)
+{
+    const bool one = (bytes & 4) != 0, two = (bytes & 8) != 0;
+    if (two) v = u32x4_t{v.z, v.w, 0u, 0u};
+    if (one) v = u32x4_t{v.y, v.z, v.w, 0u};
+    const uint32_t rest = bytes & 3;
+    return u32x4_t{__builtin_amdgcn_alignbyte(v.y, v.x, rest), __builtin_amdgcn_alignbyte(v.z, v.y, rest),
+                   __builtin_amdgcn_alignbyte(v.w, v.z, rest), __builtin_amdgcn_alignbyte(0u, v.w, rest)};
+}
+
+// Ragged operands.  A direct-to-LDS load needs a 16-byte aligned address, so an operand whose rows do not all start
+// on one (K or L no multiple of a chunk, or an unaligned pointer) takes another way: unaligned 16-byte loads into
+// registers, written to the same places of the same LDS layout two stages later; everything behind the LDS is shared.
+// (A copy of the operand with padded rows would take workspace of the operand's size and a pass over it.)  What
+// bounds the ragged form is the time a load is given: with the registers written to LDS one stage after the load
+// instead of two, and the aligned operand going the same way, B=8 T=1024 K=768 L=50257 took 1131 us against 861 us
+// (735 TFLOP/s; the scalar kernel: 219 ms; L=50264, all direct: 703 us).
+template <typename C, int WM, int WN, int MI, int NI, int kElem, bool kRaggedX, bool kRaggedG>
 __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
 {
-    constexpr bool kF32 = kElem == 4;
+    constexpr bool kF32 = kElem == 4, kRagged = kRaggedX || kRaggedG;
     constexpr int kStageT = C::kStageT, kPerChunk = 16 / kElem;       // elements per 16-byte chunk
-    constexpr int kWaves = C::kWaves, kLoadsPerWave = C::kLoadsPerWave, kStageBytes = C::kStageBytes;
+    constexpr int kWaves = C::kWaves, kStageBytes = C::kStageBytes;
     constexpr int kXRow = C::kXRow, kGRow = C::kGRow, kXBytes = C::kXBytes;
-    constexpr int kXChunks = kXRow / 16, kGChunks = kGRow / 16;       // 16-byte chunks per row
-    constexpr int kXRowsPerLoad = 64 / kXChunks, kGRowsPerLoad = 64 / kGChunks;
+    constexpr int kXLoads = C::kXLoadsPerWave, kGLoads = C::kGLoadsPerWave;
     __shared__ __align__(1024) unsigned char lds[kBufs * kStageBytes];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: branches on it are scalar
@@ -113,63 +159,131 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
     const int nstages = (b_end - b_begin) * nst;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
 
-    // ---- loading: a stage is kLoads loads of 1 KiB; wave w issues loads w*kLoadsPerWave .. +kLoadsPerWave-1.
-    // The first kXLoads are rows of x, the rest rows of g.  Per load and lane: the row and the chunk of
-    // memory that belongs at this lane's LDS position.
-    uint32_t voff[kLoadsPerWave];        // byte offset from the stage's first element of x (or g)
-    int lrow[kLoadsPerWave];             // row within the stage
-    bool lcol_ok[kLoadsPerWave];         // the chunk's columns exist (edge tiles)
-#pragma unroll
-    for (int n = 0; n < kLoadsPerWave; ++n) {
-        const int i = wave * kLoadsPerWave + n;
-        // fp32 operands are read back one element per lane along a row, which needs no swizzle
-        if (i < C::kXLoads) {
-            const int r = kXRowsPerLoad * i + lane / kXChunks;
-            const int c = kF32 ? lane % kXChunks : (lane % kXChunks) ^ ((r & 3) << 2);
-            lrow[n] = r;
-            lcol_ok[n] = k0 + c * kPerChunk < a.K;
-            voff[n] = (uint32_t)(((int64_t)r * a.K + c * kPerChunk) * kElem);
-        } else {
-            const int r = kGRowsPerLoad * (i - C::kXLoads) + lane / kGChunks;
-            const int c = kF32 ? lane % kGChunks : (lane % kGChunks) ^ ((r & 3) << 2);
-            lrow[n] = r;
-            lcol_ok[n] = l0 + c * kPerChunk < a.L;
-            voff[n] = (uint32_t)(((int64_t)r * a.L + c * kPerChunk) * kElem);
-        }
-    }
-    // A workgroup whose tile lies inside the matrix, on examples that are whole stages long, never has
-    // a lane without data: it issues the same number of loads per wave at every stage and may count on
-    // that when it waits.  Any other workgroup masks lanes, zero-fills their chunks and waits for all.
-    const bool regular = a.T % kStageT == 0 && k0 + C::kTileK <= a.K && l0 + C::kTileL <= a.L;
-    // The stage to fetch next is tracked by two running pointers: rows are contiguous in memory, within
-    // an example and from one example to the next, so a stage is 64 rows further unless it is the short
-    // last stage of an example.
-    int fs = 0;                                                // stage within the example
+    // ---- loading: a stage is loads of 1 KiB, kXLoads per wave for the rows of x and kGLoads for the rows of g.
+    // A workgroup whose tile lies inside the matrix, on examples that are whole stages long, never has a lane
+    // without data.  In any other workgroup a lane without data reads a chunk of zeros instead, so that every wave
+    // issues the same number of loads at every stage and can count on that when it waits.  (An earlier form masked
+    // such lanes, zero-filled their chunks with LDS stores and waited for all loads at every stage.)
+    const bool inside = k0 + C::kTileK <= a.K && l0 + C::kTileL <= a.L;
     const int last_rows = a.T - (nst - 1) * kStageT;           // rows of an example's last stage (64 if whole)
-    const char *xs = a.x + ((int64_t)b_begin * a.T * a.K + k0) * kElem, *gs = a.g + ((int64_t)b_begin * a.T * a.L + l0) * kElem;
-    auto fetch = [&](int buf) {
-        const uint32_t dst = lds_base + buf * kStageBytes + wave * kLoadsPerWave * 1024;
-        if (regular) {
+    // One operand: the stage to fetch next is tracked by a running pointer.  Rows are contiguous in memory, within
+    // an example and from one example to the next, so a stage is 64 rows further unless it is the short last stage
+    // of an example.
+    struct Operand {
+        const char *next;       // first element of this tile's columns, at the next stage to fetch
+        const char *last;       // the last whole chunk of the tensor
+        int stage;              // that stage's number within its example
+        int left;               // stages still to fetch; behind the last, rows of zeros
+        int width, col0;        // columns in all, first column of the tile
+    };
+    Operand ox{a.x + ((int64_t)b_begin * a.T * a.K + k0) * kElem, a.x + (int64_t)a.B * a.T * a.K * kElem - 16, 0, nstages, a.K, k0};
+    Operand og{a.g + ((int64_t)b_begin * a.T * a.L + l0) * kElem, a.g + (int64_t)a.B * a.T * a.L * kElem - 16, 0, nstages, a.L, l0};
+    // Load n of this wave: the row and the chunk of memory that belong at this lane's LDS position.  fp32 operands
+    // are read back one element per lane along a row, which needs no swizzle.
+    auto row_of = [&](int load, int chunks, int ln) { return load * (64 / chunks) + ln / chunks; };
+    auto chunk_of = [&](int row, int chunks, int ln) { return kF32 ? ln % chunks : (ln % chunks) ^ ((row & 3) << 2); };
+    // The ragged forms have no register to spare (a spilled value read back in the loop waits for every load under
+    // way: 4257 us for B=8 T=1024 K=769 L=50257 bf16): their addresses are made anew at every stage.
+    auto own_lane = [&]() {
+        int ln = lane;
+        if constexpr (kRagged) asm volatile("" : "+v"(ln));
+        return ln;
+    };
+    auto offset_of = [&](const Operand &o, int row, int chunk) { return (uint32_t)(((int64_t)row * o.width + chunk * kPerChunk) * kElem); };
+    auto rows_at = [&](const Operand &o) { return o.left <= 0 ? 0 : o.stage == nst - 1 ? last_rows : kStageT; };
+    auto advance = [&](Operand &o, int rows) {
+        --o.left;
+        o.next += (int64_t)rows * o.width * kElem;
+        o.stage = o.stage == nst - 1 ? 0 : o.stage + 1;
+    };
+    constexpr bool kTracked = kRagged && !kF32;                // (fp32 reads its operands with loads the compiler knows of)
+    // aligned rows: from memory to LDS
+    auto fetch = [&](Operand &o, auto loads, auto chunks, uint32_t dst) {
+        constexpr int kN = decltype(loads)::value, kChunks = decltype(chunks)::value;
+        const int rows = rows_at(o);
+        const int ln = own_lane();
+        auto to = [&](int n) { return dst + (wave * kN + n) * 1024; };
+        if (!kTracked && inside && rows == kStageT) {
 #pragma unroll
-            for (int n = 0; n < kLoadsPerWave; ++n)
-                load_to_lds(dst + n * 1024, voff[n],
-                            wave * kLoadsPerWave + n < C::kXLoads ? (const void *)xs : (const void *)gs);
+            for (int n = 0; n < kN; ++n) {
+                const int r = row_of(wave * kN + n, kChunks, ln);
+                load_to_lds(to(n), offset_of(o, r, chunk_of(r, kChunks, ln)), o.next);
+            }
         } else {
-            const int rows_left = fs == nst - 1 ? last_rows : kStageT;
 #pragma unroll
-            for (int n = 0; n < kLoadsPerWave; ++n) {
-                if (lcol_ok[n] && lrow[n] < rows_left)
-                    load_to_lds(dst + n * 1024, voff[n],
-                                wave * kLoadsPerWave + n < C::kXLoads ? (const void *)xs : (const void *)gs);
-                else
-                    *reinterpret_cast<u32x4_t *>(lds + buf * kStageBytes + (wave * kLoadsPerWave + n) * 1024 +
-                                                 lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
+            for (int n = 0; n < kN; ++n) {
+                const int r = row_of(wave * kN + n, kChunks, ln), c = chunk_of(r, kChunks, ln);
+                const bool data = r < rows && o.col0 + c * kPerChunk < o.width;
+                if constexpr (kTracked) load_to_lds_tracked(to(n), data ? (int)offset_of(o, r, c) : kTrackedNone, o.next);
+                else load_to_lds_lane(to(n), data ? o.next + offset_of(o, r, c) : reinterpret_cast<const char *>(kZeroChunk));
             }
         }
-        const int rows = fs == nst - 1 ? last_rows : kStageT;
-        xs += (int64_t)rows * a.K * kElem;
-        gs += (int64_t)rows * a.L * kElem;
-        fs = fs == nst - 1 ? 0 : fs + 1;
+        advance(o, rows);
+    };
+    // ragged rows: from memory to registers.  A chunk that begins inside its row may end in the next one: what it
+    // brings along lands in columns behind the matrix, which count nowhere.  Only at the very end of a tensor is
+    // there no next row; a chunk there is read from where it ends with the tensor (and shifted on its way to LDS).
+    // One load each, whatever the place: with a branch around loads the compiler no longer knows how many are under
+    // way, and waits for all of them.
+    struct Fetched {
+        const char *from;       // Operand::next
+        int rows;
+    };
+    auto past_end = [&](const Operand &o, const Fetched &f, int r, int c) {  // bytes by which a chunk leaves its tensor
+        const char *p = f.from + offset_of(o, r, c);
+        return r < f.rows && o.col0 + c * kPerChunk < o.width && p > o.last ? (int)(p - o.last) : 0;
+    };
+    auto fetch_ragged = [&](Operand &o, auto loads, auto chunks, auto &regs, Fetched &f) {
+        constexpr int kN = decltype(loads)::value, kChunks = decltype(chunks)::value;
+        const int ln = own_lane();
+        f = Fetched{o.next, rows_at(o)};
+#pragma unroll
+        for (int n = 0; n < kN; ++n) {
+            const int r = row_of(wave * kN + n, kChunks, ln), c = chunk_of(r, kChunks, ln);
+            const char *p = o.next + offset_of(o, r, c);
+            p = p > o.last ? o.last : p;
+            regs[n] = load_chunk<kElem>(r < f.rows && o.col0 + c * kPerChunk < o.width ? p : reinterpret_cast<const char *>(kZeroChunk));
+        }
+        advance(o, f.rows);
+    };
+    // ... and from there to LDS; in assembly, because a store to LDS that the compiler knows of waits for every
+    // direct load under way
+    auto put = [&](const Operand &o, auto loads, auto chunks, auto &regs, const Fetched &f, uint32_t to) {
+        constexpr int kN = decltype(loads)::value, kChunks = decltype(chunks)::value;
+        if (f.rows > 0 && f.from + (int64_t)f.rows * o.width * kElem > o.last) {
+            const int ln = own_lane();
+#pragma unroll
+            for (int n = 0; n < kN; ++n) {
+                const int r = row_of(wave * kN + n, kChunks, ln);
+                regs[n] = shift_down(regs[n], past_end(o, f, r, chunk_of(r, kChunks, ln)));
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < kN; ++n) {
+            const uint32_t at = to + (wave * kN + n) * 1024 + lane * 16;
+            asm volatile("ds_write_b128 %0, %1" : : "v"(at), "v"(regs[n]) : "memory");
+        }
+    };
+    using XLoads = std::integral_constant<int, kXLoads>;
+    using GLoads = std::integral_constant<int, kGLoads>;
+    using XChunks = std::integral_constant<int, kXRow / 16>;          // 16-byte chunks per row
+    using GChunks = std::integral_constant<int, kGRow / 16>;
+    constexpr int kSets = kRaggedX || kF32 ? 1 : 2;                    // stages under way in registers: as many as fit
+    u32x4_t x_regs[kSets][kRaggedX ? kXLoads : 1], g_regs[kSets][kRaggedG ? kGLoads : 1];
+    auto fetch_direct = [&](int buf) {                         // the aligned operands' next stage
+        if constexpr (!kRaggedX) fetch(ox, XLoads{}, XChunks{}, lds_base + buf * kStageBytes);
+        if constexpr (!kRaggedG) fetch(og, GLoads{}, GChunks{}, lds_base + buf * kStageBytes + kXBytes);
+    };
+    Fetched x_from[kSets], g_from[kSets];
+    auto fetch_regs = [&](auto set) {                          // the ragged operands' next stage
+        constexpr int s = decltype(set)::value;
+        if constexpr (kRaggedX) fetch_ragged(ox, XLoads{}, XChunks{}, x_regs[s], x_from[s]);
+        if constexpr (kRaggedG) fetch_ragged(og, GLoads{}, GChunks{}, g_regs[s], g_from[s]);
+    };
+    auto put_regs = [&](auto set, int buf) {
+        constexpr int s = decltype(set)::value;
+        if constexpr (kRaggedX) put(ox, XLoads{}, XChunks{}, x_regs[s], x_from[s], lds_base + buf * kStageBytes);
+        if constexpr (kRaggedG) put(og, GLoads{}, GChunks{}, g_regs[s], g_from[s], lds_base + buf * kStageBytes + kXBytes);
     };
 
     // ---- multiplying: wave (wm, wn) owns outputs k0 + wm*MI*32 .. , l0 + wn*NI*32 .. .
@@ -205,20 +319,23 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
     // current 16 start.  A block first waits for the reads issued by the block before it; the operands
     // those delivered are passed through it ("+v") so that no MFMA using them can be moved above the wait.
     static_assert(MI == 2 && NI == 2, "the read blocks below are written for 2 x 2 MFMA tiles per wave");
-    static_assert(kF32 || (kXRow == LIN_XROW && kGRow == LIN_GROW), "row pitches used in the assembly");
+    static_assert(kF32 || 52 * (kXRow > kGRow ? kXRow : kGRow) < 65536, "immediate offsets of the reads");
     typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
     struct Frags {
         u32x2_t a0l, a0h, a1l, a1h, b0l, b0h, b1l, b1h;
     };
-#define LIN_READS(KK)                                                                                          \
-    "ds_read_b64_tr_b16 %0, %8 offset:" LIN_STR((KK) * 16 * LIN_XROW) "\n\t"                                    \
-    "ds_read_b64_tr_b16 %1, %8 offset:" LIN_STR((KK) * 16 * LIN_XROW + 4 * LIN_XROW) "\n\t"                      \
-    "ds_read_b64_tr_b16 %2, %9 offset:" LIN_STR((KK) * 16 * LIN_XROW) "\n\t"                                    \
-    "ds_read_b64_tr_b16 %3, %9 offset:" LIN_STR((KK) * 16 * LIN_XROW + 4 * LIN_XROW) "\n\t"                      \
-    "ds_read_b64_tr_b16 %4, %10 offset:" LIN_STR((KK) * 16 * LIN_GROW) "\n\t"                                   \
-    "ds_read_b64_tr_b16 %5, %10 offset:" LIN_STR((KK) * 16 * LIN_GROW + 4 * LIN_GROW) "\n\t"                     \
-    "ds_read_b64_tr_b16 %6, %11 offset:" LIN_STR((KK) * 16 * LIN_GROW) "\n\t"                                   \
-    "ds_read_b64_tr_b16 %7, %11 offset:" LIN_STR((KK) * 16 * LIN_GROW + 4 * LIN_GROW)
+#define LIN_READS                                                                                              \
+    "ds_read_b64_tr_b16 %0, %8 offset:%12\n\t"                                                                 \
+    "ds_read_b64_tr_b16 %1, %8 offset:%13\n\t"                                                                 \
+    "ds_read_b64_tr_b16 %2, %9 offset:%12\n\t"                                                                 \
+    "ds_read_b64_tr_b16 %3, %9 offset:%13\n\t"                                                                 \
+    "ds_read_b64_tr_b16 %4, %10 offset:%14\n\t"                                                                \
+    "ds_read_b64_tr_b16 %5, %10 offset:%15\n\t"                                                                \
+    "ds_read_b64_tr_b16 %6, %11 offset:%14\n\t"                                                                \
+    "ds_read_b64_tr_b16 %7, %11 offset:%15"
+#define LIN_ADDRS(KK)                                                                                          \
+    "v"(pa0), "v"(pa1), "v"(pb0), "v"(pb1), "n"((KK) * 16 * kXRow), "n"((KK) * 16 * kXRow + 4 * kXRow),          \
+        "n"((KK) * 16 * kGRow), "n"((KK) * 16 * kGRow + 4 * kGRow)
 #define LIN_OUTS(F)                                                                                            \
     "=&v"(F.a0l), "=&v"(F.a0h), "=&v"(F.a1l), "=&v"(F.a1h), "=&v"(F.b0l), "=&v"(F.b0h), "=&v"(F.b1l), "=&v"(F.b1h)
 #define LIN_KEEP(F)                                                                                            \
@@ -236,25 +353,27 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
             for (int ni = 0; ni < 2; ++ni)
                 acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[mi], fb2[ni], acc[mi][ni], 0, 0, 0);
     };
-    auto multiply_bf16 = [&](int buf, bool refill, int refill_buf) {
+    // steps: groups of 16 positions that the stage holds (fewer than four at the end of an example)
+    auto multiply_bf16 = [&](int buf, int steps, auto refill) {
         const uint32_t base = lds_base + buf * kStageBytes;
         const uint32_t pa0 = base + a_addr[0], pa1 = base + a_addr[1], pb0 = base + b_addr[0], pb1 = base + b_addr[1];
         Frags f0, f1;
-        asm volatile(LIN_READS(0) : LIN_OUTS(f0) : "v"(pa0), "v"(pa1), "v"(pb0), "v"(pb1) : "memory");
-        asm volatile(LIN_READS(1) : LIN_OUTS(f1) : "v"(pa0), "v"(pa1), "v"(pb0), "v"(pb1) : "memory");
+        asm volatile(LIN_READS : LIN_OUTS(f0) : LIN_ADDRS(0) : "memory");
+        asm volatile(LIN_READS : LIN_OUTS(f1) : LIN_ADDRS(1) : "memory");
         asm volatile("s_waitcnt lgkmcnt(8)" : LIN_KEEP(f0) : : "memory");
         mfmas(f0);
-        asm volatile(LIN_READS(2) : LIN_OUTS(f0) : "v"(pa0), "v"(pa1), "v"(pb0), "v"(pb1) : "memory");
-        if (refill) fetch(refill_buf);                         // stage st+2 goes out in the shadow of those MFMAs
+        asm volatile(LIN_READS : LIN_OUTS(f0) : LIN_ADDRS(2) : "memory");
+        refill();                                              // later stages go out in the shadow of those MFMAs
         asm volatile("s_waitcnt lgkmcnt(8)" : LIN_KEEP(f1) : : "memory");
-        mfmas(f1);
-        asm volatile(LIN_READS(3) : LIN_OUTS(f1) : "v"(pa0), "v"(pa1), "v"(pb0), "v"(pb1) : "memory");
+        if (steps > 1) mfmas(f1);
+        asm volatile(LIN_READS : LIN_OUTS(f1) : LIN_ADDRS(3) : "memory");
         asm volatile("s_waitcnt lgkmcnt(8)" : LIN_KEEP(f0) : : "memory");
-        mfmas(f0);
+        if (steps > 2) mfmas(f0);
         asm volatile("s_waitcnt lgkmcnt(0)" : LIN_KEEP(f1) : : "memory");
-        mfmas(f1);
+        if (steps > 3) mfmas(f1);
     };
 #undef LIN_READS
+#undef LIN_ADDRS
 #undef LIN_OUTS
 #undef LIN_KEEP
     // fp32 operands (v_mfma_f32_32x32x2_f32: lane l holds row l%32 of A, column l%32 of B, position l/32 of
@@ -267,15 +386,14 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
     for (int i = 0; i < MI; ++i) fa_addr[i] = (lane >> 5) * kXRow + ((wm * MI + i) * 32 + (lane & 31)) * 4;
 #pragma unroll
     for (int i = 0; i < NI; ++i) fb_addr[i] = kXBytes + (lane >> 5) * kGRow + ((wn * NI + i) * 32 + (lane & 31)) * 4;
-    auto multiply_f32 = [&](int buf, bool refill, int refill_buf) {
+    auto multiply_f32 = [&](int buf, int steps, auto refill) {         // steps: pairs of positions
         const lds_byte_t *base = (const lds_byte_t *)lds + buf * kStageBytes;
         const lds_byte_t *pa[MI], *pb[NI];
 #pragma unroll
         for (int i = 0; i < MI; ++i) pa[i] = base + fa_addr[i];
 #pragma unroll
         for (int i = 0; i < NI; ++i) pb[i] = base + fb_addr[i];
-#pragma unroll
-        for (int ks = 0; ks < kStageT / 2; ++ks) {
+        auto step = [&](int ks) {
             float fa[MI], fb2[NI];
 #pragma unroll
             for (int i = 0; i < MI; ++i) fa[i] = *(const lds_float_t *)(pa[i] + ks * 2 * kXRow);
@@ -286,19 +404,34 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni)
                     acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[mi], fb2[ni], acc[mi][ni], 0, 0, 0);
-            if (ks == 1 && refill) fetch(refill_buf);          // stage st+2 goes out in the shadow of the MFMAs
+        };
+        step(0);
+        refill();                                              // later stages go out in the shadow of the MFMAs
+        if (steps < kStageT / 2) {
+#pragma nounroll
+            for (int ks = 1; ks < steps; ++ks) step(ks);
+        } else {
+#pragma unroll
+            for (int ks = 1; ks < kStageT / 2; ++ks) step(ks);
         }
     };
-    auto multiply = [&](int buf, bool refill, int refill_buf) {
-        if constexpr (kF32) multiply_f32(buf, refill, refill_buf);
-        else multiply_bf16(buf, refill, refill_buf);
-    };
+    // outputs of a lane: rows (i/4)*8 + (lane/32)*4 + i%4, column lane%32 of each 32x32 tile
+    auto out_k = [&](int mi, int i) { return k0 + (wm * MI + mi) * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3); };
+    auto out_l = [&](int ni) { return l0 + (wn * NI + ni) * 32 + (lane & 31); };
     int cb = b_begin, cs = 0;                                  // the stage being multiplied
+    auto multiply = [&](int buf, auto refill) {
+        const int rows = cs == nst - 1 ? last_rows : kStageT;
+        if constexpr (kF32) multiply_f32(buf, (rows + 1) / 2, refill);
+        else multiply_bf16(buf, (rows + 15) / 16, refill);
+    };
     auto boundary = [&]() {
         if (++cs < nst) return;
         cs = 0;
-        // example boundary: step 2 on this wave's part, then fold it into the total (step 3)
+        // example boundary: step 2 on this wave's part, then fold it into the total (step 3).  Outputs behind the
+        // edge of the matrix are zero, or (ragged rows) made of whatever the rows' neighbours hold: not counted.
         float ssq = 0.f;
+        int k_left = a.K, l_left = a.L;
+        if constexpr (kRagged) asm volatile("" : "+s"(k_left), "+s"(l_left));   // 64 masks: made here, not kept in registers
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -306,7 +439,8 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const float v = acc[mi][ni][i];
-                    ssq = fmaf(v, v, ssq);
+                    const float counted = !kRagged || inside || (out_k(mi, i) < k_left && out_l(ni) < l_left) ? v : 0.f;
+                    ssq = fmaf(counted, counted, ssq);
                     tot[mi][ni][i] += v;
                     acc[mi][ni][i] = 0.f;
                 }
@@ -315,35 +449,64 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
         ++cb;
     };
 
-    // ---- pipeline: before multiplying stage st a wave waits for its own loads of that stage (those of
-    // stage st+1, issued later, may still be under way), the barrier then says that every wave's part has
-    // landed and that stage st-1 has been read by all, so its buffer can take stage st+2.
-    if (nstages > 0) fetch(0);
-    if (nstages > 1) fetch(1);
-    int cur = 0, nxt2 = 2;                                     // buffers of stage st and of stage st+2
-    for (int st = 0; st < nstages; ++st) {
-        if (regular && st + 1 < nstages)
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerWave) : "memory");
-        else
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        multiply(cur, st + 2 < nstages, nxt2);
-        cur = cur == kBufs - 1 ? 0 : cur + 1;
-        nxt2 = nxt2 == kBufs - 1 ? 0 : nxt2 + 1;
+    // ---- pipeline: while stage st is multiplied the direct loads of stage st+2 go out, a ragged operand's registers
+    // of stage st+1 (loaded one or two stages ago) are written to LDS, and the same registers receive the stage after
+    // those under way.  Before it multiplies stage st a wave waits for its own direct loads of that stage (what it
+    // issued later may still be under way); the barrier then says that every wave's part has landed and that stage
+    // st-1 has been read by all, so its buffer can take stage st+2.
+    constexpr int kDirect = (kRaggedX ? 0 : kXLoads) + (kRaggedG ? 0 : kGLoads);      // loads per wave and stage
+    constexpr int kStaged = (kRaggedX ? kXLoads : 0) + (kRaggedG ? kGLoads : 0);
+    static_assert(!(kRaggedX && !kRaggedG), "an x with ragged rows takes the kernel with both in registers");
+    int cur = 0;                                               // buffer of stage st
+    auto buffer = [&](int ahead) { return cur + ahead >= kBufs ? cur + ahead - kBufs : cur + ahead; };
+    auto do_stage = [&](auto next_set) {
+        // younger than the direct loads of stage st: those of st+1, the register loads of st+1 and st+2
+        if constexpr (kDirect > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kDirect + kSets * kStaged) : "memory");
+        if constexpr (kRagged) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // loads into registers stay under way
+        else __syncthreads();
+        // Every stage issues the same loads, also where no stage is left (of zeros then): the counts above, and the
+        // compiler's own for the registers, hold only if no path issues fewer.
+        multiply(cur, [&]() {
+            if constexpr (kRagged) put_regs(next_set, buffer(1));
+            fetch_direct(buffer(2));
+            if constexpr (kRagged) fetch_regs(next_set);
+        });
+        cur = buffer(1);
         boundary();
+    };
+    using Set0 = std::integral_constant<int, 0>;
+    using Set1 = std::integral_constant<int, kSets - 1>;
+    fetch_direct(0);
+    if constexpr (kRagged) {
+        fetch_regs(Set0{});
+        put_regs(Set0{}, 0);
     }
+    if constexpr (kRagged) fetch_regs(Set1{});
+    fetch_direct(1);
+    if constexpr (kRagged) {
+        if constexpr (kSets == 2) fetch_regs(Set0{});
+        int st = 0;
+        for (; st + 2 <= nstages; st += 2) {
+            do_stage(Set1{});
+            do_stage(Set0{});
+        }
+        if (st < nstages) do_stage(Set1{});
+    } else {
+        for (int st = 0; st < nstages; ++st) do_stage(Set0{});
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // no load may reach LDS after the workgroup has left it
 
-    // ---- write the total: lane holds rows (i/4)*8 + (lane/32)*4 + i%4, column lane%32 of each 32x32 tile
+    // ---- write the total
     float *out = a.out + (a.nsplit > 1 ? (int64_t)split * a.K * a.L : 0);
     double bsq = 0.0;
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
-            const int l = l0 + (wn * NI + ni) * 32 + (lane & 31);
+            const int l = out_l(ni);
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int k = k0 + (wm * MI + mi) * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
+                const int k = out_k(mi, i);
                 if (k < a.K && l < a.L) {
                     float *p = out + (int64_t)k * a.L + l;
                     float v = tot[mi][ni][i];
@@ -359,10 +522,20 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
     }
 }
 
-template <int kElem>
+template <int kElem, bool kRaggedX, bool kRaggedG>
 __global__ __launch_bounds__(Cfg::kThreads) void linear_pegn_kernel(LinArgs a)
 {
-    linear_pegn_body<LinCfg<LIN_CFG, kElem>, LIN_CFG, kElem>(a);
+    linear_pegn_body<LinCfg<4, 2, 2, 2, kElem>, 4, 2, 2, 2, kElem, kRaggedX, kRaggedG>(a);
+}
+
+// (ragged g beside aligned x: the rows of x are reached through 31-bit offsets)
+template <int kElem>
+hipError_t launch_linear(const LinArgs &a, bool ragged_x, bool ragged_g, hipStream_t st)
+{
+    const dim3 grid(a.tiles_k * a.tiles_l, a.nsplit), block(Cfg::kThreads);
+    if (ragged_x || (ragged_g && a.K > (1 << 23))) return launch(linear_pegn_kernel<kElem, true, true>, grid, block, 0, st, a);
+    if (ragged_g) return launch(linear_pegn_kernel<kElem, false, true>, grid, block, 0, st, a);
+    return launch(linear_pegn_kernel<kElem, false, false>, grid, block, 0, st, a);
 }
 
 // Any shape, any alignment, fp32 or bf16: one thread per output (k,l), fp32 FMA over t, no MFMA.
@@ -438,7 +611,8 @@ __global__ __launch_bounds__(1024) void linear_final_kernel(const float *part_s,
 }
 
 struct LinPlan {
-    bool mfma;
+    bool mfma;             // matrix-core kernel
+    bool ragged_x, ragged_g;   // rows of x, of g do not all start on 16-byte boundaries
     int tiles_k, tiles_l, nsplit, b_per_split;
     int nparts;            // rows of the s parts
     int64_t nbig;          // entries of the ||w'||^2 parts
@@ -447,11 +621,25 @@ struct LinPlan {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-LinPlan make_lin_plan(int B, int T, int K, int L, int dt, bool aligned)
+// What make_lin_plan is told about the pointers.
+struct LinAlign {
+    bool x16, g16;         // on 16-byte boundaries
+    bool element;          // on multiples of an element, both
+};
+
+// max_split: most workgroups that may share an output tile's examples (each but the first costs workspace).
+LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, int max_split = kMaxSplit)
 {
     LinPlan p{};
     const int per_chunk = dt == LNPEGN_BF16 ? 8 : 4;          // elements per 16-byte vector
-    p.mfma = K % per_chunk == 0 && L % per_chunk == 0 && aligned;
+    p.ragged_x = K % per_chunk != 0 || !align.x16;
+    p.ragged_g = L % per_chunk != 0 || !align.g16;
+    // The matrix-core kernel takes every shape but ragged tensors of less than one chunk and rows whose stage is
+    // beyond its 32-bit offsets; those, and pointers that split an element, are left to the scalar kernel, which is
+    // slower by two orders of magnitude (figures above).
+    const int64_t rows = (int64_t)B * T;
+    p.mfma = K <= (1 << 25) && L <= (1 << 25) &&
+             (!(p.ragged_x || p.ragged_g) || (align.element && rows * K >= per_chunk && rows * L >= per_chunk));
     if (p.mfma) {
         p.tiles_k = (K + Cfg::kTileK - 1) / Cfg::kTileK;
         p.tiles_l = (L + Cfg::kTileL - 1) / Cfg::kTileL;
@@ -459,7 +647,7 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, bool aligned)
         // enough workgroups for 256 CUs: split the examples when the output has few tiles
         int want = (256 + ntiles - 1) / ntiles;
         if (want > B) want = B;
-        if (want > kMaxSplit) want = kMaxSplit;
+        if (want > max_split) want = max_split;
         p.b_per_split = (B + want - 1) / want;
         p.nsplit = (B + p.b_per_split - 1) / p.b_per_split;
         p.nparts = ntiles * Cfg::kWaves;
@@ -495,8 +683,13 @@ size_t linear_pegn_workspace_bytes(int B, int T, int K, int L, lnpegn_dtype dt)
 {
     if (!lin_shape_ok(B, T, K, L) || (dt != LNPEGN_F32 && dt != LNPEGN_BF16)) return 0;
     // sized for either kernel, whatever the alignment of the pointers turns out to be
-    const size_t m = make_lin_plan(B, T, K, L, dt, true).bytes, g = make_lin_plan(B, T, K, L, dt, false).bytes;
-    return m > g ? m : g;
+    size_t most = 0;
+    for (int aligned = 0; aligned < 2; ++aligned)
+        for (int element = aligned; element < 2; ++element) {
+            const size_t n = make_lin_plan(B, T, K, L, dt, LinAlign{aligned != 0, aligned != 0, element != 0}).bytes;
+            if (n > most) most = n;
+        }
+    return most;
 }
 
 int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq, int B, int T, int K, int L,
@@ -506,8 +699,14 @@ int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq,
     if (flags & ~(unsigned)LNPEGN_ACCUMULATE) return LNPEGN_EINVAL;
     if (dt != LNPEGN_F32 && dt != LNPEGN_BF16) return LNPEGN_EUNSUPPORTED;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return LNPEGN_EINVAL;
-    const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(g)) & 15u) == 0;
-    const LinPlan p = make_lin_plan(B, T, K, L, dt, aligned);
+    const uintptr_t px = reinterpret_cast<uintptr_t>(x), pg = reinterpret_cast<uintptr_t>(g), elem = dt == LNPEGN_BF16 ? 2 : 4;
+    const LinAlign align{(px & 15u) == 0, (pg & 15u) == 0, ((px | pg) & (elem - 1)) == 0};
+    LinPlan p = make_lin_plan(B, T, K, L, dt, align);
+    // Ragged rows run in less workspace too, down to what the scalar kernel asks for: without a split, or there.
+    if ((p.ragged_x || p.ragged_g) && workspace_bytes < p.bytes) {
+        p = make_lin_plan(B, T, K, L, dt, align, 1);
+        if (workspace_bytes < p.bytes) p = make_lin_plan(B, T, K, L, dt, LinAlign{false, false, false});
+    }
     if (workspace_bytes < p.bytes) return LNPEGN_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int accumulate = (flags & LNPEGN_ACCUMULATE) ? 1 : 0;
@@ -525,10 +724,9 @@ int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq,
         a.B = B; a.T = T; a.K = K; a.L = L;
         a.tiles_k = p.tiles_k; a.tiles_l = p.tiles_l; a.nsplit = p.nsplit; a.b_per_split = p.b_per_split;
         a.accumulate = accumulate;
-        const dim3 grid(p.tiles_k * p.tiles_l, p.nsplit), block(Cfg::kThreads);
-        if ((dt == LNPEGN_BF16 ? launch(linear_pegn_kernel<2>, grid, block, 0, st, a)
-                               : launch(linear_pegn_kernel<4>, grid, block, 0, st, a)) != hipSuccess)
-            return LNPEGN_EHIP;
+        const hipError_t e = dt == LNPEGN_BF16 ? launch_linear<2>(a, p.ragged_x, p.ragged_g, st)
+                                               : launch_linear<4>(a, p.ragged_x, p.ragged_g, st);
+        if (e != hipSuccess) return LNPEGN_EHIP;
         if (p.nsplit > 1) {
             const int64_t n = (int64_t)K * L;
             if (launch(linear_sum_splits_kernel, dim3((unsigned)p.nbig), dim3(256), 0, st, part_w, w, part_big, n, p.nsplit, accumulate) != hipSuccess) return LNPEGN_EHIP;

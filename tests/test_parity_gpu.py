@@ -707,6 +707,44 @@ def test_linear_pegn_generic_kernel(dtype, B, T, K, L):
     _check_linear(x, g, _run_linear(x, g, dtype, w0=w0), w0=w0)
 
 
+@pytest.mark.parametrize("dtype,B,T,K,L,off", [
+    ("bf16", 2, 64, 255, 127, 0), ("bf16", 1, 65, 257, 129, 0),      # a tile less and more one column, both ragged
+    ("bf16", 3, 70, 264, 131, 0), ("bf16", 2, 130, 512, 257, 0),     # aligned x beside a ragged g
+    ("bf16", 2, 63, 33, 264, 0), ("bf16", 1, 1, 9, 8, 0), ("bf16", 1, 3, 3, 5, 0), ("bf16", 1, 2, 7, 3, 0),
+    ("bf16", 2, 40, 264, 136, 1), ("bf16", 2, 40, 264, 136, 4),      # aligned widths behind unaligned pointers
+    ("bf16", 70, 17, 129, 1, 0), ("f32", 2, 33, 255, 129, 0), ("f32", 3, 64, 512, 130, 0), ("f32", 2, 31, 257, 128, 1),
+])
+def test_linear_pegn_ragged_rows(dtype, B, T, K, L, off):
+    """Rows that do not start on 16-byte boundaries, through the matrix-core kernel; the same sums in the least
+    workspace that was ever asked for such a shape (no split over the examples, or the scalar kernel)."""
+    import torch
+    from paper_2411_00999_amd import binding
+    x, g = workloads.make_linear_inputs(B * 1000 + K + L, B, T, K, L, dtype)
+
+    def at_offset(a):
+        t = pu.to_device(a, dtype)
+        flat = torch.empty(t.numel() + off, dtype=t.dtype, device="cuda")[off:]
+        return flat.copy_(t.view(-1)).view(t.shape)
+    xd, gd = at_offset(x), at_offset(g)
+    host = lambda r: tuple(pu.to_host64(t) for t in r)
+    _check_linear(x, g, host(binding.linear_pegn(xd, gd)))
+    tiles = -(-K // 16) * -(-L // 16)
+    least = (-(-tiles * B * 4 // 256) + -(-tiles * 8 // 256)) * 256
+    _check_linear(x, g, host(binding.linear_pegn(xd, gd, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))))
+
+
+@pytest.mark.parametrize("K,L", [(264, 131), (257, 129), (264, 136)])
+def test_linear_pegn_keeps_infinities_to_their_example(K, L):
+    """T is no multiple of a stage: the rows behind an example's end are zeros, not what another example left there."""
+    x, g = workloads.make_linear_inputs(K + L, 3, 70, K, L, "bf16")
+    from oracle import linear_pegn_oracle as lin
+    ref = lin.linear_pegn(x, g)["s"]
+    x[0], g[0] = np.inf, np.nan
+    _, s, _ = _run_linear(x, g, "bf16")
+    assert not np.isfinite(s[0])
+    np.testing.assert_allclose(s[1:], ref[1:], rtol=pu.TOL_SUMS)
+
+
 def test_linear_pegn_special_cases_and_estimate():
     import torch
     from paper_2411_00999_amd import binding
