@@ -13,6 +13,8 @@ constexpr int kWave = 64;
 struct DeferHeader {
     float *dgamma, *dbeta, *pe_gamma_sq, *pe_beta_sq, *big_sq;
     int n_slots, gs, G1, n_ex, ex_gs, accumulate;
+    int one_pass;       // reduced by the slab kernel (else in two levels)
+    unsigned arrived;   // workgroups of the slab kernel that are done; cleared by the row kernel, on every call
 };
 
 // ---------------------------------------------------------------------------------------

@@ -1,9 +1,8 @@
 // Second level of the two-level deterministic reduction: sums of the per-chunk column sums,
 // the per-example squared norms (Appendix B steps 2 and 6), the batch gradients (steps 3
 // and 7) and the gradient-noise-scale estimator (Section 2.1, Eq. 3-5).  Every sum runs in a
-// fixed order, in fp64, so results do not depend on scheduling.  The levels are separate
-// launches on purpose: a device-scope fence inside a kernel writes back and invalidates the
-// whole L2 of an XCD on this part, which costs more than a launch.
+// fixed order, in fp64, so results do not depend on scheduling.  Two forms: one launch whose workgroups each
+// finish a slab of columns (reduce_slab_kernel), and two levels of launches for many examples of many chunks.
 #pragma once
 #include "lnpegn_device.h"
 
@@ -30,6 +29,9 @@ struct ReduceArgs {
     int D;
     int ntile;
     int accumulate;        // dgamma, dbeta: add to what is there (gradient accumulation) instead of overwrite
+    int nslab;             // slab kernel: slabs of columns
+    double *slab;          // [n_ex + 1][nslab][2] squared norms per slab: the examples', then the batch gradients'
+    unsigned *arrived;     // workgroups that have left theirs
 };
 
 // An example's chunks are also one of the groups (as many groups as examples, of as many chunks): one workgroup
@@ -43,7 +45,187 @@ __host__ __device__ inline int reduce_groups_count(const ReduceArgs &a)
 // These kernels are a handful of dependent memory round trips long, so every level issues its
 // loads in batches of eight before it adds them (in index order: the sums are reproducible).
 
-// Level 1.  grid (ntile, reduce_groups_count), 256 threads: the column tiles of a run of chunks are neighbours in
+// ---------------------------------------------------------------------------------------
+// The whole reduction in one launch.  A workgroup owns a slab of 4*kQ columns and reads all chunks' sums of it: it
+// writes dgamma and dbeta there, and leaves its part of every squared norm; the workgroup that arrives last adds
+// those parts up.  Latency bound (three dependent trips to memory); against two levels it saves a launch and the
+// trip of the group sums.  Whole backward calls, us, two levels -> this: B=4 T=128 D=256 fp32 12.2 -> 9.5, B=8 T=1024
+// D=768 bf16 21.7 -> 18.3, B=8 T=4096 D=8192 284 -> 277, B=8 T=500 D=1001 78.0 -> 48.5; the deferred reduction of 48
+// layers of B=16 T=2048 D=2048 45.0 -> 38.5.
+//
+// The parts cross from one XCD's cache to another's without a fence (a release at device scope writes back the
+// whole L2, for every workgroup one after the other: the form with fences took longer than the two launches):
+// they are stored and loaded by device-scope atomic accesses, which go to the memory that all XCDs share, a
+// workgroup waits until its stores are acknowledged there before it counts itself as arrived, and the last one
+// loads after it has read the full count.  Every sum has its order from the shape alone, whoever is last.
+//
+// 512 threads are kWalkers groups of 2*kQ lanes (kQ quads of columns for dgamma, kQ for dbeta).  With fewer examples
+// than walkers an example's chunks are split over kWalkers / n_ex of them; otherwise a walker takes a run of whole
+// examples, or of chunks when no example's norm is wanted here.
+// ---------------------------------------------------------------------------------------
+constexpr int kSlabThreads = 512;
+__host__ __device__ inline int slab_quads(int D) { return D >= 512 ? 8 : 4; }   // kQ: whole 128-byte lines for wide rows
+
+template <int kLanes>
+__device__ __forceinline__ double group_sum_f64(double v)   // over aligned groups of kLanes lanes
+{
+#pragma unroll
+    for (int off = kLanes / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
+    return v;
+}
+
+__device__ __forceinline__ void store_shared_f64(double *p, double v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_shared_f64(const double *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int kQ>
+__device__ __forceinline__ void reduce_slab_body(const ReduceArgs &a, int slab)
+{
+    constexpr int kCols = 4 * kQ, kLanes = 2 * kQ, kWalkers = kSlabThreads / kLanes, kItems = 2 * kCols;
+    constexpr int kUnits = kSlabThreads / kItems;      // walkers or examples combined side by side
+    __shared__ double sums[kWalkers][2][kCols];
+    __shared__ double totals[kUnits][kItems];
+    __shared__ bool last;
+    const int tid = threadIdx.x;
+    {
+        const int walker = tid / kLanes, arr = tid / kQ % 2, quad = tid % kQ;
+        const int col = slab * kCols + quad * 4;
+        const int left = arr == 0 || a.dbeta ? a.D - col : 0;   // columns this lane has (4 or more: a whole quad)
+        const int split = a.n_ex > 0 && a.n_ex <= kWalkers ? kWalkers / a.n_ex : 1;   // walkers per example
+        int m0, m1, flush = 0;                                  // chunks of this walker; chunks per example to finish
+        if (a.n_ex > 0 && a.n_ex <= kWalkers) {
+            const int e = walker / split, part = walker % split, per = (a.ex_gs + split - 1) / split;
+            m0 = e < a.n_ex ? e * a.ex_gs + min(part * per, a.ex_gs) : 0;
+            m1 = e < a.n_ex ? e * a.ex_gs + min((part + 1) * per, a.ex_gs) : 0;
+        } else {
+            const int unit = a.n_ex > 0 ? a.ex_gs : 1, n = a.n_slots / unit, per = (n + kWalkers - 1) / kWalkers;
+            m0 = min(walker * per, n) * unit;
+            m1 = min((walker + 1) * per, n) * unit;
+            flush = a.n_ex > 0 ? a.ex_gs : 0;
+        }
+        double acc[4] = {0, 0, 0, 0}, run[4] = {0, 0, 0, 0};
+        const int64_t stride = 2 * (int64_t)a.D;
+        const float *base = a.part + (int64_t)arr * a.D + col;
+        const bool vec = (a.D & 3) == 0;                        // rows of the workspace are 16-byte aligned
+        auto finish_example = [&](int e) {
+            double q = 0.0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float f = (float)acc[i];                  // an example's gradient as fp32 values, squared in fp64
+                q += (double)f * f;
+                run[i] += acc[i];
+                acc[i] = 0.0;
+            }
+            q = group_sum_f64<kQ>(q);
+            if (quad == 0) store_shared_f64(a.slab + ((int64_t)e * a.nslab + slab) * 2 + arr, q);
+        };
+        int to_go = flush, e = flush > 0 ? m0 / flush : 0;
+        for (int m = m0; m < m1; m += 8) {
+            float4 u[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float *p = base + min(m + i, m1 - 1) * stride;
+                u[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (vec && left > 0) u[i] = *reinterpret_cast<const float4 *>(p);
+                if (!vec) {
+                    if (left > 0) u[i].x = p[0];
+                    if (left > 1) u[i].y = p[1];
+                    if (left > 2) u[i].z = p[2];
+                    if (left > 3) u[i].w = p[3];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (m + i < m1) {
+                    acc[0] += u[i].x; acc[1] += u[i].y; acc[2] += u[i].z; acc[3] += u[i].w;
+                    if (flush > 0 && --to_go == 0) {
+                        finish_example(e++);
+                        to_go = flush;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sums[walker][arr][quad * 4 + i] = flush > 0 ? run[i] : acc[i];
+    }
+    __syncthreads();
+    // item = (array, column); the units are the examples when walkers share them, else the walkers
+    const int item = tid % kItems, lane0 = tid / kItems, arr = item / kCols, c = item % kCols;
+    {
+        const bool shared_ex = a.n_ex > 0 && a.n_ex <= kWalkers;
+        const int split = shared_ex ? kWalkers / a.n_ex : 1, units = shared_ex ? a.n_ex : kWalkers;
+        double total = 0.0;
+        for (int e = lane0; e < units; e += kUnits) {
+            double v = 0.0;
+            for (int j = 0; j < split; ++j) v += sums[e * split + j][arr][c];
+            total += v;
+            if (shared_ex) {
+                const float f = (float)v;
+                const double q = group_sum_f64<kCols>((double)f * f);
+                if (c == 0) store_shared_f64(a.slab + ((int64_t)e * a.nslab + slab) * 2 + arr, q);
+            }
+        }
+        totals[lane0][item] = total;
+    }
+    __syncthreads();
+    if (tid < kItems) {
+        double v = 0.0;
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) v += totals[u][tid];
+        const int col = slab * kCols + c;
+        float *dst = arr == 0 ? a.dgamma : a.dbeta;
+        const bool mine = col < a.D && dst;
+        if (mine && a.accumulate) v += (double)dst[col];
+        const float f = (float)v;
+        if (mine) dst[col] = f;
+        const double q = group_sum_f64<kCols>(mine ? (double)f * f : 0.0);     // squares of the values as stored
+        if (c == 0) store_shared_f64(a.slab + ((int64_t)a.n_ex * a.nslab + slab) * 2 + arr, q);
+    }
+    if (a.n_ex == 0 && !a.big_sq) return;
+    // every thread: this thread's parts have reached the memory that all XCDs share
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0)
+        last = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)a.nslab - 1u;
+    __syncthreads();
+    if (!last) return;
+    if (tid == 0) __hip_atomic_store(a.arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // sums over the slabs, in an order fixed by the shape: `lanes` threads per sum
+    const int nsums = 2 * (a.n_ex + 1);
+    int lanes = 16;
+    while (lanes > 1 && nsums * lanes > kSlabThreads) lanes >>= 1;
+    for (int i = tid / lanes; i < nsums; i += kSlabThreads / lanes) {
+        const double *p = a.slab + (int64_t)(i >> 1) * a.nslab * 2 + (i & 1);
+        double v = 0.0;
+        for (int k = tid % lanes; k < a.nslab; k += lanes * 8) {
+            double u[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) u[j] = load_shared_f64(p + 2 * (int64_t)min(k + j * lanes, a.nslab - 1));
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v += k + j * lanes < a.nslab ? u[j] : 0.0;
+        }
+        for (int off = lanes / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
+        if (tid % lanes == 0) {
+            float *dst = i < 2 * a.n_ex ? (i & 1 ? a.pe_beta_sq : a.pe_gamma_sq) : a.big_sq;
+            if (dst && (i & 1) && !a.dbeta) dst = nullptr;      // no beta
+            if (dst) dst[i < 2 * a.n_ex ? i >> 1 : i & 1] = (float)v;
+        }
+    }
+}
+
+// grid (nslab) for one layer
+template <int kQ>
+__global__ __launch_bounds__(kSlabThreads) void reduce_slab_kernel(ReduceArgs a)
+{
+    reduce_slab_body<kQ>(a, blockIdx.x);
+}
+
+// Level 1 of two.  grid (ntile, reduce_groups_count), 256 threads: the column tiles of a run of chunks are neighbours in
 // launch order, so that the 1 KiB pieces they read of the same chunk vectors are fetched together (with the tiles
 // as the slow grid index the batched launch of the 48-layer step took 57 us instead of 35).  A workgroup adds
 // the column sums of a run of consecutive chunks: the four waves split the run, add in chunk order, then the
@@ -241,14 +423,20 @@ struct BatchArgs {
     int n;
     int D;
     int ntile;
+    int nslab;
     size_t off_grp, off_part_s, off_part_big, off_part;
 };
 
-__device__ __forceinline__ ReduceArgs batch_layer_args(const BatchArgs &b, int layer)
+__device__ __forceinline__ ReduceArgs batch_layer_args(const BatchArgs &b, int layer, bool &one_pass)
 {
     char *ws = b.ws[layer];
-    const DeferHeader h = *reinterpret_cast<const DeferHeader *>(ws);
+    DeferHeader *head = reinterpret_cast<DeferHeader *>(ws);
+    const DeferHeader h = *head;
+    one_pass = h.one_pass != 0;
     ReduceArgs a;
+    a.nslab = b.nslab;
+    a.slab = reinterpret_cast<double *>(ws + b.off_grp);
+    a.arrived = &head->arrived;
     a.part = reinterpret_cast<const float *>(ws + b.off_part);
     a.grp = reinterpret_cast<float *>(ws + b.off_grp);
     a.part_s = reinterpret_cast<double *>(ws + b.off_part_s);
@@ -260,18 +448,30 @@ __device__ __forceinline__ ReduceArgs batch_layer_args(const BatchArgs &b, int l
     return a;
 }
 
+// grid (nslab, layers)
+template <int kQ>
+__global__ __launch_bounds__(kSlabThreads) void reduce_slab_batch_kernel(BatchArgs b)
+{
+    bool one_pass;
+    const ReduceArgs a = batch_layer_args(b, blockIdx.y, one_pass);
+    if (one_pass) reduce_slab_body<kQ>(a, blockIdx.x);
+}
+
 // grid (ntile, most examples + groups of any layer, layers): workgroups beyond a layer's own count leave at once
 __global__ __launch_bounds__(kTile) void reduce_groups_batch_kernel(BatchArgs b)
 {
-    const ReduceArgs a = batch_layer_args(b, blockIdx.z);
-    if ((int)blockIdx.y >= reduce_groups_count(a)) return;
+    bool one_pass;
+    const ReduceArgs a = batch_layer_args(b, blockIdx.z, one_pass);
+    if (one_pass || (int)blockIdx.y >= reduce_groups_count(a)) return;
     reduce_groups_body(a, blockIdx.y, blockIdx.x);
 }
 
 // grid (layers)
 __global__ __launch_bounds__(1024) void reduce_final_batch_kernel(BatchArgs b)
 {
-    const ReduceArgs a = batch_layer_args(b, blockIdx.x);
+    bool one_pass;
+    const ReduceArgs a = batch_layer_args(b, blockIdx.x, one_pass);
+    if (one_pass) return;
     if (a.G1 == 1 && a.n_ex == 0 && !a.big_sq) return;
     reduce_final_body(a);
 }

@@ -325,6 +325,58 @@ def test_deferred_reduction_of_more_layers_than_one_launch_takes():
             assert torch.equal(u, v), l
 
 
+@pytest.mark.parametrize("B,T,D,dtype", [
+    (31, 40, 1032, "bf16"), (32, 40, 1032, "bf16"), (33, 40, 1032, "bf16"),   # examples around the slab kernel's 32 walkers
+    (64, 16, 264, "f32"), (65, 16, 264, "f32"),       # ... its 64 narrow walkers, and the line to two levels
+    (63, 12, 520, "bf16"),                            # the last slab half empty
+    (5, 30, 37, "f32"), (3, 20, 2, "bf16"), (2, 11, 1003, "f32"),             # rows of the workspace not 16-byte aligned
+])
+def test_reduction_in_one_launch(B, T, D, dtype):
+    """Edges of the slab kernel, immediate and (bitwise the same) deferred; plain and RMS calls through the same."""
+    import torch
+    from paper_2411_00999_amd import binding
+    inp = workloads.make_inputs(1, B=B, T=T, D=D, dtype=dtype, signal=1e-2)
+    ref = _oracle(inp)
+    pu.compare_with_oracle(inp, pu.run_gpu(inp), ref)
+    pu.compare_with_oracle(inp, pu.run_gpu(inp, pegn=False), ref, pegn=False)
+    code = binding.BF16 if dtype == "bf16" else binding.F32
+    x, dy, gamma = (pu.to_device(a, dtype) for a in (inp.x, inp.dy, inp.gamma))
+    now = binding.ln_bwd_pegn(x, dy, gamma, inp.eps)
+    wss = [binding.alloc_workspace(B, T, D, code) for _ in range(3)]
+    late = [binding.ln_bwd_pegn(x, dy, gamma, inp.eps, workspace=w, deferred=True) for w in wss[:2]]
+    plain = binding.ln_bwd(x, dy, gamma, inp.eps, workspace=wss[2], deferred=True)
+    binding.reduce_deferred(wss, B, T, D, code)
+    torch.cuda.synchronize()
+    for got in late:
+        assert all(torch.equal(p, q) for p, q in zip(now, got))
+    np.testing.assert_allclose(pu.to_host64(plain[1]), pu.to_host64(now[1]), rtol=1e-5,
+                               atol=1e-5 * float(now[1].square().mean().sqrt()))
+
+
+def test_deferred_layers_of_both_reductions():
+    """Layers whose row kernels ran under different launch overrides, one reduced in one launch and one in two levels,
+    finished by one call under none."""
+    import torch
+    from paper_2411_00999_amd import binding
+    B, T, D = 8, 4096, 64
+    inp = workloads.make_inputs(1, B=B, T=T, D=D, signal=1e-2)
+    x, dy, gamma = (pu.to_device(a, "f32") for a in (inp.x, inp.dy, inp.gamma))
+    wss = [torch.empty(16 << 20, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    got = [binding.ln_bwd_pegn(x, dy, gamma, inp.eps, workspace=wss[0], deferred=True)]
+    binding.set_tuning(0, 16384)
+    try:
+        assert binding.plan_query(B, T, D, binding.F32)["chunks"] > 2048
+        got.append(binding.ln_bwd_pegn(x, dy, gamma, inp.eps, workspace=wss[1], deferred=True))
+    finally:
+        binding.set_tuning(0, 0)
+    binding.reduce_deferred(wss, B, T, D, binding.F32)
+    torch.cuda.synchronize()
+    ref = _oracle(inp)
+    for out in got:
+        names = ("dx", "dgamma", "dbeta", "s_gamma", "s_beta", "big_sq")
+        pu.compare_with_oracle(inp, dict(zip(names, map(pu.to_host64, out))), ref)
+
+
 @pytest.mark.parametrize("cfg,B,T,D", [(1, 4, 128, 256), (2, 3, 37, 768), (3, 2, 50, 2048), (5, 2, 9, 8192),
                                       (1, 2, 7, 257), (2, 2, 5, 1001), (5, 2, 7, 12288), (5, 1, 5, 16384),
                                       (1, 2, 5, 12288), (1, 1, 3, 16384), (5, 1, 3, 20480)])
