@@ -119,9 +119,12 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    """Handle of the given stream, or of the current device's current one.  The handle itself is asked for:
+    torch.cuda.current_stream() makes a Stream object first, 2.9 us of the 8.4 us of a call with one launch."""
+    if stream is None:
+        c = _torch()._C
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice()) or None
+    return stream.cuda_stream or None
 
 
 def _check3(x):
