@@ -5,17 +5,17 @@
 // The positions p = b*T + t are sorted by id (stable, so positions ascend inside an id and the rows of one
 // example are adjacent): a "segment" is all positions of one id, a "run" those of one id in one example, a
 // "piece" at most kPiece consecutive sorted positions of one run (a run is cut wherever the sorted index is a
-// multiple of kPiece).  Kernel A reads g, every row once.  An id with at most kShort positions is finished
-// there by one wave (each run's share of step 3, the row of w').  A longer id is handed out piece by piece:
-// a piece that is a whole run yields that run's share at once, the piece sums are parked in the workspace,
-// and kernel B (two launches: per run, then per id) adds the parked sums in sorted order, finding them by
-// binary search of the sorted list rather than by walking it.  No wave reads more than kChunk + kPiece rows
-// however skewed the ids are, and nothing is atomic: results are bitwise reproducible.
+// multiple of kPiece).  Kernel A reads g, every row once, and fills the rows of w' that no id selects.  An id with at
+// most kShort positions is finished there by one wave (each run's share of step 3, the row of w').  A longer id is
+// handed out piece by piece: a piece that is a whole run yields that run's share at once, the piece sums are parked
+// in the workspace, and kernel B adds the parked sums in sorted order, finding them by search of the sorted list
+// rather than by walking it.  No wave reads more than kChunk + kPiece rows however skewed the ids are, and nothing
+// is atomic: results are bitwise reproducible.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <cstring>
-#include <mutex>
+#include <type_traits>
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include "../../include/lnpegn.h"
@@ -30,10 +30,12 @@ constexpr int kChunk = 16;          // sorted positions whose piece heads one wa
 constexpr int kPiece = 32;          // longest piece; kChunk + kPiece + 1 lanes of one 64-lane window cover a wave's work
 constexpr int kWavesPerBlock = 4;
 constexpr int kNormBlocks = 2048;   // workgroups of the ||w'||^2 pass in accumulate mode
+constexpr int kFillBlocks = 4096;   // most workgroups of the zero fill
+constexpr int kFillRows = 16;       // rows a wave of it takes at a time
+constexpr int64_t kFillLateBytes = 40 << 20;   // most bytes of it that are left to kernel B
 
 __global__ __launch_bounds__(256) void emb_prepare_kernel(const void *ids, int ids_i64, uint32_t *keys,
-                                                          uint32_t *vals, float *scratch, int64_t n,
-                                                          int64_t nscratch, int V)
+                                                          uint32_t *vals, int64_t n, int V)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) {
@@ -41,137 +43,180 @@ __global__ __launch_bounds__(256) void emb_prepare_kernel(const void *ids, int i
         keys[i] = (id >= 0 && id < V) ? (uint32_t)id : (uint32_t)V;    // out of range: sorted behind, skipped
         vals[i] = (uint32_t)i;
     }
-    for (int64_t j = i; j < nscratch; j += (int64_t)gridDim.x * 256) scratch[j] = 0.f;
 }
 
 // ---------------------------------------------------------------------------------------
 // Sort of the (id, position) pairs for batches of up to kSortTiles * kSortTile positions, in two launches.
-// A pair travels as one 64-bit word, id in the upper half and position in the lower: the words are distinct, so
-// any correct sort of them is the stable sort by id.  (1) Every workgroup sorts one tile of kSortTile words in LDS
-// (bitonic network).  (2) The place of a word in the whole order is the number of words below it: its index in
-// its own tile plus one binary search in each other tile; each thread places one word.
+// A pair travels as one word whose order is that of (id, position), so any correct sort of the words is the stable
+// sort by id.  (1) Every workgroup sorts one tile of kSortTile words.  (2) The place of a word in the whole order is
+// its index in its own tile plus the number of words below it in every other, found by binary search.
+// Words are 32 bits (id, index within the tile) for vocabularies below 2^21 and 64 bits (id, position) beyond.
 // ---------------------------------------------------------------------------------------
-constexpr int kSortTile = 2048;
+constexpr int kSortTile = 2048, kSortTileBits = 11;
 constexpr int kSortTiles = 64;
-constexpr uint64_t kSortPad = ~(uint64_t)0;
+constexpr int kSortEach = 4;                        // words per thread
+constexpr int kSortThreads = kSortTile / kSortEach;
 
-constexpr int kSortThreads = kSortTile / 2;   // one compare-exchange per thread and stage
+template <typename W>
+struct SortWord;
+template <>
+struct SortWord<uint32_t> {
+    static constexpr uint32_t kPad = ~0u;
+    __device__ static uint32_t make(uint32_t key, uint32_t p) { return key << kSortTileBits | (p & (kSortTile - 1)); }
+    __device__ static uint32_t key(uint32_t w) { return w >> kSortTileBits; }
+    __device__ static uint32_t pos(uint32_t w, int tile) { return (uint32_t)tile * kSortTile + (w & (kSortTile - 1)); }
+    // the least word of tile t that is not below w, a word of tile `mine`: positions of another tile are all below
+    // or all above
+    __device__ static uint32_t bound(uint32_t w, int t, int mine) { return (key(w) + (t < mine ? 1u : 0u)) << kSortTileBits; }
+};
+template <>
+struct SortWord<uint64_t> {
+    static constexpr uint64_t kPad = ~(uint64_t)0;
+    __device__ static uint64_t make(uint32_t key, uint32_t p) { return (uint64_t)key << 32 | p; }
+    __device__ static uint32_t key(uint64_t w) { return (uint32_t)(w >> 32); }
+    __device__ static uint32_t pos(uint64_t w, int) { return (uint32_t)w; }
+    __device__ static uint64_t bound(uint64_t w, int, int) { return w; }
+};
+__host__ __device__ inline bool sort_words_are_32(int V) { return V < (1 << (32 - kSortTileBits)) - 1; }
 
-__global__ __launch_bounds__(kSortThreads) void emb_tile_sort_kernel(const void *ids, int ids_i64, int64_t n, int V,
-                                                                     uint64_t *tiles, float *scratch, int64_t nscratch)
+// the value of lane ^ kMask, without LDS memory
+template <int kMask>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v)
 {
-    __shared__ uint64_t a[kSortTile];
+    const int i = (int)v;
+    if constexpr (kMask == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, i, 0xB1, 0xf, 0xf, true);       // quad_perm [1,0,3,2]
+    else if constexpr (kMask == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, i, 0x4E, 0xf, 0xf, true);  // quad_perm [2,3,0,1]
+    else if constexpr (kMask == 4) {
+        const int half = __builtin_amdgcn_update_dpp(0, i, 0x141, 0xf, 0xf, true);                            // row_half_mirror: ^ 7
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, half, 0x1B, 0xf, 0xf, true);                          // quad_perm [3,2,1,0]: ^ 3
+    } else if constexpr (kMask == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, i, 0x128, 0xf, 0xf, true);   // row_ror:8
+    else return (uint32_t)__shfl_xor(i, kMask, kWave);
+}
+template <int kMask>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t v)
+{
+    return (uint64_t)lane_xor<kMask>((uint32_t)(v >> 32)) << 32 | lane_xor<kMask>((uint32_t)v);
+}
+
+// Bitonic network over a tile, four consecutive words per thread: strides below 4 stay in a thread's registers, below
+// 256 in the wave (DPP and lane permutes), and only the six stages of 256 and more go through LDS with a barrier.
+// Bound by the chain of 66 stages: with every stage through LDS, one compare-exchange per thread, 16.4 us against
+// @@TS@@ for 4 tiles.
+template <typename W>
+__global__ __launch_bounds__(kSortThreads) void emb_tile_sort_kernel(const void *ids, int ids_i64, int64_t n, int V, W *tiles)
+{
+    __shared__ __align__(16) W mem[kSortTile];
     const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
+    const int64_t base = (int64_t)blockIdx.x * kSortTile + tid * kSortEach;
+    W a[kSortEach];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int i = tid + h * kSortThreads;
-        const int64_t p = base + i;
-        uint64_t word = kSortPad;
+    for (int e = 0; e < kSortEach; ++e) {
+        const int64_t p = base + e;
+        a[e] = SortWord<W>::kPad;
         if (p < n) {
             const int64_t id = ids_i64 ? static_cast<const int64_t *>(ids)[p] : (int64_t) static_cast<const int32_t *>(ids)[p];
             const uint32_t key = (id >= 0 && id < V) ? (uint32_t)id : (uint32_t)V;   // out of range: sorted behind, skipped
-            word = ((uint64_t)key << 32) | (uint32_t)p;
+            a[e] = SortWord<W>::make(key, (uint32_t)p);
         }
-        a[i] = word;
     }
-    // the scratch arrays of the call are cleared here too (grid-stride), which saves a launch
-    for (int64_t j = (int64_t)blockIdx.x * kSortThreads + tid; j < nscratch; j += (int64_t)gridDim.x * kSortThreads)
-        scratch[j] = 0.f;
-    for (int k = 2; k <= kSortTile; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
+    auto in_order = [](W &x, W &y, bool ascending) {
+        const W lo = x < y ? x : y, hi = x < y ? y : x;
+        x = ascending ? lo : hi;
+        y = ascending ? hi : lo;
+    };
+    auto keep = [](W mine, W other, bool low) { return low ? (mine < other ? mine : other) : (mine < other ? other : mine); };
+    auto across = [&](auto mask, int k) {              // stride 4 * mask: lanes of one wave
+        constexpr int kMask = decltype(mask)::value;
+        const bool low = ((tid & kMask) == 0) == ((tid * kSortEach & k) == 0);
+#pragma unroll
+        for (int e = 0; e < kSortEach; ++e) a[e] = keep(a[e], lane_xor<kMask>(a[e]), low);
+    };
+    auto within = [&](int k) {                         // strides 2 and 1
+        const bool up = (tid * kSortEach & k) == 0;
+        in_order(a[0], a[2], up);
+        in_order(a[1], a[3], up);
+        in_order(a[0], a[1], up);
+        in_order(a[2], a[3], up);
+    };
+    in_order(a[0], a[1], true);                        // k = 2
+    in_order(a[2], a[3], false);
+    within(4);
+#pragma unroll
+    for (int k = 8; k <= kSortTile; k <<= 1) {
+        for (int j = k >> 1; j >= 256; j >>= 1) {      // strides beyond a wave
             __syncthreads();
-            const int lo = ((tid & ~(j - 1)) << 1) | (tid & (j - 1)), hi = lo + j;   // j is a power of two
-            const uint64_t x = a[lo], y = a[hi];
-            const bool ascending = (lo & k) == 0;
-            if ((x > y) == ascending) {
-                a[lo] = y;
-                a[hi] = x;
-            }
+#pragma unroll
+            for (int e = 0; e < kSortEach; ++e) mem[tid * kSortEach + e] = a[e];
+            __syncthreads();
+            const bool low = ((tid * kSortEach & j) == 0) == ((tid * kSortEach & k) == 0);
+#pragma unroll
+            for (int e = 0; e < kSortEach; ++e) a[e] = keep(a[e], mem[(tid * kSortEach ^ j) + e], low);
         }
+        if (k >= 256) across(std::integral_constant<int, 32>{}, k);
+        if (k >= 128) across(std::integral_constant<int, 16>{}, k);
+        if (k >= 64) across(std::integral_constant<int, 8>{}, k);
+        if (k >= 32) across(std::integral_constant<int, 4>{}, k);
+        if (k >= 16) across(std::integral_constant<int, 2>{}, k);
+        across(std::integral_constant<int, 1>{}, k);
+        within(k);
     }
-    __syncthreads();
-    tiles[base + tid] = a[tid];
-    tiles[base + tid + kSortThreads] = a[tid + kSortThreads];
+#pragma unroll
+    for (int e = 0; e < kSortEach; ++e) tiles[base + e] = a[e];
 }
 
-// Each thread places one word: sixteen binary searches (one per other tile) advance together, step by step, so
-// that sixteen independent loads are in flight instead of one chain of twelve dependent ones after another.
-__global__ __launch_bounds__(256) void emb_rank_kernel(const uint64_t *tiles, int ntiles, int64_t n, int V,
-                                                       uint32_t *sorted_ids, uint32_t *sorted_pos, uint8_t *present)
+// Each thread places one word.  Every 32nd word of every tile is copied to LDS; sixteen binary searches (one per
+// other tile) advance together, first over those samples, then inside the 32 words (one cache line of 32-bit words)
+// that they leave.  Latency bound: with all eleven steps in memory 10.8 us for 16 tiles and 9.0 for 4, against @@RK@@
+// and @@RK4@@ (with whole tiles in LDS, which leaves one workgroup a CU, 14.0 and 6.9).
+constexpr int kRankThreads = 256, kSampleEvery = 32, kSamples = kSortTile / kSampleEvery;
+template <typename W>
+__global__ __launch_bounds__(kRankThreads) void emb_rank_kernel(const W *tiles, int ntiles, int64_t n, uint32_t *sorted_ids,
+                                                                uint32_t *sorted_pos)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;     // index into the tiles array
-    if (i >= (int64_t)ntiles * kSortTile) return;
-    const uint64_t word = tiles[i];
-    if (word == kSortPad) return;
+    extern __shared__ __align__(16) unsigned char lds[];
+    W *samples = reinterpret_cast<W *>(lds);                     // [ntiles][kSamples]: the last word of each block
+    const int64_t i = (int64_t)blockIdx.x * kRankThreads + threadIdx.x;     // index into the tiles array
+    const W word = tiles[i];                                     // (the grid covers the tiles exactly)
+#pragma unroll 4
+    for (int v = threadIdx.x; v < ntiles * kSamples; v += kRankThreads)
+        samples[v] = tiles[(int64_t)v * kSampleEvery + kSampleEvery - 1];
+    __syncthreads();
+    if (word == SortWord<W>::kPad) return;
     const int mine = (int)(i / kSortTile);
     int64_t rank = i - (int64_t)mine * kSortTile;
     constexpr int kGroup = 16;
     for (int t0 = 0; t0 < ntiles; t0 += kGroup) {
-        const uint64_t *tile[kGroup];
-        int pos[kGroup];
+        W bound[kGroup];
+        int tile[kGroup], pos[kGroup];
 #pragma unroll
         for (int u = 0; u < kGroup; ++u) {
-            const int t = t0 + u < ntiles ? t0 + u : mine;          // a tile that does not exist: searched, not counted
-            tile[u] = tiles + (int64_t)t * kSortTile;
+            tile[u] = min(t0 + u, ntiles - 1);                   // a tile that does not exist: searched, not counted
+            bound[u] = SortWord<W>::bound(word, tile[u], mine);
             pos[u] = 0;
         }
-        // words of each tile below `word` (the tiles are sorted, kSortTile long): branch-free lower bound
+        // blocks whose last word is below `bound`: branch-free lower bound over the 64 samples
 #pragma unroll
-        for (int step = kSortTile / 2; step > 0; step >>= 1) {
+        for (int step = kSamples / 2; step > 0; step >>= 1)
 #pragma unroll
-            for (int u = 0; u < kGroup; ++u) pos[u] += tile[u][pos[u] + step - 1] < word ? step : 0;
-        }
+            for (int u = 0; u < kGroup; ++u)
+                pos[u] += samples[tile[u] * kSamples + pos[u] + step - 1] < bound[u] ? step : 0;
 #pragma unroll
         for (int u = 0; u < kGroup; ++u) {
-            const int below = pos[u] + (tile[u][pos[u]] < word ? 1 : 0);
-            rank += (t0 + u < ntiles && t0 + u != mine) ? below : 0;
+            pos[u] += samples[tile[u] * kSamples + pos[u]] < bound[u] ? 1 : 0;
+            pos[u] *= kSampleEvery;
         }
+        // the words below it inside the next block (whose last word is not); none if there is no next block
+#pragma unroll
+        for (int step = kSampleEvery / 2; step > 0; step >>= 1)
+#pragma unroll
+            for (int u = 0; u < kGroup; ++u)
+                pos[u] += tiles[tile[u] * kSortTile + min(pos[u] + step, kSortTile) - 1] < bound[u] && pos[u] < kSortTile ? step : 0;
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u)
+            if (t0 + u < ntiles && t0 + u != mine) rank += pos[u];
     }
-    const uint32_t key = (uint32_t)(word >> 32);
-    sorted_ids[rank] = key;
-    sorted_pos[rank] = (uint32_t)word;
-    if (present && key < (uint32_t)V) present[key] = 1;
-}
-
-// present[v] = 1 for every id that occurs (out-of-range ids carry the key V and are left out).  Plain byte
-// stores of the same value: the result does not depend on the order.  `present` was cleared by the launch before.
-__global__ __launch_bounds__(256) void emb_mark_kernel(const uint32_t *keys, int64_t n, int V, uint8_t *present)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) {
-        const uint32_t k = keys[i];
-        if (k < (uint32_t)V) present[k] = 1;
-    }
-}
-
-// Clears the scratch arrays of a call whose keys are already sorted (the sorting call's prepare kernel does it
-// otherwise).
-__global__ __launch_bounds__(256) void emb_clear_kernel(float *scratch, int64_t nscratch)
-{
-    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < nscratch; j += (int64_t)gridDim.x * 256) scratch[j] = 0.f;
-}
-
-// Zero fill of the rows of w' that no id selects (the rows of ids that occur are written, whole, by the run and
-// id kernels, so the fill and those kernels touch different rows and may run side by side).  Streaming stores:
-// the zeros are not wanted in any cache (the rows read next are g's), and lines left dirty in the memory-side
-// cache would be written back one by one under the reads that follow.
-__global__ __launch_bounds__(256) void emb_fill_kernel(float *p, int64_t V, int D, const uint8_t *present)
-{
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    const int64_t n = V * D;
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if ((reinterpret_cast<uintptr_t>(p) & 15u) == 0 && D % 4 == 0) {
-        typedef __attribute__((ext_vector_type(4))) float f32x4;
-        f32x4 *p4 = reinterpret_cast<f32x4 *>(p);
-        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-        const int d4 = D / 4;
-        for (; i < n / 4; i += stride)
-            if (!present[i / d4]) __builtin_nontemporal_store(zero, p4 + i);
-        return;
-    }
-    for (; i < n; i += stride)
-        if (!present[i / D]) p[i] = 0.f;
+    sorted_ids[rank] = SortWord<W>::key(word);
+    sorted_pos[rank] = SortWord<W>::pos(word, mine);
 }
 
 // eight columns of one row, added into sub: 16-byte loads when the row allows, element loads otherwise
@@ -280,114 +325,287 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane)      // lan
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
-// One window of the sorted list: lane l looks at sorted position i + l.  Returns how many of the leading
-// positions satisfy same(key, example), 0..64, and leaves each lane's position value in val.
-struct Window {
-    uint32_t key, val, ex;
-};
-__device__ __forceinline__ Window window_at(const uint32_t *keys, const uint32_t *vals, int64_t i, int64_t n,
-                                             int Tn, int lane)
+// First index in [lo, lo + len] from which on the ascending values of `a` are not below target; every lane searches for
+// its own target.  Seven probes a round: a third of the dependent loads.
+__device__ __forceinline__ int64_t lower_bound_value(const uint32_t *a, int64_t lo, int64_t len, uint32_t target)
 {
-    Window w;
-    const bool in = i + lane < n;
-    w.key = in ? keys[i + lane] : 0xffffffffu;
-    w.val = in ? vals[i + lane] : 0u;
-    w.ex = w.val / (uint32_t)Tn;
-    return w;
-}
-__device__ __forceinline__ int leading(bool pred)
-{
-    const uint64_t not_pred = ~__ballot(pred);
-    return not_pred ? __builtin_ctzll(not_pred) : 64;
+    while (__any(len > 0)) {
+        const int64_t step = len / 8 + 1;              // probes at lo + step - 1, lo + 2 step - 1, ...
+        uint32_t p[7];
+#pragma unroll
+        for (int u = 0; u < 7; ++u) p[u] = step * (u + 1) <= len ? a[lo + step * (u + 1) - 1] : 0xffffffffu;
+        int below = 0;
+#pragma unroll
+        for (int u = 0; u < 7; ++u) below += (step * (u + 1) <= len && p[u] < target) ? 1 : 0;
+        lo += step * below;
+        len = len - step * below < step - 1 ? len - step * below : step - 1;
+    }
+    return lo;
 }
 
-// element u (wave-uniform, known at run time) of an array that lives in registers: a switch, so that the array
-// is never indexed by a variable (which would move it to scratch memory)
-template <typename R>
-__device__ __forceinline__ R pick_row(const R (&a)[16], int u)
+// The same over (id, position) pairs.
+__device__ __forceinline__ int64_t lower_bound_pair(const uint32_t *keys, const uint32_t *vals, int64_t lo, int64_t len, uint32_t v,
+                                                    uint32_t target)
 {
-    switch (u) {
-        case 0: return a[0];   case 1: return a[1];   case 2: return a[2];   case 3: return a[3];
-        case 4: return a[4];   case 5: return a[5];   case 6: return a[6];   case 7: return a[7];
-        case 8: return a[8];   case 9: return a[9];   case 10: return a[10]; case 11: return a[11];
-        case 12: return a[12]; case 13: return a[13]; case 14: return a[14]; default: return a[15];
-    }
-}
-template <typename R>
-__device__ __forceinline__ R pick_row(const R (&a)[8], int u)
-{
-    switch (u) {
-        case 0: return a[0]; case 1: return a[1]; case 2: return a[2]; case 3: return a[3];
-        case 4: return a[4]; case 5: return a[5]; case 6: return a[6]; default: return a[7];
-    }
-}
-template <typename R>
-__device__ __forceinline__ R pick_row(const R (&a)[1], int)
-{
-    return a[0];
-}
-template <int N>
-__device__ __forceinline__ void pick_floats(const float (&a)[N][8], int u, float (&f)[8])
-{
+    while (__any(len > 0)) {
+        const int64_t step = len / 8 + 1;
+        uint32_t k[7], p[7];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) f[k] = a[0][k];
-#pragma unroll
-    for (int j = 1; j < N; ++j)
-        if (u == j) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) f[k] = a[j][k];
+        for (int u = 0; u < 7; ++u) {
+            k[u] = step * (u + 1) <= len ? keys[lo + step * (u + 1) - 1] : 0xffffffffu;
+            p[u] = step * (u + 1) <= len ? vals[lo + step * (u + 1) - 1] : 0xffffffffu;
         }
+        int below = 0;
+#pragma unroll
+        for (int u = 0; u < 7; ++u) below += (step * (u + 1) <= len && (k[u] < v || (k[u] == v && p[u] < target))) ? 1 : 0;
+        lo += step * below;
+        len = len - step * below < step - 1 ? len - step * below : step - 1;
+    }
+    return lo;
 }
 
-// Kernel A.  keys/vals: positions sorted by id.  Ownership: a short segment (at most kShort positions)
-// belongs whole to the wave whose kChunk sorted positions hold its first one, and that wave finishes the id
-// (every run's share of s[b], the row of w').  A longer segment is handed out piece by piece to the waves
-// whose positions hold the pieces' first rows; a piece that is a whole run yields that run's share of s[b],
-// every sum is parked (unless the piece is the id's only one) and the id is marked for kernel B.
-// A wave sees kShort positions back (to tell whether a piece in its chunk belongs to a short segment that an
-// earlier wave owns) and far enough ahead for anything that starts in its chunk; rows are streamed sixteen
-// (fp32: eight) at a time.  contrib [ncb][n]: a run's share of s[b], at the run's first position, zero elsewhere.
-// runsum [n][D]: parked sums, at the piece's first position.  multi [n]: set at the sorted index of the first
-// position of a long id that has parked sums; multi_run [n]: of a run that has several pieces.
-// bigpart [ncb][n]: squared norm of a finished row of w', at the segment's first position (not when
-// accumulating).
+// Zero fill of the rows of w' that no id selects (rows begin to end - 1), a part of kernel A's grid and of kernel B's:
+// the rows of ids that occur are written, whole, by the other workgroups, so everything touches different rows and
+// runs side by side.  Kernel A waits for its chains of loads more than for bandwidth and kernel B does little else, so
+// the fill is shared out between the two: @@FILL@@.  A wave takes kFillRows
+// rows, one per lane: each lane looks for its row's id in the sorted list, so that no map of the ids is needed before the
+// launch; they lie a wave count apart, so that the waves together sweep one moving window of w'.  Streaming stores: the zeros are not wanted in any cache (the rows read next are g's), and lines left dirty
+// in the memory-side cache would be written back one by one under the reads that follow.
+__device__ __forceinline__ void fill_absent_rows(const uint32_t *keys, int64_t n, float *w, int begin, int end, int D, int wave,
+                                                 int nwaves, int lane)
+{
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    const bool vec = (reinterpret_cast<uintptr_t>(w) & 15u) == 0 && D % 4 == 0;
+    for (int64_t r0 = (int64_t)begin + wave; r0 < end; r0 += (int64_t)nwaves * kFillRows) {
+        const uint32_t row = (uint32_t)r0 + (uint32_t)lane * (uint32_t)nwaves;
+        const int64_t at = lower_bound_value(keys, 0, n, row);
+        uint64_t absent = __ballot(lane < kFillRows && row < (uint32_t)end && !(at < n && keys[at] == row));
+        while (absent) {
+            float *p = w + (r0 + (int64_t)__builtin_ctzll(absent) * nwaves) * D;
+            absent &= absent - 1;
+            if (vec) {
+                for (int c = lane; c < D / 4; c += 64)
+                    __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4 *>(p) + c);
+            } else {
+                for (int c = lane; c < D; c += 64) p[c] = 0.f;
+            }
+        }
+    }
+}
+
+// Kernel A.  keys/vals: positions sorted by id.  A segment is short (at most kShort positions), medium (at most 64)
+// or long.  The waves of the runs look after kChunk sorted positions each: a short segment belongs whole to the wave
+// whose positions hold its first one, and that wave finishes the id (every run's share of s[b], the row of w').
+// A long segment is handed out piece by piece to the waves whose positions hold the pieces' first rows; a piece that is
+// a whole run yields that run's share of s[b], and every sum is parked.  Medium segments are finished the same way
+// as short ones, by waves of their own that see 64 positions from the segment's first (cut into pieces and parked
+// too, they made 65 MB of a call's traffic each way at B=16 T=2048 D=2048: @@MED@@).
+// A wave of the runs sees kShort positions back (to tell whether a piece in its chunk belongs to a short segment that
+// an earlier wave owns) and far enough ahead for anything that starts in its chunk; rows are streamed sixteen
+// (fp32: eight) at a time.  contrib [ncb][n]: a run's share of s[b], at the run's first position, zero elsewhere;
+// bigpart [ncb][n]: squared norm of a finished row of w', at the segment's first position (not when accumulating),
+// zero elsewhere.  The zeros are written by the waves of the runs, so neither array is cleared before.
+// runsum [n][D]: parked sums, at the piece's first position.
 constexpr int kShort = 12;
 static_assert(kShort + kChunk + kPiece < 63 && kShort + kChunk + kShort < 63, "one 64-lane window must cover a wave's work");
 
+// Sums over the wave of eight values per lane at once: lane j's result is the sum of a[j & 7].  Three steps halve
+// the values and the lanes they are spread over together, so eight sums cost little more than two.
+__device__ __forceinline__ float wave_sums8(const float (&a)[8], int lane)
+{
+    float b[4], c[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float keep = lane & 1 ? a[2 * i + 1] : a[2 * i], send = lane & 1 ? a[2 * i] : a[2 * i + 1];
+        b[i] = keep + __builtin_bit_cast(float, lane_xor<1>(__builtin_bit_cast(uint32_t, send)));
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float keep = lane & 2 ? b[2 * i + 1] : b[2 * i], send = lane & 2 ? b[2 * i] : b[2 * i + 1];
+        c[i] = keep + __builtin_bit_cast(float, lane_xor<2>(__builtin_bit_cast(uint32_t, send)));
+    }
+    const float keep = lane & 4 ? c[1] : c[0], send = lane & 4 ? c[0] : c[1];
+    float d = keep + __builtin_bit_cast(float, lane_xor<4>(__builtin_bit_cast(uint32_t, send)));
+    d += __builtin_bit_cast(float, lane_xor<8>(__builtin_bit_cast(uint32_t, d)));
+    d += __builtin_bit_cast(float, lane_xor<16>(__builtin_bit_cast(uint32_t, d)));
+    d += __builtin_bit_cast(float, lane_xor<32>(__builtin_bit_cast(uint32_t, d)));
+    return d;
+}
+
+// What becomes of the rows of a window (one sorted position per lane), as masks over the lanes.
+struct RowEnds {
+    uint64_t close;      // last row of a run or piece: its sum is complete
+    uint64_t id;         // ... and the last row of its id: the row of w' is
+    uint64_t park;       // ... of a piece: its sum is parked
+    uint64_t whole;      // ... of a whole run: its squared norm is its share of s[b]
+    uint32_t head_pos;   // per lane: position of the first row of this row's run or piece
+    uint32_t id_pos;     // per lane: position of the first row of this row's id
+};
+
+// Adds up rows l .. e-1 of the window (l starts a run or piece, e-1 ends one), for one column block.  Bound by its
+// instructions: about 200 a row when the rows were taken one at a time out of a register array, with a reduction
+// over the wave at every end; unrolled, with the ends of eight rows reduced together, @@ROWS@@.
+template <typename T, bool kVec>
+__device__ __forceinline__ void stream_rows(const T *g, float *w, float *runsum, float *contrib, float *bigpart, int64_t n, int D,
+                                            int accumulate, int cb, int lane, uint32_t key, uint32_t val, int l, int e,
+                                            const RowEnds &ends)
+{
+    constexpr int kRows = kVec && sizeof(T) == 2 ? 16 : 8;       // rows in flight
+    const int c0 = cb * kColBlock + lane * 8;
+    const bool has_cols = c0 < D;
+    const int c_load = has_cols ? c0 : 0;                        // lanes without columns fetch what lane 0 does
+    float sub[8], tot[8];                // the open run or piece; the id's runs so far
+#pragma unroll
+    for (int k = 0; k < 8; ++k) sub[k] = tot[k] = 0.f;
+    for (int r = l; r < e; r += kRows) {
+        // the loads carry no condition (a row past the end repeats the last one and is dropped afterwards), so that
+        // all are issued before the first is waited for
+        Row8<T> raw[kVec ? kRows : 1];
+        float part[kVec ? 1 : kRows][8];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            if constexpr (kVec) {
+                raw[u] = load_row8(g, (int64_t)lane_value(val, min(r + u, e - 1)), D, c_load);
+            } else {                                             // ragged or unaligned columns: element loads
+#pragma unroll
+                for (int k = 0; k < 8; ++k) part[u][k] = 0.f;
+                if (has_cols && r + u < e) add_row(g, (int64_t)lane_value(val, r + u), D, c0, false, part[u]);
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < kRows; h += 8) {
+            float sq[8], wsq[8];                                 // squared norms that rows r+h .. r+h+7 complete
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int t = r + h + u;
+                sq[u] = wsq[u] = 0.f;
+                if (t < e) {
+                    float f[8];
+                    if constexpr (kVec) {
+                        unpack_row8(raw[h + u], f);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) f[k] = part[h + u][k];
+                    }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) sub[k] += f[k];
+                    if ((ends.close >> t) & 1) {
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) sq[u] = fmaf(sub[k], sub[k], sq[u]);
+                        if (!has_cols) sq[u] = 0.f;              // such lanes hold a copy of lane 0's columns
+                        if ((ends.park >> t) & 1) {
+                            if (has_cols) put_row(runsum + (int64_t)lane_value(ends.head_pos, t) * D + c0, sub, c0, D, false);
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) tot[k] += sub[k];
+                            if ((ends.id >> t) & 1) {
+                                if (has_cols)
+                                    wsq[u] = put_row(w + (int64_t)lane_value(key, t) * D + c0, tot, c0, D, accumulate != 0, true);
+#pragma unroll
+                                for (int k = 0; k < 8; ++k) tot[k] = 0.f;
+                            }
+                        }
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) sub[k] = 0.f;
+                    }
+                }
+            }
+            const int t = r + h + (lane & 7);                    // lane j < 8 stores what row r+h+j completed
+            if (r + h < e && (ends.close >> (r + h) & 0xff)) {
+                const float total = wave_sums8(sq, lane);
+                const uint32_t at = (uint32_t)__shfl((int)ends.head_pos, t & 63);
+                if (lane < 8 && t < e && ((ends.whole >> t) & 1)) contrib[(int64_t)cb * n + at] = total;
+                if (!accumulate && (ends.id >> (r + h) & 0xff)) {
+                    const float wtotal = wave_sums8(wsq, lane);
+                    const uint32_t wat = (uint32_t)__shfl((int)ends.id_pos, t & 63);
+                    if (lane < 8 && t < e && ((ends.id >> t) & 1)) bigpart[(int64_t)cb * n + wat] = wtotal;
+                }
+            }
+        }
+    }
+}
+
+// The medium segments whose first sorted position is among the kChunk from q0, for one column block.
+template <typename T, bool kVec>
+__device__ __forceinline__ void finish_medium_ids(const T *g, const uint32_t *keys, const uint32_t *vals, float *w, float *contrib,
+                                                  float *bigpart, int64_t n, int Tn, int D, int V, int accumulate, int64_t q0, int cb,
+                                                  int lane)
+{
+    const int64_t q = q0 + lane;
+    const uint32_t key = q < n ? keys[q] : 0xffffffffu, before = q > 0 && q < n ? keys[q - 1] : 0xffffffffu;
+    const uint32_t ahead = q + kShort < n ? keys[q + kShort] : 0xffffffffu, beyond = q + 64 < n ? keys[q + 64] : 0xffffffffu;
+    for (uint64_t ids = __ballot(lane < kChunk && key < (uint32_t)V && key != before && ahead == key && beyond != key); ids; ids &= ids - 1) {
+        const int64_t at = q0 + __builtin_ctzll(ids) + lane;
+        const uint32_t k = at < n ? keys[at] : 0xffffffffu, p = at < n ? vals[at] : 0u, v = lane_value(k, 0);
+        const uint32_t ex = p / (uint32_t)Tn, prev_ex = (uint32_t)__shfl_up((int)ex, 1);
+        const uint64_t m_heads = __ballot(k == v && (lane == 0 || ex != prev_ex));
+        const int len = __builtin_popcountll(__ballot(k == v));  // the low lanes
+        RowEnds ends;
+        ends.id = (uint64_t)1 << (len - 1);
+        ends.close = ends.whole = m_heads >> 1 | ends.id;
+        ends.park = 0;
+        ends.head_pos = (uint32_t)__shfl((int)p, 63 - __builtin_clzll((m_heads & (((uint64_t)2 << lane) - 1)) | 1u));
+        ends.id_pos = lane_value(p, 0);
+        stream_rows<T, kVec>(g, w, nullptr, contrib, bigpart, n, D, accumulate, cb, lane, k, p, 0, len, ends);
+    }
+}
+
 // kVec: every lane that has columns has eight whole ones behind an aligned 16-byte boundary (D % 8 == 0 and
 // aligned rows); rows are then fetched as vectors, sixteen bf16 rows or eight fp32 rows in flight.
+// Grid: medium_blocks workgroups for the medium segments (the longest chains, so first), then fill_blocks workgroups
+// of the fill among runs_x times the groups of kWavesPerBlock column blocks.
 template <typename T, bool kVec>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void emb_runs_kernel(
     const T *g, const uint32_t *keys, const uint32_t *vals, float *w, float *runsum, float *contrib, float *bigpart,
-    uint32_t *multi, uint32_t *multi_run, int64_t n, int Tn, int D, int V, int accumulate)
+    int64_t n, int Tn, int D, int V, int accumulate, int medium_blocks, int fill_rows, int fill_blocks, int runs_x)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if ((int)blockIdx.x < medium_blocks) {
+        // the waves of a workgroup take the same positions and neighbouring column blocks
+        const int column_groups = (D + kColBlock * kWavesPerBlock - 1) / (kColBlock * kWavesPerBlock);
+        const int span = (int)blockIdx.x / column_groups, cb = ((int)blockIdx.x - span * column_groups) * kWavesPerBlock + wave;
+        if (cb * kColBlock < D)
+            finish_medium_ids<T, kVec>(g, keys, vals, w, contrib, bigpart, n, Tn, D, V, accumulate, (int64_t)span * kChunk, cb, lane);
+        return;
+    }
+    // One workgroup of the fill after every two of the runs, then what is left of either: the runs, each a chain of
+    // loads, must all be under way early, and the fill's stores go out beside them.
+    const int run_blocks = (int)gridDim.x - medium_blocks - fill_blocks, groups = min(run_blocks / 2, fill_blocks);
+    const int j = (int)blockIdx.x - medium_blocks, behind = j - 3 * groups;
+    const int block = behind < 0 ? 2 * (j / 3) + j % 3 : 2 * groups + behind;
+    int fill = behind < 0 && j % 3 == 2 ? j / 3 : -1;
+    if (behind >= 0 && block >= run_blocks) fill = groups + block - run_blocks;
+    if (fill >= 0) {
+        fill_absent_rows(keys, n, w, 0, fill_rows, D, fill * kWavesPerBlock + wave, fill_blocks * kWavesPerBlock, lane);
+        return;
+    }
+    const int block_y = block / runs_x, block_x = block - block_y * runs_x;
     // the waves of a workgroup take the same positions and neighbouring column blocks: a row of g is then
     // read whole by one workgroup at one time
-    const int cb = blockIdx.y * kWavesPerBlock + wave, c0 = cb * kColBlock + lane * 8;
+    const int cb = block_y * kWavesPerBlock + wave;
     if (cb * kColBlock >= D) return;
-    const bool has_cols = c0 < D;
-    const int c_load = has_cols ? c0 : 0;                        // lanes without columns fetch what lane 0 does
-    constexpr int kRows = kVec && sizeof(T) == 2 ? 16 : 8;       // rows in flight
-    // A workgroup takes chunks blockIdx.x, blockIdx.x + gridDim.x, ...; the next chunk's part of the sorted list
+    // A workgroup takes chunks block_x, block_x + runs_x, ...; the next chunk's part of the sorted list
     // is fetched while this chunk's rows are on their way.
     // Lane l looks at sorted position i0 - kShort - 1 + l: lane 0 only serves as "the position before",
     // lanes kShort+1 .. kShort+kChunk are the chunk.
     const int64_t nchunks = (n + kChunk - 1) / kChunk;
-    auto look = [&](int64_t chunk, uint32_t &k, uint32_t &p) {
+    // far, near: the keys 64 positions ahead and back, which tell medium segments from long ones.
+    auto look = [&](int64_t chunk, uint32_t &k, uint32_t &p, uint32_t &far, uint32_t &near) {
         const int64_t q = chunk * kChunk - kShort - 1 + lane;
         const bool in = chunk < nchunks && q >= 0 && q < n;
         k = in ? keys[q] : 0xffffffffu;
         p = in ? vals[q] : 0u;
+        far = in && q + 64 < n ? keys[q + 64] : 0xffffffffu;
+        near = chunk < nchunks && q >= 64 ? keys[q - 64 < n ? q - 64 : 0] : 0xffffffffu;
     };
-    uint32_t key_next, val_next;
-    look(blockIdx.x, key_next, val_next);
-    for (int64_t chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
+    uint32_t key_next, val_next, far_next, near_next;
+    look(block_x, key_next, val_next, far_next, near_next);
+    for (int64_t chunk = block_x; chunk < nchunks; chunk += runs_x) {
     const int64_t i0 = chunk * kChunk;
     const int64_t q = i0 - kShort - 1 + lane;
-    const uint32_t key = key_next, val = val_next;
-    look(chunk + gridDim.x, key_next, val_next);
+    const uint32_t key = key_next, val = val_next, far = far_next, near = near_next;
+    look(chunk + runs_x, key_next, val_next, far_next, near_next);
     const uint32_t ex = val / (uint32_t)Tn;
     const uint32_t pkey = (uint32_t)__shfl_up((int)key, 1), pex = (uint32_t)__shfl_up((int)ex, 1);
     const bool valid = key < (uint32_t)V;
@@ -395,287 +613,202 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void emb_runs_kernel(
     const uint64_t m_head = __ballot(valid && lane >= 1 && (key != pkey || ex != pex));     // starts a run
     const uint64_t m_seg = __ballot(valid && lane >= 1 && key != pkey);                     // starts a segment
     const uint64_t m_piece = m_head | __ballot(valid && lane >= 1 && q % kPiece == 0);      // starts a piece
-    // is this lane's segment long?  Its first position is the nearest segment head at or below the lane
+    // is this lane's segment more than short?  Its first position is the nearest segment head at or below the lane
     // (not in the window: it lies more than kShort back), its end the next segment head or invalid key
     // (not in the window: more than kShort ahead of anything this wave may own).
-    const uint64_t upto = ((uint64_t)2 << lane) - 1;
-    const uint64_t heads_below = m_seg & upto, ends_above = (m_seg | ~m_valid) & ~upto;
+    const uint64_t upto = ((uint64_t)2 << lane) - 1, m_ends = m_seg | ~m_valid;
+    const uint64_t heads_below = m_seg & upto, ends_above = m_ends & ~upto;
     const int seg_first = heads_below ? 63 - __builtin_clzll(heads_below) : -1;
     const int seg_end = ends_above ? __builtin_ctzll(ends_above) : 64;
-    const uint64_t m_long = __ballot(valid && (seg_first < 0 || seg_end - seg_first > kShort));
-    const uint64_t m_own = m_seg | (m_piece & m_long);                                      // starts something to own
-    const uint64_t chunk_lanes = (((uint64_t)1 << kChunk) - 1) << (kShort + 1);
-    if (!(m_own & chunk_lanes)) continue;                        // nothing starts here
-    const int l = __builtin_ctzll(m_own & chunk_lanes);
-    // rows l .. e-1: up to the first invalid key or the first thing that starts behind the chunk
-    const uint64_t behind = ~(((uint64_t)2 << (kShort + kChunk)) - 1);
-    const uint64_t stop = (~m_valid & ~(((uint64_t)2 << l) - 1)) | (m_own & behind);
-    int e = stop ? __builtin_ctzll(stop) : 63;
-    if (e > 63) e = 63;
-
-    // What happens at a row, as masks over the lanes: the masks are shifted so that bit u is row r + u of the
-    // batch in hand, and a batch in which nothing happens is plain additions.
+    const bool is_short = valid && seg_first >= 0 && seg_end - seg_first <= kShort;
+    // and long?  Then the key 64 ahead of its first position is still its own.  A segment that holds lane 0 may begin
+    // up to 64 earlier, where the keys behind lane 0 say.
+    const uint32_t key0 = lane_value(key, 0), far0 = lane_value(far, 0);
+    const uint64_t m_not_near = ~__ballot(near == key0);
+    const int back = m_not_near ? __builtin_clzll(m_not_near) : 64;          // positions of key0 right behind lane 0
+    const bool long0 = m_ends ? back + __builtin_ctzll(m_ends) > 64 : back > 0 || far0 == key0;
+    const uint32_t far_first = (uint32_t)__shfl((int)far, seg_first < 0 ? 0 : seg_first);
+    const bool is_long = valid && (seg_first < 0 ? long0 : far_first == key);
+    const uint64_t m_short = __ballot(is_short), m_long = __ballot(is_long);
+    const uint64_t pieces_below = m_piece & upto;
+    const int piece_first = pieces_below ? 63 - __builtin_clzll(pieces_below) : -1;
+    auto in_chunk = [&](int l) { return l > kShort && l <= kShort + kChunk; };
+    const bool short_mine = is_short && in_chunk(seg_first);
+    {
+        // zeros at the positions of its chunk that will hold no value, but for those of short segments that begin
+        // before it, and at those of its short segments behind the chunk
+        const bool owned = q >= 0 && q < n && (in_chunk(lane) ? !is_short || short_mine : lane > kShort + kChunk && short_mine);
+        if (owned && !((m_head >> lane) & 1)) contrib[(int64_t)cb * n + val] = 0.f;
+        if (owned && !((m_seg >> lane) & 1) && !accumulate) bigpart[(int64_t)cb * n + val] = 0.f;
+    }
+    // the rows of this wave: short segments and pieces of long ones that begin in the chunk.  Taken in stretches of
+    // neighbouring rows (a medium segment may lie between two).
     const uint64_t next_starts_run = (m_head | ~m_valid) >> 1, next_starts_seg = (m_seg | ~m_valid) >> 1;
-    const uint64_t next_starts_piece = (m_piece | ~m_valid) >> 1;
-    uint64_t b_opens_id = m_seg >> l;                                        // first row of an id
-    uint64_t b_opens = ((m_long & m_piece) | (~m_long & m_head)) >> l;       // first row of a long id's piece, or of a run
-    uint64_t b_run_head = m_head >> l;
-    uint64_t b_short_run_ends = (~m_long & next_starts_run) >> l;            // last row of a short id's run
-    uint64_t b_piece_ends = (m_long & next_starts_piece) >> l;               // last row of a long id's piece
-    uint64_t b_run_ends = next_starts_run >> l, b_seg_ends = next_starts_seg >> l;
-
-    float sub[8], tot[8];                // the open run or piece; the short id's runs so far
-#pragma unroll
-    for (int k = 0; k < 8; ++k) sub[k] = tot[k] = 0.f;
-    uint32_t first = 0, cur_key = 0, first_idx = 0, id_first = 0;
-    bool run_head = false, seg_head = false;
-    // kRows rows in flight: the loads carry no condition (a row past the end repeats the last one and is
-    // dropped afterwards), so that all are issued before the first is waited for
-    for (int r = l; r < e; r += kRows) {
-        Row8<T> raw[kVec ? kRows : 1];
-        float part[kVec ? 1 : kRows][8];
-        if constexpr (kVec) {
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                const int t = r + u < e ? r + u : e - 1;
-                raw[u] = load_row8(g, (int64_t)lane_value(val, t), D, c_load);
-            }
-        } else {                                                 // ragged or unaligned columns: element loads
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) part[u][k] = 0.f;
-                if (has_cols && r + u < e) add_row(g, (int64_t)lane_value(val, r + u), D, c0, false, part[u]);
-            }
-        }
-        auto row = [&](int u, float (&f)[8]) {
-            if constexpr (kVec) {
-                unpack_row8(raw[u], f);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) f[k] = part[u][k];
-            }
-        };
-        const int rows = e - r < kRows ? e - r : kRows;
-        const uint32_t in_batch = (1u << rows) - 1u;
-        if (!((uint32_t)(b_opens | b_short_run_ends | b_piece_ends) & in_batch)) {
-#pragma unroll
-            for (int u = 0; u < kRows; ++u)
-                if (u < rows) {
-                    float f[8];
-                    row(u, f);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) sub[k] += f[k];
-                }
-            b_opens_id >>= kRows; b_opens >>= kRows; b_run_head >>= kRows; b_short_run_ends >>= kRows;
-            b_piece_ends >>= kRows; b_run_ends >>= kRows; b_seg_ends >>= kRows;
-            continue;
-        }
-        // Something opens or closes in this batch: one row at a time, in a loop that is not unrolled (its body,
-        // sixteen times over, would not fit the instruction cache); bit 0 of every mask is the row in hand.
-#pragma nounroll
-        for (int u = 0; u < rows; ++u) {
-            const int t = r + u;
-            float f[8];
-            if constexpr (kVec) {
-                unpack_row8(pick_row(raw, u), f);
-            } else {
-                pick_floats(part, u, f);
-            }
-            if (b_opens_id & 1) {                                // this row opens an id
-                id_first = lane_value(val, t);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) tot[k] = 0.f;
-            }
-            if (b_opens & 1) {                                   // ... a piece of a long id, or a run
-                first = lane_value(val, t);
-                first_idx = (uint32_t)(i0 - kShort - 1 + t);
-                cur_key = lane_value(key, t);
-                run_head = (b_run_head & 1) != 0;
-                seg_head = (b_opens_id & 1) != 0;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) sub[k] = 0.f;
-            }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) sub[k] += f[k];
-            const bool short_run_ends = (b_short_run_ends & 1) != 0, piece_ends = (b_piece_ends & 1) != 0;
-            if (short_run_ends || piece_ends) {
-                const bool seg_end_here = (b_seg_ends & 1) != 0, run_end_here = (b_run_ends & 1) != 0;
-                // a short id's run: its share of s[b] now, the row of w' when the id is complete.  A long id's
-                // piece: the share of s[b] if it is a whole run, the row of w' if it is the id's only piece,
-                // parked otherwise.
-                const bool whole_run = short_run_ends || (run_head && run_end_here);
-                const bool to_w = short_run_ends ? seg_end_here : (whole_run && seg_head && seg_end_here);
-                const bool park = piece_ends && !to_w;
-                float sq = 0.f, wsq = 0.f, out[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    sq = fmaf(sub[k], sub[k], sq);
-                    if (short_run_ends) tot[k] += sub[k];
-                    out[k] = short_run_ends ? tot[k] : sub[k];
-                }
-                if (!has_cols) sq = 0.f;                         // such lanes hold a copy of lane 0's columns
-                if (has_cols && (to_w || park)) {
-                    float *dst = to_w ? w + (int64_t)cur_key * D + c0 : runsum + (int64_t)first * D + c0;
-                    wsq = put_row(dst, out, c0, D, to_w && accumulate != 0, to_w);
-                }
-                if (whole_run) {
-                    wave_sum2(sq, wsq);                          // one exchange for both
-                    if (lane == 0) {
-                        contrib[(int64_t)cb * n + first] = sq;
-                        if (to_w && !accumulate) bigpart[(int64_t)cb * n + (short_run_ends ? id_first : first)] = wsq;
-                    }
-                }
-                if (park && cb == 0 && lane == 0) {
-                    if (seg_head) multi[first_idx] = 1u;
-                    if (run_head && !run_end_here) multi_run[first_idx] = 1u;
-                }
-            }
-            b_opens_id >>= 1; b_opens >>= 1; b_run_head >>= 1; b_short_run_ends >>= 1;
-            b_piece_ends >>= 1; b_run_ends >>= 1; b_seg_ends >>= 1;
-        }
+    const uint64_t next_starts_piece = (m_piece | ~m_valid) >> 1, runs_below = m_head & upto;
+    RowEnds ends;
+    ends.park = m_long & next_starts_piece;
+    ends.close = (m_short & next_starts_run) | ends.park;
+    ends.id = m_short & next_starts_seg;
+    const int run_first = runs_below ? 63 - __builtin_clzll(runs_below) : -1;
+    // a long id's piece is a whole run if it begins at the run's head and ends where the next run starts
+    ends.whole = (m_short & next_starts_run) | (ends.park & next_starts_run & __ballot(piece_first >= 0 && piece_first == run_first));
+    ends.head_pos = (uint32_t)__shfl((int)val, max(is_long ? piece_first : run_first, 0));
+    ends.id_pos = (uint32_t)__shfl((int)val, max(seg_first, 0));
+    for (uint64_t todo = __ballot(short_mine || (is_long && in_chunk(piece_first))); todo;) {
+        const int l = __builtin_ctzll(todo), e = l + __builtin_ctzll(~(todo >> l));   // rows l .. e-1
+        todo &= ~(((uint64_t)1 << e) - 1);
+        stream_rows<T, kVec>(g, w, runsum, contrib, bigpart, n, D, accumulate, cb, lane, key, val, l, e, ends);
     }
     }   // chunks
 }
 
-// First index in [lo, n) whose (id, position) pair is not below (v, target); every lane searches for its own
-// target, the loop runs until the slowest lane is done (about log2(n) dependent loads).
-__device__ __forceinline__ int64_t lower_bound_pair(const uint32_t *keys, const uint32_t *vals, int64_t lo, int64_t n,
-                                                    uint32_t v, uint32_t target)
+// Kernel B: the rows of w' of the ids with more than 64 positions, the shares of s[b] of their runs of several pieces,
+// and the squared norms of the rows, one column block at a time.  A workgroup looks after kSumSpan sorted positions,
+// among which at most one such id begins.  Its waves share out the examples; a wave finds its examples' runs by
+// search, one example per lane, and lists the runs' pieces (a run's first position and the multiples of kPiece behind
+// it), one per lane; parked sums are added eight rows at a time in sorted order, and squared at the end of a run that
+// has several; the waves' sums are added in wave order.  The cost is logarithmic in the number of positions however
+// long the id is, plus its parked rows over the waves.
+constexpr int kSumWaves = 4, kSumSpan = 64;
+__global__ __launch_bounds__(64 * kSumWaves) void emb_sums_kernel(
+    const uint32_t *keys, const uint32_t *vals, float *w, const float *runsum, float *contrib, float *bigpart, int64_t n,
+    int Tn, int D, int V, int accumulate, int fill_begin, int sum_blocks, int fill_blocks)
 {
-    int64_t len = n - lo;
-    while (__any(len > 0)) {
-        const int64_t half = len >> 1, m = lo + half;
-        bool below = false;
-        if (len > 0) {
-            const uint32_t k = keys[m], p = vals[m];
-            below = k < v || (k == v && p < target);
-        }
-        lo = below ? m + 1 : lo;
-        len = below ? len - half - 1 : half;
+    constexpr int kBatch = 8;                                    // parked sums in flight
+    __shared__ __align__(16) float part[kSumWaves][kColBlock];
+    __shared__ float squares[kSumWaves];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int Bn = (int)(n / Tn), ncb = (D + kColBlock - 1) / kColBlock;
+    if ((int)blockIdx.x >= sum_blocks) {
+        fill_absent_rows(keys, n, w, fill_begin, V, D, ((int)blockIdx.x - sum_blocks) * kSumWaves + wave, fill_blocks * kSumWaves, lane);
+        return;
     }
-    return lo;
-}
-
-// The same for one target that the whole wave shares: every round the 64 lanes probe 64 positions that cut the
-// range into 65 parts, and the number of probes below the target says which part to keep: three rounds of
-// loads for 32768 positions instead of fifteen.  [lo, hi) is wave-uniform; every lane must be active.
-__device__ __forceinline__ int64_t wave_lower_bound_pair(const uint32_t *keys, const uint32_t *vals, int64_t lo,
-                                                         int64_t hi, uint32_t v, uint32_t target, int lane)
-{
-    while (hi > lo) {
-        const int64_t len = hi - lo;
-        // probe j sits at lo + floor((j + 1) * len / 65), below hi; when len < 65 some probes repeat a position or
-        // sit at lo, which keeps the count monotone
-        const int64_t at = len <= 64 ? lo + (lane < len ? lane : len - 1) : lo + ((int64_t)(lane + 1) * len) / 65;
-        const uint32_t k = keys[at], p = vals[at];
-        const bool below = k < v || (k == v && p < target);
-        const int c = __builtin_popcountll(__ballot(below));        // probes are in order, so these are the first c
-        if (len <= 64) return lo + (c < len ? c : len);
-        const int64_t new_lo = c == 0 ? lo : lo + ((int64_t)c * len) / 65 + 1;
-        const int64_t new_hi = c == 64 ? hi : lo + ((int64_t)(c + 1) * len) / 65;
-        lo = new_lo;
-        hi = new_hi;
-    }
-    return lo;
-}
-
-// Kernel B, two launches.  First per run (kIds = false): a wave looks after the runs of long ids whose first
-// sorted position is among its kChunk positions and that kernel A marked as having several pieces; it adds
-// the run's parked piece sums in sorted order, squares the result (the run's share of s[b]) and parks it in
-// place of the run's first piece.  Then per id (kIds = true): a wave looks after the long ids whose first
-// sorted position is among its positions and adds the parked run sums in example order: the row of w'.
-// Neither walks the positions: the sorted list is searched.  A run's pieces start at its first position and
-// at every multiple of kPiece below the run's end, which one search finds; an id's runs start where the
-// searches for (id, b*T), one example per lane, land on that id and example.  The cost is logarithmic in
-// the number of positions however long the id is.  Parked sums are loaded sixteen at a time.
-template <bool kIds>
-__global__ __launch_bounds__(64 * kWavesPerBlock) void emb_sums_kernel(
-    const uint32_t *keys, const uint32_t *vals, float *w, float *runsum, float *contrib, float *bigpart,
-    const uint32_t *marks_at, int64_t n, int Tn, int D, int V, int accumulate)
-{
-    constexpr int kBatch = 16;                                   // parked sums in flight
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t i0 = (int64_t)blockIdx.x * kChunk;
-    const int cb = blockIdx.y * kWavesPerBlock + wave, c0 = cb * kColBlock + lane * 8;
-    if (cb * kColBlock >= D) return;
+    const int span = (int)blockIdx.x / ncb, cb = (int)blockIdx.x - span * ncb;
+    const int c0 = cb * kColBlock + lane * 8;
     const bool has_cols = c0 < D;
     const bool runsum_vec = c0 + 8 <= D && D % 4 == 0 && (reinterpret_cast<uintptr_t>(runsum) & 15u) == 0;
-    const int Bn = (int)(n / Tn);
-    uint64_t marks = __ballot(lane < kChunk && i0 + lane < n && marks_at[i0 + lane < n ? i0 + lane : 0] != 0u);
-    while (marks) {
-        const int64_t i = i0 + __builtin_ctzll(marks);
-        marks &= marks - 1;
-        const uint32_t v = keys[i], p0 = vals[i], ex0 = p0 / (uint32_t)Tn;
-        float acc[8];
+    const int64_t q0 = (int64_t)span * kSumSpan, q = q0 + lane;
+    const uint32_t key = q < n ? keys[q] : 0xffffffffu, before = q > 0 && q < n ? keys[q - 1] : 0xffffffffu;
+    const uint32_t beyond = q + 64 < n ? keys[q + 64] : 0xffffffffu;
+    const uint64_t starts = __ballot(key < (uint32_t)V && key != before && beyond == key);   // the same in every wave
+    if (!starts) return;
+    const int64_t i = q0 + __builtin_ctzll(starts);
+    const uint32_t v = keys[i], p0 = vals[i];
+    float acc[8], sub[8];
+    // adds the parked sums at the positions held by the lanes of `take`, in lane order: to the open run, and at its last
+    // piece (a bit of `ends`) the run to acc; a run of several pieces is squared there, its share going to head_pos
+    auto add_parked = [&](uint64_t take, uint32_t pos, uint64_t ends, uint64_t several, uint32_t head_pos) {
+        while (take) {
+            int at[kBatch], cnt = 0;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) acc[k] = 0.f;
-        // the parked sums at the positions held by the lanes of `take`, in lane order
-        auto add_parked = [&](uint64_t take, uint32_t pos) {
-            while (take) {
-                uint32_t ent[kBatch];                            // all loads first, then the additions in order
-                int cnt = 0;
+            for (int u = 0; u < kBatch; ++u) {
+                at[u] = take ? __builtin_ctzll(take) : (u > 0 ? at[u - 1] : 0);
+                cnt += take ? 1 : 0;
+                take &= take - 1;
+            }
+            float add[kBatch][8];
+            if (runsum_vec) {                                    // all loads first, then the additions in order
+                Row8<float> raw[kBatch];
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) raw[u] = load_row8(runsum, (int64_t)lane_value(pos, at[u]), D, c0);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) unpack_row8(raw[u], add[u]);
+            } else {
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
-                    if (take) {
-                        ent[u] = lane_value(pos, __builtin_ctzll(take));
-                        take &= take - 1;
-                        ++cnt;
-                    } else {
-                        ent[u] = ent[u > 0 ? u - 1 : 0];
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) add[u][c] = 0.f;
+                    if (has_cols && u < cnt) add_row(runsum, (int64_t)lane_value(pos, at[u]), D, c0, false, add[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                if (u < cnt) {
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) sub[c] += add[u][c];
+                }
+                if (u < cnt && ((ends >> at[u]) & 1)) {
+                    if ((several >> at[u]) & 1) {
+                        float sq = 0.f;
+#pragma unroll
+                        for (int c = 0; c < 8; ++c) sq = fmaf(sub[c], sub[c], sq);
+                        sq = wave_sum(has_cols ? sq : 0.f);
+                        if (lane == 0) contrib[(int64_t)cb * n + lane_value(head_pos, at[u])] = sq;
+                    }
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        acc[c] += sub[c];
+                        sub[c] = 0.f;
                     }
                 }
-                float add[kBatch][8];
-                if (runsum_vec) {
-                    Row8<float> raw[kBatch];
+            }
+        }
+    };
 #pragma unroll
-                    for (int u = 0; u < kBatch; ++u) raw[u] = load_row8(runsum, (int64_t)ent[u], D, c0);
+    for (int c = 0; c < 8; ++c) acc[c] = sub[c] = 0.f;
+    {
+        const int per = (Bn + kSumWaves - 1) / kSumWaves;
+        const int b_begin = min(wave * per, Bn), b_end = min(b_begin + per, Bn);
+        for (int b0 = b_begin; b0 < b_end; b0 += 63) {           // lane 63 only ends the run of lane 62
+            const int b = min(b0 + lane, b_end), runs = min(63, b_end - b0);
+            // where the id's positions of example b would start (b = Bn: where the next id does)
+            const int64_t at = lower_bound_pair(keys, vals, i, n - i, b < Bn ? v : v + 1u, b < Bn ? (uint32_t)b * (uint32_t)Tn : 0u);
+            const int64_t end = __shfl_down(at, 1);
+            const int64_t second = (at / kPiece + 1) * kPiece;   // where the run's second piece starts, if it gets there
+            const int mine = lane < runs && end > at ? 1 + (int)(end > second ? (end - second + kPiece - 1) / kPiece : 0) : 0;
+            int upto = mine;                                     // pieces of this batch's runs up to this lane's
 #pragma unroll
-                    for (int u = 0; u < kBatch; ++u) unpack_row8(raw[u], add[u]);
-                } else {
-#pragma unroll
-                    for (int u = 0; u < kBatch; ++u) {
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) add[u][k] = 0.f;
-                        if (has_cols && u < cnt) add_row(runsum, (int64_t)ent[u], D, c0, false, add[u]);
+            for (int d = 1; d < 64; d <<= 1) {
+                const int t = __shfl_up(upto, d);
+                upto += lane >= d ? t : 0;
+            }
+            const int total = __shfl(upto, 63);
+            for (int k0 = 0; k0 < total; k0 += 64) {
+                const int k = k0 + lane;                         // this lane's piece; its run is found below
+                int64_t idx = -1, head = 0;
+                bool ends = false, several = false;
+                for (uint64_t left = __ballot(mine > 0 && upto > k0 && upto - mine < k0 + 64); left; left &= left - 1) {
+                    const int r = __builtin_ctzll(left);
+                    const int r_upto = __shfl(upto, r), r_mine = __shfl(mine, r);
+                    const int64_t r_at = __shfl(at, r), r_second = __shfl(second, r);
+                    const int u = k - (r_upto - r_mine);
+                    if (u >= 0 && u < r_mine) {
+                        idx = u == 0 ? r_at : r_second + (int64_t)(u - 1) * kPiece;
+                        ends = u == r_mine - 1;
+                        several = ends && r_mine > 1;
+                        head = r_at;
                     }
                 }
+                const uint32_t pos = idx >= 0 ? vals[idx] : 0u, head_pos = several ? vals[head] : 0u;
+                add_parked(__ballot(idx >= 0), pos, __ballot(ends), __ballot(several), head_pos);
+            }
+        }
+        *reinterpret_cast<float4 *>(&part[wave][lane * 8]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        *reinterpret_cast<float4 *>(&part[wave][lane * 8 + 4]) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+        __syncthreads();
+        float sq = 0.f;
+        for (int c = tid; c < kColBlock; c += 64 * kSumWaves) {
+            const int col = cb * kColBlock + c;
+            float sum = 0.f;
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u)
-                    if (u < cnt) {
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) acc[k] += add[u][k];
-                    }
+            for (int u = 0; u < kSumWaves; ++u) sum += part[u][c];
+            if (col < D) {
+                float *p = w + (int64_t)v * D + col;
+                if (accumulate) sum += *p;
+                __builtin_nontemporal_store(sum, p);
+                sq = fmaf(sum, sum, sq);
             }
-        };
-        if constexpr (kIds) {
-            // the id's positions end where (v + 1, 0) would go; the examples' runs are searched for inside them
-            const int64_t seg_end = wave_lower_bound_pair(keys, vals, i, n, v + 1u, 0u, lane);
-            for (int b0 = 0; b0 < Bn; b0 += 64) {
-                const int b = b0 + lane;
-                const uint32_t target = (uint32_t)(b < Bn ? b : 0) * (uint32_t)Tn;
-                const int64_t at = lower_bound_pair(keys, vals, i, seg_end, v, target);
-                const uint32_t k = at < n ? keys[at] : 0xffffffffu, pos = at < n ? vals[at] : 0u;
-                add_parked(__ballot(b < Bn && k == v && pos - target < (uint32_t)Tn), pos);
-            }
-            float wsq = has_cols ? put_row(w + (int64_t)v * D + c0, acc, c0, D, accumulate != 0, true) : 0.f;
-            if (!accumulate) {
-                wsq = wave_sum(wsq);
-                if (lane == 0) bigpart[(int64_t)cb * n + p0] = wsq;
-            }
-        } else {
-            const int64_t end = wave_lower_bound_pair(keys, vals, i, n, v, (ex0 + 1u) * (uint32_t)Tn, lane);
-            const int64_t h1 = (i / kPiece + 1) * kPiece;        // the run's second piece, if it gets that far
-            const int64_t npieces = 1 + (end > h1 ? (end - h1 + kPiece - 1) / kPiece : 0);
-            for (int64_t u0 = 0; u0 < npieces; u0 += 64) {
-                const int64_t u = u0 + lane, at = u == 0 ? i : h1 + (u - 1) * kPiece;
-                const bool ok = u < npieces;
-                add_parked(__ballot(ok), ok ? vals[at] : 0u);
-            }
-            float sq = has_cols ? put_row(runsum + (int64_t)p0 * D + c0, acc, c0, D, false) : 0.f;
+        }
+        if (!accumulate) {
             sq = wave_sum(sq);
-            if (lane == 0) contrib[(int64_t)cb * n + p0] = sq;
+            if (lane == 0) squares[wave] = sq;
+        }
+        __syncthreads();
+        if (!accumulate && tid == 0) {
+            float t = 0.f;
+            for (int u = 0; u < kSumWaves; ++u) t += squares[u];
+            bigpart[(int64_t)cb * n + p0] = t;
         }
     }
 }
@@ -753,41 +886,6 @@ __global__ __launch_bounds__(1024) void emb_final_kernel(const float *contrib, c
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 
-// The zero fill of w' (bandwidth bound) has nothing to do with the sort (a dozen tiny launches): it runs on a
-// side stream of the library's own, forked from and joined to the caller's stream with events, so the two
-// overlap.  One side stream and event pair per device, made at the first call there and kept; calls that
-// share a device share them (the events order each call's fill with that call's own work).
-struct SideStream {
-    hipStream_t stream = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-    std::mutex in_use;   // held by a call from its fork to its join: the two events are recorded and waited
-                         // on as pairs, which another thread's call on the same device must not interleave
-};
-constexpr int kMaxDevices = 64;
-SideStream g_side[kMaxDevices];
-std::mutex g_side_mutex;
-
-SideStream *side_stream()
-{
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
-    std::lock_guard<std::mutex> lock(g_side_mutex);
-    SideStream &s = g_side[dev];
-    if (!s.stream) {
-        hipStream_t st = nullptr;
-        hipEvent_t a = nullptr, b = nullptr;
-        if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) return nullptr;   // default priority
-        if (hipEventCreateWithFlags(&a, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&b, hipEventDisableTiming) != hipSuccess) {
-            (void)hipStreamDestroy(st);
-            if (a) (void)hipEventDestroy(a);
-            return nullptr;
-        }
-        s.stream = st; s.fork = a; s.join = b;
-    }
-    return &s;
-}
-
 int key_bits(int V)
 {
     int bits = 1;
@@ -797,8 +895,9 @@ int key_bits(int V)
 
 struct EmbPlan {
     int64_t n;
-    int ncb;
-    size_t off_keys_in, off_keys_out, off_vals_in, off_vals_out, off_contrib, off_bigpart, off_multi, off_multi_run, off_present, off_wpart, off_tiles, off_temp, off_runsum;
+    int ncb, ntiles;
+    bool own_sort;          // few enough positions for the library's own sort
+    size_t off_keys_in, off_keys_out, off_vals_in, off_vals_out, off_contrib, off_bigpart, off_wpart, off_tiles, off_temp, off_runsum;
     size_t temp_bytes, bytes;
 };
 
@@ -807,34 +906,64 @@ bool emb_shape_ok(int B, int T, int D, int V)
     return B > 0 && T > 0 && D > 0 && V > 0 && (int64_t)B * T < ((int64_t)1 << 31) && V < (1 << 30);
 }
 
-// The sort's own temporary storage is sized by the library for the current device.
-hipError_t make_emb_plan(int B, int T, int D, int V, EmbPlan &p)
+// radix: whether rocPRIM's sort will run (its temporary storage is sized by that library for the current device, which
+// takes longer than a launch: not asked for where our own sort is used).
+hipError_t make_emb_plan(int B, int T, int D, int V, bool radix, EmbPlan &p)
 {
     p.n = (int64_t)B * T;
     p.ncb = (D + kColBlock - 1) / kColBlock;
-    size_t temp = 0;
-    const hipError_t e = rocprim::radix_sort_pairs(nullptr, temp, (const uint32_t *)nullptr, (uint32_t *)nullptr,
-                                                   (const uint32_t *)nullptr, (uint32_t *)nullptr, (size_t)p.n, 0,
-                                                   key_bits(V), (hipStream_t)0);
-    if (e != hipSuccess) return e;
-    const size_t arr = align256((size_t)p.n * sizeof(uint32_t)), f = align256((size_t)p.ncb * p.n * sizeof(float));
-    p.off_keys_in = 0;
-    p.off_keys_out = p.off_keys_in + arr;
-    p.off_vals_in = p.off_keys_out + arr;
-    p.off_vals_out = p.off_vals_in + arr;
-    p.off_contrib = p.off_vals_out + arr;
-    p.off_bigpart = p.off_contrib + f;            // directly behind contrib, the marks behind that: one fill
-    p.off_multi = p.off_bigpart + f;              // clears all three
-    p.off_multi_run = p.off_multi + arr;
-    p.off_present = p.off_multi_run + arr;        // one byte per vocabulary row, cleared with the rest
-    p.off_wpart = p.off_present + align256((size_t)V);
-    p.off_tiles = p.off_wpart + align256(kNormBlocks * sizeof(double));
     const int64_t ntiles = (p.n + kSortTile - 1) / kSortTile;
-    p.off_temp = p.off_tiles + (ntiles <= kSortTiles ? align256((size_t)ntiles * kSortTile * sizeof(uint64_t)) : 0);
+    p.own_sort = ntiles <= kSortTiles;
+    p.ntiles = (int)ntiles;
+    size_t temp = 0;
+    if (radix) {
+        const hipError_t e = rocprim::radix_sort_pairs(nullptr, temp, (const uint32_t *)nullptr, (uint32_t *)nullptr,
+                                                       (const uint32_t *)nullptr, (uint32_t *)nullptr, (size_t)p.n, 0,
+                                                       key_bits(V), (hipStream_t)0);
+        if (e != hipSuccess) return e;
+    }
+    const size_t arr = align256((size_t)p.n * sizeof(uint32_t)), f = align256((size_t)p.ncb * p.n * sizeof(float));
+    const size_t in = p.own_sort ? 0 : arr;       // what rocPRIM's sort reads
+    p.off_keys_in = 0;
+    p.off_keys_out = p.off_keys_in + in;
+    p.off_vals_in = p.off_keys_out + arr;
+    p.off_vals_out = p.off_vals_in + in;
+    p.off_contrib = p.off_vals_out + arr;
+    p.off_bigpart = p.off_contrib + f;
+    p.off_wpart = p.off_bigpart + f;
+    p.off_tiles = p.off_wpart + align256(kNormBlocks * sizeof(double));
+    p.off_temp = p.off_tiles + (p.own_sort ? align256((size_t)ntiles * kSortTile * sizeof(uint64_t)) : 0);
     p.temp_bytes = temp;
     p.off_runsum = p.off_temp + align256(temp);
     p.bytes = p.off_runsum + align256((size_t)p.n * D * sizeof(float));
     return hipSuccess;
+}
+
+// The library's own sort of the ids into (sorted_ids, sorted_pos): two launches.
+template <typename W>
+hipError_t own_sort(const void *ids, int ids_are_int64, const EmbPlan &p, int V, void *tiles, uint32_t *sorted_ids,
+                    uint32_t *sorted_pos, hipStream_t st)
+{
+    W *t = static_cast<W *>(tiles);
+    hipError_t e = launch(emb_tile_sort_kernel<W>, dim3(p.ntiles), dim3(kSortThreads), 0, st, ids, ids_are_int64, p.n, V, t);
+    if (e != hipSuccess) return e;
+    return launch(emb_rank_kernel<W>, dim3(p.ntiles * (kSortTile / kRankThreads)), dim3(kRankThreads),
+                  (size_t)p.ntiles * kSamples * sizeof(W), st, t, p.ntiles, p.n, sorted_ids, sorted_pos);
+}
+
+hipError_t sort_ids(const void *ids, int ids_are_int64, const EmbPlan &p, int V, char *ws, uint32_t *sorted_ids,
+                    uint32_t *sorted_pos, hipStream_t st)
+{
+    if (p.own_sort)
+        return sort_words_are_32(V) ? own_sort<uint32_t>(ids, ids_are_int64, p, V, ws + p.off_tiles, sorted_ids, sorted_pos, st)
+                                    : own_sort<uint64_t>(ids, ids_are_int64, p, V, ws + p.off_tiles, sorted_ids, sorted_pos, st);
+    uint32_t *keys_in = reinterpret_cast<uint32_t *>(ws + p.off_keys_in), *vals_in = reinterpret_cast<uint32_t *>(ws + p.off_vals_in);
+    const hipError_t e = launch(emb_prepare_kernel, dim3((unsigned)((p.n + 255) / 256)), dim3(256), 0, st, ids, ids_are_int64,
+                                keys_in, vals_in, p.n, V);
+    if (e != hipSuccess) return e;
+    size_t temp = p.temp_bytes;
+    return rocprim::radix_sort_pairs(ws + p.off_temp, temp, keys_in, sorted_ids, vals_in, sorted_pos, (size_t)p.n, 0,
+                                     key_bits(V), st);
 }
 
 }  // namespace
@@ -848,12 +977,11 @@ size_t embedding_pegn_workspace_bytes(int B, int T, int D, int V)
 {
     if (!emb_shape_ok(B, T, D, V)) return 0;
     EmbPlan p;
-    return make_emb_plan(B, T, D, V, p) == hipSuccess ? p.bytes : 0;
+    return make_emb_plan(B, T, D, V, true, p) == hipSuccess ? p.bytes : 0;
 }
 
-// The call behind embedding_pegn and embedding_pegn_presorted.  With `ids`: keys are made and sorted here (the
-// zero fill runs beside the sort).  With sorted_ids / sorted_pos: the caller sorted them earlier
-// (embedding_sort_ids), the scratch is cleared here and the fill runs beside the run and id kernels.
+// The call behind embedding_pegn (ids: sorted here) and embedding_pegn_presorted (sorted_ids / sorted_pos: by the
+// caller, with embedding_sort_ids).
 static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sorted_ids, const uint32_t *sorted_pos,
                          const void *g, float *w, float *s, float *big_sq, int B, int T, int D, int V, lnpegn_dtype dt,
                          void *workspace, size_t workspace_bytes, unsigned flags, void *stream)
@@ -864,77 +992,39 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     if (dt != LNPEGN_F32 && dt != LNPEGN_BF16) return LNPEGN_EUNSUPPORTED;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return LNPEGN_EINVAL;
     EmbPlan p;
-    if (make_emb_plan(B, T, D, V, p) != hipSuccess) return LNPEGN_EHIP;
+    const bool radix = ids && (int64_t)B * T > (int64_t)kSortTiles * kSortTile;
+    if (make_emb_plan(B, T, D, V, radix, p) != hipSuccess) return LNPEGN_EHIP;
     if (workspace_bytes < p.bytes) return LNPEGN_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int accumulate = (flags & LNPEGN_ACCUMULATE) ? 1 : 0;
     char *ws = static_cast<char *>(workspace);
-    uint32_t *keys_in = reinterpret_cast<uint32_t *>(ws + p.off_keys_in);
-    uint32_t *vals_in = reinterpret_cast<uint32_t *>(ws + p.off_vals_in);
-    const uint32_t *keys_out = ids ? reinterpret_cast<uint32_t *>(ws + p.off_keys_out) : sorted_ids;
-    const uint32_t *vals_out = ids ? reinterpret_cast<uint32_t *>(ws + p.off_vals_out) : sorted_pos;
+    const uint32_t *keys = ids ? reinterpret_cast<uint32_t *>(ws + p.off_keys_out) : sorted_ids;
+    const uint32_t *vals = ids ? reinterpret_cast<uint32_t *>(ws + p.off_vals_out) : sorted_pos;
     float *contrib = reinterpret_cast<float *>(ws + p.off_contrib);
     float *bigpart = reinterpret_cast<float *>(ws + p.off_bigpart);
-    uint32_t *multi = reinterpret_cast<uint32_t *>(ws + p.off_multi);
-    uint32_t *multi_run = reinterpret_cast<uint32_t *>(ws + p.off_multi_run);
-    uint8_t *present = reinterpret_cast<uint8_t *>(ws + p.off_present);
     double *wpart = reinterpret_cast<double *>(ws + p.off_wpart);
-    const int64_t nscratch = (int64_t)((p.off_wpart - p.off_contrib) / sizeof(float));
-    const unsigned nblk = (unsigned)((p.n + 255) / 256);
-
-    const int ntiles = (int)((p.n + kSortTile - 1) / kSortTile);
-    const bool own_sort = ids && ntiles <= kSortTiles;
-    uint64_t *tiles = reinterpret_cast<uint64_t *>(ws + p.off_tiles);
-    // 1. scratch cleared, the ids sorted (two launches of our own for up to kSortTiles * kSortTile positions; the
-    //    library's radix sort beyond that, after the fork), and the ids that occur marked for the fill
-    if (own_sort) {
-        if (launch(emb_tile_sort_kernel, dim3(ntiles), dim3(kSortThreads), 0, st, ids, ids_are_int64, p.n, V, tiles, contrib, nscratch) != hipSuccess) return LNPEGN_EHIP;
-        if (launch(emb_rank_kernel, dim3(ntiles * (kSortTile / 256)), dim3(256), 0, st, tiles, ntiles, p.n, V,
-                   const_cast<uint32_t *>(keys_out), const_cast<uint32_t *>(vals_out), accumulate ? nullptr : present) != hipSuccess)
-            return LNPEGN_EHIP;
-    } else if (ids) {
-        if (launch(emb_prepare_kernel, dim3(nblk), dim3(256), 0, st, ids, ids_are_int64, keys_in, vals_in, contrib, p.n, nscratch, V) != hipSuccess) return LNPEGN_EHIP;
-    } else {
-        const unsigned cb = (unsigned)(nscratch / 256 / 4 + 1 < 4096 ? nscratch / 256 / 4 + 1 : 4096);
-        if (launch(emb_clear_kernel, dim3(cb), dim3(256), 0, st, contrib, nscratch) != hipSuccess) return LNPEGN_EHIP;
-    }
-    // 2. fork: the fill of the rows no id selects, on the side stream (on the caller's stream if there is none)
-    SideStream *side = accumulate ? nullptr : side_stream();
-    std::unique_lock<std::mutex> side_lock;
-    if (side) side_lock = std::unique_lock<std::mutex>(side->in_use);
-    if (!accumulate) {
-        if (!own_sort &&
-            launch(emb_mark_kernel, dim3(nblk), dim3(256), 0, st, ids ? keys_in : keys_out, p.n, V, present) != hipSuccess)
-            return LNPEGN_EHIP;
-        hipStream_t fs = st;
-        if (side) {
-            if (hipEventRecord(side->fork, st) != hipSuccess || hipStreamWaitEvent(side->stream, side->fork, 0) != hipSuccess)
-                return LNPEGN_EHIP;
-            fs = side->stream;
-        }
-        const int64_t nw = (int64_t)V * D;
-        const unsigned fb = (unsigned)(nw / 256 / 8 + 1 < 65536 ? nw / 256 / 8 + 1 : 65536);
-        if (launch(emb_fill_kernel, dim3(fb), dim3(256), 0, fs, w, (int64_t)V, D, present) != hipSuccess) return LNPEGN_EHIP;
-        if (side && hipEventRecord(side->join, fs) != hipSuccess) return LNPEGN_EHIP;
-    }
-    // 3. the library's sort for batches beyond our own
-    if (ids && !own_sort) {
-        size_t temp = p.temp_bytes;
-        if (rocprim::radix_sort_pairs(ws + p.off_temp, temp, keys_in, const_cast<uint32_t *>(keys_out), vals_in,
-                                      const_cast<uint32_t *>(vals_out), (size_t)p.n, 0, key_bits(V), st) != hipSuccess)
-            return LNPEGN_EHIP;
-    }
-    // 4. runs, then the marked runs and ids: these write the rows of the ids that occur, the fill the others
+    float *runsum = reinterpret_cast<float *>(ws + p.off_runsum);
+    // 1. the ids sorted
+    if (ids && sort_ids(ids, ids_are_int64, p, V, ws, const_cast<uint32_t *>(keys), const_cast<uint32_t *>(vals), st) != hipSuccess)
+        return LNPEGN_EHIP;
+    // 2. runs, and beside them the fill of the rows no id selects
     const int esz = dt == LNPEGN_BF16 ? 2 : 4;
     // 8 columns per lane: 16 bytes of bf16, 32 bytes of fp32; rows must keep that alignment
-    const int vec_ok = ((reinterpret_cast<uintptr_t>(g) & 15u) == 0 && ((int64_t)D * esz) % 16 == 0) ? 1 : 0;
-    const dim3 grid((unsigned)((p.n + kChunk - 1) / kChunk), (unsigned)((p.ncb + kWavesPerBlock - 1) / kWavesPerBlock));
-    const dim3 grid_runs(grid.x < (unsigned)g_emb_run_blocks ? grid.x : (unsigned)g_emb_run_blocks, grid.y);
-    float *runsum = reinterpret_cast<float *>(ws + p.off_runsum);
-    const bool vec = vec_ok && D % 8 == 0;
+    const bool vec = (reinterpret_cast<uintptr_t>(g) & 15u) == 0 && ((int64_t)D * esz) % 16 == 0 && D % 8 == 0;
+    const int64_t chunks = (p.n + kChunk - 1) / kChunk;
+    const int runs_x = (int)(chunks < g_emb_run_blocks ? chunks : g_emb_run_blocks), runs_y = (p.ncb + kWavesPerBlock - 1) / kWavesPerBlock;
+    // the rows filled beside kernel A; the rest beside kernel B
+    const int64_t row_bytes = (int64_t)D * 4, late = V / 2 < kFillLateBytes / row_bytes ? V / 2 : kFillLateBytes / row_bytes;
+    const int fill_a = accumulate ? 0 : V - (int)late, fill_b = accumulate ? 0 : (int)late;
+    auto blocks_for = [](int rows) {
+        const int64_t most = ((int64_t)rows + kFillRows * kWavesPerBlock - 1) / (kFillRows * kWavesPerBlock);
+        return (int)(most < kFillBlocks ? most : kFillBlocks);
+    };
+    const int fill_blocks = blocks_for(fill_a), fill_blocks_b = blocks_for(fill_b), medium_blocks = (int)chunks * runs_y;
     hipError_t runs_status = hipSuccess;
     auto runs = [&](auto kernel, auto *gp) {
-        runs_status = launch(kernel, grid_runs, dim3(64 * kWavesPerBlock), 0, st, gp, keys_out, vals_out, w, runsum, contrib, bigpart, multi, multi_run, p.n, T, D, V, accumulate);
+        runs_status = launch(kernel, dim3((unsigned)(medium_blocks + fill_blocks + runs_x * runs_y)), dim3(64 * kWavesPerBlock), 0, st, gp, keys, vals, w, runsum,
+                             contrib, bigpart, p.n, T, D, V, accumulate, medium_blocks, fill_a, fill_blocks, runs_x);
     };
     if (dt == LNPEGN_BF16) {
         if (vec) runs(emb_runs_kernel<bf16_t, true>, static_cast<const bf16_t *>(g));
@@ -944,16 +1034,18 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
         else runs(emb_runs_kernel<float, false>, static_cast<const float *>(g));
     }
     if (runs_status != hipSuccess) return LNPEGN_EHIP;
-    if (launch(emb_sums_kernel<false>, grid, dim3(64 * kWavesPerBlock), 0, st, keys_out, vals_out, w, runsum, contrib, bigpart, multi_run, p.n, T, D, V, accumulate) != hipSuccess) return LNPEGN_EHIP;
-    if (launch(emb_sums_kernel<true>, grid, dim3(64 * kWavesPerBlock), 0, st, keys_out, vals_out, w, runsum, contrib, bigpart, multi, p.n, T, D, V, accumulate) != hipSuccess) return LNPEGN_EHIP;
-    // 5. join: w' is complete on the caller's stream from here
-    if (side && hipStreamWaitEvent(st, side->join, 0) != hipSuccess) return LNPEGN_EHIP;
-    if (side) side_lock.unlock();
+    // 3. the parked sums
+    const int64_t sum_blocks = (p.n + kSumSpan - 1) / kSumSpan * p.ncb;
+    if (launch(emb_sums_kernel, dim3((unsigned)(sum_blocks + fill_blocks_b)), dim3(64 * kSumWaves), 0, st, keys, vals, w, runsum, contrib, bigpart,
+               p.n, T, D, V, accumulate, fill_a, (int)sum_blocks, fill_blocks_b) != hipSuccess)
+        return LNPEGN_EHIP;
+    // 4. the norms
     const bool wnorm = accumulate && big_sq;
     if (wnorm) {
         if (launch(emb_wnorm_kernel, dim3(kNormBlocks), dim3(256), 0, st, w, (int64_t)V * D, wpart) != hipSuccess) return LNPEGN_EHIP;
     }
-    return launch(emb_final_kernel, dim3(B + 1), dim3(1024), 0, st, contrib, bigpart, wnorm ? wpart : nullptr, kNormBlocks, s, big_sq, B, T, p.ncb, p.n) == hipSuccess ? LNPEGN_OK : LNPEGN_EHIP;
+    return launch(emb_final_kernel, dim3(B + 1), dim3(1024), 0, st, contrib, bigpart, wnorm ? wpart : nullptr, kNormBlocks, s, big_sq, B, T,
+                  p.ncb, p.n) == hipSuccess ? LNPEGN_OK : LNPEGN_EHIP;
 }
 
 int embedding_pegn(const void *ids, int ids_are_int64, const void *g, float *w, float *s, float *big_sq, int B, int T,
@@ -970,32 +1062,10 @@ int embedding_sort_ids(const void *ids, int ids_are_int64, int B, int T, int V, 
     if (!emb_shape_ok(B, T, 1, V) || !ids || !sorted_ids || !sorted_pos || !workspace) return LNPEGN_EINVAL;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return LNPEGN_EINVAL;
     EmbPlan p;
-    if (make_emb_plan(B, T, 1, V, p) != hipSuccess) return LNPEGN_EHIP;
+    if (make_emb_plan(B, T, 1, V, (int64_t)B * T > (int64_t)kSortTiles * kSortTile, p) != hipSuccess) return LNPEGN_EHIP;
     if (workspace_bytes < p.bytes) return LNPEGN_EWORKSPACE;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    char *ws = static_cast<char *>(workspace);
-    uint32_t *keys_in = reinterpret_cast<uint32_t *>(ws + p.off_keys_in);
-    uint32_t *vals_in = reinterpret_cast<uint32_t *>(ws + p.off_vals_in);
-    const int ntiles = (int)((p.n + kSortTile - 1) / kSortTile);
-    if (ntiles <= kSortTiles) {
-        uint64_t *tiles = reinterpret_cast<uint64_t *>(ws + p.off_tiles);
-        if (launch(emb_tile_sort_kernel, dim3(ntiles), dim3(kSortThreads), 0, st, ids, ids_are_int64, p.n, V, tiles,
-                   static_cast<float *>(nullptr), (int64_t)0) != hipSuccess)
-            return LNPEGN_EHIP;
-        return launch(emb_rank_kernel, dim3(ntiles * (kSortTile / 256)), dim3(256), 0, st, tiles, ntiles, p.n, V, sorted_ids,
-                      sorted_pos, static_cast<uint8_t *>(nullptr)) == hipSuccess
-                   ? LNPEGN_OK
-                   : LNPEGN_EHIP;
-    }
-    const unsigned nblk = (unsigned)((p.n + 255) / 256);
-    if (launch(emb_prepare_kernel, dim3(nblk), dim3(256), 0, st, ids, ids_are_int64, keys_in, vals_in,
-               static_cast<float *>(nullptr), p.n, (int64_t)0, V) != hipSuccess)
-        return LNPEGN_EHIP;
-    size_t temp = p.temp_bytes;
-    return rocprim::radix_sort_pairs(ws + p.off_temp, temp, keys_in, sorted_ids, vals_in, sorted_pos, (size_t)p.n, 0,
-                                     key_bits(V), st) == hipSuccess
-               ? LNPEGN_OK
-               : LNPEGN_EHIP;
+    return sort_ids(ids, ids_are_int64, p, V, static_cast<char *>(workspace), sorted_ids, sorted_pos,
+                    static_cast<hipStream_t>(stream)) == hipSuccess ? LNPEGN_OK : LNPEGN_EHIP;
 }
 
 int embedding_pegn_presorted(const uint32_t *sorted_ids, const uint32_t *sorted_pos, const void *g, float *w, float *s,
