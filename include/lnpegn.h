@@ -13,7 +13,7 @@
  *     every buffer, the workspace included.  The library allocates no memory,
  *     frees none and never synchronises.  The only state it keeps is named where
  *     it arises: the benchmarking overrides (lnpegn_set_tuning,
- *     lnpegn_set_profile_events) and the side stream of embedding_pegn.
+ *     lnpegn_set_profile_events).
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     All work is enqueued on it and the call returns before it completes; a
  *     call may therefore be captured into a HIP graph.
@@ -284,10 +284,7 @@ int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq,
  * reproducible).  workspace: embedding_pegn_workspace_bytes(...) bytes (0 if the shape is invalid or
  * no device is present: the sort's scratch is sized for the current device), 256-byte aligned,
  * caller-owned, contents scratch.  B*T < 2^31, V < 2^30.  Enqueued on stream, never synchronises.
- * Without LNPEGN_ACCUMULATE the zero fill of w (of the rows that no id selects) runs on a side stream that the library creates once per
- * device (default priority, kept until the process ends), forked from and joined back to `stream` with
- * events inside this call: to the caller the call is still one piece of work on `stream`; calls issued
- * from several streams of one device share the side stream and may serialise on it.
+ * The zero fill of w (without LNPEGN_ACCUMULATE, of the rows that no id selects) is part of the kernels that read g.
  */
 size_t embedding_pegn_workspace_bytes(int B, int T, int D, int V);
 /*
@@ -299,7 +296,6 @@ size_t embedding_pegn_workspace_bytes(int B, int T, int D, int V);
  *     embedding_pegn_presorted, which requires exactly that order (it is not checked).
  *   workspace: embedding_pegn_workspace_bytes(B, T, D, V) for embedding_pegn_presorted,
  *     embedding_pegn_workspace_bytes(B, T, 1, V) suffices for embedding_sort_ids.
- * Without the sort in front of it the zero fill of the rows that no id selects runs beside the kernels that read g.
  */
 int embedding_sort_ids(const void *ids, int ids_are_int64, int B, int T, int V, uint32_t *sorted_ids,
                        uint32_t *sorted_pos, void *workspace, size_t workspace_bytes, void *stream);

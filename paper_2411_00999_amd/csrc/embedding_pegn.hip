@@ -101,7 +101,7 @@ __device__ __forceinline__ uint64_t lane_xor(uint64_t v)
 // Bitonic network over a tile, four consecutive words per thread: strides below 4 stay in a thread's registers, below
 // 256 in the wave (DPP and lane permutes), and only the six stages of 256 and more go through LDS with a barrier.
 // Bound by the chain of 66 stages: with every stage through LDS, one compare-exchange per thread, 16.4 us against
-// @@TS@@ for 4 tiles.
+// 5.9 for 4 tiles.
 template <typename W>
 __global__ __launch_bounds__(kSortThreads) void emb_tile_sort_kernel(const void *ids, int ids_i64, int64_t n, int V, W *tiles)
 {
@@ -166,8 +166,8 @@ __global__ __launch_bounds__(kSortThreads) void emb_tile_sort_kernel(const void 
 
 // Each thread places one word.  Every 32nd word of every tile is copied to LDS; sixteen binary searches (one per
 // other tile) advance together, first over those samples, then inside the 32 words (one cache line of 32-bit words)
-// that they leave.  Latency bound: with all eleven steps in memory 10.8 us for 16 tiles and 9.0 for 4, against @@RK@@
-// and @@RK4@@ (with whole tiles in LDS, which leaves one workgroup a CU, 14.0 and 6.9).
+// that they leave.  Latency bound: with all eleven steps in memory 10.8 us for 16 tiles and 9.0 for 4, against 7.6
+// and 6.9 (with whole tiles in LDS, which leaves one workgroup a CU, 14.0 and 6.9).
 constexpr int kRankThreads = 256, kSampleEvery = 32, kSamples = kSortTile / kSampleEvery;
 template <typename W>
 __global__ __launch_bounds__(kRankThreads) void emb_rank_kernel(const W *tiles, int ntiles, int64_t n, uint32_t *sorted_ids,
@@ -367,7 +367,8 @@ __device__ __forceinline__ int64_t lower_bound_pair(const uint32_t *keys, const 
 // Zero fill of the rows of w' that no id selects (rows begin to end - 1), a part of kernel A's grid and of kernel B's:
 // the rows of ids that occur are written, whole, by the other workgroups, so everything touches different rows and
 // runs side by side.  Kernel A waits for its chains of loads more than for bandwidth and kernel B does little else, so
-// the fill is shared out between the two: @@FILL@@.  A wave takes kFillRows
+// the fill is shared out between the two (half of it, at most 40 MiB, beside kernel B: the presorted call
+// 48.7 -> 46.2 us at B=8 T=1024 D=768 V=50257, no difference at B=16 T=2048 D=2048).  A wave takes kFillRows
 // rows, one per lane: each lane looks for its row's id in the sorted list, so that no map of the ids is needed before the
 // launch; they lie a wave count apart, so that the waves together sweep one moving window of w'.  Streaming stores: the zeros are not wanted in any cache (the rows read next are g's), and lines left dirty
 // in the memory-side cache would be written back one by one under the reads that follow.
@@ -399,7 +400,8 @@ __device__ __forceinline__ void fill_absent_rows(const uint32_t *keys, int64_t n
 // A long segment is handed out piece by piece to the waves whose positions hold the pieces' first rows; a piece that is
 // a whole run yields that run's share of s[b], and every sum is parked.  Medium segments are finished the same way
 // as short ones, by waves of their own that see 64 positions from the segment's first (cut into pieces and parked
-// too, they made 65 MB of a call's traffic each way at B=16 T=2048 D=2048: @@MED@@).
+// too, they added a fifth to the traffic of B=16 T=2048 D=2048; with kernel B left to the long ones 129 -> 127 us, and
+// B=64 T=512 D=1024 fp32 106 -> 91).
 // A wave of the runs sees kShort positions back (to tell whether a piece in its chunk belongs to a short segment that
 // an earlier wave owns) and far enough ahead for anything that starts in its chunk; rows are streamed sixteen
 // (fp32: eight) at a time.  contrib [ncb][n]: a run's share of s[b], at the run's first position, zero elsewhere;
@@ -444,7 +446,8 @@ struct RowEnds {
 
 // Adds up rows l .. e-1 of the window (l starts a run or piece, e-1 ends one), for one column block.  Bound by its
 // instructions: about 200 a row when the rows were taken one at a time out of a register array, with a reduction
-// over the wave at every end; unrolled, with the ends of eight rows reduced together, @@ROWS@@.
+// over the wave at every end; unrolled, with the ends of eight rows reduced together, kernel A
+// alone takes 14.8 us instead of 18.7 at B=8 T=1024 D=768 and 59 instead of 68 at B=16 T=2048 D=2048.
 template <typename T, bool kVec>
 __device__ __forceinline__ void stream_rows(const T *g, float *w, float *runsum, float *contrib, float *bigpart, int64_t n, int D,
                                             int accumulate, int cb, int lane, uint32_t key, uint32_t val, int l, int e,

@@ -82,7 +82,7 @@ def test_linear_and_embedding_replay_from_a_graph():
 
     def step():
         binding.linear_pegn(xd, gd, w=w1, s=s1, big_sq=b1, workspace=ws1)
-        binding.embedding_pegn(idd, ged, V, w=w2, s=s2, big_sq=b2, workspace=ws2)   # forks its fill and joins it
+        binding.embedding_pegn(idd, ged, V, w=w2, s=s2, big_sq=b2, workspace=ws2)
 
     step()
     torch.cuda.synchronize()

@@ -1042,9 +1042,40 @@ def test_embedding_pegn_long_runs(dtype, D):
     _check_embedding(ids, g, V, _run_embedding(ids, g, V, dtype, w0=w0), w0=w0)
 
 
+@pytest.mark.parametrize("dtype,D,V,shift", [("bf16", 24, 700, 0), ("bf16", 520, 700, 5), ("f32", 12, 700, 11), ("bf16", 7, 700, 3),
+                                             ("bf16", 8, (1 << 21) - 2, 1),      # the last vocabulary sorted as 32-bit words
+                                             ("bf16", 8, (1 << 21) - 1, 2)])     # ... and the first as 64-bit words
+def test_embedding_pegn_segment_lengths(dtype, D, V, shift):
+    """Ids that occur as often as the kernels' lines between short, medium and long ids say, at every offset from the
+    waves' chunks and the pieces, over more than one sort tile; overwritten and accumulated."""
+    rng = np.random.default_rng(workloads.BASE_SEED + 84 + shift)
+    lengths = [1] * shift + [12, 13, 1, 64, 65, 2, 63, 66, 11, 12, 13, 14, 31, 32, 33, 1, 128, 129, 64, 13, 12, 200, 65, 5, 340] + [1] * 40
+    lengths += [int(rng.integers(1, 90)) for _ in range(25)]
+    B, T = 6, -(-sum(lengths) // 6)
+    used = np.sort(rng.choice(np.arange(1, V - 1), size=len(lengths) + 1, replace=False))
+    used[-1] = V - 1
+    flat = np.concatenate([np.full(n, v) for n, v in zip(lengths, used)] + [np.full(B * T - sum(lengths), used[-1])])
+    ids = rng.permutation(flat).reshape(B, T).astype(np.int64)
+    ids[2][rng.random(T) < 0.05] = V + 3             # skipped
+    _, g = workloads.make_embedding_inputs(84, B, T, D, 50, dtype)
+    keep = ids < V
+    # the oracle on the ids that occur, renumbered
+    names, small = np.unique(np.where(keep, ids, used[0]), return_inverse=True)
+    small, gk = small.reshape(B, T), g * keep[..., None]
+    w, s, big = _run_embedding(ids, g, V, dtype)
+    _check_embedding(small, gk, len(names), (w[names], s, big))
+    assert np.count_nonzero(w.any(1)) == np.count_nonzero(w[names].any(1))      # every other row is zero
+    if V < 1000:
+        w0 = rng.normal(0, 1e-2, (V, D))
+        w, s, big = _run_embedding(ids, g, V, dtype, w0=w0)
+        rest = np.setdiff1d(np.arange(V), names)
+        np.testing.assert_array_equal(w[rest], w0.astype(np.float32)[rest])
+        _check_embedding(small, gk, len(names), (w[names], s, big - np.sum(w[rest] ** 2)), w0=w0[names])
+
+
 def test_embedding_pegn_two_threads_two_streams():
-    """Calls from two host threads on two streams of one device share the library's side stream: every call must
-    still give the single-call result bit for bit."""
+    """Calls from two host threads on two streams of one device: every call must give the single-call result bit for
+    bit."""
     import threading
     import torch
     from paper_2411_00999_amd import binding
