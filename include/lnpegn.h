@@ -28,7 +28,8 @@
  *   - Index arithmetic is 64-bit; B*T*D may exceed 2^31.
  *   - Any D >= 1 is computed correctly.  The bandwidth-tuned kernels need
  *     D % 8 == 0 (bf16) or D % 4 == 0 (fp32), D <= 16384
- *     and 16-byte aligned x, dy, dx; other cases take a slower generic kernel.
+ *     and 16-byte aligned x, dy, dx; other widths from one vector (8 or 4) up to 8192 (ln_fwd: 16384) and
+ *     element-aligned pointers take a form of them with unaligned vectors; the rest a much slower generic kernel.
  *   - Loading.  The library links against the HIP runtime (libamdhip64) by its soname.  A
  *     process must hold ONE copy of that runtime: a host program that also loads another
  *     package which ships a HIP runtime of its own (PyTorch-ROCm does) must load that package
@@ -325,9 +326,9 @@ int lnpegn_set_tuning(int key, int value);
 /*
  * Benchmarking and testing aid, host only (touches no device): the launch plan that ln_bwd (per_example = 0) or
  * ln_bwd_pegn (per_example = 1) would use for this shape under the tuning in force, with 16-byte aligned pointers
- * (aligned = 1: the vector kernels where the row width allows) or without (aligned = 0: the generic kernel).
+ * (aligned = 1: the vector kernels where the row width allows) or without (aligned = 0).
  * Writes min(n_out, LNPEGN_PLAN_FIELDS) values to the HOST array out, in this order:
- *    0 vector kernel (1) or generic kernel (0)      1 waves per row                2 row groups per workgroup
+ *    0 aligned vectors (1) or another kernel (0)      1 waves per row                2 row groups per workgroup
  *    3 16-byte vectors per lane and array           4 chunks per example (of the whole tensor for ln_bwd)
  *    5 chunks in all = workgroups of the row kernel 6 rows of a chunk when they are consecutive, else 0 (every
  *      C-th row)                                    7 rows between the sweep starts of consecutive examples

@@ -20,7 +20,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(8))) short s16x8_t;
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
 // Workgroup tile: (WM*MI*32) (k) x (WN*NI*32) (l) outputs, 64 positions t per stage, WM x WN waves, each
 // wave MI x NI MFMA tiles of 32 x 32 (v_mfma_f32_32x32x16_bf16).
@@ -110,25 +109,12 @@ __device__ __forceinline__ void load_to_lds_tracked(uint32_t lds_addr, int voff,
 __device__ __constant__ uint32_t kZeroChunk[4] __attribute__((aligned(16))) = {0u, 0u, 0u, 0u};
 
 // Sixteen bytes from an address that is only aligned to an element.
-typedef u32x4_t u32x4_at2_t __attribute__((aligned(2)));
-typedef u32x4_t u32x4_at4_t __attribute__((aligned(4)));
 template <int kElem>
 __device__ __forceinline__ u32x4_t load_chunk(const void *p)
 {
     // (named as global memory: the waits behind a flat load are for everything under way)
     if constexpr (kElem == 2) return *(const __attribute__((address_space(1))) u32x4_at2_t *)p;
     else return *(const __attribute__((address_space(1))) u32x4_at4_t *)p;
-}
-
-// v shifted towards its low end by `bytes` (0..15); zeros come in behind.
-__device__ __forceinline__ u32x4_t shift_down(u32x4_t v, int bytes)
-{
-    const bool one = (bytes & 4) != 0, two = (bytes & 8) != 0;
-    if (two) v = u32x4_t{v.z, v.w, 0u, 0u};
-    if (one) v = u32x4_t{v.y, v.z, v.w, 0u};
-    const uint32_t rest = bytes & 3;
-    return u32x4_t{__builtin_amdgcn_alignbyte(v.y, v.x, rest), __builtin_amdgcn_alignbyte(v.z, v.y, rest),
-                   __builtin_amdgcn_alignbyte(v.w, v.z, rest), __builtin_amdgcn_alignbyte(0u, v.w, rest)};
 }
 
 // Ragged operands.  A direct-to-LDS load needs a 16-byte aligned address, so an operand whose rows do not all start

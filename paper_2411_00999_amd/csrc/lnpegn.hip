@@ -54,7 +54,8 @@ inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 struct Plan {
     // row kernel
     bool plain;       // no per-example outputs: the plain backward's kernel
-    bool fast;        // vectorised kernels usable (shape-wise; pointer alignment checked apart)
+    bool fast;        // vectorised kernels
+    bool ragged;      // ... in their form for rows of any width and address
     bool sync;        // several waves per row
     int vpt;          // 16-byte vectors per lane
     int S, R;         // waves per row, row groups per workgroup
@@ -99,8 +100,10 @@ int64_t chunks_per_example(int64_t B, int64_t T, int64_t W)
     return (c3 <= 16 && T / c3 >= 16) ? c3 : c0;    // ... unless that leaves a chunk fewer than 16 rows
 }
 
-// `vector_ok`: the 16-byte aligned fast kernels will run (else the generic kernel does).
-Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, bool vector_ok)
+// What the pointers of a call allow: nothing but element accesses, vectors at element addresses, aligned vectors.
+enum Access { kGenericAccess, kElementAccess, kVectorAccess };
+
+Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
 {
     Plan p{};
     p.plain = !pegn;
@@ -110,8 +113,12 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, bool vector_ok)
     if (g_vpt_max > 0 && g_vpt_max < vpt_max) vpt_max = g_vpt_max;
     // ... up to 32 for rows beyond eight waves of 16 (D > 8192): eight waves of 24 or 32 elements per lane
     if (D % E == 0 && D / E > 64 * vpt_max * 8) vpt_max = 32 / E;
-    p.fast = vector_ok && (D % E == 0) && (D / E <= 64 * vpt_max * 8);
-    p.nvec = p.fast ? D / E : 0;
+    p.fast = access == kVectorAccess && (D % E == 0) && (D / E <= 64 * vpt_max * 8);
+    // Other widths and addresses: the same kernels with unaligned vectors, for rows of one vector up to eight waves of
+    // 16 elements per lane; narrower and wider ones take the generic kernel.
+    p.ragged = !p.fast && access != kGenericAccess && D >= E && ceil_div(D, E) <= 64 * vpt_max * 8 && vpt_max <= 16 / E;
+    p.fast = p.fast || p.ragged;
+    p.nvec = p.fast ? ceil_div(D, E) : 0;
     p.sync = false;
     p.vpt = 1;
     p.S = 1;
@@ -125,7 +132,7 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, bool vector_ok)
         const int elems = p.vpt * E;                 // per lane
         waves_per_simd = elems > 8 ? 2 : 4;          // measured: more waves of 16-element lanes only add contention
         // launch bound of the instantiation that will run: 256 threads for S = 1, 2, 4; 512 else
-        const int max_waves = (elems <= 8 && p.S <= 2) ? 4 : 8;
+        const int max_waves = (elems <= 8 && (p.ragged ? p.S == 1 : p.S <= 2)) ? 4 : 8;
         // row groups per workgroup.  Wide lanes: six waves per workgroup, one workgroup per CU (measured, B*T =
         // 32768 rows: bf16 D=2048 69.2 -> 66.9 us per-example and 69.0 -> 65.4 plain against four waves; fp32
         // D=2048 151.7 -> 145.6 and 133 -> 131; eight waves are slower than six; no difference where a row
@@ -136,7 +143,7 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, bool vector_ok)
         // (rows of two waves with lanes left over, D=1280, 1536 or 1600 in bf16, have fewer bytes in flight per
         // wave and take four row groups: D=1280 64.5 -> 52.0 us, D=1536 65.0 -> 55.3; rows of three waves take two:
         // bf16 D=3072 147.7 -> 111.5 per-example and 107.6 -> 100.3 plain, fp32 D=3072 216.3 -> 205.1)
-        const bool full = p.nvec == 64 * p.S * p.vpt;
+        const bool full = !p.ragged && p.nvec == 64 * p.S * p.vpt;
         int R = g_waves > 0 ? g_waves / p.S
                 : (elems > 8 && p.S == 2) ? (full ? 3 : 4)
                 : p.S == 3 ? 2
@@ -234,7 +241,7 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, bool vector_ok)
         const size_t merge = p.fast && p.R > 1 ? (size_t)nw * 2 * p.vpt * E * kWave * sizeof(float) : 0;
         p.lds_bytes = xchg + (merge > 512 ? merge : 512);
     }
-    p.emit_pe = pegn && p.fast && p.C == 1;
+    p.emit_pe = pegn && p.fast && !p.ragged && p.C == 1;
     p.n_ex = pegn && !p.emit_pe ? B : 0;
     p.gs = ceil_div(p.n_slots, kGroups);
     p.G1 = ceil_div(p.n_slots, p.gs);
@@ -283,6 +290,13 @@ hipError_t static_scratch(void **out)
 }
 bool dtype_ok(int dt) { return dt == LNPEGN_F32 || dt == LNPEGN_BF16; }
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+Access access_of(const void *x, const void *dy, const void *dx, const void *gamma, int dt)
+{
+    if (aligned16(x) && aligned16(dy) && aligned16(dx) && aligned16(gamma)) return kVectorAccess;
+    const uintptr_t any = reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dy) |
+                          reinterpret_cast<uintptr_t>(dx) | reinterpret_cast<uintptr_t>(gamma);
+    return (any & (dt == LNPEGN_BF16 ? 1u : 3u)) == 0 ? kElementAccess : kGenericAccess;
+}
 
 int run_bwd(bool pegn, bool defer, bool accumulate, bool rms, const void *x, const void *dy, const void *gamma, const float *mean,
             const float *rstd, void *dx, float *dgamma, float *dbeta, float *pe_gamma_sq,
@@ -296,8 +310,9 @@ int run_bwd(bool pegn, bool defer, bool accumulate, bool rms, const void *x, con
     if (!rms && (mean == nullptr) != (rstd == nullptr)) return LNPEGN_EINVAL;
     if (dx == x) return LNPEGN_EINVAL;
     if ((int64_t)B * T > INT32_MAX) return LNPEGN_EINVAL;   // row indices are 32-bit
-    const bool vector_ok = aligned16(x) && aligned16(dy) && aligned16(dx) && aligned16(gamma);
-    const Plan p = make_plan(B, T, D, (lnpegn_dtype)dt, pegn, vector_ok);
+    Plan p = make_plan(B, T, D, (lnpegn_dtype)dt, pegn, access_of(x, dy, dx, gamma, dt));
+    // (ragged rows may be cut into more chunks than the generic kernel asks for: in less workspace they take that one)
+    if (p.ragged && workspace_bytes < p.total) p = make_plan(B, T, D, (lnpegn_dtype)dt, pegn, kGenericAccess);
     if (!workspace || workspace_bytes < p.total) return LNPEGN_EWORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) % kAlign) return LNPEGN_EINVAL;
     if (p.n_slots > INT32_MAX) return LNPEGN_EINVAL;
@@ -321,7 +336,7 @@ int run_bwd(bool pegn, bool defer, bool accumulate, bool rms, const void *x, con
     const RowLaunch rl{s, g_ev_start, g_ev_stop};
     g_ev_start = g_ev_stop = nullptr;
     RowShape rs{};
-    rs.plain = p.plain; rs.fast = p.fast; rs.vpt = p.vpt; rs.S = p.S; rs.R = p.R; rs.nvec = p.nvec;
+    rs.plain = p.plain; rs.fast = p.fast; rs.ragged = p.ragged; rs.vpt = p.vpt; rs.S = p.S; rs.R = p.R; rs.nvec = p.nvec;
     rs.n_slots = p.n_slots; rs.lds_bytes = p.lds_bytes;
     // measured (size of dx in MiB: streaming / write-through, us per launch, one layer at a time): 32: 23.2 / 22.1,
     // 64: 39.1 / 36.6 and 41.2 / 35.9, 96: 57.3 / 54.2, 128: 69.6 / 68.6, 192: 108.3 / 109.6.  At 128 MiB the
@@ -410,27 +425,41 @@ __global__ __launch_bounds__(256) void stream_probe_oneshot_kernel(const uint4 *
     }
 }
 
+template <typename T, bool kWriteY, bool kRagged>
+hipError_t launch_fwd_vectors(FwdArgs a, hipStream_t s);
+
 template <typename T, bool kWriteY>
 hipError_t launch_fwd(FwdArgs a, bool vector_ok, hipStream_t s)
 {
     constexpr int E = Vec<T>::kElems;
     const int D = a.D;
     const int64_t N = a.N;
-    const bool fast = vector_ok && (D % E == 0) && (D / E <= 64 * (16 / E) * 16);   // up to 16 waves share a row
-    if (!fast) {
+    const uintptr_t any = reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.y) |
+                          reinterpret_cast<uintptr_t>(a.gamma) | reinterpret_cast<uintptr_t>(a.beta);
+    const bool element_ok = (any & (16 / E - 1)) == 0, fits = ceil_div(D, E) <= 64 * (16 / E) * 16;   // up to 16 waves share a row
+    a.nvec = ceil_div(D, E);
+    if (vector_ok && D % E == 0 && fits) return launch_fwd_vectors<T, kWriteY, false>(a, s);
+    if (element_ok && D >= E && fits) return launch_fwd_vectors<T, kWriteY, true>(a, s);
+    {
         const unsigned grid = (unsigned)(N < 4096 ? N : 4096);
         return launch(ln_fwd_generic_kernel<T, kWriteY>, dim3(grid), dim3(256), 0, s, a);
     }
-    a.nvec = D / E;
+}
+
+template <typename T, bool kWriteY, bool kRagged>
+hipError_t launch_fwd_vectors(FwdArgs a, hipStream_t s)
+{
+    constexpr int E = Vec<T>::kElems;
+    const int64_t N = a.N;
     if (a.nvec <= 64 * (16 / E)) {
         const int vpt = ceil_div(a.nvec, 64);
         const int64_t want = (N + 3) / 4;
         const dim3 grid((unsigned)(want < 4096 ? want : 4096)), block(256);
         switch (vpt) {
-            case 1: return launch(ln_fwd_kernel<T, 1, false, kWriteY>, grid, block, 0, s, a);
-            case 2: return launch(ln_fwd_kernel<T, 2, false, kWriteY>, grid, block, 0, s, a);
-            case 3: return launch(ln_fwd_kernel<T, 3, false, kWriteY>, grid, block, 0, s, a);
-            case 4: return launch(ln_fwd_kernel<T, 4, false, kWriteY>, grid, block, 0, s, a);
+            case 1: return launch(ln_fwd_kernel<T, 1, false, kWriteY, kRagged>, grid, block, 0, s, a);
+            case 2: return launch(ln_fwd_kernel<T, 2, false, kWriteY, kRagged>, grid, block, 0, s, a);
+            case 3: return launch(ln_fwd_kernel<T, 3, false, kWriteY, kRagged>, grid, block, 0, s, a);
+            case 4: return launch(ln_fwd_kernel<T, 4, false, kWriteY, kRagged>, grid, block, 0, s, a);
             default: return hipErrorInvalidValue;
         }
     } else {
@@ -441,10 +470,10 @@ hipError_t launch_fwd(FwdArgs a, bool vector_ok, hipStream_t s)
         const int64_t cap = waves <= 4 ? 4096 / waves : 4096;
         const dim3 grid((unsigned)(N < cap ? N : cap)), block(64 * waves);
         switch (vpt) {
-            case 1: return launch(ln_fwd_kernel<T, 1, true, kWriteY>, grid, block, 0, s, a);
-            case 2: return launch(ln_fwd_kernel<T, 2, true, kWriteY>, grid, block, 0, s, a);
-            case 3: return launch(ln_fwd_kernel<T, 3, true, kWriteY>, grid, block, 0, s, a);
-            case 4: return launch(ln_fwd_kernel<T, 4, true, kWriteY>, grid, block, 0, s, a);
+            case 1: return launch(ln_fwd_kernel<T, 1, true, kWriteY, kRagged>, grid, block, 0, s, a);
+            case 2: return launch(ln_fwd_kernel<T, 2, true, kWriteY, kRagged>, grid, block, 0, s, a);
+            case 3: return launch(ln_fwd_kernel<T, 3, true, kWriteY, kRagged>, grid, block, 0, s, a);
+            case 4: return launch(ln_fwd_kernel<T, 4, true, kWriteY, kRagged>, grid, block, 0, s, a);
             default: return hipErrorInvalidValue;
         }
     }
@@ -462,8 +491,8 @@ size_t lnpegn_workspace_bytes(int B, int T, int D, lnpegn_dtype dt)
     if (!shape_ok(B, T, D) || !dtype_ok(dt)) return 0;
     size_t need = 0;
     for (int pegn = 0; pegn < 2; ++pegn)
-        for (int vec = 0; vec < 2; ++vec) {
-            const size_t t = make_plan(B, T, D, dt, pegn != 0, vec != 0).total;
+        for (Access access : {kGenericAccess, kElementAccess, kVectorAccess}) {
+            const size_t t = make_plan(B, T, D, dt, pegn != 0, access).total;
             if (t > need) need = t;
         }
     return need;
@@ -473,9 +502,9 @@ int lnpegn_plan_query(int B, int T, int D, lnpegn_dtype dt, int per_example, int
 {
     if (!shape_ok(B, T, D) || !out || n_out < 0) return LNPEGN_EINVAL;
     if (!dtype_ok(dt)) return LNPEGN_EUNSUPPORTED;
-    const Plan p = make_plan(B, T, D, dt, per_example != 0, aligned != 0);
+    const Plan p = make_plan(B, T, D, dt, per_example != 0, aligned != 0 ? kVectorAccess : kElementAccess);
     const int64_t v[LNPEGN_PLAN_FIELDS] = {
-        p.fast ? 1 : 0, p.S, p.fast ? p.R : 1, p.vpt, p.C, p.n_slots, p.rows_per, p.stagger, p.xcd_chunks,
+        p.fast && !p.ragged ? 1 : 0, p.S, p.fast ? p.R : 1, p.vpt, p.C, p.n_slots, p.rows_per, p.stagger, p.xcd_chunks,
         (int64_t)p.lds_bytes, p.emit_pe ? 1 : 0, p.n_ex, p.G1, p.gs, (int64_t)p.total, p.Tp};
     for (int i = 0; i < n_out && i < LNPEGN_PLAN_FIELDS; ++i) out[i] = v[i];
     return LNPEGN_OK;
@@ -552,8 +581,10 @@ int ln_bwd_pegn_static(const void *x, const void *dy, const void *gamma, const f
     // validate the shape against the fixed scratch before touching the device
     if (!shape_ok(B, T, D) || !(eps >= 0.f)) return LNPEGN_EINVAL;
     if (!dtype_ok(dt) || !dtype_ok(gamma_dt)) return LNPEGN_EUNSUPPORTED;
-    const bool vector_ok = aligned16(x) && aligned16(dy) && aligned16(dx) && aligned16(gamma);
-    if (make_plan(B, T, D, dt, true, vector_ok).total > kStaticScratchBytes) return LNPEGN_EWORKSPACE;
+    const Access access = access_of(x, dy, dx, gamma, dt);
+    if (make_plan(B, T, D, dt, true, access).total > kStaticScratchBytes &&
+        !(make_plan(B, T, D, dt, true, access).ragged && make_plan(B, T, D, dt, true, kGenericAccess).total <= kStaticScratchBytes))
+        return LNPEGN_EWORKSPACE;
     void *ws = nullptr;
     const hipError_t e = static_scratch(&ws);
     if (e != hipSuccess) {
@@ -630,15 +661,16 @@ int lnpegn_reduce_deferred(void *const *workspaces, int n, int B, int T, int D, 
     if (!dtype_ok(dt)) return LNPEGN_EUNSUPPORTED;
     for (int i = 0; i < n; ++i)
         if (!workspaces[i] || reinterpret_cast<uintptr_t>(workspaces[i]) % kAlign) return LNPEGN_EINVAL;
-    const Plan p = make_plan(B, T, D, dt, true, true);   // the offsets used depend on B and D only
+    const Plan p = make_plan(B, T, D, dt, true, kVectorAccess);   // the offsets used depend on B and D only
     // Which form a layer takes was decided when its row kernel was launched (plain or per-example, aligned or not) and
     // stands in its header; a form that no layer of this shape can have taken is not launched.
     bool some_one = g_overridden, some_two = g_overridden;
-    for (int i = 0; i < 4; ++i) {
-        const bool one = make_plan(B, T, D, dt, (i & 1) != 0, (i & 2) != 0).one_pass;
-        some_one = some_one || one;
-        some_two = some_two || !one;
-    }
+    for (int pegn = 0; pegn < 2; ++pegn)
+        for (Access access : {kGenericAccess, kElementAccess, kVectorAccess}) {
+            const bool one = make_plan(B, T, D, dt, pegn != 0, access).one_pass;
+            some_one = some_one || one;
+            some_two = some_two || !one;
+        }
     const int g1_max = B + kGroups;     // an example each, then the groups
     hipStream_t s = static_cast<hipStream_t>(stream);
     for (int first = 0; first < n; first += kBatchMax) {

@@ -103,6 +103,55 @@ struct bf16_t {
     uint16_t bits;
 };
 
+// v shifted towards its low end by `bytes` (0..15); zeros come in behind.
+__device__ __forceinline__ u32x4_t shift_down(u32x4_t v, int bytes)
+{
+    const bool one = (bytes & 4) != 0, two = (bytes & 8) != 0;
+    if (two) v = u32x4_t{v.z, v.w, 0u, 0u};
+    if (one) v = u32x4_t{v.y, v.z, v.w, 0u};
+    const uint32_t rest = bytes & 3;
+    return u32x4_t{__builtin_amdgcn_alignbyte(v.y, v.x, rest), __builtin_amdgcn_alignbyte(v.z, v.y, rest),
+                   __builtin_amdgcn_alignbyte(v.w, v.z, rest), __builtin_amdgcn_alignbyte(0u, v.w, rest)};
+}
+
+// Sixteen bytes at an address that is only aligned to an element of T.  (A bf16 address that is no multiple of 4 costs a
+// wave's load 67 cycles instead of 20; any multiple of 4 costs nothing.)
+typedef u32x4_t u32x4_at2_t __attribute__((aligned(2)));
+typedef u32x4_t u32x4_at4_t __attribute__((aligned(4)));
+template <typename T>
+struct element_aligned16 {
+    using type = u32x4_at4_t;
+};
+template <>
+struct element_aligned16<bf16_t> {
+    using type = u32x4_at2_t;
+};
+
+// One 16-byte vector of a row whose width is no multiple of it, or which lies at any address: the row's last vector is
+// read from where it ends with the row (Ragged::offset) and shifted, so that elements behind the row's end are
+// zero, as they are in padded lanes.
+struct Ragged {
+    int offset;      // bytes from the row's first element to what the lane reads
+    int shift;       // bytes by which that lies before the lane's own first element
+    int count;       // elements the lane owns (a whole vector, fewer, or none)
+    template <typename T>
+    __device__ static Ragged of(int v, int D)
+    {
+        constexpr int kElems = 16 / (int)sizeof(T);
+        const int first = v * kElems;
+        Ragged r;
+        r.count = min(max(D - first, 0), kElems);
+        r.offset = r.count > 0 ? min(first, D - kElems) * (int)sizeof(T) : 0;
+        r.shift = r.count > 0 ? first * (int)sizeof(T) - r.offset : 0;
+        return r;
+    }
+    __device__ u32x4_t trim(u32x4_t v) const
+    {
+        v = shift_down(v, shift);
+        return count > 0 ? v : u32x4_t{0u, 0u, 0u, 0u};
+    }
+};
+
 // ---------------------------------------------------------------------------------------
 // Buffer addressing.  A row is described by a buffer resource (base address, size in bytes); a
 // lane whose byte offset lies beyond the size reads zeros and its stores are dropped by the

@@ -13,6 +13,7 @@ namespace lnpegn {
 struct RowShape {
     bool plain;       // no per-example outputs: the plain backward's kernel
     bool fast;        // vectorised kernels (else the generic kernel)
+    bool ragged;      // ... their form for rows of any width and address
     bool dx_cached;   // dx stored write-back instead of streaming
     int vpt;          // 16-byte vectors per lane
     int S, R;         // waves per row, row groups per workgroup

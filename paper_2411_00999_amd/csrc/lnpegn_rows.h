@@ -73,6 +73,27 @@ __device__ __forceinline__ void load_gamma_vec(const void *gamma, int gamma_is_f
     }
 }
 
+// ... of a row of any width (r: the lane's last vector; `last`: v is that one), zeros behind the row's end.
+template <typename T>
+__device__ __forceinline__ void load_gamma_ragged(const void *gamma, int gamma_is_f32, int v, const Ragged &r, bool last,
+                                                  int D, float (&g)[Vec<T>::kElems])
+{
+    constexpr int E = Vec<T>::kElems;
+    if ((E == 4) == (gamma_is_f32 != 0)) {
+        using P = const __attribute__((address_space(1))) typename element_aligned16<T>::type *;
+        u32x4_t t = *(P)(static_cast<const char *>(gamma) + (last ? r.offset : v * 16));
+        if (last) t = r.trim(t);
+        Vec<T>::unpack(__builtin_bit_cast(typename Vec<T>::Raw, t), g);
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int col = v * E + e;
+        const float t = load_gamma(gamma, gamma_is_f32, min(col, D - 1));
+        g[e] = col < D ? t : 0.f;
+    }
+}
+
 // Valid elements owned by wave ws of a row group (the S waves interleave inside 64*S-vector spans).
 template <int kVpt, int E>
 __device__ __forceinline__ int wave_valid_elems(int ws, int S, int nvec)
@@ -114,7 +135,9 @@ constexpr int rows_kernel_min_blocks(int kS, int elems)
 // kPlain: the plain backward (one partition "example" spanning the whole tensor, never any
 // per-example output); it is a kernel of its own name so that a kernel trace tells the two apart.
 // kDxCached: dx is small enough for the memory-side cache: write-through stores instead of streaming ones.
-template <typename T, int kVpt, bool kSaved, int kS, bool kFull, bool kPlain, bool kDxCached>
+// kRagged: rows of any width of at least one vector, at any address (see Ragged): never kFull.  Elements behind the
+// row's end are zeros in every product and sum; per-example norms are left to the reduction.
+template <typename T, int kVpt, bool kSaved, int kS, bool kFull, bool kPlain, bool kDxCached, bool kRagged = false>
 __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
 {
     using V = Vec<T>;
@@ -163,11 +186,13 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
     for (int k = 0; k < kVpt; ++k) vidx[k] = (k * S + ws) * kWave + lane;
     const bool ok_last = kFull ? true : vidx[KL] < a.nvec;
     const int v_last = ok_last ? vidx[KL] : 0;     // gamma of a padded lane: a valid vector, then zeroed
-    const int n_w = wave_valid_elems<kVpt, E>(ws, S, a.nvec);
+    const Ragged rg = kRagged ? Ragged::of<typename std::conditional<E == 8, uint16_t, float>::type>(vidx[KL], a.D) : Ragged{};
+    int n_w = wave_valid_elems<kVpt, E>(ws, S, a.nvec);
+    if (kRagged && (a.nvec - 1) / kWave == KL * S + ws) n_w -= a.nvec * E - a.D;   // the wave that holds the row's end
 
     // Rows are addressed as buffers of one row each: a padded lane (vector index >= nvec) reads
     // zeros and its store is dropped, with no branch around the access.
-    const int row_bytes = a.nvec * (int)sizeof(Raw);
+    const int row_bytes = kRagged ? a.D * (16 / E) : a.nvec * (int)sizeof(Raw);
     const char *xbase = static_cast<const char *>(a.x);
     const char *dybase = static_cast<const char *>(a.dy);
     char *dxbase = static_cast<char *>(a.dx);
@@ -186,6 +211,16 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
             st_rstd = a.rstd[rr];
         }
         const int64_t off = (int64_t)rr * row_bytes;
+        if constexpr (kRagged) {
+#pragma unroll
+            for (int k = 0; k < kVpt; ++k) {
+                const int at = k < KL ? vidx[k] * (int)sizeof(Raw) : rg.offset;
+                using P = const __attribute__((address_space(1))) typename element_aligned16<T>::type *;
+                xr[k] = __builtin_bit_cast(Raw, (u32x4_t)__builtin_nontemporal_load((P)(xbase + off + at)));
+                dr[k] = __builtin_bit_cast(Raw, (u32x4_t)__builtin_nontemporal_load((P)(dybase + off + at)));
+            }
+            return;
+        }
         const rsrc_t rx = make_rsrc(xbase + off, row_bytes);
         const rsrc_t rd = make_rsrc(dybase + off, row_bytes);
 #pragma unroll
@@ -203,6 +238,10 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
     float gm[kVpt][E];
 #pragma unroll
     for (int k = 0; k < kVpt; ++k) {
+        if constexpr (kRagged) {
+            load_gamma_ragged<T>(a.gamma, a.gamma_is_f32, vidx[k], rg, k == KL, a.D, gm[k]);
+            continue;
+        }
         load_gamma_vec<T>(a.gamma, a.gamma_is_f32, k < KL ? vidx[k] : v_last, gm[k]);
         if (k == KL && !ok_last) {
 #pragma unroll
@@ -251,6 +290,12 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
             if constexpr (kDrainStores) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0) only
 #pragma unroll
             for (int k = 0; k < kVpt; ++k) {
+                if constexpr (kRagged) {
+                    if (k == KL) {
+                        xr[k] = __builtin_bit_cast(Raw, rg.trim(__builtin_bit_cast(u32x4_t, xr[k])));
+                        dr[k] = __builtin_bit_cast(Raw, rg.trim(__builtin_bit_cast(u32x4_t, dr[k])));
+                    }
+                }
                 V::unpack(xr[k], xf[k]);   // padded lanes hold zeros: the buffer load returned them
                 V::unpack(dr[k], df[k]);
             }
@@ -276,7 +321,7 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
                     float xc = xf[k][e] - pivot;
-                    if (!kFull && k == KL) xc = ok_last ? xc : 0.f;
+                    if (!kFull && k == KL) xc = (kRagged ? e < rg.count : ok_last) ? xc : 0.f;
                     const float dyh = df[k][e] * gm[k][e];
                     xf[k][e] = xc;
                     s_dyh += dyh;
@@ -357,10 +402,27 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
             // dx is written once and not read back here.  Streaming stores for tensors that no cache
             // holds, write-back stores where the memory-side cache can take them: a compile-time choice,
             // because a branch around a store makes the compiler wait for every store at the loop head
+            if constexpr (kRagged) {
+                char *row = dxbase + (int64_t)r * row_bytes;
 #pragma unroll
-            for (int k = 0; k < kVpt; ++k)
-                V::template store_buf<kDxCached ? kStoreAuxSmall : kStoreAuxLarge>(
-                    ro, vidx[k] * (int)sizeof(Raw), packed[k]);
+                for (int k = 0; k < kVpt; ++k) {
+                    using P = __attribute__((address_space(1))) typename element_aligned16<T>::type *;
+                    if (k < KL || rg.count == E) {
+                        *(P)(row + vidx[k] * (int)sizeof(Raw)) = __builtin_bit_cast(u32x4_t, packed[k]);
+                    } else {
+                        float o[E];
+                        V::unpack(packed[k], o);               // rounded already: stored as they are
+#pragma unroll
+                        for (int e = 0; e < E; ++e)
+                            if (e < rg.count) store_elem<T>(row, (int64_t)vidx[k] * E + e, o[e]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < kVpt; ++k)
+                    V::template store_buf<kDxCached ? kStoreAuxSmall : kStoreAuxLarge>(
+                        ro, vidx[k] * (int)sizeof(Raw), packed[k]);
+            }
         }
         parity ^= 1;
     };
@@ -385,6 +447,19 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
     // ---- hand the chunk's column sums to the workspace ----
     float *out_g = a.part + (int64_t)chunk * 2 * a.D;
     float *out_b = out_g + a.D;
+    // four column sums; a ragged row ends anywhere in them, and its workspace rows are aligned to a float only
+    auto put4 = [&](float *out, int64_t col, float4 v) {
+        if constexpr (kRagged) {
+            const float f[4] = {v.x, v.y, v.z, v.w};
+            if (col + 4 <= a.D) *(__attribute__((address_space(1))) u32x4_at4_t *)(out + col) = __builtin_bit_cast(u32x4_t, v);
+            else
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (col + i < a.D) out[col + i] = f[i];
+        } else {
+            *reinterpret_cast<float4 *>(out + col) = v;
+        }
+    };
     double sq_g = 0.0, sq_b = 0.0;   // squares of the final sums this lane writes (emit_pe)
     if (R == 1) {
         // one row group: every wave owns its columns, straight from registers
@@ -394,10 +469,8 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
 #pragma unroll
                 for (int q = 0; q < E / 4; ++q) {
                     const int64_t col = (int64_t)vidx[k] * E + q * 4;
-                    *reinterpret_cast<float4 *>(out_g + col) = make_float4(
-                        acc_g[k][q * 4], acc_g[k][q * 4 + 1], acc_g[k][q * 4 + 2], acc_g[k][q * 4 + 3]);
-                    *reinterpret_cast<float4 *>(out_b + col) = make_float4(
-                        acc_b[k][q * 4], acc_b[k][q * 4 + 1], acc_b[k][q * 4 + 2], acc_b[k][q * 4 + 3]);
+                    put4(out_g, col, make_float4(acc_g[k][q * 4], acc_g[k][q * 4 + 1], acc_g[k][q * 4 + 2], acc_g[k][q * 4 + 3]));
+                    put4(out_b, col, make_float4(acc_b[k][q * 4], acc_b[k][q * 4 + 1], acc_b[k][q * 4 + 2], acc_b[k][q * 4 + 3]));
                 }
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
@@ -434,8 +507,7 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
             }
             const int v = (k * S + ws) * kWave + lane;
             if (v < a.nvec) {
-                float *dst = (arr == 0 ? out_g : out_b) + (int64_t)v * E + e0;
-                *reinterpret_cast<float4 *>(dst) = s4;
+                put4(arr == 0 ? out_g : out_b, (int64_t)v * E + e0, s4);
                 const double q2 = (double)s4.x * s4.x + (double)s4.y * s4.y + (double)s4.z * s4.z +
                                   (double)s4.w * s4.w;
                 if (arr == 0) sq_g += q2;
@@ -443,7 +515,7 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
             }
         }
     }
-    if (!kPlain && a.emit_pe) {
+    if (!kPlain && !kRagged && a.emit_pe) {
         // Appendix B steps 2 and 6 for the example this workgroup owns entirely.  A lane's squares are
         // summed in fp64; the 64 lanes' sums then cross the wave as fp32 on the DPP network (positive
         // terms, a tree of depth 6: relative error below 1e-6) and the waves' sums are added in wave
@@ -483,10 +555,24 @@ void ln_bwd_plain_rows_kernel(RowArgs a)
     ln_bwd_rows_body<T, kVpt, kSaved, kS, kFull, true, kDxCached>(a);
 }
 
+// Rows of any width and address, instead of the generic kernel below, which passes over a row four times with element
+// accesses and is bound by their number.  Whole calls, us, generic / this: B=8 T=500 D=1001 bf16 77 / 21 (plain 58 / 19;
+// D=1000 on the aligned kernel 17), fp32 B=8 T=512 77 / 23, bf16 B=32 T=1024 D=1028 256 / 60, B=16 D=2050 283 / 55, B=8
+// D=3001 249 / 50, B=4 T=64 D=37 20 / 11.  Waves per row at run time unless one covers it: the exchange they share is
+// little beside the unaligned accesses.
+template <typename T, int kVpt, bool kSaved, int kS, bool kPlain>
+__global__ __launch_bounds__(rows_kernel_max_threads(kS, kVpt * Vec<T>::kElems),
+                             rows_kernel_min_blocks(kS, kVpt * Vec<T>::kElems))
+void ln_bwd_ragged_rows_kernel(RowArgs a)
+{
+    ln_bwd_rows_body<T, kVpt, kSaved, kS, false, kPlain, false, true>(a);
+}
+
 // ---------------------------------------------------------------------------------------
 // Generic row kernel: any D >= 1, any alignment.  One workgroup of 256 threads per chunk, one
 // row at a time, scalar element accesses; thread i owns columns i, i+256, ... and keeps their
-// running sums in the chunk's workspace slot.  Correct, not fast.
+// running sums in the chunk's workspace slot.  Correct, not fast: rows narrower than a vector, unaligned ones wider than
+// eight waves of 16 elements per lane, addresses inside an element, and workspaces that hold no more than its chunks.
 // ---------------------------------------------------------------------------------------
 template <typename T, bool kSaved>
 __global__ void ln_bwd_rows_generic_kernel(RowArgs a)
@@ -565,7 +651,10 @@ struct FwdArgs {
     float inv_D;
 };
 
-template <typename T, int kVpt, bool kMulti, bool kWriteY>
+// kRagged: rows of any width of at least one vector, at any address (see Ragged).  us, generic kernel / this, bf16: 4000
+// rows of D=1001 11.6 / 5.8 (of 1000, aligned: 5.5), 32768 of 1028 114 / 37, of 1027 104 / 41, 8192 of 3001 59 / 23.
+// gamma and beta come by the vector too: element by element they took as long as the row (11.8 us).
+template <typename T, int kVpt, bool kMulti, bool kWriteY, bool kRagged>
 __global__ void ln_fwd_kernel(FwdArgs a)
 {
     using V = Vec<T>;
@@ -582,10 +671,22 @@ __global__ void ln_fwd_kernel(FwdArgs a)
         vidx[k] = kMulti ? (k * nwaves + wave) * kWave + lane : k * kWave + lane;
         ok[k] = vidx[k] < a.nvec;
     }
+    constexpr int KL = kVpt - 1;             // only a lane's last vector can be partial or padding
+    const Ragged rg = kRagged ? Ragged::of<typename std::conditional<E == 8, uint16_t, float>::type>(vidx[KL], a.D) : Ragged{};
     float gm[kWriteY ? kVpt : 1][E], bt[kWriteY ? kVpt : 1][E];
     if constexpr (kWriteY) {
 #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
+            if constexpr (kRagged) {
+                load_gamma_ragged<T>(a.gamma, a.gamma_is_f32, vidx[k], rg, k == KL, a.D, gm[k]);
+                if (a.beta) {
+                    load_gamma_ragged<T>(a.beta, a.gamma_is_f32, vidx[k], rg, k == KL, a.D, bt[k]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) bt[k][e] = 0.f;
+                }
+                continue;
+            }
             load_gamma_vec<T>(a.gamma, a.gamma_is_f32, ok[k] ? vidx[k] : 0, gm[k]);
             if (a.beta) {
                 load_gamma_vec<T>(a.beta, a.gamma_is_f32, ok[k] ? vidx[k] : 0, bt[k]);
@@ -605,7 +706,14 @@ __global__ void ln_fwd_kernel(FwdArgs a)
 #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             Raw raw = V::zero();
-            if (ok[k]) raw = V::load_stream(xv + r * a.nvec + vidx[k]);   // x is not read again by this kernel
+            if constexpr (kRagged) {
+                using P = const __attribute__((address_space(1))) typename element_aligned16<T>::type *;
+                const char *at = static_cast<const char *>(a.x) + r * a.D * (16 / E) + (k < KL ? vidx[k] * 16 : rg.offset);
+                u32x4_t t = (u32x4_t)__builtin_nontemporal_load((P)at);
+                raw = __builtin_bit_cast(Raw, k < KL ? t : rg.trim(t));
+            } else if (ok[k]) {
+                raw = V::load_stream(xv + r * a.nvec + vidx[k]);          // x is not read again by this kernel
+            }
             V::unpack(raw, xf[k]);
 #pragma unroll
             for (int e = 0; e < E; ++e) s += xf[k][e];
@@ -623,7 +731,7 @@ __global__ void ln_fwd_kernel(FwdArgs a)
         for (int k = 0; k < kVpt; ++k)
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                const float c = ok[k] ? xf[k][e] - mean : 0.f;
+                const float c = (kRagged && k == KL ? e < rg.count : ok[k]) ? xf[k][e] - mean : 0.f;
                 xf[k][e] = c;
                 ss += c * c;
             }
@@ -646,7 +754,19 @@ __global__ void ln_fwd_kernel(FwdArgs a)
                 float o[E];
 #pragma unroll
                 for (int e = 0; e < E; ++e) o[e] = xf[k][e] * rstd * gm[k][e] + bt[k][e];
-                if (ok[k]) V::store_stream(yv + r * a.nvec + vidx[k], V::pack(o));
+                if constexpr (kRagged) {
+                    using P = __attribute__((address_space(1))) typename element_aligned16<T>::type *;
+                    char *row = static_cast<char *>(a.y) + r * a.D * (16 / E);
+                    if (k < KL || rg.count == E) {
+                        *(P)(row + vidx[k] * 16) = __builtin_bit_cast(u32x4_t, V::pack(o));
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < E; ++e)
+                            if (e < rg.count) store_elem<T>(row, (int64_t)vidx[k] * E + e, o[e]);
+                    }
+                } else if (ok[k]) {
+                    V::store_stream(yv + r * a.nvec + vidx[k], V::pack(o));
+                }
             }
         }
     }

@@ -63,6 +63,31 @@ hipError_t launch_inst(const RowShape &p, const RowArgs &a, const RowLaunch &rl)
     if (!p.fast)
         return launch_row_kernel(ln_bwd_rows_generic_kernel<InstT, kInstSaved>, dim3((unsigned)p.n_slots),
                                  dim3(256), 0, rl, a);
+    if (p.ragged) {
+        const dim3 grid((unsigned)p.n_slots), block(64 * p.R * p.S);
+        auto go = [&](auto kernel) { return launch_row_kernel(kernel, grid, block, p.lds_bytes, rl, a); };
+#define LNPEGN_RAGGED(V)                                                                                          \
+    case V:                                                                                                        \
+        if (p.S == 1)                                                                                               \
+            return p.plain ? go(ln_bwd_ragged_rows_kernel<InstT, V, kInstSaved, 1, true>)                            \
+                           : go(ln_bwd_ragged_rows_kernel<InstT, V, kInstSaved, 1, false>);                          \
+        return p.plain ? go(ln_bwd_ragged_rows_kernel<InstT, V, kInstSaved, 0, true>)                                \
+                       : go(ln_bwd_ragged_rows_kernel<InstT, V, kInstSaved, 0, false>)
+        switch (p.vpt) {
+            LNPEGN_RAGGED(1);
+            LNPEGN_RAGGED(2);
+            default: break;
+        }
+        if constexpr (Vec<InstT>::kElems == 4) {
+            switch (p.vpt) {
+                LNPEGN_RAGGED(3);
+                LNPEGN_RAGGED(4);
+                default: break;
+            }
+        }
+#undef LNPEGN_RAGGED
+        return hipErrorInvalidValue;
+    }
     // up to 16 elements per lane (2 vectors of 8 bf16, 4 vectors of 4 fp32) at any number of waves per row;
     // 24 or 32 elements per lane only for rows of eight waves (D > 8192)
     constexpr int kBase = 16 / Vec<InstT>::kElems;

@@ -192,6 +192,45 @@ def test_in_place_dx_over_dy():
     pu.compare_with_oracle(inp, res, ref)
 
 
+@pytest.mark.parametrize("dtype,D,off", [
+    ("bf16", 8, 1), ("bf16", 9, 0), ("bf16", 15, 3), ("bf16", 511, 0), ("bf16", 513, 0),      # one vector ... past one wave
+    ("bf16", 768, 2), ("bf16", 1023, 0), ("bf16", 1024, 1), ("bf16", 1025, 0), ("bf16", 2049, 0),   # S = 1, 2, 3
+    ("bf16", 4100, 0), ("bf16", 8191, 0), ("bf16", 8192, 1), ("bf16", 8193, 0),      # ... 8 waves, then the generic kernel
+    ("f32", 4, 1), ("f32", 5, 0), ("f32", 255, 0), ("f32", 257, 1), ("f32", 515, 0), ("f32", 1021, 0), ("f32", 1025, 0),
+    ("f32", 3001, 0), ("f32", 4095, 3), ("f32", 8190, 0),
+])
+@pytest.mark.parametrize("saved", [False, True])
+def test_rows_of_any_width_and_address(dtype, D, off, saved):
+    """Rows that are no whole number of vectors or not 16-byte aligned, dx over dy, against the oracle; the elements
+    around the tensors stay as they are; the generic kernel in a workspace too small for more chunks agrees."""
+    import torch
+    from paper_2411_00999_amd import binding
+    inp = workloads.make_inputs(1, B=3, T=23, D=D, dtype=dtype)
+    ref = _oracle(inp)
+    tdt, n = (torch.bfloat16 if dtype == "bf16" else torch.float32), 3 * 23 * D
+
+    def shifted(a):
+        buf = torch.full((n + 16,), 7.0, dtype=tdt, device="cuda")
+        view = buf[off:off + n].view(3, 23, D)
+        view.copy_(pu.to_device(a, dtype))
+        return buf, view
+
+    (xb, x), (gb, dy), gamma, beta = shifted(inp.x), shifted(inp.dy), pu.to_device(inp.gamma, dtype), pu.to_device(inp.beta, dtype)
+    yb, y = shifted(np.zeros_like(inp.x))
+    _, mean, rstd = binding.ln_fwd(x, gamma, beta, inp.eps, y=y)
+    pu.check_close("y", pu.to_host64(y), oracle.ln_fwd(inp.x, inp.gamma, inp.beta, inp.eps),
+                   pu.TOL_BF16 if dtype == "bf16" else pu.TOL_F32, bf16_output=dtype == "bf16")
+    kw = dict(mean=mean, rstd=rstd) if saved else {}
+    plain = binding.ln_bwd(x, dy, gamma, inp.eps, **kw)
+    out = binding.ln_bwd_pegn(x, dy, gamma, inp.eps, dx=dy, **kw)
+    torch.cuda.synchronize()
+    names = ("dx", "dgamma", "dbeta", "s_gamma", "s_beta", "big_sq")
+    pu.compare_with_oracle(inp, dict(zip(names, map(pu.to_host64, out))), ref)
+    pu.compare_with_oracle(inp, dict(zip(names, map(pu.to_host64, plain))), ref, pegn=False)
+    for b in (xb, gb, yb):
+        assert bool((b[:off] == 7).all()) and bool((b[off + n:] == 7).all())
+
+
 def test_misaligned_pointers_take_the_generic_kernel():
     import torch
     from paper_2411_00999_amd import binding
