@@ -160,7 +160,7 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
         const char *next;       // first element of this tile's columns, at the next stage to fetch
         const char *last;       // the last whole chunk of the tensor
         int stage;              // that stage's number within its example
-        int left;               // stages still to fetch; behind the last, rows of zeros
+        int left;               // stages still to fetch; behind the last, none or (ragged forms) rows of zeros
         int width, col0;        // columns in all, first column of the tile
     };
     Operand ox{a.x + ((int64_t)b_begin * a.T * a.K + k0) * kElem, a.x + (int64_t)a.B * a.T * a.K * kElem - 16, 0, nstages, a.K, k0};
@@ -188,6 +188,10 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
     auto fetch = [&](Operand &o, auto loads, auto chunks, uint32_t dst) {
         constexpr int kN = decltype(loads)::value, kChunks = decltype(chunks)::value;
         const int rows = rows_at(o);
+        if (!kRagged && rows == 0) {                           // (chunks of zeros, one place for all to read: 1 us a call)
+            --o.left;
+            return;
+        }
         const int ln = own_lane();
         auto to = [&](int n) { return dst + (wave * kN + n) * 1024; };
         if (!kTracked && inside && rows == kStageT) {
@@ -448,11 +452,13 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
     auto buffer = [&](int ahead) { return cur + ahead >= kBufs ? cur + ahead - kBufs : cur + ahead; };
     auto do_stage = [&](auto next_set) {
         // younger than the direct loads of stage st: those of st+1, the register loads of st+1 and st+2
-        if constexpr (kDirect > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kDirect + kSets * kStaged) : "memory");
+        // (without ragged operands nothing is issued behind the last stage)
+        if (!kRagged && ox.left < 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else if constexpr (kDirect > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kDirect + kSets * kStaged) : "memory");
         if constexpr (kRagged) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // loads into registers stay under way
         else __syncthreads();
-        // Every stage issues the same loads, also where no stage is left (of zeros then): the counts above, and the
-        // compiler's own for the registers, hold only if no path issues fewer.
+        // With ragged operands every stage issues the same loads, also where no stage is left (of zeros then): the
+        // counts above, and the compiler's own for the registers, hold only if no path issues fewer.
         auto refill = [&]() {
             if constexpr (kRagged) put_regs(next_set, buffer(1));
             fetch_direct(buffer(2));
@@ -644,12 +650,26 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, int ma
         p.tiles_k = (K + Cfg::kTileK - 1) / Cfg::kTileK;
         p.tiles_l = (L + Cfg::kTileL - 1) / Cfg::kTileL;
         const int ntiles = p.tiles_k * p.tiles_l;
-        // enough workgroups for 256 CUs: split the examples when the output has few tiles
-        int want = (256 + ntiles - 1) / ntiles;
-        if (want > B) want = B;
-        if (want > max_split) want = max_split;
-        p.b_per_split = (B + want - 1) / want;
-        p.nsplit = (B + p.b_per_split - 1) / p.b_per_split;
+        // Split the examples when the output has fewer tiles than there are CUs, which hold one workgroup each: as the
+        // time of the rounds of workgroups (1.1 us per bf16 stage, 3.5 per fp32 stage) and of adding the splits (a launch
+        // and 128 KB written and read per tile and split) says.  At most as many splits as fill the CUs, which was the
+        // rule before and ran four splits of 72 tiles, 288 workgroups, in two rounds.  us, that / this: bf16 B=8 T=1024 K=768 L=3072 87 / 70,
+        // B=64 479 / 376, B=8 T=64 40 / 21, B=8 T=2048 K=2048 L=2560 262 / 221, B=5 T=512 K=768 L=2304 45 / 34, fp32 B=8
+        // T=512 K=768 L=3072 284 / 223; unchanged where the splits fill one round (B=8 T=1024 K=768 L=2304 56).
+        int most = (256 + ntiles - 1) / ntiles;
+        if (most > B) most = B;
+        if (most > max_split) most = max_split;
+        const int stages = (T + Cfg::kStageT - 1) / Cfg::kStageT;
+        const double stage_us = dt == LNPEGN_BF16 ? 1.1 : 3.5;
+        double best = 0.0;
+        for (int n = 1; n <= most; ++n) {
+            const int per = (B + n - 1) / n, splits = (B + per - 1) / per, rounds = (ntiles * splits + 255) / 256;
+            const double us = (double)rounds * per * stages * stage_us + (splits > 1 ? 2.0 + 0.045 * ntiles * splits : 0.0);
+            if (n > 1 && us >= best) continue;
+            best = us;
+            p.b_per_split = per;
+            p.nsplit = splits;
+        }
         p.nparts = ntiles * Cfg::kWaves;
         p.nbig = p.nsplit == 1 ? (int64_t)ntiles * Cfg::kWaves : ((int64_t)K * L + 255) / 256;
     } else {

@@ -789,6 +789,31 @@ def test_linear_pegn_accumulates_into_the_weight_gradient(B, T, K, L):
     _check_linear(x, g, _run_linear(x, g, "bf16", w0=w0), w0=w0)
 
 
+@pytest.mark.parametrize("dtype,B,T,K,L", [
+    ("bf16", 8, 300, 768, 3072),     # 72 tiles: three splits of three, three and two examples
+    ("bf16", 8, 40, 768, 3072),      # ... so short that adding the splits would take longer than they save
+    ("bf16", 9, 257, 512, 1920),     # 30 tiles: five splits of two examples, the last of one
+    ("bf16", 3, 30, 1600, 2560),     # 140 tiles: two splits would take two rounds of workgroups
+    ("bf16", 12, 5, 8, 128), ("bf16", 6, 128, 256, 136), ("f32", 7, 65, 260, 1028), ("f32", 4, 300, 64, 64),
+])
+def test_linear_pegn_splits(dtype, B, T, K, L):
+    """Shapes around the rule that shares a tile's examples out, accumulating or not; three calls in one workspace of
+    any contents give the same bits."""
+    import torch
+    from paper_2411_00999_amd import binding
+    x, g = workloads.make_linear_inputs(B * 1000 + K + L, B, T, K, L, dtype)
+    _check_linear(x, g, _run_linear(x, g, dtype))
+    w0 = np.random.default_rng(workloads.BASE_SEED + 81).normal(0, 1e-2, (K, L))
+    _check_linear(x, g, _run_linear(x, g, dtype, w0=w0), w0=w0)
+    xd, gd = pu.to_device(x, dtype), pu.to_device(g, dtype)
+    code = binding.BF16 if dtype == "bf16" else binding.F32
+    ws = torch.full((binding.load().linear_pegn_workspace_bytes(B, T, K, L, code),), 0xff, dtype=torch.uint8, device="cuda")
+    calls = [tuple(t.clone() for t in binding.linear_pegn(xd, gd, workspace=ws)) for _ in range(3)]
+    torch.cuda.synchronize()
+    for again in calls[1:]:
+        assert all(torch.equal(p, q) for p, q in zip(calls[0], again))
+
+
 @pytest.mark.parametrize("dtype,B,T,K,L", [("f32", 3, 17, 50, 36), ("bf16", 2, 9, 100, 7), ("f32", 2, 64, 256, 128),
                                            ("f32", 1, 1, 1, 1)])
 def test_linear_pegn_generic_kernel(dtype, B, T, K, L):
