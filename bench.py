@@ -33,7 +33,7 @@ HBM_PEAK_GBS = 8000.0   # MI355X published HBM3E peak
 MEASURED_TRAFFIC_BYTES = {3: 407_060_000}
 # The same for one whole call of linear_pegn / embedding_pegn on the named shapes (all kernels of the call;
 # profiles/linear_pegn_gpt1p3b_up_rocprofv3.md, profiles/embedding_pegn_gpt1p3b_wte_rocprofv3.md).
-MEASURED_CALL_TRAFFIC_BYTES = {"gpt1p3b_up": 3_134_000_000, "gpt1p3b_wte": 611_800_000}
+MEASURED_CALL_TRAFFIC_BYTES = {"gpt1p3b_up": 3_134_000_000, "gpt1p3b_wte": 603_100_000}
 
 
 # ----------------------------------------------------------------------------- HIP events
@@ -247,7 +247,7 @@ def embedding_leg(shape_name, steps, warmup, log):
         "workload": f"{shape_name}: ids [B={B},T={T}] Zipf over V={V} ({len(np.unique(ids_h))} distinct), g [B,T,D={D}] bf16 "
                     f"-> w' [V,D] fp32, s [B], ||w'||^2",
         "ms_per_call": round(ms, 4),
-        "roofline": {"kernel": "embedding_pegn (whole call: sort and fill side by side, runs, sums, final)", "bound": "hbm",
+        "roofline": {"kernel": "embedding_pegn (whole call: sort, runs and fill side by side, sums, final)", "bound": "hbm",
                      "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(gbs / HBM_PEAK_GBS, 4),
                      "traffic": MEASURED_CALL_TRAFFIC_BYTES.get(shape_name), "algorithmic_bytes_per_call": alg},
