@@ -5,12 +5,13 @@
 // The positions p = b*T + t are sorted by id (stable, so positions ascend inside an id and the rows of one
 // example are adjacent): a "segment" is all positions of one id, a "run" those of one id in one example, a
 // "piece" at most kPiece consecutive sorted positions of one run (a run is cut wherever the sorted index is a
-// multiple of kPiece).  Kernel A reads g, every row once, and fills the rows of w' that no id selects.  An id with at
-// most kShort positions is finished there by one wave (each run's share of step 3, the row of w').  A longer id is
-// handed out piece by piece: a piece that is a whole run yields that run's share at once, the piece sums are parked
-// in the workspace, and kernel B adds the parked sums in sorted order, finding them by search of the sorted list
-// rather than by walking it.  No wave reads more than kChunk + kPiece rows however skewed the ids are, and nothing
-// is atomic: results are bitwise reproducible.
+// multiple of kPiece).  Kernel A reads g, every row once, and fills the rows of w' that no id selects.  An id of at
+// most kShort positions is finished there by one wave (each run's share of step 3, the row of w'), and so is an id of up
+// to 64, by a wave that looks after nothing else but such ids.  A longer id is handed out piece by piece: a piece that is
+// a whole run yields that run's share at once, the piece sums are parked in the workspace, and kernel B adds the
+// parked sums in sorted order, an id of more than a thousand positions in parts shared out over workgroups.  However
+// skewed the ids are, a wave of kernel A reads at most kChunk + kPiece rows, or those of the ids of 13 to 64 positions that
+// begin in its 16; no floating-point number is added atomically: results are bitwise reproducible.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -343,27 +344,6 @@ __device__ __forceinline__ int64_t lower_bound_value(const uint32_t *a, int64_t 
     return lo;
 }
 
-// The same over (id, position) pairs.
-__device__ __forceinline__ int64_t lower_bound_pair(const uint32_t *keys, const uint32_t *vals, int64_t lo, int64_t len, uint32_t v,
-                                                    uint32_t target)
-{
-    while (__any(len > 0)) {
-        const int64_t step = len / 8 + 1;
-        uint32_t k[7], p[7];
-#pragma unroll
-        for (int u = 0; u < 7; ++u) {
-            k[u] = step * (u + 1) <= len ? keys[lo + step * (u + 1) - 1] : 0xffffffffu;
-            p[u] = step * (u + 1) <= len ? vals[lo + step * (u + 1) - 1] : 0xffffffffu;
-        }
-        int below = 0;
-#pragma unroll
-        for (int u = 0; u < 7; ++u) below += (step * (u + 1) <= len && (k[u] < v || (k[u] == v && p[u] < target))) ? 1 : 0;
-        lo += step * below;
-        len = len - step * below < step - 1 ? len - step * below : step - 1;
-    }
-    return lo;
-}
-
 // Zero fill of the rows of w' that no id selects (rows begin to end - 1), a part of kernel A's grid and of kernel B's:
 // the rows of ids that occur are written, whole, by the other workgroups, so everything touches different rows and
 // runs side by side.  Kernel A waits for its chains of loads more than for bandwidth and kernel B does little else, so
@@ -404,9 +384,11 @@ __device__ __forceinline__ void fill_absent_rows(const uint32_t *keys, int64_t n
 // B=64 T=512 D=1024 fp32 106 -> 91).
 // A wave of the runs sees kShort positions back (to tell whether a piece in its chunk belongs to a short segment that
 // an earlier wave owns) and far enough ahead for anything that starts in its chunk; rows are streamed sixteen
-// (fp32: eight) at a time.  contrib [ncb][n]: a run's share of s[b], at the run's first position, zero elsewhere;
+// (fp32: eight) at a time.  contrib [ncb][n]: a run's share of s[b], at the run's first position (from
+// kernel B: at another of the run's), zero elsewhere;
 // bigpart [ncb][n]: squared norm of a finished row of w', at the segment's first position (not when accumulating),
-// zero elsewhere.  The zeros are written by the waves of the runs, so neither array is cleared before.
+// zero elsewhere.  The zeros are written by the waves of the runs, so neither array is cleared before; also where kernel B
+// puts a norm afterwards.  arrived [n / part + 1][ncb] (part = 1 << part_bits): kernel B's counters, cleared here.
 // runsum [n][D]: parked sums, at the piece's first position.
 constexpr int kShort = 12;
 static_assert(kShort + kChunk + kPiece < 63 && kShort + kChunk + kShort < 63, "one 64-lane window must cover a wave's work");
@@ -479,38 +461,71 @@ __device__ __forceinline__ void stream_rows(const T *g, float *w, float *runsum,
         for (int h = 0; h < kRows; h += 8) {
             float sq[8], wsq[8];                                 // squared norms that rows r+h .. r+h+7 complete
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < 8; ++u) sq[u] = wsq[u] = 0.f;
+            auto row = [&](int u, float (&f)[8]) {
+                if constexpr (kVec) {
+                    unpack_row8(raw[h + u], f);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) f[k] = part[h + u][k];
+                }
+            };
+            auto add = [&](int u, const float (&f)[8]) {
                 const int t = r + h + u;
-                sq[u] = wsq[u] = 0.f;
-                if (t < e) {
-                    float f[8];
-                    if constexpr (kVec) {
-                        unpack_row8(raw[h + u], f);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sub[k] += f[k];
+                if ((ends.close >> t) & 1) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) sq[u] = fmaf(sub[k], sub[k], sq[u]);
+                    if (!has_cols) sq[u] = 0.f;                  // such lanes hold a copy of lane 0's columns
+                    if ((ends.park >> t) & 1) {
+                        if (has_cols) put_row(runsum + (int64_t)lane_value(ends.head_pos, t) * D + c0, sub, c0, D, false);
                     } else {
 #pragma unroll
-                        for (int k = 0; k < 8; ++k) f[k] = part[h + u][k];
-                    }
+                        for (int k = 0; k < 8; ++k) tot[k] += sub[k];
+                        if ((ends.id >> t) & 1) {
+                            if (has_cols)
+                                wsq[u] = put_row(w + (int64_t)lane_value(key, t) * D + c0, tot, c0, D, accumulate != 0, true);
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) sub[k] += f[k];
-                    if ((ends.close >> t) & 1) {
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) sq[u] = fmaf(sub[k], sub[k], sq[u]);
-                        if (!has_cols) sq[u] = 0.f;              // such lanes hold a copy of lane 0's columns
-                        if ((ends.park >> t) & 1) {
-                            if (has_cols) put_row(runsum + (int64_t)lane_value(ends.head_pos, t) * D + c0, sub, c0, D, false);
-                        } else {
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) tot[k] += sub[k];
-                            if ((ends.id >> t) & 1) {
-                                if (has_cols)
-                                    wsq[u] = put_row(w + (int64_t)lane_value(key, t) * D + c0, tot, c0, D, accumulate != 0, true);
-#pragma unroll
-                                for (int k = 0; k < 8; ++k) tot[k] = 0.f;
-                            }
+                            for (int k = 0; k < 8; ++k) tot[k] = 0.f;
                         }
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) sub[k] = 0.f;
                     }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) sub[k] = 0.f;
+                }
+            };
+            // Eight rows of one run or piece are added as a tree, which rounds less than one after the other (the parked
+            // sums of a long id cancel) and checks nothing in between.
+            float all[8];
+            int from = 0;
+            if (r + h + 7 < e && !(ends.close >> (r + h) & 0x7f)) {
+                float f2[8], f3[8];
+                auto pair = [&](int u, float (&to)[8]) {
+                    float next[8];
+                    row(u, to);
+                    row(u + 1, next);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) to[k] += next[k];
+                };
+                pair(0, all);
+                pair(2, f2);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) all[k] += f2[k];
+                pair(4, f2);
+                pair(6, f3);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) all[k] += f2[k] + f3[k];
+                from = 7;
+            } else {
+                row(7, all);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (r + h + u < e && u >= from) {
+                    float f[8];
+                    if (u < 7) row(u, f);
+                    if (u < 7) add(u, f);
+                    else add(u, all);
                 }
             }
             const int t = r + h + (lane & 7);                    // lane j < 8 stores what row r+h+j completed
@@ -558,9 +573,10 @@ __device__ __forceinline__ void finish_medium_ids(const T *g, const uint32_t *ke
 // Grid: medium_blocks workgroups for the medium segments (the longest chains, so first), then fill_blocks workgroups
 // of the fill among runs_x times the groups of kWavesPerBlock column blocks.
 template <typename T, bool kVec>
-__global__ __launch_bounds__(64 * kWavesPerBlock) void emb_runs_kernel(
+__global__ __launch_bounds__(64 * kWavesPerBlock, kVec && sizeof(T) == 2 ? 3 : 4) void emb_runs_kernel(
     const T *g, const uint32_t *keys, const uint32_t *vals, float *w, float *runsum, float *contrib, float *bigpart,
-    int64_t n, int Tn, int D, int V, int accumulate, int medium_blocks, int fill_rows, int fill_blocks, int runs_x)
+    uint32_t *arrived, int64_t n, int part_bits, int Tn, int D, int V, int accumulate, int medium_blocks, int fill_rows,
+    int fill_blocks, int runs_x)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -638,11 +654,15 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void emb_runs_kernel(
     auto in_chunk = [&](int l) { return l > kShort && l <= kShort + kChunk; };
     const bool short_mine = is_short && in_chunk(seg_first);
     {
-        // zeros at the positions of its chunk that will hold no value, but for those of short segments that begin
-        // before it, and at those of its short segments behind the chunk
+        // zeros at the positions of its chunk that will hold no value of this kernel's, but for those of short segments
+        // that begin before it, and at those of its short segments behind the chunk
         const bool owned = q >= 0 && q < n && (in_chunk(lane) ? !is_short || short_mine : lane > kShort + kChunk && short_mine);
-        if (owned && !((m_head >> lane) & 1)) contrib[(int64_t)cb * n + val] = 0.f;
-        if (owned && !((m_seg >> lane) & 1) && !accumulate) bigpart[(int64_t)cb * n + val] = 0.f;
+        // the first piece of a long id's run is the whole run if a run starts where the next piece does
+        const uint64_t pieces_above = (m_piece | ~m_valid) & ~upto, runs_or_end = m_head | ~m_valid;
+        const bool cut_run = is_long && !(pieces_above && ((runs_or_end >> __builtin_ctzll(pieces_above)) & 1));
+        if (owned && (!((m_head >> lane) & 1) || cut_run)) contrib[(int64_t)cb * n + val] = 0.f;
+        if (owned && (!((m_seg >> lane) & 1) || is_long) && !accumulate) bigpart[(int64_t)cb * n + val] = 0.f;
+        if (lane == 0 && i0 > 0 && i0 >> part_bits << part_bits == i0) arrived[(i0 >> part_bits) * ((D + kColBlock - 1) / kColBlock) + cb] = 0u;
     }
     // the rows of this wave: short segments and pieces of long ones that begin in the chunk.  Taken in stretches of
     // neighbouring rows (a medium segment may lie between two).
@@ -666,153 +686,397 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void emb_runs_kernel(
 }
 
 // Kernel B: the rows of w' of the ids with more than 64 positions, the shares of s[b] of their runs of several pieces,
-// and the squared norms of the rows, one column block at a time.  A workgroup looks after kSumSpan sorted positions,
-// among which at most one such id begins.  Its waves share out the examples; a wave finds its examples' runs by
-// search, one example per lane, and lists the runs' pieces (a run's first position and the multiples of kPiece behind
-// it), one per lane; parked sums are added eight rows at a time in sorted order, and squared at the end of a run that
-// has several; the waves' sums are added in wave order.  The cost is logarithmic in the number of positions however
-// long the id is, plus its parked rows over the waves.
+// and the squared norms of the rows, one column block at a time.
+//
+// An id's positions are cut into parts at the multiples of `part` that have kSumSpan of its positions on either side, and
+// every part is a workgroup's (the one whose span of kSumSpan positions holds the part's first; at most one part begins
+// in a span).  The workgroup's waves take a quarter of the part's positions each, list the pieces among them and add
+// their parked sums in order, eight rows in flight.  A run may be cut anywhere, so what is added up is held in three
+// sums: `open` of a run that began before and ends here, `closed` of all runs that begin and end here (each squared
+// at its end), and `rest` of a run that has not ended; neighbours combine by finishing the run between them.
+// Waves combine through LDS.  The parts of an id leave their three sums in three rows of the workspace that they have
+// read, and the last workgroup to arrive adds them up in the same way, in order: results do not depend on who is last.
+// They cross between XCDs as in the one-launch reduction of the LayerNorm gradients: device-scope stores, acknowledged
+// before the workgroup counts itself as arrived, and device-scope loads.
+//
+// Bound by latency: some 1 us each for the span, the part's positions and the combination, 2 for sixteen rows, and, for an
+// id of several parts, another 5 for the arrival and the parts' sums.  Whole calls, us, a launch for the runs and one for
+// the ids / one workgroup for all of an id's pieces / this: one id, bf16 B=64 T=2048 D=1024 278 / 273 / 187, presorted
+// B=69 T=4815 D=26 613 / 2425 / 412; half of every example one id, bf16 B=128 T=2048 D=768 471 / 482 / 364, fp32 B=16 T=2048
+// D=501 196 / 279 / 130; Zipf ids, presorted, bf16 B=16 T=2048 D=2048 128 / 125 / 124.
 constexpr int kSumWaves = 4, kSumSpan = 64;
-__global__ __launch_bounds__(64 * kSumWaves) void emb_sums_kernel(
-    const uint32_t *keys, const uint32_t *vals, float *w, const float *runsum, float *contrib, float *bigpart, int64_t n,
-    int Tn, int D, int V, int accumulate, int fill_begin, int sum_blocks, int fill_blocks)
+constexpr int kSumWindows = 4;                                   // windows of 64 positions that a wave lists at a time
+constexpr uint32_t kNoEmit = 0xffffffffu, kEndsRun = 0x80000000u, kBeginsRun = 0x80000000u;
+constexpr int kDeviceScope = 16;                                 // sc1
+static_assert(kPiece == 32, "two pieces to a window");
+
+// For each half of the wave, the first of its lo .. lo+len for which below(index) is false, where it is true up to there:
+// 32 probes a round, the two halves side by side.
+template <typename F>
+__device__ __forceinline__ uint32_t half_wave_first_not(uint32_t lo, uint32_t len, int lane, F below)
 {
-    constexpr int kBatch = 8;                                    // parked sums in flight
-    __shared__ __align__(16) float part[kSumWaves][kColBlock];
-    __shared__ float squares[kSumWaves];
+    while (__any(len > 0)) {
+        const uint32_t step = len / 33 + 1, at = step * ((lane & 31) + 1);      // probes at lo + step - 1, lo + 2 step - 1, ...
+        const uint64_t yes = __ballot(at <= len && below(lo + min(at, len) - 1));
+        const uint32_t c = __builtin_popcount((uint32_t)(lane < 32 ? yes : yes >> 32));
+        lo += step * c;
+        len = min(len - step * c, step - 1);
+    }
+    return lo;
+}
+
+// (Positions are 32-bit here, and what need not be unrolled is not: a workgroup runs through the code once or twice, and
+// fetching the instructions is a good part of its time.)
+__global__ __launch_bounds__(64 * kSumWaves, 4) void emb_sums_kernel(
+    const uint32_t *keys, const uint32_t *vals, float *w, float *runsum, float *contrib, float *bigpart, uint32_t *arrived,
+    uint32_t n, int part_bits, uint32_t Tn, int D, int V, int accumulate, int fill_begin, int sum_blocks, int fill_blocks)
+{
+    constexpr int kBatch = 8;                                    // rows in flight
+    constexpr int kOwn = kColBlock / (64 * kSumWaves);           // columns per thread where the waves combine
+    __shared__ __align__(16) uint32_t mem[kSumWaves][3 * kColBlock];           // a wave's list, then its sums: closed, open, rest
+    static_assert(64 * kSumWindows + 1 <= kColBlock && 2 * 64 * 3 <= kColBlock, "the list lies where `closed` will");
+    __shared__ uint32_t flags[kSumWaves], wave_emit[kSumWaves];  // opens, and ended << 1; emit_open
+    __shared__ float squares[kSumWaves][kSumWaves + 1];
+    __shared__ uint32_t last;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int Bn = (int)(n / Tn), ncb = (D + kColBlock - 1) / kColBlock;
+    const int ncb = (D + kColBlock - 1) / kColBlock;
     if ((int)blockIdx.x >= sum_blocks) {
         fill_absent_rows(keys, n, w, fill_begin, V, D, ((int)blockIdx.x - sum_blocks) * kSumWaves + wave, fill_blocks * kSumWaves, lane);
         return;
     }
-    const int span = (int)blockIdx.x / ncb, cb = (int)blockIdx.x - span * ncb;
-    const int c0 = cb * kColBlock + lane * 8;
-    const bool has_cols = c0 < D;
-    const bool runsum_vec = c0 + 8 <= D && D % 4 == 0 && (reinterpret_cast<uintptr_t>(runsum) & 15u) == 0;
-    const int64_t q0 = (int64_t)span * kSumSpan, q = q0 + lane;
-    const uint32_t key = q < n ? keys[q] : 0xffffffffu, before = q > 0 && q < n ? keys[q - 1] : 0xffffffffu;
-    const uint32_t beyond = q + 64 < n ? keys[q + 64] : 0xffffffffu;
-    const uint64_t starts = __ballot(key < (uint32_t)V && key != before && beyond == key);   // the same in every wave
-    if (!starts) return;
-    const int64_t i = q0 + __builtin_ctzll(starts);
-    const uint32_t v = keys[i], p0 = vals[i];
-    float acc[8], sub[8];
-    // adds the parked sums at the positions held by the lanes of `take`, in lane order: to the open run, and at its last
-    // piece (a bit of `ends`) the run to acc; a run of several pieces is squared there, its share going to head_pos
-    auto add_parked = [&](uint64_t take, uint32_t pos, uint64_t ends, uint64_t several, uint32_t head_pos) {
-        while (take) {
-            int at[kBatch], cnt = 0;
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                at[u] = take ? __builtin_ctzll(take) : (u > 0 ? at[u - 1] : 0);
-                cnt += take ? 1 : 0;
-                take &= take - 1;
-            }
-            float add[kBatch][8];
-            if (runsum_vec) {                                    // all loads first, then the additions in order
-                Row8<float> raw[kBatch];
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) raw[u] = load_row8(runsum, (int64_t)lane_value(pos, at[u]), D, c0);
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) unpack_row8(raw[u], add[u]);
+    const int span = (int)blockIdx.x / ncb, cb = (int)blockIdx.x - span * ncb, col0 = cb * kColBlock;
+    const uint32_t part = 1u << part_bits, q0 = (uint32_t)span * kSumSpan, next = ((q0 >> part_bits) + 1) << part_bits;
+    // what the span and the multiples of `part` around it hold, in one trip to memory; the same in every wave
+    auto key_at = [&](uint32_t q) { return q < n ? keys[q] : 0xffffffffu; };     // (also of what lies before the first: it wraps)
+    const uint32_t key = key_at(q0 + lane), before = key_at(q0 + lane - 1), beyond = key_at(q0 + lane + 64), below = key_at(q0 - kSumSpan);
+    const uint32_t below1 = key_at(next - kSumSpan), above1 = key_at(next + kSumSpan);
+    const uint32_t below2 = key_at(next + part - kSumSpan), above2 = key_at(next + part + kSumSpan);
+    const uint32_t ahead = key_at(q0 + 64 + lane * 64);
+    const uint64_t starts = __ballot(key < (uint32_t)V && key != before && beyond == key);
+    const uint32_t first = lane_value(key, 0);
+    // the part begins at a cut (an id that is cut at q0 covers the span)
+    const bool cut_lo = (q0 & (part - 1)) == 0 && first < (uint32_t)V && below == first && lane_value(beyond, 0) == first;
+    if (!starts && !cut_lo) return;
+    const int at_start = cut_lo ? 0 : __builtin_ctzll(starts);
+    const uint32_t lo = q0 + at_start, v = lane_value(key, at_start);
+    // The part's end: the next cut.  Where the next multiple of `part` is none the id begins less than kSumSpan before it
+    // (and the one behind may be a cut) or ends within kSumSpan behind it.  A window at a time the keys ahead say more.
+    const bool cut1 = below1 == v && above1 == v, cut2 = !cut1 && below2 == v && above2 == v, cut_hi = cut1 || cut2;
+    const uint32_t limit = min((lo + kSumSpan > next ? next + part : next) + kSumSpan, n);
+    const uint64_t m_ahead = ~__ballot(ahead == v);
+    const uint32_t seen = m_ahead ? q0 + 64 + __builtin_ctzll(m_ahead) * 64 : limit;
+    const uint32_t hi = cut1 ? next : cut2 ? next + part : min(limit, seen);             // (or before: where the id ends)
+
+    float sub[8], closed[8];                                     // the run in hand; the wave's closed runs (its `open` goes to LDS at once)
+    uint32_t opens = 0, ended = 0, emit_open = kNoEmit;          // the wave begins inside a run; a run has ended; where that run's square goes
+    // What to add up: of a part, the pieces' rows of runsum and whether a run begins there (a run ends where the next one
+    // begins: one more entry says so of the last); of the parts' sums, row and whether a run ends, and where its square goes.
+    uint32_t *const list = mem[wave];
+    const int row_bytes = min(kColBlock, D - col0) * (int)sizeof(float);
+    const bool strided = D % 8 != 0;                             // (runsum is 256-byte aligned)
+    auto column = [&](int j) { return strided ? j * 64 + lane : lane * 8 + j; };
+    // Adds up the rows of the list.  Eight neighbouring columns per lane, or columns 64 apart (any D).  shared: rows that
+    // other workgroups of this launch have stored.
+    auto add_list = [&](int count, bool shared) {
+        for (int k = 0; k < count; k += kBatch) {
+            const int at = min(k + lane % kBatch, count - 1);
+            uint32_t rows, emits;                                // row, and kEndsRun; where the square of a run of several goes
+            if (shared) {
+                rows = list[2 * at];
+                emits = list[2 * at + 1];
             } else {
+                const uint32_t here = list[at], after = list[at + 1];
+                rows = (here & ~kBeginsRun) | (after & kBeginsRun ? kEndsRun : 0u);
+                emits = after & ~here & kBeginsRun ? here : kNoEmit;
+            }
+            int at_lane = lane * (strided ? 4 : 32), open_row = -1;
+            asm volatile("" : "+v"(at_lane));                    // (the constants behind it go into the instructions, not into registers)
+            float add[kBatch][8], sq[kBatch];                    // all loads first, then the additions in order
+            auto buffer = [&](int u) {                           // a row as a buffer: columns behind its end read as zeros
+                return make_rsrc(runsum + (int64_t)(lane_value(rows, u) & ~kEndsRun) * D + col0, row_bytes);
+            };
+            auto eight = [&](auto aux) {
+                constexpr int kAux = decltype(aux)::value;
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) add[u][c] = 0.f;
-                    if (has_cols && u < cnt) add_row(runsum, (int64_t)lane_value(pos, at[u]), D, c0, false, add[u]);
+                    const rsrc_t r = buffer(u);
+                    unpack_row8(Row8<float>{__builtin_bit_cast(float4, buffer_load16<kAux>(r, at_lane)), __builtin_bit_cast(float4, buffer_load16<kAux>(r, at_lane + 16))}, add[u]);
                 }
+            };
+            if (strided) {
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    const rsrc_t r = buffer(u);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        add[u][j] = __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, at_lane + j * 256, 0, kDeviceScope));
+                }
+            } else if (shared) {
+                eight(std::integral_constant<int, kDeviceScope>{});
+            } else {
+                eight(std::integral_constant<int, 0>{});
             }
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                if (u < cnt) {
+                sq[u] = 0.f;
+                if (k + u >= count) continue;
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) sub[c] += add[u][c];
-                }
-                if (u < cnt && ((ends >> at[u]) & 1)) {
-                    if ((several >> at[u]) & 1) {
-                        float sq = 0.f;
+                for (int j = 0; j < 8; ++j) sub[j] += add[u][j];
+                if (!(lane_value(rows, u) & kEndsRun)) continue;
+                if (opens && !ended) {
+                    emit_open = lane_value(emits, u);
+                    open_row = u;
 #pragma unroll
-                        for (int c = 0; c < 8; ++c) sq = fmaf(sub[c], sub[c], sq);
-                        sq = wave_sum(has_cols ? sq : 0.f);
-                        if (lane == 0) contrib[(int64_t)cb * n + lane_value(head_pos, at[u])] = sq;
-                    }
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        acc[c] += sub[c];
-                        sub[c] = 0.f;
+                    for (int j = 0; j < 8; ++j) {
+                        list[kColBlock + column(j)] = __builtin_bit_cast(uint32_t, sub[j]);
+                        sub[j] = 0.f;
                     }
                 }
+                ended = 1;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    sq[u] = fmaf(sub[j], sub[j], sq[u]);
+                    closed[j] += sub[j];
+                    sub[j] = 0.f;
+                }
+            }
+            const bool mine = lane < kBatch && k + lane < count && emits != kNoEmit && lane != open_row;
+            if (__any(mine)) {
+                const float total = wave_sums8(sq, lane);
+                if (mine) contrib[(int64_t)cb * n + emits] = total;
             }
         }
     };
+    auto own_lds = [&]() {                                       // a wave's own LDS accesses, by other lanes
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    double tot_open[kOwn], tot_closed[kOwn], tot_rest[kOwn];     // the workgroup's sums of columns tid, tid + 256, ...
+    auto combine = [&]() {
+        __syncthreads();                                         // the lists have been read
+        if (strided) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] = sub[c] = 0.f;
-    {
-        const int per = (Bn + kSumWaves - 1) / kSumWaves;
-        const int b_begin = min(wave * per, Bn), b_end = min(b_begin + per, Bn);
-        for (int b0 = b_begin; b0 < b_end; b0 += 63) {           // lane 63 only ends the run of lane 62
-            const int b = min(b0 + lane, b_end), runs = min(63, b_end - b0);
-            // where the id's positions of example b would start (b = Bn: where the next id does)
-            const int64_t at = lower_bound_pair(keys, vals, i, n - i, b < Bn ? v : v + 1u, b < Bn ? (uint32_t)b * (uint32_t)Tn : 0u);
-            const int64_t end = __shfl_down(at, 1);
-            const int64_t second = (at / kPiece + 1) * kPiece;   // where the run's second piece starts, if it gets there
-            const int mine = lane < runs && end > at ? 1 + (int)(end > second ? (end - second + kPiece - 1) / kPiece : 0) : 0;
-            int upto = mine;                                     // pieces of this batch's runs up to this lane's
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int t = __shfl_up(upto, d);
-                upto += lane >= d ? t : 0;
+            for (int j = 0; j < 8; ++j) {
+                list[j * 64 + lane] = __builtin_bit_cast(uint32_t, closed[j]);
+                list[2 * kColBlock + j * 64 + lane] = __builtin_bit_cast(uint32_t, sub[j]);
             }
-            const int total = __shfl(upto, 63);
-            for (int k0 = 0; k0 < total; k0 += 64) {
-                const int k = k0 + lane;                         // this lane's piece; its run is found below
-                int64_t idx = -1, head = 0;
-                bool ends = false, several = false;
-                for (uint64_t left = __ballot(mine > 0 && upto > k0 && upto - mine < k0 + 64); left; left &= left - 1) {
-                    const int r = __builtin_ctzll(left);
-                    const int r_upto = __shfl(upto, r), r_mine = __shfl(mine, r);
-                    const int64_t r_at = __shfl(at, r), r_second = __shfl(second, r);
-                    const int u = k - (r_upto - r_mine);
-                    if (u >= 0 && u < r_mine) {
-                        idx = u == 0 ? r_at : r_second + (int64_t)(u - 1) * kPiece;
-                        ends = u == r_mine - 1;
-                        several = ends && r_mine > 1;
-                        head = r_at;
+        } else {
+#pragma unroll
+            for (int h = 0; h < 8; h += 4) {
+                *reinterpret_cast<u32x4_t *>(list + lane * 8 + h) = __builtin_bit_cast(u32x4_t, make_float4(closed[h], closed[h + 1], closed[h + 2], closed[h + 3]));
+                *reinterpret_cast<u32x4_t *>(list + 2 * kColBlock + lane * 8 + h) = __builtin_bit_cast(u32x4_t, make_float4(sub[h], sub[h + 1], sub[h + 2], sub[h + 3]));
+            }
+        }
+        if (lane == 0) {
+            flags[wave] = opens | ended << 1;
+            wave_emit[wave] = emit_open;
+        }
+        __syncthreads();
+        uint32_t fl[kSumWaves], m[kSumWaves][kOwn], a[kSumWaves][kOwn], z[kSumWaves][kOwn];
+#pragma unroll
+        for (int u = 0; u < kSumWaves; ++u) {
+            fl[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)flags[u]);
+#pragma unroll
+            for (int o = 0; o < kOwn; ++o) {
+                const int c = tid + o * 64 * kSumWaves;
+                m[u][o] = mem[u][c];
+                a[u][o] = mem[u][kColBlock + c];
+                z[u][o] = mem[u][2 * kColBlock + c];
+            }
+        }
+#pragma unroll
+        for (int o = 0; o < kOwn; ++o) tot_open[o] = tot_closed[o] = tot_rest[o] = 0.0;
+        bool any = false;
+        uint32_t to_emit = 0;                                    // waves whose first end completes a run of the part
+#pragma unroll
+        for (int u = 0; u < kSumWaves; ++u) {
+            const bool u_opens = fl[u] & 1, u_ends = fl[u] & 2;
+            const bool before_part = !any && (fl[0] & 1);        // that run began before the part
+            float sq = 0.f;
+#pragma unroll
+            for (int o = 0; o < kOwn; ++o) {
+                const double rest = (double)__builtin_bit_cast(float, z[u][o]), r = tot_rest[o] + (double)__builtin_bit_cast(float, a[u][o]);
+                if (u_ends) {
+                    tot_closed[o] += (double)__builtin_bit_cast(float, m[u][o]);
+                    if (u_opens && before_part) tot_open[o] = r;
+                    if (u_opens && !before_part) {
+                        tot_closed[o] += r;
+                        sq = fmaf((float)r, (float)r, sq);
                     }
+                    tot_rest[o] = rest;
+                } else {
+                    tot_rest[o] += rest;
                 }
-                const uint32_t pos = idx >= 0 ? vals[idx] : 0u, head_pos = several ? vals[head] : 0u;
-                add_parked(__ballot(idx >= 0), pos, __ballot(ends), __ballot(several), head_pos);
             }
-        }
-        *reinterpret_cast<float4 *>(&part[wave][lane * 8]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-        *reinterpret_cast<float4 *>(&part[wave][lane * 8 + 4]) = make_float4(acc[4], acc[5], acc[6], acc[7]);
-        __syncthreads();
-        float sq = 0.f;
-        for (int c = tid; c < kColBlock; c += 64 * kSumWaves) {
-            const int col = cb * kColBlock + c;
-            float sum = 0.f;
-#pragma unroll
-            for (int u = 0; u < kSumWaves; ++u) sum += part[u][c];
-            if (col < D) {
-                float *p = w + (int64_t)v * D + col;
-                if (accumulate) sum += *p;
-                __builtin_nontemporal_store(sum, p);
-                sq = fmaf(sum, sum, sq);
+            if (u_ends && u_opens && !before_part) {
+                to_emit |= 1u << u;
+                sq = wave_sum(sq);
+                if (lane == 0) squares[u][wave] = sq;
             }
+            any = any || u_ends;
         }
-        if (!accumulate) {
-            sq = wave_sum(sq);
-            if (lane == 0) squares[wave] = sq;
-        }
+        if (!to_emit) return;
         __syncthreads();
-        if (!accumulate && tid == 0) {
+        if (tid < kSumWaves && ((to_emit >> tid) & 1)) {
             float t = 0.f;
-            for (int u = 0; u < kSumWaves; ++u) t += squares[u];
-            bigpart[(int64_t)cb * n + p0] = t;
+            for (int u = 0; u < kSumWaves; ++u) t += squares[tid][u];
+            contrib[(int64_t)cb * n + wave_emit[tid]] = t;
         }
+    };
+
+    // ---- first the rows of the part, then, for the last workgroup of several, the sums that the parts have left
+    uint32_t first_cut = 0, parts = 1;
+    uint32_t park[3] = {0, 0, 0};                                // rows of runsum for the part's three sums
+#pragma unroll 1
+    for (bool over_parts = false;; over_parts = true) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sub[j] = closed[j] = 0.f;
+        ended = opens = 0;
+        emit_open = kNoEmit;
+        // a wave takes a quarter of the windows of 64 positions, or of the parts
+        const uint32_t it_first = over_parts ? 0 : lo / 64, its = over_parts ? parts : (hi - 1) / 64 - it_first + 1;
+        const uint32_t per = (its + kSumWaves - 1) / kSumWaves, it_begin = it_first + min(wave * per, its);
+        const uint32_t it_end = min(it_begin + per, it_first + its);
+        // the example of the position before the windows in hand if it is the id's, and the next windows' pairs, on their
+        // way while rows are added
+        uint32_t ex_before = kNoEmit, next_key[kSumWindows], next_val[kSumWindows], key_behind = 0, val_behind = 0;
+        auto fetch = [&](uint32_t window) {
+#pragma unroll
+            for (int x = 0; x < kSumWindows; ++x) {
+                const uint32_t q = (window + x) * 64 + lane;
+                next_key[x] = key_at(q);
+                next_val[x] = q < n ? vals[q] : 0u;
+            }
+            const uint32_t q = (window + kSumWindows) * 64;
+            key_behind = key_at(q);
+            val_behind = q < n ? vals[q] : 0u;
+        };
+        if (!over_parts && it_begin < it_end) {
+            const uint32_t q = it_begin * 64 - 1, key_before = key_at(q), val_before = q < n ? vals[q] : 0u;
+            fetch(it_begin);
+            if (key_before == v) ex_before = val_before / Tn;
+        }
+        if (!over_parts && (cut_lo || cut_hi)) {
+            // the id's cuts are the multiples first_cut .. last_cut of `part` (found while the windows are on their way)
+            const uint32_t some = (cut_lo ? lo : hi) >> part_bits, most = n >> part_bits;
+            const bool up = lane >= 32;
+            const uint32_t found = half_wave_first_not(up ? some : 1, up ? most - some + 1 : some - 1, lane, [&](uint32_t k) {
+                return up ? key_at((k << part_bits) + kSumSpan) <= v : key_at((k << part_bits) - kSumSpan) < v;
+            });
+            first_cut = lane_value(found, 0);
+            const uint32_t last_cut = lane_value(found, 32) - 1;
+            parts = last_cut - first_cut + 2;
+            // the sums go to the rows of the last three positions before the part's end, or, of the id's last part, of the first three
+            const uint32_t base = cut_hi ? hi - 3 : lo;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) park[i] = vals[base + i];
+        }
+#pragma unroll 1
+        for (uint32_t it = it_begin; it < it_end; it += over_parts ? 64 : kSumWindows) {
+            int count = 0;
+            own_lds();
+            if (!over_parts) {
+                uint32_t ex[kSumWindows + 1], val[kSumWindows];  // the examples of the id's positions, kNoEmit elsewhere
+#pragma unroll
+                for (int x = 0; x < kSumWindows; ++x) {
+                    val[x] = next_val[x];
+                    ex[x] = next_key[x] == v ? val[x] / Tn : kNoEmit;
+                }
+                ex[kSumWindows] = key_behind == v ? val_behind / Tn : kNoEmit;
+                if (it + kSumWindows < it_end) fetch(it + kSumWindows);
+                bool goes_on = false;                            // the last run listed, behind the last position
+#pragma unroll
+                for (int x = 0; x < kSumWindows; ++x) {
+                    const uint32_t q = (it + x) * 64 + lane;
+                    const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)ex_before, (int)ex[x], 0x138, 0xf, 0xf, false);   // wave_shr:1
+                    const bool mine = ex[x] != kNoEmit && q >= lo && q < hi && it + x < it_end, begins = ex[x] != prev;
+                    const bool piece = mine && (begins || lane % kPiece == 0);                   // (windows begin at multiples of kPiece)
+                    const uint64_t m_mine = __ballot(mine), m_new = __ballot(begins), m_piece = __ballot(piece);
+                    ex_before = lane_value(ex[x], 63);
+                    if (!m_mine) continue;
+                    if (it == it_begin && x == 0) opens = (m_new >> __builtin_ctzll(m_mine)) & 1 ? 0 : 1;
+                    if (piece) {
+                        const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(m_piece >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m_piece, (uint32_t)count));
+                        list[to] = val[x] | (begins ? kBeginsRun : 0u);
+                    }
+                    count += __builtin_popcountll(m_piece);
+                    const uint64_t behind = m_new & ~m_mine;     // the id's positions are neighbours
+                    goes_on = m_mine >> 63 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)ex[x + 1]) == ex_before
+                                           : !((behind >> (64 - __builtin_clzll(m_mine))) & 1);
+                }
+                if (lane == 0) list[count] = goes_on ? 0u : kBeginsRun;
+            } else {                                             // part m lies between cuts first_cut + m - 1 and first_cut + m
+                const uint32_t m = it + lane;
+                const bool in = m < it_end, has_lo = in && m > 0, has_hi = in && m < parts - 1;
+                const uint32_t at_lo = (first_cut + m - 1) << part_bits, at_hi = at_lo + part, at = has_hi ? at_hi - 3 : at_lo;
+                auto position = [&](bool there, uint32_t q) { return there ? vals[q] : 0u; };
+                const uint32_t r0 = position(in, at), r1 = position(in, at + 1), r2 = position(in, at + 2);
+                const uint32_t p_lo = position(has_lo, at_lo), e_before = position(has_lo, at_lo - 1) / Tn;
+                const uint32_t e_last = position(has_hi, at_hi - 1) / Tn, e_behind = position(has_hi, at_hi) / Tn;
+                const bool from = has_lo && p_lo / Tn == e_before, on = has_hi && e_last == e_behind;   // a run goes on over the lower cut, over the upper
+                const bool through = from && on && p_lo / Tn == e_last;
+                const uint64_t m_open = __ballot(from && !through), m_closed = __ballot(in && !through), m_rest = __ballot(on);
+                const uint64_t lower = ((uint64_t)1 << lane) - 1;
+                int to = __builtin_popcountll(m_open & lower) + __builtin_popcountll(m_closed & lower) + __builtin_popcountll(m_rest & lower);
+                if (it == it_begin) opens = (uint32_t)(__ballot(from) & 1);
+                if (from && !through) {
+                    list[2 * to] = r0 | kEndsRun;
+                    list[2 * to++ + 1] = p_lo;
+                }
+                if (in && !through) {
+                    list[2 * to] = r1 | kEndsRun;
+                    list[2 * to++ + 1] = kNoEmit;
+                }
+                if (on) {
+                    list[2 * to] = r2;
+                    list[2 * to + 1] = kNoEmit;
+                }
+                count = __builtin_popcountll(m_open) + __builtin_popcountll(m_closed) + __builtin_popcountll(m_rest);
+            }
+            own_lds();
+            add_list(count, over_parts);
+        }
+        combine();
+        if (over_parts || (!cut_lo && !cut_hi)) break;
+        // one of several parts
+#pragma unroll
+        for (int o = 0; o < kOwn; ++o) {
+            const int col = col0 + tid + o * 64 * kSumWaves;
+            if (col < D) {
+                __hip_atomic_store(runsum + (int64_t)park[0] * D + col, (float)tot_open[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(runsum + (int64_t)park[1] * D + col, (float)tot_closed[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(runsum + (int64_t)park[2] * D + col, (float)tot_rest[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        // every thread: this thread's sums have reached the memory that all XCDs share
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0)
+            last = __hip_atomic_fetch_add(arrived + (int64_t)first_cut * ncb + cb, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+        __syncthreads();
+        if (!last) return;
+    }
+    // ---- the id's row of w' is complete
+    float sq = 0.f;
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o) {
+        const int col = col0 + tid + o * 64 * kSumWaves;
+        if (col < D) {
+            float *p = w + (int64_t)v * D + col;
+            const float sum = (float)(tot_closed[o] + (accumulate ? (double)*p : 0.0));
+            __builtin_nontemporal_store(sum, p);
+            sq = fmaf(sum, sum, sq);
+        }
+    }
+    if (accumulate) return;
+    sq = wave_sum(sq);
+    if (lane == 0) squares[wave][kSumWaves] = sq;
+    __syncthreads();
+    if (tid == 0) {
+        float t = 0.f;
+        for (int u = 0; u < kSumWaves; ++u) t += squares[u][kSumWaves];
+        bigpart[(int64_t)cb * n + vals[parts > 1 ? first_cut << part_bits : lo]] = t;
     }
 }
 
@@ -1025,9 +1289,18 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     };
     const int fill_blocks = blocks_for(fill_a), fill_blocks_b = blocks_for(fill_b), medium_blocks = (int)chunks * runs_y;
     hipError_t runs_status = hipSuccess;
+    // kernel B's counters lie where the sort had its words; parts large enough that they fit
+    const size_t counter_bytes = p.own_sort ? p.off_temp - p.off_tiles : p.off_keys_out - p.off_keys_in;
+    uint32_t *arrived = reinterpret_cast<uint32_t *>(ws + (p.own_sort ? p.off_tiles : p.off_keys_in));
+    // Parts small enough to run side by side, large enough that few sums are left to add; small batches are spared the
+    // second level.  Parts of 1024 / 2048 / 4096 positions, us: Zipf ids in 8192 47.3 / 48.3 / 44.8 (D=768), in 32768
+    // 36.6 / 39.0 / 43.9 (D=512, V=256); one id in 32768 67.6 / 70.2 / 76.7 (D=768), in 131072 164 / 150 / 149; half of
+    // 262144 one id 295 / 273 / 266; one id in 306557 415 / 387 / 380.
+    int part_bits = p.n <= 16384 ? 12 : p.n <= 65536 ? 10 : p.n <= 131072 ? 11 : p.n <= 262144 ? 12 : 13;
+    while ((size_t)((p.n >> part_bits) + 1) * p.ncb * sizeof(uint32_t) > counter_bytes && p.n >> part_bits) ++part_bits;
     auto runs = [&](auto kernel, auto *gp) {
         runs_status = launch(kernel, dim3((unsigned)(medium_blocks + fill_blocks + runs_x * runs_y)), dim3(64 * kWavesPerBlock), 0, st, gp, keys, vals, w, runsum,
-                             contrib, bigpart, p.n, T, D, V, accumulate, medium_blocks, fill_a, fill_blocks, runs_x);
+                             contrib, bigpart, arrived, p.n, part_bits, T, D, V, accumulate, medium_blocks, fill_a, fill_blocks, runs_x);
     };
     if (dt == LNPEGN_BF16) {
         if (vec) runs(emb_runs_kernel<bf16_t, true>, static_cast<const bf16_t *>(g));
@@ -1040,7 +1313,7 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     // 3. the parked sums
     const int64_t sum_blocks = (p.n + kSumSpan - 1) / kSumSpan * p.ncb;
     if (launch(emb_sums_kernel, dim3((unsigned)(sum_blocks + fill_blocks_b)), dim3(64 * kSumWaves), 0, st, keys, vals, w, runsum, contrib, bigpart,
-               p.n, T, D, V, accumulate, fill_a, (int)sum_blocks, fill_blocks_b) != hipSuccess)
+               arrived, (uint32_t)p.n, part_bits, (uint32_t)T, D, V, accumulate, fill_a, (int)sum_blocks, fill_blocks_b) != hipSuccess)
         return LNPEGN_EHIP;
     // 4. the norms
     const bool wnorm = accumulate && big_sq;

@@ -1,0 +1,54 @@
+"""Sizes at which a call once took a multiple of what a call of the same traffic takes: each is held to a multiple of such
+a neighbour, timed beside it on the same device (GPU time of graph replays, the best of several)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _us(call, calls=4):
+    """GPU time of one call, us."""
+    import torch
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(calls):
+            call()
+    best = float("inf")
+    for _ in range(8):
+        start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        start.record()
+        graph.replay()
+        stop.record()
+        torch.cuda.synchronize()
+        best = min(best, start.elapsed_time(stop) / calls * 1e3)
+    return best
+
+
+def _embedding_us(ids, D, V, dtype):
+    import torch
+    from paper_2411_00999_amd import binding
+    B, T = ids.shape
+    ids = torch.from_numpy(np.ascontiguousarray(ids, dtype=np.int64)).cuda()
+    g = (torch.randn(B, T, D, device="cuda") * 1e-3).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    out = dict(w=torch.empty(V, D, device="cuda"), s=torch.empty(B, device="cuda"), big_sq=torch.empty(1, device="cuda"),
+               workspace=torch.empty(binding.load().embedding_pegn_workspace_bytes(B, T, D, V), dtype=torch.uint8, device="cuda"))
+    in_order = binding.embedding_sort_ids(ids, V)
+    return _us(lambda: binding.embedding_pegn_presorted(*in_order, g, V, **out))
+
+
+@pytest.mark.parametrize("B,T,D,V,dtype,times", [
+    (69, 4815, 26, 920, "bf16", 2.0),        # with one workgroup for all of an id's rows: 6.7 times
+    (36, 4546, 64, 2096, "f32", 1.8),        # 2.6
+    (73, 4476, 1, 6, "f32", 2.0),            # 3.3
+])
+def test_embedding_of_one_id(B, T, D, V, dtype, times):
+    """A batch of one id against one whose ids all occur about equally often."""
+    spread = np.random.default_rng(1).integers(0, V, (B, T))
+    one, many = _embedding_us(np.full((B, T), V - 1), D, V, dtype), _embedding_us(spread, D, V, dtype)
+    assert one < times * many, (one, many)
