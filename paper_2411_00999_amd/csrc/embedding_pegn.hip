@@ -31,8 +31,8 @@ constexpr int kChunk = 16;          // sorted positions whose piece heads one wa
 constexpr int kPiece = 32;          // longest piece; kChunk + kPiece + 1 lanes of one 64-lane window cover a wave's work
 constexpr int kWavesPerBlock = 4;
 constexpr int kNormBlocks = 2048;   // workgroups of the ||w'||^2 pass in accumulate mode
-constexpr int kFillBlocks = 4096;   // most workgroups of the zero fill
-constexpr int kFillRows = 16;       // rows a wave of it takes at a time
+constexpr int kFillBlocks = 16384;  // most workgroups of the zero fill
+constexpr int64_t kFillLeast = 8 << 10, kFillMost = 32 << 10;   // bytes that a wave of it takes at a time
 constexpr int64_t kFillLateBytes = 40 << 20;   // most bytes of it that are left to kernel B
 
 __global__ __launch_bounds__(256) void emb_prepare_kernel(const void *ids, int ids_i64, uint32_t *keys,
@@ -344,32 +344,68 @@ __device__ __forceinline__ int64_t lower_bound_value(const uint32_t *a, int64_t 
     return lo;
 }
 
+// For each half of the wave, the first of its lo .. lo+len for which below(index) is false, where it is true up to there:
+// 32 probes a round, the two halves side by side.
+template <typename F>
+__device__ __forceinline__ uint32_t half_wave_first_not(uint32_t lo, uint32_t len, int lane, F below)
+{
+    while (__any(len > 0)) {
+        const uint32_t step = len / 33 + 1, at = step * ((lane & 31) + 1);      // probes at lo + step - 1, lo + 2 step - 1, ...
+        const uint64_t yes = __ballot(at <= len && below(lo + min(at, len) - 1));
+        const uint32_t c = __builtin_popcount((uint32_t)(lane < 32 ? yes : yes >> 32));
+        lo += step * c;
+        len = min(len - step * c, step - 1);
+    }
+    return lo;
+}
+
 // Zero fill of the rows of w' that no id selects (rows begin to end - 1), a part of kernel A's grid and of kernel B's:
 // the rows of ids that occur are written, whole, by the other workgroups, so everything touches different rows and
 // runs side by side.  Kernel A waits for its chains of loads more than for bandwidth and kernel B does little else, so
 // the fill is shared out between the two (half of it, at most 40 MiB, beside kernel B: the presorted call
-// 48.7 -> 46.2 us at B=8 T=1024 D=768 V=50257, no difference at B=16 T=2048 D=2048).  A wave takes kFillRows
-// rows, one per lane: each lane looks for its row's id in the sorted list, so that no map of the ids is needed before the
-// launch; they lie a wave count apart, so that the waves together sweep one moving window of w'.  Streaming stores: the zeros are not wanted in any cache (the rows read next are g's), and lines left dirty
+// 48.7 -> 46.2 us at B=8 T=1024 D=768 V=50257, no difference at B=16 T=2048 D=2048).  A wave takes `rows` neighbouring
+// rows (at most 64) and finds their ids in the sorted list, so that no map of the ids is needed before the launch;
+// waves beside each other take rows beside each other, so that together they sweep one moving window of w'.  Absent rows
+// in a row are one stretch of memory: whole lines but at its ends, whatever the width.  (A row at a time, a lane's
+// search each, sixteen rows of which lay far apart / this, us a presorted call: B=8 T=1024 D=8 V=1000000 fp32 140 / 25,
+// B=512 T=512 D=64 V=1000000 360 / 145, D=2344 V=240547 511 / 443, B=8 T=1024 D=768 V=50257 46 / 37.5.  By a map of the ids
+// and a kernel of its own on a second stream: 54, 207, 408, 60.)
+// Streaming stores: the zeros are not wanted in any cache (the rows read next are g's), and lines left dirty
 // in the memory-side cache would be written back one by one under the reads that follow.
-__device__ __forceinline__ void fill_absent_rows(const uint32_t *keys, int64_t n, float *w, int begin, int end, int D, int wave,
-                                                 int nwaves, int lane)
+__device__ __forceinline__ void fill_absent_rows(const uint32_t *keys, uint32_t n, float *w, int begin, int end, int D, int rows,
+                                                 int wave, int nwaves, int lane)
 {
     typedef __attribute__((ext_vector_type(4))) float f32x4;
-    const bool vec = (reinterpret_cast<uintptr_t>(w) & 15u) == 0 && D % 4 == 0;
-    for (int64_t r0 = (int64_t)begin + wave; r0 < end; r0 += (int64_t)nwaves * kFillRows) {
-        const uint32_t row = (uint32_t)r0 + (uint32_t)lane * (uint32_t)nwaves;
-        const int64_t at = lower_bound_value(keys, 0, n, row);
-        uint64_t absent = __ballot(lane < kFillRows && row < (uint32_t)end && !(at < n && keys[at] == row));
-        while (absent) {
-            float *p = w + (r0 + (int64_t)__builtin_ctzll(absent) * nwaves) * D;
-            absent &= absent - 1;
-            if (vec) {
-                for (int c = lane; c < D / 4; c += 64)
-                    __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4 *>(p) + c);
-            } else {
-                for (int c = lane; c < D; c += 64) p[c] = 0.f;
+    for (int64_t r0 = begin + (int64_t)wave * rows; r0 < end; r0 += (int64_t)nwaves * rows) {
+        const uint32_t first = (uint32_t)r0, behind = (uint32_t)(r0 + rows < end ? r0 + rows : end), target = lane < 32 ? first : behind;
+        const uint32_t found = half_wave_first_not(0, n, lane, [&](uint32_t k) { return keys[k] < target; });
+        const uint32_t q_begin = lane_value(found, 0), q_end = lane_value(found, 32);
+        uint64_t absent = ~(uint64_t)0 >> (64 - (behind - first));
+        if (q_end - q_begin <= 512) {                  // the ids that occur, one after the other
+            for (uint32_t q = q_begin; q < q_end; q += 64) {
+                const uint32_t key = q + lane < q_end ? keys[q + lane] : 0xffffffffu;
+                const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)key, 0x138, 0xf, 0xf, false);   // wave_shr:1
+                for (uint64_t ids = __ballot(key != before && key < behind); ids; ids &= ids - 1)
+                    absent &= ~((uint64_t)1 << (lane_value(key, __builtin_ctzll(ids)) - first));
             }
+        } else {                                       // ... or a search for each
+            const uint32_t row = first + lane;
+            const int64_t at = lower_bound_value(keys, q_begin, q_end - q_begin, row);
+            absent &= ~__ballot(row < behind && at < q_end && keys[at] == row);
+        }
+        while (absent) {
+            const int r = __builtin_ctzll(absent);
+            const uint64_t others = ~(absent >> r);
+            const int count = others ? __builtin_ctzll(others) : 64;
+            absent &= count + r < 64 ? ~(uint64_t)0 << (count + r) : 0;
+            float *p = w + (r0 + r) * D;
+            const int64_t len = (int64_t)count * D;
+            const int head = (int)(min((int64_t)((16 - (reinterpret_cast<uintptr_t>(p) & 15u)) & 15u) / 4, len));
+            const int64_t quads = (len - head) / 4;
+            if (lane < head) p[lane] = 0.f;
+            for (int64_t i = lane; i < quads; i += 64)
+                __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4 *>(p + head) + i);
+            if (lane < len - head - quads * 4) p[head + quads * 4 + lane] = 0.f;
         }
     }
 }
@@ -576,7 +612,7 @@ template <typename T, bool kVec>
 __global__ __launch_bounds__(64 * kWavesPerBlock, kVec && sizeof(T) == 2 ? 3 : 4) void emb_runs_kernel(
     const T *g, const uint32_t *keys, const uint32_t *vals, float *w, float *runsum, float *contrib, float *bigpart,
     uint32_t *arrived, int64_t n, int part_bits, int Tn, int D, int V, int accumulate, int medium_blocks, int fill_rows,
-    int fill_blocks, int runs_x)
+    int fill_each, int fill_blocks, int runs_x)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -596,7 +632,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, kVec && sizeof(T) == 2 ? 3 : 4
     int fill = behind < 0 && j % 3 == 2 ? j / 3 : -1;
     if (behind >= 0 && block >= run_blocks) fill = groups + block - run_blocks;
     if (fill >= 0) {
-        fill_absent_rows(keys, n, w, 0, fill_rows, D, fill * kWavesPerBlock + wave, fill_blocks * kWavesPerBlock, lane);
+        fill_absent_rows(keys, (uint32_t)n, w, 0, fill_rows, D, fill_each, fill * kWavesPerBlock + wave, fill_blocks * kWavesPerBlock, lane);
         return;
     }
     const int block_y = block / runs_x, block_x = block - block_y * runs_x;
@@ -710,26 +746,11 @@ constexpr uint32_t kNoEmit = 0xffffffffu, kEndsRun = 0x80000000u, kBeginsRun = 0
 constexpr int kDeviceScope = 16;                                 // sc1
 static_assert(kPiece == 32, "two pieces to a window");
 
-// For each half of the wave, the first of its lo .. lo+len for which below(index) is false, where it is true up to there:
-// 32 probes a round, the two halves side by side.
-template <typename F>
-__device__ __forceinline__ uint32_t half_wave_first_not(uint32_t lo, uint32_t len, int lane, F below)
-{
-    while (__any(len > 0)) {
-        const uint32_t step = len / 33 + 1, at = step * ((lane & 31) + 1);      // probes at lo + step - 1, lo + 2 step - 1, ...
-        const uint64_t yes = __ballot(at <= len && below(lo + min(at, len) - 1));
-        const uint32_t c = __builtin_popcount((uint32_t)(lane < 32 ? yes : yes >> 32));
-        lo += step * c;
-        len = min(len - step * c, step - 1);
-    }
-    return lo;
-}
-
 // (Positions are 32-bit here, and what need not be unrolled is not: a workgroup runs through the code once or twice, and
 // fetching the instructions is a good part of its time.)
 __global__ __launch_bounds__(64 * kSumWaves, 4) void emb_sums_kernel(
     const uint32_t *keys, const uint32_t *vals, float *w, float *runsum, float *contrib, float *bigpart, uint32_t *arrived,
-    uint32_t n, int part_bits, uint32_t Tn, int D, int V, int accumulate, int fill_begin, int sum_blocks, int fill_blocks)
+    uint32_t n, int part_bits, uint32_t Tn, int D, int V, int accumulate, int fill_begin, int fill_each, int sum_blocks, int fill_blocks)
 {
     constexpr int kBatch = 8;                                    // rows in flight
     constexpr int kOwn = kColBlock / (64 * kSumWaves);           // columns per thread where the waves combine
@@ -742,7 +763,7 @@ __global__ __launch_bounds__(64 * kSumWaves, 4) void emb_sums_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ncb = (D + kColBlock - 1) / kColBlock;
     if ((int)blockIdx.x >= sum_blocks) {
-        fill_absent_rows(keys, n, w, fill_begin, V, D, ((int)blockIdx.x - sum_blocks) * kSumWaves + wave, fill_blocks * kSumWaves, lane);
+        fill_absent_rows(keys, n, w, fill_begin, V, D, fill_each, ((int)blockIdx.x - sum_blocks) * kSumWaves + wave, fill_blocks * kSumWaves, lane);
         return;
     }
     const int span = (int)blockIdx.x / ncb, cb = (int)blockIdx.x - span * ncb, col0 = cb * kColBlock;
@@ -1283,11 +1304,22 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     // the rows filled beside kernel A; the rest beside kernel B
     const int64_t row_bytes = (int64_t)D * 4, late = V / 2 < kFillLateBytes / row_bytes ? V / 2 : kFillLateBytes / row_bytes;
     const int fill_a = accumulate ? 0 : V - (int)late, fill_b = accumulate ? 0 : (int)late;
-    auto blocks_for = [](int rows) {
-        const int64_t most = ((int64_t)rows + kFillRows * kWavesPerBlock - 1) / (kFillRows * kWavesPerBlock);
+    // Rows to a wave: 8 to 32 KB, so that there are many waves and the search for their ids is hidden, and whole lines of 128
+    // bytes (32 / gcd(D, 32) rows are) where 64 KB are enough for that.
+    const int whole = 32 / (int)((D & -D) < 32 ? (D & -D) : 32);
+    auto rows_each = [&](int rows) {
+        int64_t bytes = rows * row_bytes / kFillBlocks;
+        bytes = bytes < kFillLeast ? kFillLeast : bytes > kFillMost ? kFillMost : bytes;
+        int64_t each = bytes / row_bytes > 1 ? bytes / row_bytes : 1;
+        if (whole * row_bytes <= 2 * kFillMost) each = (each + whole - 1) / whole * whole;
+        return (int)(each < 64 ? each : 64);
+    };
+    auto blocks_for = [&](int rows, int each) {
+        const int64_t most = ((int64_t)rows + each * kWavesPerBlock - 1) / (each * kWavesPerBlock);
         return (int)(most < kFillBlocks ? most : kFillBlocks);
     };
-    const int fill_blocks = blocks_for(fill_a), fill_blocks_b = blocks_for(fill_b), medium_blocks = (int)chunks * runs_y;
+    const int each_a = rows_each(fill_a), each_b = rows_each(fill_b);
+    const int fill_blocks = blocks_for(fill_a, each_a), fill_blocks_b = blocks_for(fill_b, each_b), medium_blocks = (int)chunks * runs_y;
     hipError_t runs_status = hipSuccess;
     // kernel B's counters lie where the sort had its words; parts large enough that they fit
     const size_t counter_bytes = p.own_sort ? p.off_temp - p.off_tiles : p.off_keys_out - p.off_keys_in;
@@ -1300,7 +1332,7 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     while ((size_t)((p.n >> part_bits) + 1) * p.ncb * sizeof(uint32_t) > counter_bytes && p.n >> part_bits) ++part_bits;
     auto runs = [&](auto kernel, auto *gp) {
         runs_status = launch(kernel, dim3((unsigned)(medium_blocks + fill_blocks + runs_x * runs_y)), dim3(64 * kWavesPerBlock), 0, st, gp, keys, vals, w, runsum,
-                             contrib, bigpart, arrived, p.n, part_bits, T, D, V, accumulate, medium_blocks, fill_a, fill_blocks, runs_x);
+                             contrib, bigpart, arrived, p.n, part_bits, T, D, V, accumulate, medium_blocks, fill_a, each_a, fill_blocks, runs_x);
     };
     if (dt == LNPEGN_BF16) {
         if (vec) runs(emb_runs_kernel<bf16_t, true>, static_cast<const bf16_t *>(g));
@@ -1313,7 +1345,7 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     // 3. the parked sums
     const int64_t sum_blocks = (p.n + kSumSpan - 1) / kSumSpan * p.ncb;
     if (launch(emb_sums_kernel, dim3((unsigned)(sum_blocks + fill_blocks_b)), dim3(64 * kSumWaves), 0, st, keys, vals, w, runsum, contrib, bigpart,
-               arrived, (uint32_t)p.n, part_bits, (uint32_t)T, D, V, accumulate, fill_a, (int)sum_blocks, fill_blocks_b) != hipSuccess)
+               arrived, (uint32_t)p.n, part_bits, (uint32_t)T, D, V, accumulate, fill_a, each_b, (int)sum_blocks, fill_blocks_b) != hipSuccess)
         return LNPEGN_EHIP;
     // 4. the norms
     const bool wnorm = accumulate && big_sq;

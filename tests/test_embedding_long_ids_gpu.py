@@ -88,3 +88,38 @@ def test_one_id_beyond_the_own_sort(B, T, D):
     ids = np.full((B, T), 3, dtype=np.int64)
     ids[:, ::1000] = 5
     _check(ids, g, V, "f32")
+
+
+@pytest.mark.parametrize("V,D,off,kind", [
+    (70001, 8, 0, "few"), (70001, 1, 3, "few"), (1000, 3, 1, "few"), (64, 5, 2, "all"), (65, 5, 1, "all but one"),
+    (200, 4, 0, "every other"), (300, 7, 1, "every other"), (129, 260, 0, "crowded"), (500, 2, 2, "crowded"),
+    (5000, 1021, 3, "few"), (9, 20000, 1, "few"), (1, 12, 1, "few"), (3000, 64, 0, "out of range"),
+])
+def test_rows_no_id_selects_are_zero(V, D, off, kind):
+    """The fill over rows of any width and address, with none, some, most of 64 neighbouring rows present, many positions
+    among them, and nothing outside w' touched."""
+    import torch
+    from paper_2411_00999_amd import binding
+    rng = np.random.default_rng(V + D)
+    if kind == "few":
+        ids = rng.integers(0, V, (2, 30))
+        ids[0, 0], ids[0, 1] = 0, V - 1
+    elif kind == "all":
+        ids = rng.permutation(np.arange(V)).reshape(2, -1)
+    elif kind == "all but one":
+        ids = rng.permutation(np.delete(np.arange(V), V // 2)).reshape(2, -1)
+    elif kind == "every other":
+        ids = np.arange(V // 2)[None] * 2
+    elif kind == "crowded":                          # more than 512 positions on the rows of one wave
+        ids = rng.choice([3, 5, 6, 63, 64, V - 2], (3, 400))
+    else:
+        ids = np.full((2, 20), V + 1)
+    ids = ids.astype(np.int64)
+    g = torch.ones((*ids.shape, D), device="cuda")
+    flat = torch.full((V * D + off + 5,), 7.0, device="cuda")
+    w = flat[off:off + V * D].view(V, D)
+    _, s, big = binding.embedding_pegn(torch.from_numpy(ids).cuda(), g, V, w=w)
+    torch.cuda.synchronize()
+    count = np.bincount(ids[ids < V].reshape(-1), minlength=V)
+    np.testing.assert_array_equal(w.cpu().numpy(), np.repeat(count[:, None], D, 1).astype(np.float32))
+    assert bool((flat[:off] == 7).all()) and bool((flat[off + V * D:] == 7).all())

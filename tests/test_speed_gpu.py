@@ -52,3 +52,18 @@ def test_embedding_of_one_id(B, T, D, V, dtype, times):
     spread = np.random.default_rng(1).integers(0, V, (B, T))
     one, many = _embedding_us(np.full((B, T), V - 1), D, V, dtype), _embedding_us(spread, D, V, dtype)
     assert one < times * many, (one, many)
+
+
+@pytest.mark.parametrize("B,T,D,V,times", [
+    (8, 1024, 8, 1000000, 3.0),              # with a search per row and rows far apart: 12 times
+    (2, 36, 3, 1263217, 6.0),                # 14
+])
+def test_embedding_over_a_large_vocabulary(B, T, D, V, times):
+    """Rows that no id selects cost what filling memory costs: the call against the call over a small vocabulary and a
+    fill of as much memory."""
+    import torch
+    ids = np.random.default_rng(2).integers(0, 200, (B, T))
+    large, small = _embedding_us(ids, D, V, "bf16"), _embedding_us(ids, D, 200, "bf16")
+    w = torch.empty(V, D, device="cuda")
+    fill = _us(lambda: w.zero_())
+    assert large < small + times * fill, (large, small, fill)
