@@ -633,19 +633,22 @@ struct LinAlign {
     bool element;          // on multiples of an element, both
 };
 
+// Which kernel: the faster one by the estimates below, or the one that is asked for.
+enum LinKernel { kLinFaster, kLinMfma, kLinScalar };
+
 // max_split: most workgroups that may share an output tile's examples (each but the first costs workspace).
-LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, int max_split = kMaxSplit)
+LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, LinKernel which = kLinFaster, int max_split = kMaxSplit)
 {
     LinPlan p{};
     const int per_chunk = dt == LNPEGN_BF16 ? 8 : 4;          // elements per 16-byte vector
     p.ragged_x = K % per_chunk != 0 || !align.x16;
     p.ragged_g = L % per_chunk != 0 || !align.g16;
     // The matrix-core kernel takes every shape but ragged tensors of less than one chunk and rows whose stage is
-    // beyond its 32-bit offsets; those, and pointers that split an element, are left to the scalar kernel, which is
-    // slower by two orders of magnitude (figures above).
-    const int64_t rows = (int64_t)B * T;
-    p.mfma = K <= (1 << 25) && L <= (1 << 25) &&
-             (!(p.ragged_x || p.ragged_g) || (align.element && rows * K >= per_chunk && rows * L >= per_chunk));
+    // beyond its 32-bit offsets; those, and pointers that split an element, are left to the scalar kernel.
+    const int64_t rows = (int64_t)B * T, tiles16 = (int64_t)((K + 15) / 16) * ((L + 15) / 16);
+    const bool ragged = p.ragged_x || p.ragged_g;
+    p.mfma = which != kLinScalar && K <= (1 << 25) && L <= (1 << 25) &&
+             (!ragged || (align.element && rows * K >= per_chunk && rows * L >= per_chunk));
     if (p.mfma) {
         p.tiles_k = (K + Cfg::kTileK - 1) / Cfg::kTileK;
         p.tiles_l = (L + Cfg::kTileL - 1) / Cfg::kTileL;
@@ -672,7 +675,19 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, int ma
         }
         p.nparts = ntiles * Cfg::kWaves;
         p.nbig = p.nsplit == 1 ? (int64_t)ntiles * Cfg::kWaves : ((int64_t)K * L + 255) / 256;
-    } else {
+        // A few short ragged examples cost the matrix-core kernel its start and the scalar one little: the latter runs its
+        // outputs side by side, an example and a position after the other.  us, matrix cores / scalar: bf16 B=1 T=8
+        // K=257 L=300 14.3 / 6.5, T=100 16.0 / 15.8, T=300 20.5 / 36; B=3 T=8 K=1000 L=499 23 / 11; B=16 T=1 K=129 L=65 20 / 13,
+        // T=8 20 / 24; fp32 B=1 T=300 K=129 L=65 58 / 37, B=3 T=100 33 / 37.
+        const bool bf16 = dt == LNPEGN_BF16;
+        const double mfma_us = (bf16 ? 12.4 : 13.6) + (double)((ntiles * p.nsplit + 255) / 256) * p.b_per_split * stages * (bf16 ? 1.3 : 8.0) +
+                               4.5 * (p.b_per_split - 1) + (p.nsplit > 1 ? 3.0 + 0.045 * ntiles * p.nsplit : 0.0);
+        const double position_us = ((tiles16 < 2 ? 0.065 : tiles16 < 16 ? 0.087 : 0.105) + 4e-6 * ((double)K + L) * (bf16 ? 2 : 4)) *
+                                   (tiles16 > 2048 ? (double)tiles16 / 2048 : 1.0);
+        const double scalar_us = 5.0 + B * (0.42 + 0.0002 * (double)tiles16 + position_us * T);
+        if (ragged && which == kLinFaster && scalar_us < mfma_us) p.mfma = false;
+    }
+    if (!p.mfma) {
         p.tiles_k = (K + 15) / 16;
         p.tiles_l = (L + 15) / 16;
         p.nsplit = 1;
@@ -723,9 +738,10 @@ int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq,
     const LinAlign align{(px & 15u) == 0, (pg & 15u) == 0, ((px | pg) & (elem - 1)) == 0};
     LinPlan p = make_lin_plan(B, T, K, L, dt, align);
     // Ragged rows run in less workspace too, down to what the scalar kernel asks for: without a split, or there.
-    if ((p.ragged_x || p.ragged_g) && workspace_bytes < p.bytes) {
-        p = make_lin_plan(B, T, K, L, dt, align, 1);
-        if (workspace_bytes < p.bytes) p = make_lin_plan(B, T, K, L, dt, LinAlign{false, false, false});
+    if (p.ragged_x || p.ragged_g) {
+        if (workspace_bytes < p.bytes) p = make_lin_plan(B, T, K, L, dt, align, kLinMfma);
+        if (workspace_bytes < p.bytes) p = make_lin_plan(B, T, K, L, dt, align, kLinMfma, 1);
+        if (workspace_bytes < p.bytes) p = make_lin_plan(B, T, K, L, dt, align, kLinScalar);
     }
     if (workspace_bytes < p.bytes) return LNPEGN_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);

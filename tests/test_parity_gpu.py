@@ -849,6 +849,53 @@ def test_linear_pegn_ragged_rows(dtype, B, T, K, L, off):
     _check_linear(x, g, host(binding.linear_pegn(xd, gd, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))))
 
 
+def _linear_workspaces(B, K, L):
+    """Least workspace of the scalar kernel and of the matrix-core kernel without a split."""
+    up = lambda v: -(-v // 256) * 256
+    tiles, blocks = -(-K // 16) * -(-L // 16), -(-K // 256) * -(-L // 128) * 8
+    return up(tiles * B * 4) + up(tiles * 8), up(blocks * B * 4) + up(blocks * 8)
+
+
+@pytest.mark.parametrize("dtype,B,T,K,L,off", [
+    ("bf16", 2, 256, 255, 127, 0), ("bf16", 1, 257, 257, 129, 0), ("bf16", 3, 262, 264, 131, 0), ("bf16", 2, 258, 512, 257, 0),
+    ("bf16", 2, 255, 33, 264, 0), ("bf16", 3, 193, 9, 8, 0), ("bf16", 4, 130, 3, 5, 0), ("bf16", 2, 232, 264, 136, 1),
+    ("bf16", 2, 232, 264, 136, 4), ("bf16", 70, 17, 129, 1, 0), ("bf16", 100, 1, 33, 17, 0),
+    ("f32", 4, 129, 255, 129, 0), ("f32", 4, 128, 512, 130, 0), ("f32", 4, 127, 257, 128, 1), ("f32", 20, 33, 5, 3, 0),
+])
+def test_linear_pegn_ragged_rows_on_the_matrix_cores(dtype, B, T, K, L, off):
+    """As above with examples long or many enough that the scalar kernel would take longer; in a workspace that holds no
+    split, too, and in one that only the scalar kernel's parts fill."""
+    import torch
+    from paper_2411_00999_amd import binding
+    x, g = workloads.make_linear_inputs(B * 1000 + K + L + 1, B, T, K, L, dtype)
+
+    def at_offset(a):
+        t = pu.to_device(a, dtype)
+        flat = torch.empty(t.numel() + off, dtype=t.dtype, device="cuda")[off:]
+        return flat.copy_(t.view(-1)).view(t.shape)
+    xd, gd = at_offset(x), at_offset(g)
+    _check_linear(x, g, tuple(pu.to_host64(t) for t in binding.linear_pegn(xd, gd)))
+    for nbytes in _linear_workspaces(B, K, L):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        _check_linear(x, g, tuple(pu.to_host64(t) for t in binding.linear_pegn(xd, gd, workspace=ws)))
+
+
+@pytest.mark.parametrize("dtype,B,T,K,L", [("bf16", 1, 8, 1000, 499), ("f32", 2, 5, 255, 129), ("bf16", 1, 90, 257, 300)])
+def test_linear_pegn_short_ragged_rows_in_less_workspace(dtype, B, T, K, L):
+    """The scalar kernel is chosen where its parts fit, and what held the matrix-core kernel's alone is still enough."""
+    import torch
+    from paper_2411_00999_amd import binding
+    x, g = workloads.make_linear_inputs(B * 1000 + K + L + 2, B, T, K, L, dtype)
+    scalar, cores = _linear_workspaces(B, K, L)
+    assert cores < scalar
+    xd, gd = pu.to_device(x, dtype), pu.to_device(g, dtype)
+    for nbytes in (scalar, cores):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        _check_linear(x, g, tuple(pu.to_host64(t) for t in binding.linear_pegn(xd, gd, workspace=ws)))
+    with pytest.raises(binding.LnpegnError):
+        binding.linear_pegn(xd, gd, workspace=torch.empty(cores - 256, dtype=torch.uint8, device="cuda"))
+
+
 @pytest.mark.parametrize("K,L", [(264, 131), (257, 129), (264, 136)])
 def test_linear_pegn_keeps_infinities_to_their_example(K, L):
     """T is no multiple of a stage: the rows behind an example's end are zeros, not what another example left there."""

@@ -67,3 +67,25 @@ def test_embedding_over_a_large_vocabulary(B, T, D, V, times):
     w = torch.empty(V, D, device="cuda")
     fill = _us(lambda: w.zero_())
     assert large < small + times * fill, (large, small, fill)
+
+
+def _linear_us(B, T, K, L, dtype):
+    import torch
+    from paper_2411_00999_amd import binding
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x, g = torch.randn(B, T, K, device="cuda").to(dt), torch.randn(B, T, L, device="cuda").to(dt)
+    nbytes = max(256, binding.load().linear_pegn_workspace_bytes(B, T, K, L, binding.BF16 if dtype == "bf16" else binding.F32))
+    out = dict(w=torch.empty(K, L, device="cuda"), s=torch.empty(B, device="cuda"), big_sq=torch.empty(1, device="cuda"),
+               workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+    return _us(lambda: binding.linear_pegn(x, g, **out), calls=10)
+
+
+@pytest.mark.parametrize("B,T,K,L,dtype,times", [
+    (2, 4, 9, 3, "bf16", 2.0),               # on the matrix cores: 3.4 times
+    (1, 8, 257, 300, "f32", 2.2),            # 3.4
+    (3, 8, 1000, 499, "bf16", 3.2),          # 4.5
+])
+def test_linear_of_a_few_short_ragged_examples(B, T, K, L, dtype, times):
+    """Against the smallest call there is."""
+    few, least = _linear_us(B, T, K, L, dtype), _linear_us(1, 1, 1, 1, "f32")
+    assert few < times * least, (few, least)
