@@ -86,11 +86,29 @@ __device__ __forceinline__ void load_gamma_ragged(const void *gamma, int gamma_i
         Vec<T>::unpack(__builtin_bit_cast(typename Vec<T>::Raw, t), g);
         return;
     }
+    // of another type than the rows': whole vectors too, and only the lane that holds the row's end goes element by element
+    // (all of them doing so made the forward of B=8 T=500 D=1001 bf16 with fp32 gamma 18.6 us instead of 5.7)
+    if (!last || r.count == E) {
+        if constexpr (E == 8) {                                // fp32 gamma over bf16 rows
+            using P = const __attribute__((address_space(1))) u32x4_at4_t *;
+            const char *at = static_cast<const char *>(gamma) + (int64_t)v * 32;
+            const float4 lo = __builtin_bit_cast(float4, (u32x4_t) * (P)at), hi = __builtin_bit_cast(float4, (u32x4_t) * (P)(at + 16));
+            g[0] = lo.x; g[1] = lo.y; g[2] = lo.z; g[3] = lo.w;
+            g[4] = hi.x; g[5] = hi.y; g[6] = hi.z; g[7] = hi.w;
+        } else {                                               // bf16 gamma over fp32 rows
+            typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
+            typedef u32x2_t u32x2_at2_t __attribute__((aligned(2)));
+            const u32x2_t t = *(const __attribute__((address_space(1))) u32x2_at2_t *)(static_cast<const char *>(gamma) + (int64_t)v * 8);
+            const uint32_t w0 = t.x, w1 = t.y;
+            g[0] = __builtin_bit_cast(float, w0 << 16); g[1] = __builtin_bit_cast(float, w0 & 0xffff0000u);
+            g[2] = __builtin_bit_cast(float, w1 << 16); g[3] = __builtin_bit_cast(float, w1 & 0xffff0000u);
+        }
+        return;
+    }
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int col = v * E + e;
-        const float t = load_gamma(gamma, gamma_is_f32, min(col, D - 1));
-        g[e] = col < D ? t : 0.f;
+        g[e] = 0.f;
+        if (e < r.count) g[e] = load_gamma(gamma, gamma_is_f32, v * E + e);
     }
 }
 

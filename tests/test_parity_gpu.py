@@ -231,6 +231,29 @@ def test_rows_of_any_width_and_address(dtype, D, off, saved):
         assert bool((b[:off] == 7).all()) and bool((b[off + n:] == 7).all())
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 9), ("bf16", 511), ("bf16", 1001), ("bf16", 1025), ("bf16", 3001), ("bf16", 8191),
+                                     ("f32", 5), ("f32", 257), ("f32", 1001), ("f32", 2049), ("f32", 8190)])
+def test_ragged_rows_with_gamma_of_the_other_type(dtype, D):
+    """fp32 gamma and beta over bf16 rows and bf16 ones over fp32 rows, of no whole number of vectors."""
+    import torch
+    from paper_2411_00999_amd import binding
+    inp = workloads.make_inputs(1, B=3, T=11, D=D, dtype=dtype)
+    rng = np.random.default_rng(workloads.BASE_SEED + D)
+    gt = torch.float32 if dtype == "bf16" else torch.bfloat16
+    gamma, beta = (torch.from_numpy(rng.normal(m, 0.1, D).astype(np.float32)).to(gt).cuda() for m in (1.0, 0.0))
+    inp.gamma, inp.beta = pu.to_host64(gamma), pu.to_host64(beta)
+    ref = _oracle(inp)
+    x, dy = pu.to_device(inp.x, dtype), pu.to_device(inp.dy, dtype)
+    y, mean, rstd = binding.ln_fwd(x, gamma, beta, inp.eps)
+    pu.check_close("y", pu.to_host64(y), oracle.ln_fwd(inp.x, inp.gamma, inp.beta, inp.eps),
+                   pu.TOL_BF16 if dtype == "bf16" else pu.TOL_F32, bf16_output=dtype == "bf16")
+    for kw in (dict(mean=mean, rstd=rstd), {}):
+        out = binding.ln_bwd_pegn(x, dy, gamma, inp.eps, **kw)
+        torch.cuda.synchronize()
+        names = ("dx", "dgamma", "dbeta", "s_gamma", "s_beta", "big_sq")
+        pu.compare_with_oracle(inp, dict(zip(names, map(pu.to_host64, out))), ref)
+
+
 def test_misaligned_pointers_take_the_generic_kernel():
     import torch
     from paper_2411_00999_amd import binding

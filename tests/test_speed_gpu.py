@@ -89,3 +89,17 @@ def test_linear_of_a_few_short_ragged_examples(B, T, K, L, dtype, times):
     """Against the smallest call there is."""
     few, least = _linear_us(B, T, K, L, dtype), _linear_us(1, 1, 1, 1, "f32")
     assert few < times * least, (few, least)
+
+
+def test_forward_of_ragged_rows_with_gamma_of_the_other_type():
+    """fp32 gamma and beta over bf16 rows cost what bf16 ones do (element by element: 3.3 times)."""
+    import torch
+    from paper_2411_00999_amd import binding
+    B, T, D = 8, 500, 1001
+    x = torch.randn(B, T, D, device="cuda").bfloat16()
+    y, mean, rstd = torch.empty_like(x), torch.empty(B, T, device="cuda"), torch.empty(B, T, device="cuda")
+    us = {}
+    for dt in (torch.bfloat16, torch.float32):
+        gamma, beta = torch.ones(D, device="cuda", dtype=dt), torch.zeros(D, device="cuda", dtype=dt)
+        us[dt] = _us(lambda: binding.ln_fwd(x, gamma, beta, 1e-5, y=y, mean=mean, rstd=rstd), calls=10)
+    assert us[torch.float32] < 2.0 * us[torch.bfloat16], us
