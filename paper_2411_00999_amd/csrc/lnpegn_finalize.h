@@ -476,6 +476,39 @@ __global__ __launch_bounds__(1024) void reduce_final_batch_kernel(BatchArgs b)
     reduce_final_body(a);
 }
 
+// The same two levels for shapes whose layers are nearly always reduced in one launch, but may have been cut for two
+// levels (other pointers, a plain call).  A workgroup takes every gridDim.y-th of a layer's examples and groups, at most
+// kBatchGroups workgroups to a column tile: one for each of hundreds of examples took some 10 us to come and go in
+// vain.  The slabs of the others share the launch of the second level.  16 layers, us, two levels / slabs and two levels
+// one after the other / this: bf16 B=512 T=64 D=1024 24 / 33 / 19, D=2048 40 / 55 / 30, B=1000 T=33 D=768 31 / 45 / 25.
+constexpr int kBatchGroups = 64;
+__global__ __launch_bounds__(kTile) void reduce_groups_few_batch_kernel(BatchArgs b)
+{
+    bool one_pass;
+    const ReduceArgs a = batch_layer_args(b, blockIdx.z, one_pass);
+    if (one_pass) return;
+    const int n = reduce_groups_count(a);
+    for (int g = blockIdx.y; g < n; g += gridDim.y) {
+        if (g != (int)blockIdx.y) __syncthreads();             // the last one's sums in LDS have been read
+        reduce_groups_body(a, g, blockIdx.x);
+    }
+}
+
+// grid (nslab, layers): a slab of a layer that is reduced in one launch (by half of the waves, the others end at once), or,
+// by its first workgroup, the second level of one that is not.
+template <int kQ>
+__global__ __launch_bounds__(1024) void reduce_last_batch_kernel(BatchArgs b)
+{
+    bool one_pass;
+    const ReduceArgs a = batch_layer_args(b, blockIdx.y, one_pass);
+    if (one_pass) {
+        if (threadIdx.x < kSlabThreads) reduce_slab_body<kQ>(a, blockIdx.x);
+        return;
+    }
+    if (blockIdx.x > 0 || (a.G1 == 1 && a.n_ex == 0 && !a.big_sq)) return;
+    reduce_final_body(a);
+}
+
 // Level 2 for large shapes: grid ntile, 256 threads, one column per thread.
 __global__ __launch_bounds__(kTile) void reduce_final_tiles_kernel(ReduceArgs a)
 {

@@ -415,6 +415,32 @@ def test_reduction_in_one_launch(B, T, D, dtype):
                                atol=1e-5 * float(now[1].square().mean().sqrt()))
 
 
+@pytest.mark.parametrize("B,T,D,dtype", [(80, 9, 520, "bf16"), (300, 5, 128, "f32"), (70, 3, 1001, "bf16"), (520, 7, 1024, "bf16")])
+def test_deferred_layers_of_every_access(B, T, D, dtype):
+    """Layers of one shape behind aligned and unaligned pointers, per-example and plain, which are reduced in one launch or
+    in two levels, finished by one call: bitwise the immediate results."""
+    import torch
+    from paper_2411_00999_amd import binding
+    inp = workloads.make_inputs(1, B=B, T=T, D=D, dtype=dtype, signal=1e-2)
+    code, n = (binding.BF16 if dtype == "bf16" else binding.F32), B * T * D
+    x, dy, gamma = (pu.to_device(a, dtype) for a in (inp.x, inp.dy, inp.gamma))
+
+    def moved(t):
+        return torch.empty(n + 1, dtype=t.dtype, device="cuda")[1:].copy_(t.view(-1)).view(B, T, D)
+    calls = [(f, src) for src in ((x, dy), (moved(x), moved(dy))) for f in (binding.ln_bwd_pegn, binding.ln_bwd)]
+    now = [f(*src, gamma, inp.eps) for f, src in calls]
+    wss = [binding.alloc_workspace(B, T, D, code) for _ in calls]
+    late = [f(*src, gamma, inp.eps, workspace=w, deferred=True) for (f, src), w in zip(calls, wss)]
+    binding.reduce_deferred(wss, B, T, D, code)
+    torch.cuda.synchronize()
+    for p, q in zip(now, late):
+        assert all(torch.equal(a, b) for a, b in zip(p, q))
+    names = ("dx", "dgamma", "dbeta", "s_gamma", "s_beta", "big_sq")
+    ref = _oracle(inp)
+    for p in now:
+        pu.compare_with_oracle(inp, dict(zip(names, map(pu.to_host64, p))), ref, pegn=len(p) > 3)
+
+
 def test_deferred_layers_of_both_reductions():
     """Layers whose row kernels ran under different launch overrides, one reduced in one launch and one in two levels,
     finished by one call under none."""

@@ -103,3 +103,22 @@ def test_forward_of_ragged_rows_with_gamma_of_the_other_type():
         gamma, beta = torch.ones(D, device="cuda", dtype=dt), torch.zeros(D, device="cuda", dtype=dt)
         us[dt] = _us(lambda: binding.ln_fwd(x, gamma, beta, 1e-5, y=y, mean=mean, rstd=rstd), calls=10)
     assert us[torch.float32] < 2.0 * us[torch.bfloat16], us
+
+
+def _deferred_us(B, T, D, dtype, layers=16):
+    """GPU time of the deferred reduction of some layers, us."""
+    import torch
+    from paper_2411_00999_amd import binding
+    dt, code = (torch.bfloat16, binding.BF16) if dtype == "bf16" else (torch.float32, binding.F32)
+    x, dy, gamma = torch.randn(B, T, D, device="cuda").to(dt), torch.randn(B, T, D, device="cuda").to(dt), torch.ones(D, device="cuda", dtype=dt)
+    workspaces = [binding.alloc_workspace(B, T, D, code) for _ in range(layers)]
+    keep = [binding.ln_bwd_pegn(x, dy, gamma, 1e-5, workspace=w, deferred=True) for w in workspaces]
+    us = _us(lambda: binding.reduce_deferred(workspaces, B, T, D, code), calls=10)
+    return us, keep
+
+
+def test_deferred_reduction_of_many_short_examples():
+    """512 examples of a chunk each against 64 of eight chunks each: the same sums of the same 512 chunks (with a
+    workgroup sent for every example in vain: 1.7 times)."""
+    many, few = _deferred_us(512, 64, 1024, "bf16")[0], _deferred_us(64, 512, 1024, "bf16")[0]
+    assert many < 1.45 * few, (many, few)
