@@ -265,6 +265,12 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
         if constexpr (!kRaggedX) fetch(ox, XLoads{}, XChunks{}, lds_base + buf * kStageBytes);
         if constexpr (!kRaggedG) fetch(og, GLoads{}, GChunks{}, lds_base + buf * kStageBytes + kXBytes);
     };
+    // The counts by which a wave waits for its direct loads hold only if those of a stage are issued before the register
+    // loads that follow them here; both are loads that the compiler could order otherwise.
+    auto in_order = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
     Fetched x_from[kSets], g_from[kSets];
     auto fetch_regs = [&](auto set) {                          // the ragged operands' next stage
         constexpr int s = decltype(set)::value;
@@ -462,7 +468,11 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
         auto refill = [&]() {
             if constexpr (kRagged) put_regs(next_set, buffer(1));
             fetch_direct(buffer(2));
-            if constexpr (kRagged) fetch_regs(next_set);
+            if constexpr (kRagged) {
+                in_order();
+                fetch_regs(next_set);
+                in_order();
+            }
         };
         multiply(cur, refill);
         cur = buffer(1);
@@ -487,9 +497,13 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
         fetch_regs(Set0{});
         put_regs(Set0{}, 0);
     }
-    if constexpr (kRagged) fetch_regs(Set1{});
+    if constexpr (kRagged) {
+        fetch_regs(Set1{});
+        in_order();
+    }
     fetch_direct(1);
     if constexpr (kRagged) {
+        in_order();
         if constexpr (kSets == 2) fetch_regs(Set0{});
         int st = 0;
         for (; st + 2 <= nstages; st += 2) {
