@@ -1331,8 +1331,14 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     int part_bits = p.n <= 16384 ? 12 : p.n <= 65536 ? 10 : p.n <= 131072 ? 11 : p.n <= 262144 ? 12 : 13;
     while ((size_t)((p.n >> part_bits) + 1) * p.ncb * sizeof(uint32_t) > counter_bytes && p.n >> part_bits) ++part_bits;
     auto runs = [&](auto kernel, auto *gp) {
-        runs_status = launch(kernel, dim3((unsigned)(medium_blocks + fill_blocks + runs_x * runs_y)), dim3(64 * kWavesPerBlock), 0, st, gp, keys, vals, w, runsum,
-                             contrib, bigpart, arrived, p.n, part_bits, T, D, V, accumulate, medium_blocks, fill_a, each_a, fill_blocks, runs_x);
+        auto go = [&](int medium, int fill, int run) {
+            return launch(kernel, dim3((unsigned)(medium + fill + run)), dim3(64 * kWavesPerBlock), 0, st, gp, keys, vals, w, runsum, contrib,
+                          bigpart, arrived, p.n, part_bits, T, D, V, accumulate, medium, fill_a, each_a, fill, runs_x);
+        };
+        // a launch holds less than 2^32 threads: the medium segments of nearly 2^28 positions need one of their own
+        const bool one = ((int64_t)medium_blocks + fill_blocks + runs_x * runs_y) * 64 * kWavesPerBlock <= 0xffffffffll;
+        if (!one) runs_status = go(medium_blocks, 0, 0);
+        if (runs_status == hipSuccess) runs_status = go(one ? medium_blocks : 0, fill_blocks, runs_x * runs_y);
     };
     if (dt == LNPEGN_BF16) {
         if (vec) runs(emb_runs_kernel<bf16_t, true>, static_cast<const bf16_t *>(g));

@@ -123,3 +123,19 @@ def test_rows_no_id_selects_are_zero(V, D, off, kind):
     count = np.bincount(ids[ids < V].reshape(-1), minlength=V)
     np.testing.assert_array_equal(w.cpu().numpy(), np.repeat(count[:, None], D, 1).astype(np.float32))
     assert bool((flat[:off] == 7).all()) and bool((flat[off + V * D:] == 7).all())
+
+
+def test_positions_just_below_the_limit():
+    """Nearly 2^28 positions: the workgroups of the runs, the medium segments and the fill are more than one launch holds.
+    Whole numbers, so sums are exact in any order."""
+    import torch
+    from paper_2411_00999_amd import binding
+    n, D, V = (1 << 28) - 200000, 1, 1 << 24
+    ids = torch.randint(0, V // 2, (1, n), device="cuda", dtype=torch.int32) * 2      # about 32 positions to an id
+    ids[0, :5000], ids[0, -300:] = 8, 1
+    g = torch.randint(-1, 2, (1, n, D), device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    w, s, big = binding.embedding_pegn(ids, g, V)
+    want = torch.zeros(V, device="cuda").index_add_(0, ids[0], g.view(-1).float())
+    assert torch.equal(w.view(-1), want)
+    square = float(want.double().square().sum())
+    np.testing.assert_allclose([float(s[0]), float(big[0])], square, rtol=pu.TOL_SUMS)
