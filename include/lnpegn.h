@@ -264,9 +264,10 @@ int gns_linear_accum_steps(int64_t tokens_seen, int64_t ramp_tokens, int accum_f
  *   big_sq [1] fp32 or NULL: ||w||^2 of the (accumulated) weight gradient.
  * The per-example tensor [B,K,L] is never written to memory.  The contraction runs on the matrix cores (bf16 or
  * fp32 MFMA, fp32 accumulation) for any T, K and L, fastest with 16-byte aligned x, g and K, L multiples of 8
- * (bf16) or 4 (fp32); only operands of less than 16 bytes, pointers that split an element and K or L beyond
- * 2^25 take a slow scalar kernel.  workspace: linear_pegn_workspace_bytes(...) bytes, 256-byte aligned, caller-owned,
- * contents scratch.  K*L <= 2^31.  Enqueued on stream, never synchronises; status codes as above.
+ * (bf16) or 4 (fp32).  Otherwise a few short examples, operands of less than 16 bytes, pointers that split an element,
+ * workspaces of a scalar kernel's size, and (aligned or not) K or L beyond some 2^24 are left to that kernel.
+ * workspace: linear_pegn_workspace_bytes(...) bytes, 256-byte aligned, caller-owned, contents scratch.  K*L <= 2^31.
+ * Enqueued on stream, never synchronises; status codes as above.
  */
 size_t linear_pegn_workspace_bytes(int B, int T, int K, int L, lnpegn_dtype dt);
 int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq, int B, int T, int K, int L,

@@ -657,11 +657,16 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, LinKer
     const int per_chunk = dt == LNPEGN_BF16 ? 8 : 4;          // elements per 16-byte vector
     p.ragged_x = K % per_chunk != 0 || !align.x16;
     p.ragged_g = L % per_chunk != 0 || !align.g16;
-    // The matrix-core kernel takes every shape but ragged tensors of less than one chunk and rows whose stage is
-    // beyond its 32-bit offsets; those, and pointers that split an element, are left to the scalar kernel.
+    // The matrix-core kernel takes every shape but ragged tensors of less than one chunk and rows so wide that the last of
+    // a stage is beyond its offsets; those, and pointers that split an element, are left to the scalar kernel.
     const int64_t rows = (int64_t)B * T, tiles16 = (int64_t)((K + 15) / 16) * ((L + 15) / 16);
     const bool ragged = p.ragged_x || p.ragged_g;
-    p.mfma = which != kLinScalar && K <= (1 << 25) && L <= (1 << 25) &&
+    auto in_reach = [&](int width, bool own_ragged) {          // tracked loads: 31 bits of offset, all others 32
+        const int esz = dt == LNPEGN_BF16 ? 2 : 4, stage = 128 / esz, last = (T < stage ? T : stage) - 1;
+        const int64_t end = ((int64_t)last * width + Cfg::kTileK) * esz;
+        return end <= (ragged && !own_ragged && dt == LNPEGN_BF16 ? (int64_t)kTrackedBytes : (int64_t)UINT32_MAX);
+    };
+    p.mfma = which != kLinScalar && in_reach(K, p.ragged_x) && in_reach(L, p.ragged_g) &&
              (!ragged || (align.element && rows * K >= per_chunk && rows * L >= per_chunk));
     if (p.mfma) {
         p.tiles_k = (K + Cfg::kTileK - 1) / Cfg::kTileK;

@@ -945,6 +945,27 @@ def test_linear_pegn_short_ragged_rows_in_less_workspace(dtype, B, T, K, L):
         binding.linear_pegn(xd, gd, workspace=torch.empty(cores - 256, dtype=torch.uint8, device="cuda"))
 
 
+@pytest.mark.parametrize("T,K,L", [
+    (40, (1 << 25) - 8, 9),         # aligned x beside a ragged g: its last rows lie more than 2^31 bytes behind the first
+    (33, (1 << 25) - 8, 8),         # both aligned, offsets of 2^31 and more
+    (2, (1 << 25) + 8, 8), (2, 8, (1 << 25) + 8),
+])
+def test_linear_pegn_of_very_wide_rows(T, K, L):
+    """Small whole numbers, so every sum is exact."""
+    import torch
+    from paper_2411_00999_amd import binding
+    x, g = (torch.randint(-2, 3, (1, T, n), device="cuda", dtype=torch.int8).to(torch.bfloat16) for n in (K, L))
+    w, s, big = binding.linear_pegn(x, g)
+    square = 0.0
+    for k in range(0, K, 1 << 20):
+        want = torch.zeros((min(K, k + (1 << 20)) - k, L), device="cuda")
+        for t in range(T):
+            want += x[0, t, k:k + (1 << 20), None].float() * g[0, t].float()
+        assert torch.equal(w[k:k + (1 << 20)], want)
+        square += float(want.double().square().sum())
+    np.testing.assert_allclose([float(s[0]), float(big[0])], square, rtol=pu.TOL_SUMS)
+
+
 @pytest.mark.parametrize("K,L", [(264, 131), (257, 129), (264, 136)])
 def test_linear_pegn_keeps_infinities_to_their_example(K, L):
     """T is no multiple of a stage: the rows behind an example's end are zeros, not what another example left there."""
