@@ -105,7 +105,7 @@ def test_reduced_workloads_bf16(cfg, B, T, D, saved):
     (2, 5, 12288, "bf16"), (2, 3, 2048, "f32"), (2, 3, 8192, "f32"), (2, 9, 64, "f32"), (2, 9, 8, "bf16"),
 ])
 def test_any_D_is_correct(B, T, D, dtype):
-    """Generic kernel (odd D, D above the tuned range) and the small/large ends of the tuned ones."""
+    """Ragged rows (odd D), the generic kernel (less than a vector, D above the tuned range), the ends of the tuned ones."""
     inp = workloads.make_inputs(1, B=B, T=T, D=D, dtype=dtype)
     ref = _oracle(inp)
     for saved in (False, True):
@@ -197,12 +197,12 @@ def test_in_place_dx_over_dy():
     ("bf16", 768, 2), ("bf16", 1023, 0), ("bf16", 1024, 1), ("bf16", 1025, 0), ("bf16", 2049, 0),   # S = 1, 2, 3
     ("bf16", 4100, 0), ("bf16", 8191, 0), ("bf16", 8192, 1), ("bf16", 8193, 0),      # ... 8 waves, then the generic kernel
     ("f32", 4, 1), ("f32", 5, 0), ("f32", 255, 0), ("f32", 257, 1), ("f32", 515, 0), ("f32", 1021, 0), ("f32", 1025, 0),
-    ("f32", 3001, 0), ("f32", 4095, 3), ("f32", 8190, 0),
+    ("f32", 3001, 0), ("f32", 4095, 3), ("f32", 8190, 0), ("f32", 8193, 0), ("f32", 9000, 1),
 ])
 @pytest.mark.parametrize("saved", [False, True])
 def test_rows_of_any_width_and_address(dtype, D, off, saved):
     """Rows that are no whole number of vectors or not 16-byte aligned, dx over dy, against the oracle; the elements
-    around the tensors stay as they are; the generic kernel in a workspace too small for more chunks agrees."""
+    around the tensors stay as they are.  (Wider than 8192, or narrower than a vector: the generic kernel.)"""
     import torch
     from paper_2411_00999_amd import binding
     inp = workloads.make_inputs(1, B=3, T=23, D=D, dtype=dtype)
@@ -254,7 +254,76 @@ def test_ragged_rows_with_gamma_of_the_other_type(dtype, D):
         pu.compare_with_oracle(inp, dict(zip(names, map(pu.to_host64, out))), ref)
 
 
-def test_misaligned_pointers_take_the_generic_kernel():
+@pytest.mark.parametrize("dtype,B,T,D,chunks,least", [("bf16", 16, 450, 9, 896, 800), ("f32", 16, 468, 9, 928, 832),
+                                                      ("f32", 3, 45, 4095, 33, 27), ("bf16", 200, 137, 1001, 1600, 1000)])
+def test_ragged_rows_in_the_generic_kernels_workspace(dtype, B, T, D, chunks, least):
+    """Shapes of which the ragged rows are cut into more chunks than the generic kernel's: a workspace that holds the
+    latter is still enough, for an immediate and a deferred call, and one of less is refused."""
+    import torch
+    from paper_2411_00999_amd import binding
+    inp = workloads.make_inputs(1, B=B, T=T, D=D, dtype=dtype)
+    ref, code = _oracle(inp), (binding.BF16 if dtype == "bf16" else binding.F32)
+    plan = binding.plan_query(B, T, D, code, aligned=False)
+    assert plan["chunks"] == chunks
+    sums = lambda n: -(-n * 2 * D * 4 // 256) * 256
+    ws = torch.empty(plan["workspace_bytes"] - sums(chunks) + sums(least), dtype=torch.uint8, device="cuda")
+    x, dy, gamma = (pu.to_device(a, dtype) for a in (inp.x, inp.dy, inp.gamma))
+    names = ("dx", "dgamma", "dbeta", "s_gamma", "s_beta", "big_sq")
+    now = binding.ln_bwd_pegn(x, dy, gamma, inp.eps, workspace=ws)
+    torch.cuda.synchronize()
+    pu.compare_with_oracle(inp, dict(zip(names, map(pu.to_host64, now))), ref)
+    late = binding.ln_bwd_pegn(x, dy, gamma, inp.eps, workspace=ws, deferred=True)
+    binding.reduce_deferred([ws], B, T, D, code)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(now, late))
+    with pytest.raises(binding.LnpegnError):
+        binding.ln_bwd_pegn(x, dy, gamma, inp.eps, workspace=ws[:-256])
+
+
+def test_ragged_rows_in_the_static_scratch():
+    """The generic kernel's chunks fit the library's own scratch where the ragged rows' do not."""
+    import torch
+    from paper_2411_00999_amd import binding
+    B, T, D = 200, 133, 8190
+    plan = binding.plan_query(B, T, D, binding.BF16, aligned=False)
+    assert plan["workspace_bytes"] > binding.STATIC_SCRATCH_BYTES
+    torch.manual_seed(workloads.BASE_SEED)
+    x, dy = (torch.randn(B, T, D, device="cuda").to(torch.bfloat16) for _ in range(2))
+    gamma = torch.ones(D, dtype=torch.bfloat16, device="cuda")
+    want = binding.ln_bwd_pegn(x, dy, gamma, 1e-5)
+    got = tuple(torch.empty_like(t) for t in want)
+    binding.ln_bwd_pegn_static(x, dy, gamma, 1e-5, *got)
+    torch.cuda.synchronize()
+    pu.check_close("dx", pu.to_host64(got[0][:2]), pu.to_host64(want[0][:2]), pu.TOL_BF16, bf16_output=True)
+    for a, b in zip(got[1:], want[1:]):
+        np.testing.assert_allclose(pu.to_host64(a), pu.to_host64(b), rtol=1e-5, atol=1e-5 * float(b.square().mean().sqrt()))
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 1001), ("bf16", 3001), ("f32", 515), ("f32", 2049)])
+def test_ragged_rows_keep_infinities_to_their_row(dtype, D):
+    """Infinities and NaN in the last row of one example: a vector that reaches into the neighbouring row brings nothing
+    along into that row's results, nor into the next example's norms."""
+    import torch
+    from paper_2411_00999_amd import binding
+    B, T = 3, 7
+    inp = workloads.make_inputs(1, B=B, T=T, D=D, dtype=dtype)
+    x, dy, gamma, beta = (pu.to_device(a, dtype) for a in (inp.x, inp.dy, inp.gamma, inp.beta))
+    want, (y_want, _, _) = binding.ln_bwd_pegn(x, dy, gamma, inp.eps), binding.ln_fwd(x, gamma, beta, inp.eps)
+    x[0, -1], dy[0, -1] = float("inf"), float("nan")
+    y, mean, rstd = binding.ln_fwd(x, gamma, beta, inp.eps)
+    for kw in ({}, dict(mean=mean, rstd=rstd)):
+        got = binding.ln_bwd_pegn(x, dy, gamma, inp.eps, **kw)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(got[0].view(B * T, D)[[r for r in range(B * T) if r != T - 1]]).all())
+        for a, b in ((got[0][1:], want[0][1:]), (got[0][0, :-1], want[0][0, :-1])):
+            pu.check_close("dx", pu.to_host64(a), pu.to_host64(b), pu.TOL_BF16 if dtype == "bf16" else pu.TOL_F32, bf16_output=dtype == "bf16")
+        for a, b in zip(got[3:5], want[3:5]):
+            assert not bool(torch.isfinite(a[0]))
+            np.testing.assert_allclose(pu.to_host64(a[1:]), pu.to_host64(b[1:]), rtol=1e-5)
+    assert torch.equal(y[1:], y_want[1:]) and torch.equal(y[0, :-1], y_want[0, :-1])
+
+
+def test_misaligned_pointers():
     import torch
     from paper_2411_00999_amd import binding
     inp = workloads.make_inputs(2, B=2, T=10, D=768)
@@ -415,7 +484,8 @@ def test_reduction_in_one_launch(B, T, D, dtype):
                                atol=1e-5 * float(now[1].square().mean().sqrt()))
 
 
-@pytest.mark.parametrize("B,T,D,dtype", [(80, 9, 520, "bf16"), (300, 5, 128, "f32"), (70, 3, 1001, "bf16"), (520, 7, 1024, "bf16")])
+@pytest.mark.parametrize("B,T,D,dtype", [(80, 9, 520, "bf16"), (300, 5, 128, "f32"), (70, 3, 1001, "bf16"), (520, 7, 1024, "bf16"),
+                                         (520, 33, 1001, "bf16"), (40, 50, 1001, "bf16"), (70, 40, 515, "f32")])
 def test_deferred_layers_of_every_access(B, T, D, dtype):
     """Layers of one shape behind aligned and unaligned pointers, per-example and plain, which are reduced in one launch or
     in two levels, finished by one call: bitwise the immediate results."""
@@ -495,7 +565,7 @@ def test_forward_against_oracle(cfg, B, T, D):
 @pytest.mark.parametrize("cfg,B,T,D,defer", [(3, 4, 40, 2048, False), (2, 3, 21, 768, False),
                                             (4, 300, 2, 1024, False), (3, 4, 40, 2048, True), (1, 2, 9, 257, True),
                                             # one example per micro-batch (Section 5.1's setting), spanning several
-                                            # chunks: vector kernel and generic kernel, immediate and deferred
+                                            # chunks: aligned and ragged rows, immediate and deferred
                                             (3, 1, 200, 2048, False), (3, 1, 200, 2048, True),
                                             (1, 1, 50, 257, False), (1, 1, 50, 257, True)])
 def test_gradient_accumulation_over_micro_batches(cfg, B, T, D, defer):
@@ -866,6 +936,7 @@ def test_linear_pegn_splits(dtype, B, T, K, L):
 @pytest.mark.parametrize("dtype,B,T,K,L", [("f32", 3, 17, 50, 36), ("bf16", 2, 9, 100, 7), ("f32", 2, 64, 256, 128),
                                            ("f32", 1, 1, 1, 1)])
 def test_linear_pegn_generic_kernel(dtype, B, T, K, L):
+    """A few short examples, ragged (the scalar kernel) and aligned (the matrix cores' all the same)."""
     x, g = workloads.make_linear_inputs(B * 1000 + K, B, T, K, L, dtype)
     _check_linear(x, g, _run_linear(x, g, dtype))
     w0 = np.random.default_rng(workloads.BASE_SEED + 79).normal(0, 1e-2, (K, L))

@@ -35,7 +35,7 @@ def _both_ways(inp, saved):
 
 
 # first call, then a smaller second call; vector kernels with several chunks per example, one workgroup
-# per example (B > 256), the generic kernel (odd D), fp32
+# per example (B > 256), ragged rows (odd D), fp32
 SEQUENCES = [
     [(3, 8, 256, 2048), (3, 2, 50, 2048)],
     [(4, 300, 8, 1024), (2, 3, 37, 768)],
