@@ -153,7 +153,7 @@ int ln_bwd_pegn_static(const void *x, const void *dy, const void *gamma, const f
  * The per-chunk column sums (Appendix B steps 1 and 5 over a chunk of rows) and the output
  * pointers stay in that call's workspace, which must therefore be private to the call and left
  * untouched until lnpegn_reduce_deferred has run.  lnpegn_reduce_deferred then finishes n such
- * calls in one launch (two for shapes of many examples; steps 2, 3, 6, 7 for every layer), instead of one or two
+ * calls in one launch (two or three for shapes of many examples; steps 2, 3, 6, 7 for every layer), instead of one or two
  * per layer.  Results are bitwise the same as those of the immediate calls.
  *   workspaces  HOST array of n device workspace pointers, each used by one deferred call with
  *               exactly these B, T, D, dt (plain and per-example calls may be mixed)
