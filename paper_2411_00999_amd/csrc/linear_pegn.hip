@@ -267,10 +267,7 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
     };
     // The counts by which a wave waits for its direct loads hold only if those of a stage are issued before the register
     // loads that follow them here; both are loads that the compiler could order otherwise.
-    auto in_order = [&]() {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    };
+    auto in_order = [&]() { asm volatile("" ::: "memory"); };
     Fetched x_from[kSets], g_from[kSets];
     auto fetch_regs = [&](auto set) {                          // the ragged operands' next stage
         constexpr int s = decltype(set)::value;
@@ -471,7 +468,6 @@ __device__ __forceinline__ void linear_pegn_body(const LinArgs &a)
             if constexpr (kRagged) {
                 in_order();
                 fetch_regs(next_set);
-                in_order();
             }
         };
         multiply(cur, refill);
