@@ -251,12 +251,14 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
     // up nslab parts of every norm.  Few chunks and few norms: one launch.  Many: two levels.  Measured, us a call, two
     // levels / one launch: 64 examples (B=64 T=512 D=1024 bf16) 48.1 / 46.9, 128 (B=128 T=256) 48.3 / 49.7, 200 in 1600
     // chunks (B=200 T=128) 44.8 / 51.1; 8192 parts (B=32 T=300 D=8192) 108.2 / 103.3; 2048 chunks (B=16 T=2048 D=2048
-    // fp32) 157.5 / 153.6.  More than 32 examples, of which a walker then takes several: B=40 T=512 bf16 D=512 23.5 / 26.8,
-    // D=640 27.4 / 27.0, D=768 28.9 / 28.4, fp32 D=768 in 2048 chunks (B=64 T=512) 63.0 / 66.1.  Whole-example chunks (T=16)
+    // fp32) 157.5 / 153.6.  More than 32 examples, of which a walker then takes several: bf16 B=40 D=512 in 1000
+    // chunks (T=512) 23.5 / 26.8, D=640 27.4 / 27.0, D=768 28.9 / 28.4; D=256 in 320 chunks (T=64) 13.1 / 11.4; B=33 to 64,
+    // D=64 to 512: two levels 0 to 2.2 more up to 512 chunks, 0 to 4.5 less from 825 on; fp32 B=64 T=512 D=768 in 2048 63.0 /
+    // 66.1.  Whole-example chunks (T=16)
     // of too few slabs for their number: bf16 D=768 B=1024 27.5 / 26.7, 1536 37.0 / 37.7, 2048 43.4 / 45.1, D=1536
     // B=2048 79.0 / 79.4, D=2048 100.1 / 96.9, fp32 D=256 B=2048 29.8 / 31.8, D=128 23.9 / 23.2.  The parts lie
     // where the two levels keep their group sums.
-    const bool many_ex_ok = p.n_ex <= 32 || (D >= 640 && p.n_slots <= 1024);
+    const bool many_ex_ok = p.n_ex <= 32 || (p.n_slots <= 1024 && (D >= 640 || p.n_slots <= 640));
     const bool many_chunks_ok = !p.emit_pe || p.n_slots <= 1024 || D <= 192 || D >= 1536;
     p.one_pass = p.n_slots <= kSlabChunks && p.n_ex <= kSlabExamples && many_ex_ok && many_chunks_ok && (int64_t)p.n_ex * p.nslab <= kSlabParts &&
                  (size_t)(p.n_ex + 1) * p.nslab * 2 * sizeof(double) <= (size_t)kGroups * 2 * D * sizeof(float);
