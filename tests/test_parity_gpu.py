@@ -485,7 +485,8 @@ def test_reduction_in_one_launch(B, T, D, dtype):
 
 
 @pytest.mark.parametrize("B,T,D,dtype", [(80, 9, 520, "bf16"), (300, 5, 128, "f32"), (70, 3, 1001, "bf16"), (520, 7, 1024, "bf16"),
-                                         (520, 33, 1001, "bf16"), (40, 50, 1001, "bf16"), (70, 40, 515, "f32")])
+                                         (520, 33, 1001, "bf16"), (40, 50, 1001, "bf16"), (70, 40, 515, "f32"),
+                                         (40, 64, 256, "bf16"), (64, 64, 256, "f32"), (64, 200, 256, "f32")])
 def test_deferred_layers_of_every_access(B, T, D, dtype):
     """Layers of one shape behind aligned and unaligned pointers, per-example and plain, which are reduced in one launch or
     in two levels, finished by one call: bitwise the immediate results."""
