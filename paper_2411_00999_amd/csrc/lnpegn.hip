@@ -89,7 +89,7 @@ constexpr size_t kHeaderBytes = 256;
 // 40.0 -> 37.0, B=384 T=64 30.0 -> 29.1, B=200 T=128 31.4 -> 30.2; D=2048: B=300 T=100 104.5 -> 77.9, B=600 T=64
 // 105.3 -> 91.5; D=4096: B=300 T=100 170.1 -> 153.5.  (B=700 T=48 and B=1000 T=32, whose second round is more
 // than a third full, are faster with one chunk per example: 35.8 against 36.9 and 34.1 against 35.2.)
-int64_t chunks_per_example(int64_t B, int64_t T, int64_t W)
+int64_t chunks_per_example(int64_t B, int64_t T, int64_t W, int R)
 {
     const int64_t c0 = W / B > 1 ? W / B : 1;
     const int64_t n = B * c0, full = n / W, rest = n % W;   // rounds that are full, workgroups in the last one
@@ -97,7 +97,7 @@ int64_t chunks_per_example(int64_t B, int64_t T, int64_t W)
                              : rest == 0 || full >= 3 || (full == 1 && 10 * rest >= 3 * W);
     if (fits) return c0;
     const int64_t c3 = (3 * W + B - 1) / B;         // three rounds
-    return (c3 <= 16 && T / c3 >= 16) ? c3 : c0;    // ... unless that leaves a chunk fewer than 16 rows
+    return (c3 <= 16 && T / c3 >= (R > 4 ? 4 * R : 16)) ? c3 : c0;    // ... unless that leaves a chunk fewer than 16 rows
 }
 
 // What the pointers of a call allow: nothing but element accesses, vectors at element addresses, aligned vectors.
@@ -131,14 +131,24 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
         p.sync = p.S > 1;
         const int elems = p.vpt * E;                 // per lane
         waves_per_simd = elems > 8 ? 2 : 4;          // measured: more waves of 16-element lanes only add contention
+        // Narrow lanes, rows of one wave: half as many workgroups (512) where what the reduction saves is more than the
+        // row kernel loses.  us, 1024 workgroups / 512: bf16 B=8 T=1024 D=512 17.0 / 13.8, D=256 15.7 / 13.2, D=64
+        // 13.6 / 12.5, B=16 T=2048 D=512 29.2 / 26.9 and fp32 48.0 / 44.0; but D=256 22.7 / 24.2 (narrow rows of a longer
+        // tensor want the waves) and B=4 T=1024 D=256 12.0 / 12.3 (few rows each).
+        if (p.S == 1 && elems <= 8 && (!pegn || B <= 32) && N >= 8192 && (p.nvec > 48 * p.vpt || N <= 12288)) waves_per_simd = 2;
         // launch bound of the instantiation that will run: 256 threads for S = 1, 2, 4; 512 else
         const int max_waves = (elems <= 8 && (p.ragged ? p.S == 1 : p.S <= 2)) ? 4 : 8;
         // row groups per workgroup.  Wide lanes: six waves per workgroup, one workgroup per CU (measured, B*T =
         // 32768 rows: bf16 D=2048 69.2 -> 66.9 us per-example and 69.0 -> 65.4 plain against four waves; fp32
         // D=2048 151.7 -> 145.6 and 133 -> 131; eight waves are slower than six; no difference where a row
         // already takes four or eight waves).
-        // (rows that one wave covers stay at four row groups: six made the short kernels of B=8 T=1024 D=768 and
-        // B=512 T=64 D=1024 3-10 % slower)
+        // Rows that one wave covers, wide lanes: eight row groups, one workgroup per CU, as soon as a chunk has two rows
+        // for each.  The same waves as with two workgroups of four, but half the chunks, whose column sums the reduction
+        // reads back.  us a call, row kernel + reduction, four / eight: bf16 B=8 T=1024 D=768 9.8 + 8.2 / 9.2 + 6.3, B=16 T=2048
+        // D=768 27.7 + 8.1 / 27.0 + 7.0, B=8 T=500 D=1001 9.6 + 11.5 / 8.3 + 8.5, B=48 T=256 D=768 14.6 + 8.1 / 14.0 + 6.9, B=100
+        // T=24 15.5 / 12.3, fp32 B=16 T=2048 D=1024 68.7 + 15.6 / 68.7 + 11.5; T=24 B=8 11.0 / 11.4; plain B=8 T=1024 D=768
+        // 9.8 + 6.2 / 9.1 + 4.6.  Many examples in long tensors, whose chunks come from rounds of workgroups, stay at four.
+        const bool eight = (!pegn || B <= 32 || N <= 16384) && (pegn ? T : N) >= 16;
         // (fp32 rows of four waves: two row groups, measured with the per-example sweeps, 288.7 -> 273.8 us)
         // (rows of two waves with lanes left over, D=1280, 1536 or 1600 in bf16, have fewer bytes in flight per
         // wave and take four row groups: D=1280 64.5 -> 52.0 us, D=1536 65.0 -> 55.3; rows of three waves take two:
@@ -148,6 +158,7 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
                 : (elems > 8 && p.S == 2) ? (full ? 3 : 4)
                 : p.S == 3 ? 2
                 : (pegn && E == 4 && p.S == 4 && p.vpt >= 3) ? 2
+                : (elems > 8 && p.S == 1 && eight) ? 8
                 : (p.S >= 4 ? 1 : 4 / p.S);
         if (R < 1) R = 1;
         while (R > 1 && R * p.S > max_waves) --R;
@@ -190,7 +201,10 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
     };
     if (pegn) {
         p.Tp = T;
-        int64_t c = g_chunks_pegn > 0 || !p.fast ? target / B : chunks_per_example(B, T, target);
+        // Eight row groups: where one workgroup per CU does not come out even, two (they fit side by side).  us a call, one / two:
+        // bf16 D=768 B=130 T=126 28.0 / 25.8, B=100 T=160 25.8 / 25.4, B=90 T=180 27.1 / 25.2 (B=50 T=300, even, 22.0 / 23.2).
+        const bool uneven = p.R == 8 && B < kCUs && 20 * (kCUs / B * B) < 17 * kCUs;
+        int64_t c = g_chunks_pegn > 0 || !p.fast ? target / B : chunks_per_example(B, T, uneven ? 2 * target : target, p.R);
         // Long launches over fp32 rows of 16 elements per lane: several rounds of shorter workgroups, which even
         // out the CUs' unequal progress (measured, us per launch, one round -> this: B=16 T=2048 D=2048
         // 138.3 -> 134.3, B=8 T=4096 D=2048 137.2 -> 134.2, B=16 T=4096 D=2048 280.9 -> 265.9, B=16 T=2048 D=1024
