@@ -33,7 +33,7 @@ constexpr int kWavesPerBlock = 4;
 constexpr int kNormBlocks = 2048;   // workgroups of the ||w'||^2 pass in accumulate mode
 constexpr int kFillBlocks = 16384;  // most workgroups of the zero fill
 constexpr int64_t kFillLeast = 8 << 10, kFillMost = 32 << 10;   // bytes that a wave of it takes at a time
-constexpr int64_t kFillLateBytes = 40 << 20;   // most bytes of it that are left to kernel B
+constexpr int64_t kFillLateBytes = 128 << 20;   // most bytes of it that are left to kernel B
 
 __global__ __launch_bounds__(256) void emb_prepare_kernel(const void *ids, int ids_i64, uint32_t *keys,
                                                           uint32_t *vals, int64_t n, int V)
@@ -57,6 +57,7 @@ constexpr int kSortTile = 2048, kSortTileBits = 11;
 constexpr int kSortTiles = 64;
 constexpr int kSortEach = 4;                        // words per thread
 constexpr int kSortThreads = kSortTile / kSortEach;
+constexpr int kRankThreads = 256;
 
 template <typename W>
 struct SortWord;
@@ -97,6 +98,30 @@ template <int kMask>
 __device__ __forceinline__ uint64_t lane_xor(uint64_t v)
 {
     return (uint64_t)lane_xor<kMask>((uint32_t)(v >> 32)) << 32 | lane_xor<kMask>((uint32_t)v);
+}
+
+// Zero fill beside the sort's second launch, a chain of a few workgroups' loads under which the memory idles: workgroup
+// `block` clears kShadowBytes of w', whose first rows are cleared here whether their ids occur (kernel A writes those again)
+// or not.  us a call, without / 32 MiB so / 48 MiB so / 12 beside the first launch and 32 beside the second: bf16 B=8 T=1024
+// D=768 V=50257 47.3 / 46.0 / 46.6 / 45.7, B=16 T=2048 D=2048 124.6 / 118.5 / 118.0 / 118.1, B=16 T=512 D=1024 V=60000
+// 63.0 / 58.2 / 58.1 / 57.6, B=16 T=1024 D=512 V=32000 49.0 / 49.6 / 49.3 / 49.1.
+struct ShadowFill {
+    float *begin;        // 16-byte aligned
+    int64_t len;         // floats
+    int blocks;          // workgroups
+};
+constexpr int kShadowBytes = 32 << 10;               // of a workgroup
+constexpr int64_t kShadowMost = 32 << 20;            // in all
+__device__ __forceinline__ void shadow_fill(const ShadowFill &f, int block)
+{
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    constexpr int kFloats = kShadowBytes / 4;
+    const int64_t at = (int64_t)block * kFloats;
+    const int len = (int)min((int64_t)kFloats, f.len - at), quads = len / 4;
+    float *p = f.begin + at;
+#pragma unroll 8
+    for (int i = threadIdx.x; i < quads; i += kRankThreads) __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4 *>(p) + i);
+    if ((int)threadIdx.x < len - quads * 4) p[quads * 4 + threadIdx.x] = 0.f;
 }
 
 // Bitonic network over a tile, four consecutive words per thread: strides below 4 stay in a thread's registers, below
@@ -169,12 +194,17 @@ __global__ __launch_bounds__(kSortThreads) void emb_tile_sort_kernel(const void 
 // other tile) advance together, first over those samples, then inside the 32 words (one cache line of 32-bit words)
 // that they leave.  Latency bound: with all eleven steps in memory 10.8 us for 16 tiles and 9.0 for 4, against 7.6
 // and 6.9 (with whole tiles in LDS, which leaves one workgroup a CU, 14.0 and 6.9).
-constexpr int kRankThreads = 256, kSampleEvery = 32, kSamples = kSortTile / kSampleEvery;
+constexpr int kSampleEvery = 32, kSamples = kSortTile / kSampleEvery;
 template <typename W>
 __global__ __launch_bounds__(kRankThreads) void emb_rank_kernel(const W *tiles, int ntiles, int64_t n, uint32_t *sorted_ids,
-                                                                uint32_t *sorted_pos)
+                                                                uint32_t *sorted_pos, ShadowFill fill)
 {
     extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int kPerTile = kSortTile / kRankThreads;
+    if ((int)blockIdx.x >= ntiles * kPerTile) {
+        shadow_fill(fill, (int)blockIdx.x - ntiles * kPerTile);
+        return;
+    }
     W *samples = reinterpret_cast<W *>(lds);                     // [ntiles][kSamples]: the last word of each block
     const int64_t i = (int64_t)blockIdx.x * kRankThreads + threadIdx.x;     // index into the tiles array
     const W word = tiles[i];                                     // (the grid covers the tiles exactly)
@@ -362,8 +392,9 @@ __device__ __forceinline__ uint32_t half_wave_first_not(uint32_t lo, uint32_t le
 // Zero fill of the rows of w' that no id selects (rows begin to end - 1), a part of kernel A's grid and of kernel B's:
 // the rows of ids that occur are written, whole, by the other workgroups, so everything touches different rows and
 // runs side by side.  Kernel A waits for its chains of loads more than for bandwidth and kernel B does little else, so
-// the fill is shared out between the two (half of it, at most 40 MiB, beside kernel B: the presorted call
-// 48.7 -> 46.2 us at B=8 T=1024 D=768 V=50257, no difference at B=16 T=2048 D=2048).  A wave takes `rows` neighbouring
+// the fill is shared out between the two (half of it, at most 128 MiB, beside kernel B; presorted calls, us, with at most
+// 40 / 96 / 128 / 200 MiB there: B=8 T=1024 D=768 V=50257 37.8 / 35.0 / 35.2 / 34.9, B=16 T=2048 D=2048 118.2 / 112.5 / 110.7 /
+// 111.4, B=8 T=512 D=768 V=60000 fp32 41.2 / 37.9 / 38.2 / 37.8).  A wave takes `rows` neighbouring
 // rows (at most 64) and finds their ids in the sorted list, so that no map of the ids is needed before the launch;
 // waves beside each other take rows beside each other, so that together they sweep one moving window of w'.  Absent rows
 // in a row are one stretch of memory: whole lines but at its ends, whatever the width.  (A row at a time, a lane's
@@ -611,8 +642,8 @@ __device__ __forceinline__ void finish_medium_ids(const T *g, const uint32_t *ke
 template <typename T, bool kVec>
 __global__ __launch_bounds__(64 * kWavesPerBlock, kVec && sizeof(T) == 2 ? 3 : 4) void emb_runs_kernel(
     const T *g, const uint32_t *keys, const uint32_t *vals, float *w, float *runsum, float *contrib, float *bigpart,
-    uint32_t *arrived, int64_t n, int part_bits, int Tn, int D, int V, int accumulate, int medium_blocks, int fill_rows,
-    int fill_each, int fill_blocks, int runs_x)
+    uint32_t *arrived, int64_t n, int part_bits, int Tn, int D, int V, int accumulate, int medium_blocks, int fill_begin,
+    int fill_end, int fill_each, int fill_blocks, int runs_x)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -632,7 +663,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, kVec && sizeof(T) == 2 ? 3 : 4
     int fill = behind < 0 && j % 3 == 2 ? j / 3 : -1;
     if (behind >= 0 && block >= run_blocks) fill = groups + block - run_blocks;
     if (fill >= 0) {
-        fill_absent_rows(keys, (uint32_t)n, w, 0, fill_rows, D, fill_each, fill * kWavesPerBlock + wave, fill_blocks * kWavesPerBlock, lane);
+        fill_absent_rows(keys, (uint32_t)n, w, fill_begin, fill_end, D, fill_each, fill * kWavesPerBlock + wave, fill_blocks * kWavesPerBlock, lane);
         return;
     }
     const int block_y = block / runs_x, block_x = block - block_y * runs_x;
@@ -1230,21 +1261,21 @@ hipError_t make_emb_plan(int B, int T, int D, int V, bool radix, EmbPlan &p)
 // The library's own sort of the ids into (sorted_ids, sorted_pos): two launches.
 template <typename W>
 hipError_t own_sort(const void *ids, int ids_are_int64, const EmbPlan &p, int V, void *tiles, uint32_t *sorted_ids,
-                    uint32_t *sorted_pos, hipStream_t st)
+                    uint32_t *sorted_pos, const ShadowFill &fill, hipStream_t st)
 {
     W *t = static_cast<W *>(tiles);
     hipError_t e = launch(emb_tile_sort_kernel<W>, dim3(p.ntiles), dim3(kSortThreads), 0, st, ids, ids_are_int64, p.n, V, t);
     if (e != hipSuccess) return e;
-    return launch(emb_rank_kernel<W>, dim3(p.ntiles * (kSortTile / kRankThreads)), dim3(kRankThreads),
-                  (size_t)p.ntiles * kSamples * sizeof(W), st, t, p.ntiles, p.n, sorted_ids, sorted_pos);
+    return launch(emb_rank_kernel<W>, dim3(p.ntiles * (kSortTile / kRankThreads) + fill.blocks), dim3(kRankThreads),
+                  (size_t)p.ntiles * kSamples * sizeof(W), st, t, p.ntiles, p.n, sorted_ids, sorted_pos, fill);
 }
 
 hipError_t sort_ids(const void *ids, int ids_are_int64, const EmbPlan &p, int V, char *ws, uint32_t *sorted_ids,
-                    uint32_t *sorted_pos, hipStream_t st)
+                    uint32_t *sorted_pos, const ShadowFill &fill, hipStream_t st)
 {
     if (p.own_sort)
-        return sort_words_are_32(V) ? own_sort<uint32_t>(ids, ids_are_int64, p, V, ws + p.off_tiles, sorted_ids, sorted_pos, st)
-                                    : own_sort<uint64_t>(ids, ids_are_int64, p, V, ws + p.off_tiles, sorted_ids, sorted_pos, st);
+        return sort_words_are_32(V) ? own_sort<uint32_t>(ids, ids_are_int64, p, V, ws + p.off_tiles, sorted_ids, sorted_pos, fill, st)
+                                    : own_sort<uint64_t>(ids, ids_are_int64, p, V, ws + p.off_tiles, sorted_ids, sorted_pos, fill, st);
     uint32_t *keys_in = reinterpret_cast<uint32_t *>(ws + p.off_keys_in), *vals_in = reinterpret_cast<uint32_t *>(ws + p.off_vals_in);
     const hipError_t e = launch(emb_prepare_kernel, dim3((unsigned)((p.n + 255) / 256)), dim3(256), 0, st, ids, ids_are_int64,
                                 keys_in, vals_in, p.n, V);
@@ -1292,18 +1323,30 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     float *bigpart = reinterpret_cast<float *>(ws + p.off_bigpart);
     double *wpart = reinterpret_cast<double *>(ws + p.off_wpart);
     float *runsum = reinterpret_cast<float *>(ws + p.off_runsum);
-    // 1. the ids sorted
-    if (ids && sort_ids(ids, ids_are_int64, p, V, ws, const_cast<uint32_t *>(keys), const_cast<uint32_t *>(vals), st) != hipSuccess)
+    // 1. the ids sorted, and beside the library's own sort the first rows of w' cleared: whole rows that end on a boundary
+    // of 16 bytes, or all of a w' that is no more than that.  Only where the fill is what kernel A waits for: a large w', or few
+    // rows of g.  (us a call, without / with: B=64 T=512 D=1024 V=32000 fp32, more bytes of g than of w', 78.1 / 78.5; B=16 T=1024
+    // D=512 V=32000, 65 MB, 49.0 / 49.6; B=4 T=64 D=128 V=50257 fp32 26.7 / 24.9, B=4 T=256 D=768 43.3 / 40.2.)
+    const int esz = dt == LNPEGN_BF16 ? 2 : 4;
+    const int64_t row_bytes = (int64_t)D * 4;
+    int cleared = 0;                                              // rows
+    if (ids && p.own_sort && !accumulate && (reinterpret_cast<uintptr_t>(w) & 15u) == 0 && p.n * esz < (int64_t)V * 4 &&
+        (V * row_bytes >= 3 * kShadowMost || p.n <= 4096)) {
+        const int64_t rows = kShadowMost / row_bytes;
+        const int unit = 4 / (int)((D & -D) < 4 ? (D & -D) : 4);
+        cleared = rows < V ? (int)(rows / unit * unit) : V;
+    }
+    const ShadowFill shadow{w, (int64_t)cleared * D, (int)(((int64_t)cleared * row_bytes + kShadowBytes - 1) / kShadowBytes)};
+    if (ids && sort_ids(ids, ids_are_int64, p, V, ws, const_cast<uint32_t *>(keys), const_cast<uint32_t *>(vals), shadow, st) != hipSuccess)
         return LNPEGN_EHIP;
     // 2. runs, and beside them the fill of the rows no id selects
-    const int esz = dt == LNPEGN_BF16 ? 2 : 4;
     // 8 columns per lane: 16 bytes of bf16, 32 bytes of fp32; rows must keep that alignment
     const bool vec = (reinterpret_cast<uintptr_t>(g) & 15u) == 0 && ((int64_t)D * esz) % 16 == 0 && D % 8 == 0;
     const int64_t chunks = (p.n + kChunk - 1) / kChunk;
     const int runs_x = (int)(chunks < g_emb_run_blocks ? chunks : g_emb_run_blocks), runs_y = (p.ncb + kWavesPerBlock - 1) / kWavesPerBlock;
     // the rows filled beside kernel A; the rest beside kernel B
-    const int64_t row_bytes = (int64_t)D * 4, late = V / 2 < kFillLateBytes / row_bytes ? V / 2 : kFillLateBytes / row_bytes;
-    const int fill_a = accumulate ? 0 : V - (int)late, fill_b = accumulate ? 0 : (int)late;
+    const int64_t half = (V - cleared) / 2, late = half < kFillLateBytes / row_bytes ? half : kFillLateBytes / row_bytes;
+    const int fill_end = V - (int)late, fill_a = accumulate ? 0 : fill_end - cleared, fill_b = accumulate ? 0 : (int)late;
     // Rows to a wave: 8 to 32 KB, so that there are many waves and the search for their ids is hidden, and whole lines of 128
     // bytes (32 / gcd(D, 32) rows are) where 64 KB are enough for that.
     const int whole = 32 / (int)((D & -D) < 32 ? (D & -D) : 32);
@@ -1333,7 +1376,7 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     auto runs = [&](auto kernel, auto *gp) {
         auto go = [&](int medium, int fill, int run) {
             return launch(kernel, dim3((unsigned)(medium + fill + run)), dim3(64 * kWavesPerBlock), 0, st, gp, keys, vals, w, runsum, contrib,
-                          bigpart, arrived, p.n, part_bits, T, D, V, accumulate, medium, fill_a, each_a, fill, runs_x);
+                          bigpart, arrived, p.n, part_bits, T, D, V, accumulate, medium, cleared, fill_end, each_a, fill, runs_x);
         };
         // a launch holds less than 2^32 threads: the medium segments of nearly 2^28 positions need one of their own
         const bool one = ((int64_t)medium_blocks + fill_blocks + runs_x * runs_y) * 64 * kWavesPerBlock <= 0xffffffffll;
@@ -1351,7 +1394,7 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     // 3. the parked sums
     const int64_t sum_blocks = (p.n + kSumSpan - 1) / kSumSpan * p.ncb;
     if (launch(emb_sums_kernel, dim3((unsigned)(sum_blocks + fill_blocks_b)), dim3(64 * kSumWaves), 0, st, keys, vals, w, runsum, contrib, bigpart,
-               arrived, (uint32_t)p.n, part_bits, (uint32_t)T, D, V, accumulate, fill_a, each_b, (int)sum_blocks, fill_blocks_b) != hipSuccess)
+               arrived, (uint32_t)p.n, part_bits, (uint32_t)T, D, V, accumulate, fill_end, each_b, (int)sum_blocks, fill_blocks_b) != hipSuccess)
         return LNPEGN_EHIP;
     // 4. the norms
     const bool wnorm = accumulate && big_sq;
@@ -1378,7 +1421,7 @@ int embedding_sort_ids(const void *ids, int ids_are_int64, int B, int T, int V, 
     EmbPlan p;
     if (make_emb_plan(B, T, 1, V, (int64_t)B * T > (int64_t)kSortTiles * kSortTile, p) != hipSuccess) return LNPEGN_EHIP;
     if (workspace_bytes < p.bytes) return LNPEGN_EWORKSPACE;
-    return sort_ids(ids, ids_are_int64, p, V, static_cast<char *>(workspace), sorted_ids, sorted_pos,
+    return sort_ids(ids, ids_are_int64, p, V, static_cast<char *>(workspace), sorted_ids, sorted_pos, ShadowFill{},
                     static_cast<hipStream_t>(stream)) == hipSuccess ? LNPEGN_OK : LNPEGN_EHIP;
 }
 
