@@ -50,7 +50,8 @@ __host__ __device__ inline int reduce_groups_count(const ReduceArgs &a)
 // writes dgamma and dbeta there, and leaves its part of every squared norm; the workgroup that arrives last adds
 // those parts up.  Latency bound (three dependent trips to memory); against two levels it saves a launch and the
 // trip of the group sums.  Whole backward calls, us, two levels -> this: B=4 T=128 D=256 fp32 12.2 -> 9.5, B=8 T=1024
-// D=768 bf16 21.7 -> 18.3, B=8 T=4096 D=8192 284 -> 277, B=8 T=500 D=1001 78.0 -> 48.5; the deferred reduction of 48
+// D=768 bf16 21.7 -> 18.3, B=8 T=4096 D=8192 284 -> 277, B=8 T=500 D=1001 78.0 -> 48.5 (rows of the workspace that begin at any
+// float: read by 16 bytes too, which takes no longer; element by element the call took 16.8 us, so 15.5); the deferred reduction of 48
 // layers of B=16 T=2048 D=2048 45.0 -> 38.5.
 //
 // The parts cross from one XCD's cache to another's without a fence (a release at device scope writes back the
@@ -111,7 +112,7 @@ __device__ __forceinline__ void reduce_slab_body(const ReduceArgs &a, int slab)
         double acc[4] = {0, 0, 0, 0}, run[4] = {0, 0, 0, 0};
         const int64_t stride = 2 * (int64_t)a.D;
         const float *base = a.part + (int64_t)arr * a.D + col;
-        const bool vec = (a.D & 3) == 0;                        // rows of the workspace are 16-byte aligned
+        const bool whole = left >= 4;                           // a quad at any column: rows of the workspace are aligned to a float
         auto finish_example = [&](int e) {
             double q = 0.0;
 #pragma unroll
@@ -131,12 +132,15 @@ __device__ __forceinline__ void reduce_slab_body(const ReduceArgs &a, int slab)
             for (int i = 0; i < 8; ++i) {
                 const float *p = base + min(m + i, m1 - 1) * stride;
                 u[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (vec && left > 0) u[i] = *reinterpret_cast<const float4 *>(p);
-                if (!vec) {
-                    if (left > 0) u[i].x = p[0];
+                if (whole) u[i] = __builtin_bit_cast(float4, (u32x4_t)*(const __attribute__((address_space(1))) u32x4_at4_t *)p);
+            }
+            if (left > 0 && !whole) {                           // the last quad of a ragged row
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float *p = base + min(m + i, m1 - 1) * stride;
+                    u[i].x = p[0];
                     if (left > 1) u[i].y = p[1];
                     if (left > 2) u[i].z = p[2];
-                    if (left > 3) u[i].w = p[3];
                 }
             }
 #pragma unroll
@@ -250,15 +254,16 @@ __device__ __forceinline__ void reduce_groups_body(const ReduceArgs &a, int gx, 
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (c4 < a.D) {
         const int64_t stride = 2 * (int64_t)a.D;
-        if ((a.D & 3) == 0) {                  // rows of the workspace are 16-byte aligned
+        if (c4 + 4 <= a.D) {                   // (rows of the workspace are aligned to a float)
             for (int m = w0; m < w1; m += 8) {
                 float4 u[8], v[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const int mm = min(m + i, w1 - 1);
                     const float *p = a.part + mm * stride + c4;
-                    u[i] = *reinterpret_cast<const float4 *>(p);
-                    v[i] = *reinterpret_cast<const float4 *>(p + a.D);
+                    using P = const __attribute__((address_space(1))) u32x4_at4_t *;
+                    u[i] = __builtin_bit_cast(float4, (u32x4_t)*(P)p);
+                    v[i] = __builtin_bit_cast(float4, (u32x4_t)*(P)(p + a.D));
                 }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
@@ -268,8 +273,8 @@ __device__ __forceinline__ void reduce_groups_body(const ReduceArgs &a, int gx, 
                     }
                 }
             }
-        } else {                               // any D: element by element
-            const int nc = min(4, a.D - c4);
+        } else {                               // the last columns of a ragged row: element by element
+            const int nc = a.D - c4;
             for (int m = w0; m < w1; ++m) {
                 const float *p = a.part + m * stride + c4;
                 for (int i = 0; i < nc; ++i) {
