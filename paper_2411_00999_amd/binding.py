@@ -1,6 +1,8 @@
-"""Thin ctypes binding of the lnpegn C ABI (include/lnpegn.h).
+"""Thin binding of the lnpegn C ABI (include/lnpegn.h).
 
-Argument marshalling only: every step of the path runs in the library's HIP kernels.
+Argument marshalling only: every step of the path runs in the library's HIP kernels.  The calls that a training program
+makes go through a CPython extension (csrc/marshal.cpp), which takes tensors as they are; load() hands out the
+library itself through ctypes.
 Tensors are torch tensors on the GPU (torch is used for device memory and streams and for
 nothing else); results are returned in freshly allocated torch tensors unless the caller
 passes output buffers.  A missing or unloadable library raises -- there is no fallback.
@@ -9,7 +11,6 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Optional
 
 from . import build as _build
 
@@ -27,6 +28,7 @@ EXPORTS = ("lnpegn_workspace_bytes", "lnpegn_status_string", "lnpegn_last_hip_er
 PER_EXAMPLE, DEFER, ACCUMULATE = 1, 2, 4
 
 _lib = None
+_native = None       # the extension, once the library is loaded
 
 
 class LnpegnError(RuntimeError):
@@ -96,8 +98,17 @@ def load() -> ctypes.CDLL:
                  "rms_fwd", "rms_bwd_ex", "gns_ema_update", "gns_offline", "gns_linear_accum_steps",
                  "linear_pegn", "embedding_pegn", "embedding_sort_ids", "embedding_pegn_presorted"):
         getattr(lib, name).restype = i
+    from . import _marshal
+    _marshal.bind(path)
+    global _native
+    _native = _marshal
     _lib = lib
     return lib
+
+
+def _load_native():
+    load()
+    return _native
 
 
 def _torch():
@@ -114,25 +125,6 @@ def _dt(t) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
-def _ptr(t) -> Optional[int]:
-    return None if t is None else t.data_ptr()
-
-
-def _stream(stream) -> Optional[int]:
-    """Handle of the given stream, or of the current device's current one.  The handle itself is asked for:
-    torch.cuda.current_stream() makes a Stream object first, 2.9 us of the 8.4 us of a call with one launch."""
-    if stream is None:
-        c = _torch()._C
-        return c._cuda_getCurrentRawStream(c._cuda_getDevice()) or None
-    return stream.cuda_stream or None
-
-
-def _check3(x):
-    if x.dim() != 3 or not x.is_contiguous() or not x.is_cuda:
-        raise ValueError("expected a contiguous CUDA tensor [B,T,D]")
-    return x.shape
-
-
 def workspace_bytes(B: int, T: int, D: int, dtype: int) -> int:
     return int(load().lnpegn_workspace_bytes(B, T, D, dtype))
 
@@ -140,6 +132,12 @@ def workspace_bytes(B: int, T: int, D: int, dtype: int) -> int:
 def alloc_workspace(B: int, T: int, D: int, dtype: int, device="cuda"):
     torch = _torch()
     return torch.empty(workspace_bytes(B, T, D, dtype), dtype=torch.uint8, device=device)
+
+
+def _empty(like, *shape):
+    """fp32 output on the device of a tensor."""
+    torch = _torch()
+    return torch.empty(shape, dtype=torch.float32, device=like.device)
 
 
 def gns_ema_update(state, records, alpha: float, smoothed=None, stream=None):
@@ -151,8 +149,7 @@ def gns_ema_update(state, records, alpha: float, smoothed=None, stream=None):
     if records.dtype != torch.float32 or tuple(records.shape) != (n, 5) or not records.is_contiguous():
         raise ValueError("records must be a contiguous [n,5] float32 tensor")
     smoothed = torch.empty((n, 3), dtype=torch.float32, device=state.device) if smoothed is None else smoothed
-    rc = load().gns_ema_update(_ptr(state), _ptr(records), n,
-                               float(alpha), _ptr(smoothed), _stream(stream))
+    rc = (_native or _load_native()).gns_ema_update(state, records, n, float(alpha), smoothed, stream)
     if rc:
         raise LnpegnError("gns_ema_update", rc)
     return smoothed
@@ -164,7 +161,7 @@ def gns_offline(records, out=None, stream=None):
     if records.dtype != torch.float32 or records.dim() != 2 or records.shape[1] != 5 or not records.is_contiguous():
         raise ValueError("records must be a contiguous [n,5] float32 tensor")
     out = torch.empty(5, dtype=torch.float32, device=records.device) if out is None else out
-    rc = load().gns_offline(_ptr(records), records.shape[0], _ptr(out), _stream(stream))
+    rc = (_native or _load_native()).gns_offline(records, records.shape[0], out, stream)
     if rc:
         raise LnpegnError("gns_offline", rc)
     return out
@@ -180,24 +177,24 @@ def gns_linear_accum_steps(tokens_seen: int, ramp_tokens: int, accum_final: int)
 def linear_pegn(x, g, w=None, accumulate=False, s=None, big_sq=None, workspace=None, stream=None):
     """x [B,T,K], g [B,T,L] -> (w [K,L] fp32, s [B] fp32, big_sq [1] fp32)."""
     torch = _torch()
-    B, T, K = _check3(x)
-    B2, T2, L = _check3(g)
+    native = _native or _load_native()
+    B, T, K = native.check3(x)
+    B2, T2, L = native.check3(g)
     if (B2, T2) != (B, T) or g.dtype != x.dtype:
         raise ValueError("x and g must agree in B, T and dtype")
-    f32 = dict(dtype=torch.float32, device=x.device)
     if w is None:
         if accumulate:
             raise ValueError("accumulate needs the buffer to add to")
-        w = torch.empty((K, L), **f32)
+        w = _empty(x, K, L)
     if w.dtype != torch.float32 or tuple(w.shape) != (K, L) or not w.is_contiguous():
         raise ValueError("w must be a contiguous [K,L] float32 tensor")
-    s = torch.empty(B, **f32) if s is None else s
-    big_sq = torch.empty(1, **f32) if big_sq is None else big_sq
+    s = _empty(x, B) if s is None else s
+    big_sq = _empty(x, 1) if big_sq is None else big_sq
     if workspace is None:
         nbytes = load().linear_pegn_workspace_bytes(B, T, K, L, _dt(x))
         workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=x.device)
-    rc = load().linear_pegn(_ptr(x), _ptr(g), _ptr(w), _ptr(s), _ptr(big_sq), B, T, K, L, _dt(x),
-                            _ptr(workspace), workspace.numel(), ACCUMULATE if accumulate else 0, _stream(stream))
+    rc = native.linear_pegn(x, g, w, s, big_sq, B, T, K, L, x, workspace, workspace.numel(),
+                            ACCUMULATE if accumulate else 0, stream)
     if rc:
         raise LnpegnError("linear_pegn", rc)
     return w, s, big_sq
@@ -206,26 +203,25 @@ def linear_pegn(x, g, w=None, accumulate=False, s=None, big_sq=None, workspace=N
 def embedding_pegn(ids, g, V: int, w=None, accumulate=False, s=None, big_sq=None, workspace=None, stream=None):
     """ids [B,T] int32/int64, g [B,T,D] -> (w [V,D] fp32, s [B] fp32, big_sq [1] fp32)."""
     torch = _torch()
-    B, T, D = _check3(g)
+    native = _native or _load_native()
+    B, T, D = native.check3(g)
     if tuple(ids.shape) != (B, T) or not ids.is_contiguous() or ids.dtype not in (torch.int32, torch.int64):
         raise ValueError("ids must be a contiguous [B,T] int32 or int64 tensor")
-    f32 = dict(dtype=torch.float32, device=g.device)
     if w is None:
         if accumulate:
             raise ValueError("accumulate needs the buffer to add to")
-        w = torch.empty((V, D), **f32)
+        w = _empty(g, V, D)
     if w.dtype != torch.float32 or tuple(w.shape) != (V, D) or not w.is_contiguous():
         raise ValueError("w must be a contiguous [V,D] float32 tensor")
-    s = torch.empty(B, **f32) if s is None else s
-    big_sq = torch.empty(1, **f32) if big_sq is None else big_sq
+    s = _empty(g, B) if s is None else s
+    big_sq = _empty(g, 1) if big_sq is None else big_sq
     if workspace is None:
         nbytes = load().embedding_pegn_workspace_bytes(B, T, D, V)
         if nbytes == 0:
             raise LnpegnError("embedding_pegn_workspace_bytes", 1)
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=g.device)
-    rc = load().embedding_pegn(_ptr(ids), 1 if ids.dtype == torch.int64 else 0, _ptr(g), _ptr(w), _ptr(s), _ptr(big_sq),
-                               B, T, D, V, _dt(g), _ptr(workspace), workspace.numel(),
-                               ACCUMULATE if accumulate else 0, _stream(stream))
+    rc = native.embedding_pegn(ids, 1 if ids.dtype == torch.int64 else 0, g, w, s, big_sq, B, T, D, V, g, workspace,
+                               workspace.numel(), ACCUMULATE if accumulate else 0, stream)
     if rc:
         raise LnpegnError("embedding_pegn", rc)
     return w, s, big_sq
@@ -243,8 +239,8 @@ def embedding_sort_ids(ids, V: int, workspace=None, stream=None):
     sorted_pos = torch.empty(n, dtype=torch.int32, device=ids.device)
     if workspace is None:
         workspace = torch.empty(load().embedding_pegn_workspace_bytes(B, T, 1, V), dtype=torch.uint8, device=ids.device)
-    rc = load().embedding_sort_ids(_ptr(ids), 1 if ids.dtype == torch.int64 else 0, B, T, V, _ptr(sorted_ids),
-                                   _ptr(sorted_pos), _ptr(workspace), workspace.numel(), _stream(stream))
+    rc = (_native or _load_native()).embedding_sort_ids(ids, 1 if ids.dtype == torch.int64 else 0, B, T, V, sorted_ids, sorted_pos,
+                                                        workspace, workspace.numel(), stream)
     if rc:
         raise LnpegnError("embedding_sort_ids", rc)
     return sorted_ids, sorted_pos
@@ -254,21 +250,20 @@ def embedding_pegn_presorted(sorted_ids, sorted_pos, g, V: int, w=None, accumula
                              workspace=None, stream=None):
     """embedding_pegn with the ids sorted beforehand by embedding_sort_ids -> (w [V,D], s [B], big_sq [1])."""
     torch = _torch()
-    B, T, D = _check3(g)
+    native = _native or _load_native()
+    B, T, D = native.check3(g)
     if sorted_ids.numel() != B * T or sorted_pos.numel() != B * T:
         raise ValueError("sorted_ids and sorted_pos must hold B*T entries")
-    f32 = dict(dtype=torch.float32, device=g.device)
     if w is None:
         if accumulate:
             raise ValueError("accumulate needs the buffer to add to")
-        w = torch.empty((V, D), **f32)
-    s = torch.empty(B, **f32) if s is None else s
-    big_sq = torch.empty(1, **f32) if big_sq is None else big_sq
+        w = _empty(g, V, D)
+    s = _empty(g, B) if s is None else s
+    big_sq = _empty(g, 1) if big_sq is None else big_sq
     if workspace is None:
         workspace = torch.empty(load().embedding_pegn_workspace_bytes(B, T, D, V), dtype=torch.uint8, device=g.device)
-    rc = load().embedding_pegn_presorted(_ptr(sorted_ids), _ptr(sorted_pos), _ptr(g), _ptr(w), _ptr(s), _ptr(big_sq),
-                                         B, T, D, V, _dt(g), _ptr(workspace), workspace.numel(),
-                                         ACCUMULATE if accumulate else 0, _stream(stream))
+    rc = native.embedding_pegn_presorted(sorted_ids, sorted_pos, g, w, s, big_sq, B, T, D, V, g, workspace, workspace.numel(),
+                                         ACCUMULATE if accumulate else 0, stream)
     if rc:
         raise LnpegnError("embedding_pegn_presorted", rc)
     return w, s, big_sq
@@ -306,18 +301,18 @@ def stream_probe(a, b, out, mode: int, stream=None) -> None:
     """Streaming yardstick kernel: out = a (mode 0) or a XOR b (modes 1, 2: 2 = one-shot workgroups, streaming
     loads and stores) over equal-sized buffers."""
     nbytes = out.numel() * out.element_size()
-    rc = load().lnpegn_stream_probe(_ptr(a), _ptr(b), _ptr(out), nbytes, mode, _stream(stream))
+    rc = (_native or _load_native()).lnpegn_stream_probe(a, b, out, nbytes, mode, stream)
     if rc:
         raise LnpegnError("lnpegn_stream_probe", rc)
 
 
 def ln_fwd_stats(x, eps: float, mean=None, rstd=None, stream=None):
     """mean[B,T], rstd[B,T] (fp32) of x[B,T,D]."""
-    torch = _torch()
-    B, T, D = _check3(x)
-    mean = torch.empty((B, T), dtype=torch.float32, device=x.device) if mean is None else mean
-    rstd = torch.empty((B, T), dtype=torch.float32, device=x.device) if rstd is None else rstd
-    rc = load().ln_fwd_stats(_ptr(x), _ptr(mean), _ptr(rstd), B, T, D, _dt(x), eps, _stream(stream))
+    native = _native or _load_native()
+    B, T, D = native.check3(x)
+    mean = _empty(x, B, T) if mean is None else mean
+    rstd = _empty(x, B, T) if rstd is None else rstd
+    rc = native.ln_fwd_stats(x, mean, rstd, B, T, D, x, eps, stream)
     if rc:
         raise LnpegnError("ln_fwd_stats", rc)
     return mean, rstd
@@ -325,14 +320,14 @@ def ln_fwd_stats(x, eps: float, mean=None, rstd=None, stream=None):
 
 def ln_fwd(x, gamma, beta, eps: float, y=None, mean=None, rstd=None, want_stats=True, stream=None):
     """LayerNorm forward -> (y, mean[B,T], rstd[B,T]); the statistics are None if not wanted."""
-    torch = _torch()
-    B, T, D = _check3(x)
-    y = torch.empty_like(x) if y is None else y
+    native = _native or _load_native()
+    B, T, D = native.check3(x)
+    if y is None:
+        y = _torch().empty_like(x)
     if want_stats:
-        mean = torch.empty((B, T), dtype=torch.float32, device=x.device) if mean is None else mean
-        rstd = torch.empty((B, T), dtype=torch.float32, device=x.device) if rstd is None else rstd
-    rc = load().ln_fwd(_ptr(x), _ptr(gamma), _ptr(beta), _ptr(y), _ptr(mean), _ptr(rstd), B, T, D,
-                       _dt(x), _dt(gamma), eps, _stream(stream))
+        mean = _empty(x, B, T) if mean is None else mean
+        rstd = _empty(x, B, T) if rstd is None else rstd
+    rc = native.ln_fwd(x, gamma, beta, y, mean, rstd, B, T, D, x, gamma, eps, stream)
     if rc:
         raise LnpegnError("ln_fwd", rc)
     return y, mean, rstd
@@ -342,14 +337,15 @@ def ln_bwd_ex(x, dy, gamma, eps: float, flags: int, dgamma, dbeta, mean=None, rs
               pe_gamma_sq=None, pe_beta_sq=None, big_sq=None, workspace=None, stream=None):
     """General backward (flags: PER_EXAMPLE | DEFER | ACCUMULATE); the caller passes dgamma and
     dbeta, which ACCUMULATE adds to.  Returns dx."""
-    torch = _torch()
-    B, T, D = _check3(x)
-    _check3(dy)
-    dx = torch.empty_like(x) if dx is None else dx
-    workspace = alloc_workspace(B, T, D, _dt(x), x.device) if workspace is None else workspace
-    rc = load().ln_bwd_ex(_ptr(x), _ptr(dy), _ptr(gamma), _ptr(mean), _ptr(rstd), _ptr(dx), _ptr(dgamma),
-                          _ptr(dbeta), _ptr(pe_gamma_sq), _ptr(pe_beta_sq), _ptr(big_sq), B, T, D, _dt(x),
-                          _dt(gamma), eps, _ptr(workspace), workspace.numel(), flags, _stream(stream))
+    native = _native or _load_native()
+    B, T, D = native.check3(x)
+    native.check3(dy)
+    if dx is None:
+        dx = _torch().empty_like(x)
+    if workspace is None:
+        workspace = alloc_workspace(B, T, D, _dt(x), x.device)
+    rc = native.ln_bwd_ex(x, dy, gamma, mean, rstd, dx, dgamma, dbeta, pe_gamma_sq, pe_beta_sq, big_sq, B, T, D, x, gamma,
+                          eps, workspace, workspace.numel(), flags, stream)
     if rc:
         raise LnpegnError("ln_bwd_ex", rc)
     return dx
@@ -357,13 +353,13 @@ def ln_bwd_ex(x, dy, gamma, eps: float, flags: int, dgamma, dbeta, mean=None, rs
 
 def rms_fwd(x, gamma, eps: float, y=None, rstd=None, want_rstd=True, stream=None):
     """RMSNorm forward -> (y, rstd[B,T] or None)."""
-    torch = _torch()
-    B, T, D = _check3(x)
-    y = torch.empty_like(x) if y is None else y
+    native = _native or _load_native()
+    B, T, D = native.check3(x)
+    if y is None:
+        y = _torch().empty_like(x)
     if want_rstd and rstd is None:
-        rstd = torch.empty((B, T), dtype=torch.float32, device=x.device)
-    rc = load().rms_fwd(_ptr(x), _ptr(gamma), _ptr(y), _ptr(rstd), B, T, D, _dt(x), _dt(gamma), eps,
-                        _stream(stream))
+        rstd = _empty(x, B, T)
+    rc = native.rms_fwd(x, gamma, y, rstd, B, T, D, x, gamma, eps, stream)
     if rc:
         raise LnpegnError("rms_fwd", rc)
     return y, rstd
@@ -372,19 +368,20 @@ def rms_fwd(x, gamma, eps: float, y=None, rstd=None, want_rstd=True, stream=None
 def rms_bwd_ex(x, dy, gamma, eps: float, flags: int, dgamma=None, rstd=None, dx=None, pe_gamma_sq=None,
                big_sq=None, workspace=None, stream=None):
     """RMSNorm backward (flags as ln_bwd_ex) -> (dx, dgamma, pe_gamma_sq[B] or None, big_sq[1] or None)."""
-    torch = _torch()
-    B, T, D = _check3(x)
-    _check3(dy)
-    f32 = dict(dtype=torch.float32, device=x.device)
-    dx = torch.empty_like(x) if dx is None else dx
-    dgamma = torch.zeros(D, **f32) if dgamma is None else dgamma
+    native = _native or _load_native()
+    B, T, D = native.check3(x)
+    native.check3(dy)
+    if dx is None:
+        dx = _torch().empty_like(x)
+    if dgamma is None:
+        dgamma = _torch().zeros(D, dtype=_torch().float32, device=x.device)
     if flags & PER_EXAMPLE:
-        pe_gamma_sq = torch.empty(B, **f32) if pe_gamma_sq is None else pe_gamma_sq
-        big_sq = torch.empty(1, **f32) if big_sq is None else big_sq
-    workspace = alloc_workspace(B, T, D, _dt(x), x.device) if workspace is None else workspace
-    rc = load().rms_bwd_ex(_ptr(x), _ptr(dy), _ptr(gamma), _ptr(rstd), _ptr(dx), _ptr(dgamma),
-                           _ptr(pe_gamma_sq), _ptr(big_sq), B, T, D, _dt(x), _dt(gamma), eps,
-                           _ptr(workspace), workspace.numel(), flags, _stream(stream))
+        pe_gamma_sq = _empty(x, B) if pe_gamma_sq is None else pe_gamma_sq
+        big_sq = _empty(x, 1) if big_sq is None else big_sq
+    if workspace is None:
+        workspace = alloc_workspace(B, T, D, _dt(x), x.device)
+    rc = native.rms_bwd_ex(x, dy, gamma, rstd, dx, dgamma, pe_gamma_sq, big_sq, B, T, D, x, gamma, eps, workspace,
+                           workspace.numel(), flags, stream)
     if rc:
         raise LnpegnError("rms_bwd_ex", rc)
     return dx, dgamma, pe_gamma_sq, big_sq
@@ -394,17 +391,17 @@ def ln_bwd(x, dy, gamma, eps: float, mean=None, rstd=None, dx=None, dgamma=None,
            workspace=None, stream=None, deferred=False):
     """Plain LayerNorm backward -> (dx, dgamma, dbeta).  deferred=True runs only the pass over x
     and dy; dgamma/dbeta appear after reduce_deferred() on this call's own workspace."""
-    torch = _torch()
-    B, T, D = _check3(x)
-    _check3(dy)
-    dx = torch.empty_like(x) if dx is None else dx
-    dgamma = torch.empty(D, dtype=torch.float32, device=x.device) if dgamma is None else dgamma
-    dbeta = torch.empty(D, dtype=torch.float32, device=x.device) if dbeta is None else dbeta
-    workspace = alloc_workspace(B, T, D, _dt(x), x.device) if workspace is None else workspace
-    fn = load().ln_bwd_deferred if deferred else load().ln_bwd
-    rc = fn(_ptr(x), _ptr(dy), _ptr(gamma), _ptr(mean), _ptr(rstd), _ptr(dx),
-            _ptr(dgamma), _ptr(dbeta), B, T, D, _dt(x), _dt(gamma), eps,
-            _ptr(workspace), workspace.numel(), _stream(stream))
+    native = _native or _load_native()
+    B, T, D = native.check3(x)
+    native.check3(dy)
+    if dx is None:
+        dx = _torch().empty_like(x)
+    dgamma = _empty(x, D) if dgamma is None else dgamma
+    dbeta = _empty(x, D) if dbeta is None else dbeta
+    if workspace is None:
+        workspace = alloc_workspace(B, T, D, _dt(x), x.device)
+    fn = native.ln_bwd_deferred if deferred else native.ln_bwd
+    rc = fn(x, dy, gamma, mean, rstd, dx, dgamma, dbeta, B, T, D, x, gamma, eps, workspace, workspace.numel(), stream)
     if rc:
         raise LnpegnError("ln_bwd", rc)
     return dx, dgamma, dbeta
@@ -416,22 +413,21 @@ def ln_bwd_pegn(x, dy, gamma, eps: float, mean=None, rstd=None, dx=None, dgamma=
     """Fused backward -> (dx, dgamma, dbeta, pe_gamma_sq[B], pe_beta_sq[B], big_sq[2]).
     deferred=True runs only the pass over x and dy; everything but dx appears after
     reduce_deferred() on this call's own workspace."""
-    torch = _torch()
-    B, T, D = _check3(x)
-    _check3(dy)
-    f32 = dict(dtype=torch.float32, device=x.device)
-    dx = torch.empty_like(x) if dx is None else dx
-    dgamma = torch.empty(D, **f32) if dgamma is None else dgamma
-    dbeta = torch.empty(D, **f32) if dbeta is None else dbeta
-    pe_gamma_sq = torch.empty(B, **f32) if pe_gamma_sq is None else pe_gamma_sq
-    pe_beta_sq = torch.empty(B, **f32) if pe_beta_sq is None else pe_beta_sq
-    big_sq = torch.empty(2, **f32) if big_sq is None else big_sq
-    workspace = alloc_workspace(B, T, D, _dt(x), x.device) if workspace is None else workspace
-    fn = load().ln_bwd_pegn_deferred if deferred else load().ln_bwd_pegn
-    rc = fn(_ptr(x), _ptr(dy), _ptr(gamma), _ptr(mean), _ptr(rstd), _ptr(dx),
-            _ptr(dgamma), _ptr(dbeta), _ptr(pe_gamma_sq), _ptr(pe_beta_sq),
-            _ptr(big_sq), B, T, D, _dt(x), _dt(gamma), eps, _ptr(workspace),
-            workspace.numel(), _stream(stream))
+    native = _native or _load_native()
+    B, T, D = native.check3(x)
+    native.check3(dy)
+    if dx is None:
+        dx = _torch().empty_like(x)
+    dgamma = _empty(x, D) if dgamma is None else dgamma
+    dbeta = _empty(x, D) if dbeta is None else dbeta
+    pe_gamma_sq = _empty(x, B) if pe_gamma_sq is None else pe_gamma_sq
+    pe_beta_sq = _empty(x, B) if pe_beta_sq is None else pe_beta_sq
+    big_sq = _empty(x, 2) if big_sq is None else big_sq
+    if workspace is None:
+        workspace = alloc_workspace(B, T, D, _dt(x), x.device)
+    fn = native.ln_bwd_pegn_deferred if deferred else native.ln_bwd_pegn
+    rc = fn(x, dy, gamma, mean, rstd, dx, dgamma, dbeta, pe_gamma_sq, pe_beta_sq, big_sq, B, T, D, x, gamma, eps, workspace,
+            workspace.numel(), stream)
     if rc:
         raise LnpegnError("ln_bwd_pegn", rc)
     return dx, dgamma, dbeta, pe_gamma_sq, pe_beta_sq, big_sq
@@ -442,11 +438,11 @@ def ln_bwd_pegn_static(x, dy, gamma, eps: float, dx, dgamma, dbeta, pe_gamma_sq,
     """ln_bwd_pegn without a workspace: the library's own fixed scratch is used and nothing is
     allocated, here or in the library -- every output buffer is the caller's.  Shapes whose workspace
     would exceed STATIC_SCRATCH_BYTES raise LnpegnError(LNPEGN_EWORKSPACE)."""
-    B, T, D = _check3(x)
-    _check3(dy)
-    rc = load().ln_bwd_pegn_static(_ptr(x), _ptr(dy), _ptr(gamma), _ptr(mean), _ptr(rstd), _ptr(dx), _ptr(dgamma),
-                                   _ptr(dbeta), _ptr(pe_gamma_sq), _ptr(pe_beta_sq), _ptr(big_sq), B, T, D,
-                                   _dt(x), _dt(gamma), eps, _stream(stream))
+    native = _native or _load_native()
+    B, T, D = native.check3(x)
+    native.check3(dy)
+    rc = native.ln_bwd_pegn_static(x, dy, gamma, mean, rstd, dx, dgamma, dbeta, pe_gamma_sq, pe_beta_sq, big_sq, B, T, D, x,
+                                   gamma, eps, stream)
     if rc:
         raise LnpegnError("ln_bwd_pegn_static", rc)
     return dx, dgamma, dbeta, pe_gamma_sq, pe_beta_sq, big_sq
@@ -454,9 +450,7 @@ def ln_bwd_pegn_static(x, dy, gamma, eps: float, dx, dgamma, dbeta, pe_gamma_sq,
 
 def reduce_deferred(workspaces, B: int, T: int, D: int, dtype: int, stream=None) -> None:
     """Finish every deferred backward call whose workspace is listed (all of one shape)."""
-    n = len(workspaces)
-    arr = (ctypes.c_void_p * n)(*[w.data_ptr() for w in workspaces])
-    rc = load().lnpegn_reduce_deferred(arr, n, B, T, D, dtype, _stream(stream))
+    rc = (_native or _load_native()).reduce_deferred(workspaces, B, T, D, dtype, stream)
     if rc:
         raise LnpegnError("lnpegn_reduce_deferred", rc)
 
@@ -464,19 +458,12 @@ def reduce_deferred(workspaces, B: int, T: int, D: int, dtype: int, stream=None)
 def gns_estimate(pe_sq, big_sq, pe_scale: float, out=None, stream=None):
     """pe_sq [n_groups,B] fp32, big_sq [n_groups] fp32 -> out[5] fp32 on the device:
     |G_small|^2, |G_big|^2, G2, S, B_simple."""
-    torch = _torch()
+    native = _native or _load_native()
     if pe_sq.dim() == 1:
         pe_sq = pe_sq[None]
-    if pe_sq.dtype != torch.float32 or big_sq.dtype != torch.float32:
-        raise TypeError("gns_estimate takes fp32 norms")
-    if not pe_sq.is_contiguous() or not big_sq.is_contiguous():
-        raise ValueError("gns_estimate takes contiguous tensors")
-    n_groups, B = pe_sq.shape
-    if big_sq.numel() != n_groups:
-        raise ValueError("big_sq must hold one value per group")
-    out = torch.empty(5, dtype=torch.float32, device=pe_sq.device) if out is None else out
-    rc = load().gns_estimate(_ptr(pe_sq), _ptr(big_sq), n_groups, B, pe_scale, _ptr(out),
-                             _stream(stream))
+    n_groups, B = native.check_norms(pe_sq, big_sq)
+    out = _empty(pe_sq, 5) if out is None else out
+    rc = native.gns_estimate(pe_sq, big_sq, n_groups, B, pe_scale, out, stream)
     if rc:
         raise LnpegnError("gns_estimate", rc)
     return out

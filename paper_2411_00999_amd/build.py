@@ -1,4 +1,5 @@
-"""Build the lnpegn shared library for gfx950 with hipcc (cross-compiles without a GPU).
+"""Build the lnpegn shared library for gfx950 with hipcc (cross-compiles without a GPU), and the CPython extension that
+marshals arguments to it with the host compiler.
 
     python -m paper_2411_00999_amd.build          # rebuild liblnpegn.so in-tree
 """
@@ -11,6 +12,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblnpegn.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
 SOURCES = [os.path.join(CSRC, f) for f in ("lnpegn.hip", "lnpegn_rows_inst.hip", "linear_pegn.hip", "embedding_pegn.hip")]
 HEADERS = [os.path.join(CSRC, h) for h in ("lnpegn_device.h", "lnpegn_rows.h", "lnpegn_finalize.h", "lnpegn_tracker.h",
                                            "lnpegn_launch.h")]
@@ -33,14 +36,29 @@ HIPCC_FLAGS = [
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
         return True
     t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS)
+    return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS) or \
+        any(os.path.getmtime(f) > os.path.getmtime(MARSHAL) for f in (MARSHAL_SOURCE, HEADERS[-1]))
+
+
+def _marshal_command(out: str) -> list:
+    """g++ on the extension, against the headers of the Python and the torch that run this."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            *("-I" + d for d in (*cpp_extension.include_paths(), sysconfig.get_paths()["include"])),
+            MARSHAL_SOURCE, "-o", out, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + lib]
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
-    """Compile every HIP source (side by side, one hipcc each) and link liblnpegn.so; always recompiles."""
+    """Compile every HIP source (side by side, one hipcc each) and link liblnpegn.so, and the extension beside them; always
+    recompiles."""
     import concurrent.futures as cf
     import shutil
     import tempfile
@@ -55,8 +73,17 @@ def build(verbose: bool = False, extra_flags=()) -> str:
                 print(" ".join(cmd), flush=True)
             subprocess.run(cmd, check=True)
             return obj
-        with cf.ThreadPoolExecutor(max_workers=min(len(UNITS), os.cpu_count() or 4)) as ex:
+        def compile_marshal():
+            tmp = MARSHAL + f".tmp{os.getpid()}"
+            cmd = _marshal_command(tmp)
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            subprocess.run(cmd, check=True)
+            os.replace(tmp, MARSHAL)
+        with cf.ThreadPoolExecutor(max_workers=min(len(UNITS) + 1, os.cpu_count() or 4)) as ex:
+            marshal = ex.submit(compile_marshal)
             objs = list(ex.map(compile_one, UNITS))
+            marshal.result()
         tmp = LIB + f".tmp{os.getpid()}"
         cmd = [hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", tmp, *objs]
         if verbose:
@@ -69,8 +96,8 @@ def build(verbose: bool = False, extra_flags=()) -> str:
 
 
 def ensure_built() -> str:
-    """Return the library path, building only if no library exists yet."""
-    if not os.path.exists(LIB):
+    """Return the library path, building only if it or the extension does not exist yet."""
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
         build()
     return LIB
 

@@ -1,0 +1,70 @@
+"""The extension that marshals arguments to the C ABI, without a device: what it refuses, and that addresses, numbers, types
+and the stream arrive (seen through the entry points' own validation, which launches nothing)."""
+import pytest
+import torch
+
+from paper_2411_00999_amd import binding
+
+
+class _Stream:
+    cuda_stream = 0
+
+
+@pytest.fixture(scope="module")
+def native():
+    binding.load()
+    return binding._native
+
+
+def test_shapes_and_types_that_are_refused(native):
+    with pytest.raises(ValueError, match="contiguous CUDA tensor"):
+        native.check3(torch.zeros(2, 3, 4))                        # not on a GPU
+    with pytest.raises(TypeError):
+        native.check3([1, 2, 3])
+    for bad in (torch.zeros(2, 3, dtype=torch.float64), torch.zeros(2, 3, dtype=torch.float16)):
+        with pytest.raises(TypeError, match="fp32 norms"):
+            native.check_norms(bad, torch.zeros(2))
+        with pytest.raises(TypeError, match="unsupported dtype torch.float"):
+            native.ln_fwd_stats(None, None, None, 1, 1, 1, bad, 1e-5, _Stream())
+    with pytest.raises(ValueError, match="contiguous"):
+        native.check_norms(torch.zeros(3, 2).t(), torch.zeros(2))
+    with pytest.raises(ValueError, match="one value per group"):
+        native.check_norms(torch.zeros(2, 3), torch.zeros(3))
+    assert native.check_norms(torch.zeros(2, 3), torch.zeros(2)) == (2, 3)
+
+
+def test_arguments_arrive(native):
+    t, s = torch.zeros(8), _Stream()
+    # ln_fwd_stats: EINVAL (1) for a null pointer or an empty shape, EUNSUPPORTED (2) for an unknown type
+    assert native.ln_fwd_stats(None, t, t, 1, 1, 8, t, 1e-5, s) == 1
+    assert native.ln_fwd_stats(t, t, t, 0, 1, 8, t, 1e-5, s) == 1
+    assert native.ln_fwd_stats(t, t, t, 1, 1, 8, 7, 1e-5, s) == 2
+    assert native.ln_fwd_stats(t, t, t, 1, 1, 8, t, -1.0, s) == 1
+    # the workspace's size: EWORKSPACE (3) one byte below what the shape needs, EINVAL at an address that is not aligned
+    need = binding.workspace_bytes(1, 4, 8, binding.F32)
+    args = lambda ws, size: (t, t, t, None, None, torch.zeros(8), t, t, t, t, None, 1, 4, 8, t, t, 1e-5, ws, size, s)
+    assert native.ln_bwd_pegn(*args(1 << 20, need - 1)) == 3
+    assert native.ln_bwd_pegn(*args((1 << 20) + 8, need)) == 1
+    assert native.ln_bwd_ex(*args(1 << 20, need)[:-1], 64, s) == 1          # unknown flag
+    assert native.reduce_deferred([t, None], 1, 4, 8, binding.F32, s) == 1
+    assert native.reduce_deferred([], 1, 4, 8, binding.F32, s) == 1
+
+
+def test_wrong_calls_raise(native):
+    t = torch.zeros(8)
+    with pytest.raises(TypeError, match="takes 9 arguments"):
+        native.ln_fwd_stats(t)
+    with pytest.raises(TypeError):
+        native.ln_fwd_stats(t, t, t, 1.5, 1, 8, t, 1e-5, _Stream())      # a float where a number of rows belongs
+    with pytest.raises(AttributeError):
+        native.ln_fwd_stats("x", t, t, 1, 1, 8, t, 1e-5, _Stream())
+    with pytest.raises(AttributeError):
+        native.ln_fwd_stats(t, t, t, 1, 1, 8, t, 1e-5, 3)                # no stream
+
+
+def test_a_subclass_is_asked_for_its_address(native):
+    class Sub(torch.Tensor):
+        def data_ptr(self):
+            return 0                                                       # a null pointer: refused by the library
+    x = torch.zeros(8).as_subclass(Sub)
+    assert native.ln_fwd_stats(x, torch.zeros(8), torch.zeros(8), 1, 1, 8, binding.F32, 1e-5, _Stream()) == 1
