@@ -16,7 +16,7 @@ MARSHAL = os.path.join(HERE, "_marshal.so")
 MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
 SOURCES = [os.path.join(CSRC, f) for f in ("lnpegn.hip", "lnpegn_rows_inst.hip", "linear_pegn.hip", "embedding_pegn.hip")]
 HEADERS = [os.path.join(CSRC, h) for h in ("lnpegn_device.h", "lnpegn_rows.h", "lnpegn_finalize.h", "lnpegn_tracker.h",
-                                           "lnpegn_launch.h")]
+                                           "lnpegn_launch.h", "linear_wide.h")]
 # translation units: (source, extra defines, object tag).  The row kernels are one source compiled four times.
 UNITS = [("lnpegn.hip", [], "abi"),
          ("lnpegn_rows_inst.hip", ["-DLNPEGN_INST_BF16=1", "-DLNPEGN_INST_SAVED=0"], "rows_bf16_recompute"),

@@ -544,6 +544,12 @@ __global__ __launch_bounds__(Cfg::kThreads) void linear_pegn_kernel(LinArgs a)
     linear_pegn_body<LinCfg<4, 2, 2, 2, kElem>, 4, 2, 2, 2, kElem, kRaggedX, kRaggedG>(a);
 }
 
+}  // namespace
+}  // namespace lnpegn
+#include "linear_wide.h"
+namespace lnpegn {
+namespace {
+
 // (ragged g beside aligned x: the rows of x are reached through 31-bit offsets)
 template <int kElem>
 hipError_t launch_linear(const LinArgs &a, bool ragged_x, bool ragged_g, hipStream_t st)
@@ -654,11 +660,15 @@ __global__ __launch_bounds__(1024) void linear_final_kernel(const float *part_s,
 struct LinPlan {
     bool mfma;             // matrix-core kernel
     bool ragged_x, ragged_g;   // rows of x, of g do not all start on 16-byte boundaries
+    bool wide;             // ... with the larger tile
+    int full;              // tiles of it that one workgroup finishes, whatever nsplit (of the others)
     int tiles_k, tiles_l, nsplit, b_per_split;
     int nparts;            // rows of the s parts
     int64_t nbig;          // entries of the ||w'||^2 parts
     size_t off_s, off_big, off_part, bytes;
 };
+constexpr int kCUs = 256;
+constexpr int kMaxSlots = 768;     // 192 KiB each
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -668,8 +678,8 @@ struct LinAlign {
     bool element;          // on multiples of an element, both
 };
 
-// Which kernel: the faster one by the estimates below, or the one that is asked for.
-enum LinKernel { kLinFaster, kLinMfma, kLinScalar };
+// Which kernel: the faster one by the estimates below, that without the larger tile, or the one that is asked for.
+enum LinKernel { kLinFaster, kLinNarrow, kLinMfma, kLinScalar };
 
 // max_split: most workgroups that may share an output tile's examples (each but the first costs workspace).
 LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, LinKernel which = kLinFaster, int max_split = kMaxSplit)
@@ -725,7 +735,7 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, LinKer
         const double position_us = ((tiles16 < 2 ? 0.065 : tiles16 < 16 ? 0.087 : 0.105) + 4e-6 * ((double)K + L) * (bf16 ? 2 : 4)) *
                                    (tiles16 > 2048 ? (double)tiles16 / 2048 : 1.0);
         const double scalar_us = 5.0 + B * (0.42 + 0.0002 * (double)tiles16 + position_us * T);
-        if (ragged && which == kLinFaster && scalar_us < mfma_us) p.mfma = false;
+        if (ragged && (which == kLinFaster || which == kLinNarrow) && scalar_us < mfma_us) p.mfma = false;
     }
     if (!p.mfma) {
         p.tiles_k = (K + 15) / 16;
@@ -735,10 +745,55 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, LinKer
         p.nparts = p.tiles_k * p.tiles_l;
         p.nbig = p.nparts;
     }
+    size_t slots = p.nsplit > 1 ? (size_t)p.nsplit * K * L * sizeof(float) : 0;
+    // The larger tile of bf16: whole rounds of 256 workgroups finish a tile each; the examples of the other tiles are split over
+    // workgroups.  Taken where it is the faster one by these estimates: the constants are those that fit 180 measured calls of
+    // the smaller tile and 141 of this one (T 64 to 4096, K and L 64 to 8192), within 10 % nine times in ten.  us, smaller / larger
+    // tile: B=16 T=2048 K=2048 L=8192 1047 / 933, L=2048 283 / 283, K=1280 L=5120 466 / 547; B=8 T=1024 K=768 L=50304 667 / 558,
+    // L=3072 58.5 / 54.9, L=2304 46.7 / 51.0, K=4096 L=4096 267 / 258; B=64 T=1024 K=768 L=3072 351 / 281; B=32 T=512 K=1536 L=6144
+    // 468 / 316; B=3 T=1000 K=1600 L=6400 112 / 71; B=9 T=4096 K=64 L=3840 155 / 82; B=16 T=512 K=1024 L=8192 143 / 159; B=64 T=128
+    // K=1024 L=4096 98 / 119.
+    if (p.mfma && !ragged && dt == LNPEGN_BF16 && which == kLinFaster &&
+        (int64_t)WideCfg::kStageT * (K > L ? K : L) * 2 <= (int64_t)kTrackedBytes) {
+        auto stages_of = [&](int each) { return (T + each - 1) / each; };
+        // rounds of n workgroups; the last one quicker
+        auto rounds = [](int64_t n, double least) {
+            return n == 0 ? 0.0 : (double)((n - 1) / kCUs) + least + (1.0 - least) * (double)((n - 1) % kCUs + 1) / kCUs;
+        };
+        const int64_t narrow = (int64_t)p.tiles_k * p.tiles_l * p.nsplit;
+        const bool edges = K % Cfg::kTileK != 0 || L % Cfg::kTileL != 0;       // (their loads are slower there)
+        const double narrow_us = 4.1 + rounds(narrow, 0.885) * (p.b_per_split * ((edges ? 1.167 : 0.947) * stages_of(Cfg::kStageT) + 0.37) + 7.1) +
+                                 (p.nsplit > 1 ? 2.1 + 0.044 * narrow : 0.0);
+        const int tk = (K + WideCfg::kTileK - 1) / WideCfg::kTileK, tl = (L + WideCfg::kTileL - 1) / WideCfg::kTileL;
+        const int64_t tiles = (int64_t)tk * tl, full = tiles / kCUs * kCUs, rest = tiles - full;
+        const double pair_us = 0.599 * stages_of(WideCfg::kStageT) + 1.03;
+        double us = 0.0;
+        int splits = 1, per = B;
+        for (int n = 1; n <= B && (n == 1 || rest * n <= kMaxSlots); ++n) {
+            const int each = (B + n - 1) / n, m = (B + each - 1) / each;
+            const double t = 6.3 + (double)(full / kCUs) * (B * pair_us + 11.9) + rounds(rest * m, 0.61) * (each * pair_us + 11.9) +
+                             (m > 1 ? 0.7 + 0.006 * rest * m : 0.0);
+            if (n > 1 && t >= us) continue;
+            us = t;
+            splits = m;
+            per = each;
+        }
+        if (us + 1.5 < 0.97 * narrow_us && per * stages_of(WideCfg::kStageT) >= 16) {
+            p.wide = true;
+            p.full = (int)full;
+            p.tiles_k = tk;
+            p.tiles_l = tl;
+            p.nsplit = splits;
+            p.b_per_split = per;
+            p.nparts = (int)tiles * WideCfg::kWaves;
+            p.nbig = full * WideCfg::kWaves + rest * WideCfg::kBlocks;
+            slots = splits > 1 ? (size_t)(rest * splits) * WideCfg::kPart * sizeof(float) : 0;
+        }
+    }
     p.off_s = 0;
     p.off_big = align256(p.off_s + (size_t)p.nparts * B * sizeof(float));
     p.off_part = align256(p.off_big + (size_t)p.nbig * sizeof(double));
-    p.bytes = p.off_part + (p.nsplit > 1 ? (size_t)p.nsplit * K * L * sizeof(float) : 0);
+    p.bytes = p.off_part + slots;
     return p;
 }
 
@@ -777,6 +832,8 @@ int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq,
     const uintptr_t px = reinterpret_cast<uintptr_t>(x), pg = reinterpret_cast<uintptr_t>(g), elem = dt == LNPEGN_BF16 ? 2 : 4;
     const LinAlign align{(px & 15u) == 0, (pg & 15u) == 0, ((px | pg) & (elem - 1)) == 0};
     LinPlan p = make_lin_plan(B, T, K, L, dt, align);
+    // The larger tile may ask for more workspace than the smaller one, which is taken where it is not given.
+    if (p.wide && workspace_bytes < p.bytes) p = make_lin_plan(B, T, K, L, dt, align, kLinNarrow);
     // Ragged rows run in less workspace too, down to what the scalar kernel asks for: without a split, or there.
     if (p.ragged_x || p.ragged_g) {
         if (workspace_bytes < p.bytes) p = make_lin_plan(B, T, K, L, dt, align, kLinMfma);
@@ -790,6 +847,21 @@ int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq,
     float *part_s = reinterpret_cast<float *>(ws + p.off_s);
     double *part_big = reinterpret_cast<double *>(ws + p.off_big);
     float *part_w = reinterpret_cast<float *>(ws + p.off_part);
+    if (p.wide) {
+        WideArgs a{};
+        a.x = static_cast<const char *>(x);
+        a.g = static_cast<const char *>(g);
+        a.w = w;
+        a.tile_s = part_s;
+        a.tile_big = part_big;
+        a.part = part_w;
+        a.B = B; a.T = T; a.K = K; a.L = L;
+        a.tiles_k = p.tiles_k; a.tiles = p.tiles_k * p.tiles_l;
+        a.full = p.full; a.splits = p.nsplit; a.per = p.b_per_split;
+        a.accumulate = accumulate;
+        if (launch(linear_wide_kernel, dim3(p.full + (a.tiles - p.full) * p.nsplit), dim3(64 * WideCfg::kWaves), 0, st, a) != hipSuccess) return LNPEGN_EHIP;
+        if (p.nsplit > 1 && launch(linear_wide_sum_kernel, dim3(a.tiles - p.full, WideCfg::kBlocks), dim3(256), 0, st, a) != hipSuccess) return LNPEGN_EHIP;
+    } else
     if (p.mfma) {
         LinArgs a{};
         a.x = static_cast<const char *>(x);
