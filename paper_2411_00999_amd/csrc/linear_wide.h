@@ -7,10 +7,10 @@
 // tile of 256 x 192 fetches 22 % less; 192 accumulators for the example and 192 for the running total leave room for no more,
 // at four waves with 512 registers each.  One wave to a SIMD has nobody to hide behind, so all that is not an MFMA goes out in
 // their shadow, placed by hand: the next fragments' reads, the next loads and the scalar work for those (all of it
-// between the blocks of MFMAs: B=16 T=2048 K=2048 L=8192 996 us, so 918).  A stage is 32 positions, 28 KiB, five deep; one
+// between the blocks of MFMAs: B=16 T=2048 K=2048 L=8192 996 us, in their shadow 918).  A stage is 32 positions, 28 KiB, five deep; one
 // barrier a stage.
-// Measured, smaller / larger tile: that shape 1047 / 933 us (1180 TFLOP/s; the library's plain GEMM 1060), B=8 T=1024
-// K=768 L=50304 667 / 558, B=64 T=1024 K=768 L=3072 351 / 281.
+// Measured, smaller / larger tile: that shape 1057 / 896 us (1228 TFLOP/s; the library's plain GEMM 1060), B=8 T=1024
+// K=768 L=50304 684 / 548, B=64 T=1024 K=768 L=3072 357 / 272.
 #pragma once
 
 namespace lnpegn {
@@ -77,17 +77,13 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
     // where a lane reads in a stage: see the transposing reads of the smaller tile.  Rows of g are 384 bytes: chunk ^ 4 on
     // every second pair of rows spreads four rows over all banks.
     const int s16 = lane & 15, grp = lane >> 4, rr = (grp >> 1) * 8 + (s16 >> 2);
-    uint32_t a_addr[C::kMI], b_addr[C::kNI];
+    // (for g 64 bytes further per fragment, with the swizzle's sign by parity: fragments 0 and 2, and 1)
+    const int low = (grp & 1) * 2 + ((s16 & 3) >> 1), flip = ((s16 >> 3) & 1) * (wn == 0 ? 64 : -64);
+    uint32_t a_at[C::kMI], b_at[2];                                // in the stage being read
 #pragma unroll
-    for (int i = 0; i < C::kMI; ++i) {
-        const int q = (wm * C::kMI + i) * 4 + (grp & 1) * 2 + ((s16 & 3) >> 1);
-        a_addr[i] = lds_base + rr * C::kXRow + ((q ^ ((s16 >> 2) << 2)) * 16) + (s16 & 1) * 8;
-    }
-#pragma unroll
-    for (int i = 0; i < C::kNI; ++i) {
-        const int q = (wn * C::kNI + i) * 4 + (grp & 1) * 2 + ((s16 & 3) >> 1);
-        b_addr[i] = lds_base + C::kXBytes + rr * C::kGRow + ((q ^ (((s16 >> 3) & 1) << 2)) * 16) + (s16 & 1) * 8;
-    }
+    for (int i = 0; i < C::kMI; ++i) a_at[i] = lds_base + rr * C::kXRow + (((wm * C::kMI + i) ^ (s16 >> 2)) * 4 + low) * 16 + (s16 & 1) * 8;
+    b_at[0] = lds_base + C::kXBytes + rr * C::kGRow + (wn * C::kNI * 4 + low) * 16 + (s16 & 1) * 8 + flip;
+    b_at[1] = b_at[0] - 2 * flip;
 
         const int k0 = tile % a.tiles_k * C::kTileK, l0 = tile / a.tiles_k * C::kTileL;
         const int nstages = (b_end - b_begin) * nst;
@@ -104,45 +100,53 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
             const int at = (wave * C::kGLoads + n) * 64 + lane, r = at / 24, c = (at - r * 24) ^ (((r >> 1) & 1) << 2);
             g_off[n] = l0 + c * 8 < a.L ? (uint32_t)(r * widthg + c * 16) : 0x80000000u;
         }
-        const char *x_next = a.x + ((int64_t)b_begin * a.T * a.K + k0) * 2, *g_next = a.g + ((int64_t)b_begin * a.T * a.L + l0) * 2;
-        int load_stage = 0, left = nstages, load_buf = 0;
-        auto rsrc_of = [](const char *p, uint32_t bytes) {
+        // A stage's loads go through two buffers, which end with its last row: base and size of the stage to load next, made
+        // ready in parts of a few scalar instructions.  (Bases are below 2^48: what is added to a buffer's first two words never
+        // reaches the stride.)
+        auto buffer_of = [](const char *p, uint32_t bytes) {
             const uint64_t at = reinterpret_cast<uint64_t>(p);
-            return u32x4_t{(uint32_t)at, (uint32_t)(at >> 32) & 0xffffu, bytes, 0x00020000u};
+            return u32x4_t{(uint32_t)at, (uint32_t)(at >> 32), bytes, 0x00020000u};
         };
-        // a stage's loads: where from and where to, then one after the other
-        u32x4_t x_rsrc, g_rsrc;
-        uint32_t load_to = 0;
         const uint32_t x_step = C::kStageT * widthx, x_rest = last_rows * widthx, g_step = C::kStageT * widthg, g_rest = last_rows * widthg;
-        auto prepare = [&](auto part_tag) {                        // in four parts of a few scalar instructions
+        const uint32_t x_first = nst > 1 ? x_step : x_rest, g_first = nst > 1 ? g_step : g_rest;
+        u32x4_t x_buf = buffer_of(a.x + ((int64_t)b_begin * a.T * a.K + k0) * 2, x_first - k0 * 2);
+        u32x4_t g_buf = buffer_of(a.g + ((int64_t)b_begin * a.T * a.L + l0) * 2, g_first - l0 * 2);
+        uint32_t x_bytes = x_first, g_bytes = g_first;             // of the stage that the buffers describe
+        int load_stage = 1, left = nstages - 1;                    // the one behind it
+        const uint32_t lds_x = lds_base + wave * (C::kXLoads * 1024), lds_end = lds_x + C::kBufs * C::kStageBytes;
+        uint32_t load_to = lds_x;
+        const uint32_t to_g = C::kXBytes - wave * ((C::kXLoads - C::kGLoads) * 1024);
+        auto on = [](u32x4_t &buf, uint32_t bytes) {
+            const uint64_t at = ((uint64_t)buf.y << 32 | buf.x) + bytes;
+            buf.x = (uint32_t)at;
+            buf.y = (uint32_t)(at >> 32);
+        };
+        bool last = false;
+        auto prepare = [&](auto part_tag) {
             constexpr int part = decltype(part_tag)::value;
-            const bool last = load_stage == nst - 1;
             if constexpr (part == 0) {
-                const uint32_t bytes = last ? x_rest : x_step;
-                x_rsrc = rsrc_of(x_next, left > 0 ? bytes - k0 * 2 : 0u);
-                x_next += bytes;
-            } else if constexpr (part == 1) {
-                const uint32_t bytes = last ? g_rest : g_step;
-                g_rsrc = rsrc_of(g_next, left > 0 ? bytes - l0 * 2 : 0u);
-                g_next += bytes;
-            } else if constexpr (part == 2) {
-                load_to = lds_base + load_buf * C::kStageBytes + wave * (C::kXLoads * 1024);
-                load_buf = load_buf == C::kBufs - 1 ? 0 : load_buf + 1;
-            } else {
-                --left;
+                last = load_stage >= nst - 1;                      // (nst 1: every stage is)
                 load_stage = last ? 0 : load_stage + 1;
+                on(x_buf, x_bytes);
+            } else if constexpr (part == 1) {
+                on(g_buf, g_bytes);
+                x_bytes = last ? x_rest : x_step;
+                g_bytes = last ? g_rest : g_step;
+            } else if constexpr (part == 2) {
+                x_buf.z = left > 0 ? x_bytes - k0 * 2 : 0u;
+                g_buf.z = left > 0 ? g_bytes - l0 * 2 : 0u;
+                --left;
+            } else {
+                load_to += C::kStageBytes;
+                load_to = load_to == lds_end ? lds_x : load_to;
             }
         };
         auto load = [&](auto n_tag) {
             constexpr int n = decltype(n_tag)::value;
-            if constexpr (n < C::kXLoads) load_to_lds_buffer(load_to + n * 1024, x_off[n], x_rsrc);
-            else load_to_lds_buffer(load_to + C::kXBytes - wave * ((C::kXLoads - C::kGLoads) * 1024) + (n - C::kXLoads) * 1024, g_off[n - C::kXLoads], g_rsrc);
+            if constexpr (n < C::kXLoads) load_to_lds_buffer(load_to + n * 1024, x_off[n], x_buf);
+            else load_to_lds_buffer(load_to + to_g + (n - C::kXLoads) * 1024, g_off[n - C::kXLoads], g_buf);
         };
         auto fetch = [&]() {
-            prepare(std::integral_constant<int, 0>{});
-            prepare(std::integral_constant<int, 1>{});
-            prepare(std::integral_constant<int, 2>{});
-            prepare(std::integral_constant<int, 3>{});
             load(std::integral_constant<int, 0>{});
             load(std::integral_constant<int, 1>{});
             load(std::integral_constant<int, 2>{});
@@ -150,6 +154,10 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
             load(std::integral_constant<int, 4>{});
             load(std::integral_constant<int, 5>{});
             load(std::integral_constant<int, 6>{});
+            prepare(std::integral_constant<int, 0>{});
+            prepare(std::integral_constant<int, 1>{});
+            prepare(std::integral_constant<int, 2>{});
+            prepare(std::integral_constant<int, 3>{});
         };
 
         f32x16_t acc[C::kMI][C::kNI];
@@ -162,21 +170,29 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) tot[mi][ni][i] = 0.f;
 
-        uint32_t base = 0;                                         // of the stage being read
-        // reads of one fragment (two transposing reads), kk: first or second 16 positions of the stage
-#define WIDE_READ(DST, ADDR, PITCH, KK)                                                                                   \
+        // reads of one fragment (two transposing reads), KK: first or second 16 positions of the stage
+#define WIDE_READ(DST, ADDR, FURTHER, PITCH, KK)                                                                          \
     asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"                              \
                  : "=&v"(DST[0]), "=&v"(DST[1])                                                                            \
-                 : "v"(ADDR), "n"((KK) * 16 * (PITCH)), "n"((KK) * 16 * (PITCH) + 4 * (PITCH))                              \
+                 : "v"(ADDR), "n"((KK) * 16 * (PITCH) + (FURTHER)), "n"((KK) * 16 * (PITCH) + 4 * (PITCH) + (FURTHER))       \
                  : "memory")
+        // ... and one direct load beside it (the reads keep its distance from the write of m0)
+#define WIDE_READ_AND_LOAD(DST, ADDR, FURTHER, PITCH, KK, TO, ON, VOFF, BUF)                                              \
+    asm volatile("s_add_u32 m0, %5, %6\n\tds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4\n\t"    \
+                 "buffer_load_dwordx4 %7, %8, 0 offen lds"                                                                  \
+                 : "=&v"(DST[0]), "=&v"(DST[1])                                                                            \
+                 : "v"(ADDR), "n"((KK) * 16 * (PITCH) + (FURTHER)), "n"((KK) * 16 * (PITCH) + 4 * (PITCH) + (FURTHER)), "s"(TO),  \
+                   "n"(ON), "v"(VOFF), "s"(BUF)                                                                             \
+                 : "memory", "scc")
 #define WIDE_KEEP(F)                                                                                                      \
     "+v"(F.a[0][0]), "+v"(F.a[0][1]), "+v"(F.a[1][0]), "+v"(F.a[1][1]), "+v"(F.a[2][0]), "+v"(F.a[2][1]), "+v"(F.a[3][0]), \
         "+v"(F.a[3][1]), "+v"(F.b[0][0]), "+v"(F.b[0][1]), "+v"(F.b[1][0]), "+v"(F.b[1][1]), "+v"(F.b[2][0]), "+v"(F.b[2][1])
         auto frag = [](const wide_u32x2_t (&v)[2]) { return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3)); };
-        // the MFMAs of one fragment set; in their shadow the reads of the next, and the next loads to go out: made ready in the
-        // first block of a stage, issued in the second (all at once between the blocks they took 300 cycles of a stage's
-        // 1200, with the matrix cores idle).
-        auto block = [&](WideFrags &f, WideFrags &next, auto kk_tag, auto first_tag, uint32_t from) {
+        uint32_t read_at = 0;                                      // of the stage being read, in the ring
+        // the MFMAs of one fragment set; in their shadow the reads of the next, and the next loads go out and are made ready.  A lone
+        // wave issues an instruction every four clocks, eight to an MFMA: a stage is 108 of them (242 with every address made
+        // where it is used: B=16 T=2048 K=2048 L=8192 918 us, so 896).
+        auto block = [&](WideFrags &f, WideFrags &next, auto kk_tag, auto first_tag) {
             constexpr int kk = decltype(kk_tag)::value;
             constexpr bool kFirst = decltype(first_tag)::value;    // of an example: on top of zeros
             asm volatile("s_waitcnt lgkmcnt(0)" : WIDE_KEEP(f) : : "memory");
@@ -187,17 +203,31 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
                 for (int ni = 0; ni < C::kNI; ++ni) {
                     acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(f.a[mi]), frag(f.b[ni]), kFirst ? f32x16_t{} : acc[mi][ni], 0, 0, 0);
                     const int at = mi * C::kNI + ni;
-                    if (at < 3) WIDE_READ(next.b[at], b_addr[at] + from, C::kGRow, kk);
-                    else if (at < 7) WIDE_READ(next.a[at - 3], a_addr[at - 3] + from, C::kXRow, kk);
-                    if constexpr (kk == 0) {
-                        if (at == 0) load(std::integral_constant<int, 0>{});
-                        if (at == 2) load(std::integral_constant<int, 1>{});
-                        if (at == 4) load(std::integral_constant<int, 2>{});
-                        if (at == 6) load(std::integral_constant<int, 3>{});
-                        if (at == 7) load(std::integral_constant<int, 4>{});
-                        if (at == 8) load(std::integral_constant<int, 5>{});
-                        if (at == 9) load(std::integral_constant<int, 6>{});
+                    if constexpr (kk == 1) {
+                        if (at == 0) WIDE_READ(next.b[0], b_at[0], 0, C::kGRow, kk);
+                        if (at == 1) WIDE_READ(next.b[1], b_at[1], 64, C::kGRow, kk);
+                        if (at == 2) WIDE_READ(next.b[2], b_at[0], 128, C::kGRow, kk);
+                        if (at == 3) WIDE_READ(next.a[0], a_at[0], 0, C::kXRow, kk);
+                        if (at == 4) WIDE_READ(next.a[1], a_at[1], 0, C::kXRow, kk);
+                        if (at == 5) WIDE_READ(next.a[2], a_at[2], 0, C::kXRow, kk);
+                        if (at == 6) WIDE_READ(next.a[3], a_at[3], 0, C::kXRow, kk);
+                        if (at == 7) {                             // the read addresses go on to the next stage's
+                            const uint32_t by = read_at == (C::kBufs - 1) * C::kStageBytes ? 0u - read_at : (uint32_t)C::kStageBytes;
+                            read_at += by;
+                            b_at[0] += by;
+                            b_at[1] += by;
+#pragma unroll
+                            for (int i = 0; i < C::kMI; ++i) a_at[i] += by;
+                        }
                     } else {
+                        const uint32_t load_g = load_to + to_g;
+                        if (at == 0) WIDE_READ_AND_LOAD(next.b[0], b_at[0], 0, C::kGRow, kk, load_to, 0, x_off[0], x_buf);
+                        if (at == 1) WIDE_READ_AND_LOAD(next.b[1], b_at[1], 64, C::kGRow, kk, load_to, 1024, x_off[1], x_buf);
+                        if (at == 2) WIDE_READ_AND_LOAD(next.b[2], b_at[0], 128, C::kGRow, kk, load_to, 2048, x_off[2], x_buf);
+                        if (at == 3) WIDE_READ_AND_LOAD(next.a[0], a_at[0], 0, C::kXRow, kk, load_to, 3072, x_off[3], x_buf);
+                        if (at == 4) WIDE_READ_AND_LOAD(next.a[1], a_at[1], 0, C::kXRow, kk, load_g, 0, g_off[0], g_buf);
+                        if (at == 5) WIDE_READ_AND_LOAD(next.a[2], a_at[2], 0, C::kXRow, kk, load_g, 1024, g_off[1], g_buf);
+                        if (at == 6) WIDE_READ_AND_LOAD(next.a[3], a_at[3], 0, C::kXRow, kk, load_g, 2048, g_off[2], g_buf);
                         if (at == 7) prepare(std::integral_constant<int, 0>{});
                         if (at == 8) prepare(std::integral_constant<int, 1>{});
                         if (at == 9) prepare(std::integral_constant<int, 2>{});
@@ -214,17 +244,17 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
         fetch();
         fetch();
         asm volatile("s_waitcnt vmcnt(21)\n\ts_barrier" ::: "memory");
+        WIDE_READ(f0.b[0], b_at[0], 0, C::kGRow, 0);
+        WIDE_READ(f0.b[1], b_at[1], 64, C::kGRow, 0);
+        WIDE_READ(f0.b[2], b_at[0], 128, C::kGRow, 0);
 #pragma unroll
-        for (int i = 0; i < C::kNI; ++i) WIDE_READ(f0.b[i], b_addr[i], C::kGRow, 0);
-#pragma unroll
-        for (int i = 0; i < C::kMI; ++i) WIDE_READ(f0.a[i], a_addr[i], C::kXRow, 0);
+        for (int i = 0; i < C::kMI; ++i) WIDE_READ(f0.a[i], a_at[i], 0, C::kXRow, 0);
         for (int b = b_begin; b < b_end; ++b) {
             auto stage = [&](auto first_tag) {
-                block(f0, f1, Second{}, first_tag, base);
+                block(f0, f1, Second{}, first_tag);
                 // the next stage has landed here, and everywhere; the buffer before this stage's has been read
                 asm volatile("s_waitcnt vmcnt(14)\n\ts_barrier" ::: "memory");
-                base = base == (C::kBufs - 1) * C::kStageBytes ? 0u : base + C::kStageBytes;
-                block(f1, f0, First{}, std::false_type{}, base);
+                block(f1, f0, First{}, std::false_type{});
 #pragma unroll
                 for (int t = 0; t < C::kMI * C::kNI; ++t) keep(acc[t / C::kNI][t % C::kNI]);
             };
