@@ -33,7 +33,7 @@ HBM_PEAK_GBS = 8000.0   # MI355X published HBM3E peak
 MEASURED_TRAFFIC_BYTES = {3: 407_060_000}
 # The same for one whole call of linear_pegn / embedding_pegn on the named shapes (all kernels of the call;
 # profiles/linear_pegn_gpt1p3b_up_rocprofv3.md, profiles/embedding_pegn_gpt1p3b_wte_rocprofv3.md).
-MEASURED_CALL_TRAFFIC_BYTES = {"gpt1p3b_up": 2_763_000_000, "gpt1p3b_wte": 598_700_000}
+MEASURED_CALL_TRAFFIC_BYTES = {"gpt1p3b_up": 2_360_000_000, "gpt1p3b_wte": 615_200_000}
 
 
 # ----------------------------------------------------------------------------- HIP events

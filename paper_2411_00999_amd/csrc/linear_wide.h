@@ -11,6 +11,8 @@
 // barrier a stage.
 // Measured, smaller / larger tile: that shape 1057 / 896 us (1228 TFLOP/s; the library's plain GEMM 1060), B=8 T=1024
 // K=768 L=50304 684 / 548, B=64 T=1024 K=768 L=3072 357 / 272.
+// What bounds it: the first shape takes 1.42-1.51 M clocks (smaller tile 1.98-2.11 M), 1.06 M of them MFMAs, at 1.4-1.7 GHz (1.5-1.9): the part
+// limits its power while the matrix cores toggle.
 #pragma once
 
 namespace lnpegn {
