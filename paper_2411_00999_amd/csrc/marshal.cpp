@@ -50,12 +50,11 @@ unsigned long long integer(PyObject *o)
     return v;
 }
 
-// None, a tensor (subclasses and other objects by their own data_ptr method), or an address.
+// None or a tensor (subclasses and other objects by their own data_ptr method; a number is no address).
 void *address(PyObject *o)
 {
     if (o == Py_None) return nullptr;
     if (THPVariable_CheckExact(o)) return THPVariable_Unpack(o).data_ptr();
-    if (PyLong_Check(o)) return reinterpret_cast<void *>((uintptr_t)integer(o));
     const Owned at(PyObject_CallMethodNoArgs(o, s_data_ptr));
     return reinterpret_cast<void *>((uintptr_t)integer(at.o));
 }

@@ -10,6 +10,15 @@ class _Stream:
     cuda_stream = 0
 
 
+class _At:
+    """Something at an address, which only its alignment is asked of here."""
+    def __init__(self, address):
+        self.address = address
+
+    def data_ptr(self):
+        return self.address
+
+
 @pytest.fixture(scope="module")
 def native():
     binding.load()
@@ -43,9 +52,9 @@ def test_arguments_arrive(native):
     # the workspace's size: EWORKSPACE (3) one byte below what the shape needs, EINVAL at an address that is not aligned
     need = binding.workspace_bytes(1, 4, 8, binding.F32)
     args = lambda ws, size: (t, t, t, None, None, torch.zeros(8), t, t, t, t, None, 1, 4, 8, t, t, 1e-5, ws, size, s)
-    assert native.ln_bwd_pegn(*args(1 << 20, need - 1)) == 3
-    assert native.ln_bwd_pegn(*args((1 << 20) + 8, need)) == 1
-    assert native.ln_bwd_ex(*args(1 << 20, need)[:-1], 64, s) == 1          # unknown flag
+    assert native.ln_bwd_pegn(*args(_At(1 << 20), need - 1)) == 3
+    assert native.ln_bwd_pegn(*args(_At((1 << 20) + 8), need)) == 1
+    assert native.ln_bwd_ex(*args(_At(1 << 20), need)[:-1], 64, s) == 1          # unknown flag
     assert native.reduce_deferred([t, None], 1, 4, 8, binding.F32, s) == 1
     assert native.reduce_deferred([], 1, 4, 8, binding.F32, s) == 1
 
@@ -58,6 +67,10 @@ def test_wrong_calls_raise(native):
         native.ln_fwd_stats(t, t, t, 1.5, 1, 8, t, 1e-5, _Stream())      # a float where a number of rows belongs
     with pytest.raises(AttributeError):
         native.ln_fwd_stats("x", t, t, 1, 1, 8, t, 1e-5, _Stream())
+    with pytest.raises(AttributeError):
+        native.ln_fwd_stats(1 << 20, t, t, 0, 1, 8, t, 1e-5, _Stream())  # a number is no tensor
+    with pytest.raises(AttributeError):
+        native.reduce_deferred([1 << 20], 0, 4, 8, binding.F32, _Stream())
     with pytest.raises(AttributeError):
         native.ln_fwd_stats(t, t, t, 1, 1, 8, t, 1e-5, 3)                # no stream
 
