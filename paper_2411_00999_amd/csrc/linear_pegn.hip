@@ -861,8 +861,7 @@ int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq,
         a.accumulate = accumulate;
         if (launch(linear_wide_kernel, dim3(p.full + (a.tiles - p.full) * p.nsplit), dim3(64 * WideCfg::kWaves), 0, st, a) != hipSuccess) return LNPEGN_EHIP;
         if (p.nsplit > 1 && launch(linear_wide_sum_kernel, dim3(a.tiles - p.full, WideCfg::kBlocks), dim3(256), 0, st, a) != hipSuccess) return LNPEGN_EHIP;
-    } else
-    if (p.mfma) {
+    } else if (p.mfma) {
         LinArgs a{};
         a.x = static_cast<const char *>(x);
         a.g = static_cast<const char *>(g);

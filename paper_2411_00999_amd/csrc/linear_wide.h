@@ -87,98 +87,98 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
     b_at[0] = lds_base + C::kXBytes + rr * C::kGRow + (wn * C::kNI * 4 + low) * 16 + (s16 & 1) * 8 + flip;
     b_at[1] = b_at[0] - 2 * flip;
 
-        const int k0 = tile % a.tiles_k * C::kTileK, l0 = tile / a.tiles_k * C::kTileL;
-        const int nstages = (b_end - b_begin) * nst;
+    const int k0 = tile % a.tiles_k * C::kTileK, l0 = tile / a.tiles_k * C::kTileL;
+    const int nstages = (b_end - b_begin) * nst;
 
-        // ---- loading
-        uint32_t x_off[C::kXLoads], g_off[C::kGLoads];
+    // ---- loading
+    uint32_t x_off[C::kXLoads], g_off[C::kGLoads];
 #pragma unroll
-        for (int n = 0; n < C::kXLoads; ++n) {
-            const int r = (wave * C::kXLoads + n) * 2 + (lane >> 5), c = (lane & 31) ^ ((r & 3) << 2);
-            x_off[n] = k0 + c * 8 < a.K ? (uint32_t)(r * widthx + c * 16) : 0x80000000u;
+    for (int n = 0; n < C::kXLoads; ++n) {
+        const int r = (wave * C::kXLoads + n) * 2 + (lane >> 5), c = (lane & 31) ^ ((r & 3) << 2);
+        x_off[n] = k0 + c * 8 < a.K ? (uint32_t)(r * widthx + c * 16) : 0x80000000u;
+    }
+#pragma unroll
+    for (int n = 0; n < C::kGLoads; ++n) {
+        const int at = (wave * C::kGLoads + n) * 64 + lane, r = at / 24, c = (at - r * 24) ^ (((r >> 1) & 1) << 2);
+        g_off[n] = l0 + c * 8 < a.L ? (uint32_t)(r * widthg + c * 16) : 0x80000000u;
+    }
+    // A stage's loads go through two buffers, which end with its last row: base and size of the stage to load next, made
+    // ready in parts of a few scalar instructions.  (Bases are below 2^48: what is added to a buffer's first two words never
+    // reaches the stride.)
+    auto buffer_of = [](const char *p, uint32_t bytes) {
+        const uint64_t at = reinterpret_cast<uint64_t>(p);
+        return u32x4_t{(uint32_t)at, (uint32_t)(at >> 32), bytes, 0x00020000u};
+    };
+    const uint32_t x_step = C::kStageT * widthx, x_rest = last_rows * widthx, g_step = C::kStageT * widthg, g_rest = last_rows * widthg;
+    const uint32_t x_first = nst > 1 ? x_step : x_rest, g_first = nst > 1 ? g_step : g_rest;
+    u32x4_t x_buf = buffer_of(a.x + ((int64_t)b_begin * a.T * a.K + k0) * 2, x_first - k0 * 2);
+    u32x4_t g_buf = buffer_of(a.g + ((int64_t)b_begin * a.T * a.L + l0) * 2, g_first - l0 * 2);
+    uint32_t x_bytes = x_first, g_bytes = g_first;             // of the stage that the buffers describe
+    int load_stage = 1, left = nstages - 1;                    // the one behind it
+    const uint32_t lds_x = lds_base + wave * (C::kXLoads * 1024), lds_end = lds_x + C::kBufs * C::kStageBytes;
+    uint32_t load_to = lds_x;
+    const uint32_t to_g = C::kXBytes - wave * ((C::kXLoads - C::kGLoads) * 1024);
+    auto on = [](u32x4_t &buf, uint32_t bytes) {
+        const uint64_t at = ((uint64_t)buf.y << 32 | buf.x) + bytes;
+        buf.x = (uint32_t)at;
+        buf.y = (uint32_t)(at >> 32);
+    };
+    bool last = false;
+    auto prepare = [&](auto part_tag) {
+        constexpr int part = decltype(part_tag)::value;
+        if constexpr (part == 0) {
+            last = load_stage >= nst - 1;                      // (nst 1: every stage is)
+            load_stage = last ? 0 : load_stage + 1;
+            on(x_buf, x_bytes);
+        } else if constexpr (part == 1) {
+            on(g_buf, g_bytes);
+            x_bytes = last ? x_rest : x_step;
+            g_bytes = last ? g_rest : g_step;
+        } else if constexpr (part == 2) {
+            x_buf.z = left > 0 ? x_bytes - k0 * 2 : 0u;
+            g_buf.z = left > 0 ? g_bytes - l0 * 2 : 0u;
+            --left;
+        } else {
+            load_to += C::kStageBytes;
+            load_to = load_to == lds_end ? lds_x : load_to;
         }
-#pragma unroll
-        for (int n = 0; n < C::kGLoads; ++n) {
-            const int at = (wave * C::kGLoads + n) * 64 + lane, r = at / 24, c = (at - r * 24) ^ (((r >> 1) & 1) << 2);
-            g_off[n] = l0 + c * 8 < a.L ? (uint32_t)(r * widthg + c * 16) : 0x80000000u;
-        }
-        // A stage's loads go through two buffers, which end with its last row: base and size of the stage to load next, made
-        // ready in parts of a few scalar instructions.  (Bases are below 2^48: what is added to a buffer's first two words never
-        // reaches the stride.)
-        auto buffer_of = [](const char *p, uint32_t bytes) {
-            const uint64_t at = reinterpret_cast<uint64_t>(p);
-            return u32x4_t{(uint32_t)at, (uint32_t)(at >> 32), bytes, 0x00020000u};
-        };
-        const uint32_t x_step = C::kStageT * widthx, x_rest = last_rows * widthx, g_step = C::kStageT * widthg, g_rest = last_rows * widthg;
-        const uint32_t x_first = nst > 1 ? x_step : x_rest, g_first = nst > 1 ? g_step : g_rest;
-        u32x4_t x_buf = buffer_of(a.x + ((int64_t)b_begin * a.T * a.K + k0) * 2, x_first - k0 * 2);
-        u32x4_t g_buf = buffer_of(a.g + ((int64_t)b_begin * a.T * a.L + l0) * 2, g_first - l0 * 2);
-        uint32_t x_bytes = x_first, g_bytes = g_first;             // of the stage that the buffers describe
-        int load_stage = 1, left = nstages - 1;                    // the one behind it
-        const uint32_t lds_x = lds_base + wave * (C::kXLoads * 1024), lds_end = lds_x + C::kBufs * C::kStageBytes;
-        uint32_t load_to = lds_x;
-        const uint32_t to_g = C::kXBytes - wave * ((C::kXLoads - C::kGLoads) * 1024);
-        auto on = [](u32x4_t &buf, uint32_t bytes) {
-            const uint64_t at = ((uint64_t)buf.y << 32 | buf.x) + bytes;
-            buf.x = (uint32_t)at;
-            buf.y = (uint32_t)(at >> 32);
-        };
-        bool last = false;
-        auto prepare = [&](auto part_tag) {
-            constexpr int part = decltype(part_tag)::value;
-            if constexpr (part == 0) {
-                last = load_stage >= nst - 1;                      // (nst 1: every stage is)
-                load_stage = last ? 0 : load_stage + 1;
-                on(x_buf, x_bytes);
-            } else if constexpr (part == 1) {
-                on(g_buf, g_bytes);
-                x_bytes = last ? x_rest : x_step;
-                g_bytes = last ? g_rest : g_step;
-            } else if constexpr (part == 2) {
-                x_buf.z = left > 0 ? x_bytes - k0 * 2 : 0u;
-                g_buf.z = left > 0 ? g_bytes - l0 * 2 : 0u;
-                --left;
-            } else {
-                load_to += C::kStageBytes;
-                load_to = load_to == lds_end ? lds_x : load_to;
-            }
-        };
-        auto load = [&](auto n_tag) {
-            constexpr int n = decltype(n_tag)::value;
-            if constexpr (n < C::kXLoads) load_to_lds_buffer(load_to + n * 1024, x_off[n], x_buf);
-            else load_to_lds_buffer(load_to + to_g + (n - C::kXLoads) * 1024, g_off[n - C::kXLoads], g_buf);
-        };
-        auto fetch = [&]() {
-            load(std::integral_constant<int, 0>{});
-            load(std::integral_constant<int, 1>{});
-            load(std::integral_constant<int, 2>{});
-            load(std::integral_constant<int, 3>{});
-            load(std::integral_constant<int, 4>{});
-            load(std::integral_constant<int, 5>{});
-            load(std::integral_constant<int, 6>{});
-            prepare(std::integral_constant<int, 0>{});
-            prepare(std::integral_constant<int, 1>{});
-            prepare(std::integral_constant<int, 2>{});
-            prepare(std::integral_constant<int, 3>{});
-        };
+    };
+    auto load = [&](auto n_tag) {
+        constexpr int n = decltype(n_tag)::value;
+        if constexpr (n < C::kXLoads) load_to_lds_buffer(load_to + n * 1024, x_off[n], x_buf);
+        else load_to_lds_buffer(load_to + to_g + (n - C::kXLoads) * 1024, g_off[n - C::kXLoads], g_buf);
+    };
+    auto fetch = [&]() {
+        load(std::integral_constant<int, 0>{});
+        load(std::integral_constant<int, 1>{});
+        load(std::integral_constant<int, 2>{});
+        load(std::integral_constant<int, 3>{});
+        load(std::integral_constant<int, 4>{});
+        load(std::integral_constant<int, 5>{});
+        load(std::integral_constant<int, 6>{});
+        prepare(std::integral_constant<int, 0>{});
+        prepare(std::integral_constant<int, 1>{});
+        prepare(std::integral_constant<int, 2>{});
+        prepare(std::integral_constant<int, 3>{});
+    };
 
-        f32x16_t acc[C::kMI][C::kNI];
-        float tot[C::kMI][C::kNI][16];
-        auto keep = [](f32x16_t &v) { asm volatile("" : "+a"(v)); };
+    f32x16_t acc[C::kMI][C::kNI];
+    float tot[C::kMI][C::kNI][16];
+    auto keep = [](f32x16_t &v) { asm volatile("" : "+a"(v)); };
 #pragma unroll
-        for (int mi = 0; mi < C::kMI; ++mi)
+    for (int mi = 0; mi < C::kMI; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < C::kNI; ++ni)
+        for (int ni = 0; ni < C::kNI; ++ni)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) tot[mi][ni][i] = 0.f;
+            for (int i = 0; i < 16; ++i) tot[mi][ni][i] = 0.f;
 
-        // reads of one fragment (two transposing reads), KK: first or second 16 positions of the stage
+    // reads of one fragment (two transposing reads), KK: first or second 16 positions of the stage
 #define WIDE_READ(DST, ADDR, FURTHER, PITCH, KK)                                                                          \
     asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"                              \
                  : "=&v"(DST[0]), "=&v"(DST[1])                                                                            \
                  : "v"(ADDR), "n"((KK) * 16 * (PITCH) + (FURTHER)), "n"((KK) * 16 * (PITCH) + 4 * (PITCH) + (FURTHER))       \
                  : "memory")
-        // ... and one direct load beside it (the reads keep its distance from the write of m0)
+    // ... and one direct load beside it (the reads keep its distance from the write of m0)
 #define WIDE_READ_AND_LOAD(DST, ADDR, FURTHER, PITCH, KK, TO, ON, VOFF, BUF)                                              \
     asm volatile("s_add_u32 m0, %5, %6\n\tds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4\n\t"    \
                  "buffer_load_dwordx4 %7, %8, 0 offen lds"                                                                  \
@@ -189,146 +189,147 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
 #define WIDE_KEEP(F)                                                                                                      \
     "+v"(F.a[0][0]), "+v"(F.a[0][1]), "+v"(F.a[1][0]), "+v"(F.a[1][1]), "+v"(F.a[2][0]), "+v"(F.a[2][1]), "+v"(F.a[3][0]), \
         "+v"(F.a[3][1]), "+v"(F.b[0][0]), "+v"(F.b[0][1]), "+v"(F.b[1][0]), "+v"(F.b[1][1]), "+v"(F.b[2][0]), "+v"(F.b[2][1])
-        auto frag = [](const wide_u32x2_t (&v)[2]) { return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3)); };
-        uint32_t read_at = 0;                                      // of the stage being read, in the ring
-        // the MFMAs of one fragment set; in their shadow the reads of the next, and the next loads go out and are made ready.  A lone
-        // wave issues an instruction every four clocks, eight to an MFMA: a stage is 108 of them (242 with every address made
-        // where it is used: B=16 T=2048 K=2048 L=8192 918 us, so 896).
-        auto block = [&](WideFrags &f, WideFrags &next, auto kk_tag, auto first_tag) {
-            constexpr int kk = decltype(kk_tag)::value;
-            constexpr bool kFirst = decltype(first_tag)::value;    // of an example: on top of zeros
-            asm volatile("s_waitcnt lgkmcnt(0)" : WIDE_KEEP(f) : : "memory");
-            __builtin_amdgcn_sched_barrier(0);
+    auto frag = [](const wide_u32x2_t (&v)[2]) { return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3)); };
+    uint32_t read_at = 0;                                      // of the stage being read, in the ring
+    // the MFMAs of one fragment set; in their shadow the reads of the next, and the next loads go out and are made ready.  A lone
+    // wave issues an instruction every four clocks, eight to an MFMA: a stage is 108 of them (242 with every address made
+    // where it is used: B=16 T=2048 K=2048 L=8192 918 us, so 896).
+    auto block = [&](WideFrags &f, WideFrags &next, auto kk_tag, auto first_tag) {
+        constexpr int kk = decltype(kk_tag)::value;
+        constexpr bool kFirst = decltype(first_tag)::value;    // of an example: on top of zeros
+        asm volatile("s_waitcnt lgkmcnt(0)" : WIDE_KEEP(f) : : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int mi = 0; mi < C::kMI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < C::kNI; ++ni) {
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(f.a[mi]), frag(f.b[ni]), kFirst ? f32x16_t{} : acc[mi][ni], 0, 0, 0);
+                const int at = mi * C::kNI + ni;
+                if constexpr (kk == 1) {
+                    if (at == 0) WIDE_READ(next.b[0], b_at[0], 0, C::kGRow, kk);
+                    if (at == 1) WIDE_READ(next.b[1], b_at[1], 64, C::kGRow, kk);
+                    if (at == 2) WIDE_READ(next.b[2], b_at[0], 128, C::kGRow, kk);
+                    if (at == 3) WIDE_READ(next.a[0], a_at[0], 0, C::kXRow, kk);
+                    if (at == 4) WIDE_READ(next.a[1], a_at[1], 0, C::kXRow, kk);
+                    if (at == 5) WIDE_READ(next.a[2], a_at[2], 0, C::kXRow, kk);
+                    if (at == 6) WIDE_READ(next.a[3], a_at[3], 0, C::kXRow, kk);
+                    if (at == 7) {                             // the read addresses go on to the next stage's
+                        const uint32_t by = read_at == (C::kBufs - 1) * C::kStageBytes ? 0u - read_at : (uint32_t)C::kStageBytes;
+                        read_at += by;
+                        b_at[0] += by;
+                        b_at[1] += by;
+#pragma unroll
+                        for (int i = 0; i < C::kMI; ++i) a_at[i] += by;
+                    }
+                } else {
+                    const uint32_t load_g = load_to + to_g;
+                    if (at == 0) WIDE_READ_AND_LOAD(next.b[0], b_at[0], 0, C::kGRow, kk, load_to, 0, x_off[0], x_buf);
+                    if (at == 1) WIDE_READ_AND_LOAD(next.b[1], b_at[1], 64, C::kGRow, kk, load_to, 1024, x_off[1], x_buf);
+                    if (at == 2) WIDE_READ_AND_LOAD(next.b[2], b_at[0], 128, C::kGRow, kk, load_to, 2048, x_off[2], x_buf);
+                    if (at == 3) WIDE_READ_AND_LOAD(next.a[0], a_at[0], 0, C::kXRow, kk, load_to, 3072, x_off[3], x_buf);
+                    if (at == 4) WIDE_READ_AND_LOAD(next.a[1], a_at[1], 0, C::kXRow, kk, load_g, 0, g_off[0], g_buf);
+                    if (at == 5) WIDE_READ_AND_LOAD(next.a[2], a_at[2], 0, C::kXRow, kk, load_g, 1024, g_off[1], g_buf);
+                    if (at == 6) WIDE_READ_AND_LOAD(next.a[3], a_at[3], 0, C::kXRow, kk, load_g, 2048, g_off[2], g_buf);
+                    if (at == 7) prepare(std::integral_constant<int, 0>{});
+                    if (at == 8) prepare(std::integral_constant<int, 1>{});
+                    if (at == 9) prepare(std::integral_constant<int, 2>{});
+                    if (at == 10) prepare(std::integral_constant<int, 3>{});
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    using First = std::integral_constant<int, 0>;
+    using Second = std::integral_constant<int, 1>;
+    WideFrags f0, f1;
+    fetch();
+    fetch();
+    fetch();
+    fetch();
+    asm volatile("s_waitcnt vmcnt(21)\n\ts_barrier" ::: "memory");
+    WIDE_READ(f0.b[0], b_at[0], 0, C::kGRow, 0);
+    WIDE_READ(f0.b[1], b_at[1], 64, C::kGRow, 0);
+    WIDE_READ(f0.b[2], b_at[0], 128, C::kGRow, 0);
+#pragma unroll
+    for (int i = 0; i < C::kMI; ++i) WIDE_READ(f0.a[i], a_at[i], 0, C::kXRow, 0);
+    for (int b = b_begin; b < b_end; ++b) {
+        auto stage = [&](auto first_tag) {
+            block(f0, f1, Second{}, first_tag);
+            // the next stage has landed here, and everywhere; the buffer before this stage's has been read
+            asm volatile("s_waitcnt vmcnt(14)\n\ts_barrier" ::: "memory");
+            block(f1, f0, First{}, std::false_type{});
+#pragma unroll
+            for (int t = 0; t < C::kMI * C::kNI; ++t) keep(acc[t / C::kNI][t % C::kNI]);
+        };
+        stage(std::true_type{});
+        for (int st = 1; st < nst; ++st) stage(std::false_type{});
+        // example boundary: the wave's part of the squared norm, and the tile into the total.  A tile at a time: all 384
+        // accumulators are never in vector registers together (the empty statements say which file a value lives in:
+        // the example's among the accumulation registers, the total's not).
+        float ssq[C::kMI];
+#pragma unroll
+        for (int mi = 0; mi < C::kMI; ++mi) {
+            ssq[mi] = 0.f;
+#pragma unroll
+            for (int ni = 0; ni < C::kNI; ++ni) {
+                keep(acc[mi][ni]);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float v = acc[mi][ni][i];
+                    ssq[mi] = fmaf(v, v, ssq[mi]);
+                    tot[mi][ni][i] += v;
+                    asm volatile("" : "+v"(tot[mi][ni][i]));       // here, not after the branch below
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const float sum = wave_sum((ssq[0] + ssq[1]) + (ssq[2] + ssq[3]));
+        if (lane == 0) a.tile_s[((int64_t)b * a.tiles + tile) * C::kWaves + wave] = sum;
+    }
+    // no load may reach LDS after the workgroup has left it, no read be under way when its registers are used again
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : WIDE_KEEP(f0) : : "memory");
+
+    // ---- write the total
+    if (direct) {
+        double bsq = 0.0;
+        auto write = [&](auto all_tag) {
+            constexpr bool kAll = decltype(all_tag)::value;    // all outputs lie in the matrix, and nothing is added to
 #pragma unroll
             for (int mi = 0; mi < C::kMI; ++mi)
 #pragma unroll
                 for (int ni = 0; ni < C::kNI; ++ni) {
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(f.a[mi]), frag(f.b[ni]), kFirst ? f32x16_t{} : acc[mi][ni], 0, 0, 0);
-                    const int at = mi * C::kNI + ni;
-                    if constexpr (kk == 1) {
-                        if (at == 0) WIDE_READ(next.b[0], b_at[0], 0, C::kGRow, kk);
-                        if (at == 1) WIDE_READ(next.b[1], b_at[1], 64, C::kGRow, kk);
-                        if (at == 2) WIDE_READ(next.b[2], b_at[0], 128, C::kGRow, kk);
-                        if (at == 3) WIDE_READ(next.a[0], a_at[0], 0, C::kXRow, kk);
-                        if (at == 4) WIDE_READ(next.a[1], a_at[1], 0, C::kXRow, kk);
-                        if (at == 5) WIDE_READ(next.a[2], a_at[2], 0, C::kXRow, kk);
-                        if (at == 6) WIDE_READ(next.a[3], a_at[3], 0, C::kXRow, kk);
-                        if (at == 7) {                             // the read addresses go on to the next stage's
-                            const uint32_t by = read_at == (C::kBufs - 1) * C::kStageBytes ? 0u - read_at : (uint32_t)C::kStageBytes;
-                            read_at += by;
-                            b_at[0] += by;
-                            b_at[1] += by;
-#pragma unroll
-                            for (int i = 0; i < C::kMI; ++i) a_at[i] += by;
-                        }
-                    } else {
-                        const uint32_t load_g = load_to + to_g;
-                        if (at == 0) WIDE_READ_AND_LOAD(next.b[0], b_at[0], 0, C::kGRow, kk, load_to, 0, x_off[0], x_buf);
-                        if (at == 1) WIDE_READ_AND_LOAD(next.b[1], b_at[1], 64, C::kGRow, kk, load_to, 1024, x_off[1], x_buf);
-                        if (at == 2) WIDE_READ_AND_LOAD(next.b[2], b_at[0], 128, C::kGRow, kk, load_to, 2048, x_off[2], x_buf);
-                        if (at == 3) WIDE_READ_AND_LOAD(next.a[0], a_at[0], 0, C::kXRow, kk, load_to, 3072, x_off[3], x_buf);
-                        if (at == 4) WIDE_READ_AND_LOAD(next.a[1], a_at[1], 0, C::kXRow, kk, load_g, 0, g_off[0], g_buf);
-                        if (at == 5) WIDE_READ_AND_LOAD(next.a[2], a_at[2], 0, C::kXRow, kk, load_g, 1024, g_off[1], g_buf);
-                        if (at == 6) WIDE_READ_AND_LOAD(next.a[3], a_at[3], 0, C::kXRow, kk, load_g, 2048, g_off[2], g_buf);
-                        if (at == 7) prepare(std::integral_constant<int, 0>{});
-                        if (at == 8) prepare(std::integral_constant<int, 1>{});
-                        if (at == 9) prepare(std::integral_constant<int, 2>{});
-                        if (at == 10) prepare(std::integral_constant<int, 3>{});
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-        };
-        using First = std::integral_constant<int, 0>;
-        using Second = std::integral_constant<int, 1>;
-        WideFrags f0, f1;
-        fetch();
-        fetch();
-        fetch();
-        fetch();
-        asm volatile("s_waitcnt vmcnt(21)\n\ts_barrier" ::: "memory");
-        WIDE_READ(f0.b[0], b_at[0], 0, C::kGRow, 0);
-        WIDE_READ(f0.b[1], b_at[1], 64, C::kGRow, 0);
-        WIDE_READ(f0.b[2], b_at[0], 128, C::kGRow, 0);
-#pragma unroll
-        for (int i = 0; i < C::kMI; ++i) WIDE_READ(f0.a[i], a_at[i], 0, C::kXRow, 0);
-        for (int b = b_begin; b < b_end; ++b) {
-            auto stage = [&](auto first_tag) {
-                block(f0, f1, Second{}, first_tag);
-                // the next stage has landed here, and everywhere; the buffer before this stage's has been read
-                asm volatile("s_waitcnt vmcnt(14)\n\ts_barrier" ::: "memory");
-                block(f1, f0, First{}, std::false_type{});
-#pragma unroll
-                for (int t = 0; t < C::kMI * C::kNI; ++t) keep(acc[t / C::kNI][t % C::kNI]);
-            };
-            stage(std::true_type{});
-            for (int st = 1; st < nst; ++st) stage(std::false_type{});
-            // example boundary: the wave's part of the squared norm, and the tile into the total.  A tile at a time: all 384
-            // accumulators are never in vector registers together (the empty statements say which file a value lives in:
-            // the example's and the last third of the total's among the accumulation registers).
-            float ssq[C::kMI];
-#pragma unroll
-            for (int mi = 0; mi < C::kMI; ++mi) {
-                ssq[mi] = 0.f;
-#pragma unroll
-                for (int ni = 0; ni < C::kNI; ++ni) {
-                    keep(acc[mi][ni]);
+                    const int l = l0 + (wn * C::kNI + ni) * 32 + (lane & 31);
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const float v = acc[mi][ni][i];
-                        ssq[mi] = fmaf(v, v, ssq[mi]);
-                        tot[mi][ni][i] += v;
-                        asm volatile("" : "+v"(tot[mi][ni][i]));       // here, not after the branch below
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            const float sum = wave_sum((ssq[0] + ssq[1]) + (ssq[2] + ssq[3]));
-            if (lane == 0) a.tile_s[((int64_t)b * a.tiles + tile) * C::kWaves + wave] = sum;
-        }
-        // no load may reach LDS after the workgroup has left it, no read be under way when its registers are used again
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : WIDE_KEEP(f0) : : "memory");
-
-        // ---- write the total
-        if (direct) {
-            double bsq = 0.0;
-            auto write = [&](auto all_tag) {
-                constexpr bool kAll = decltype(all_tag)::value;    // all outputs lie in the matrix, and nothing is added to
-#pragma unroll
-                for (int mi = 0; mi < C::kMI; ++mi)
-#pragma unroll
-                    for (int ni = 0; ni < C::kNI; ++ni) {
-                        const int l = l0 + (wn * C::kNI + ni) * 32 + (lane & 31);
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            const int k = k0 + (wm * C::kMI + mi) * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-                            if (kAll || (k < a.K && l < a.L)) {
-                                float *p = a.w + (int64_t)k * a.L + l;
-                                float v = tot[mi][ni][i];
-                                if (!kAll && a.accumulate) v += *p;
-                                *p = v;
-                                bsq += (double)v * (double)v;
-                            }
+                        const int k = k0 + (wm * C::kMI + mi) * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
+                        if (kAll || (k < a.K && l < a.L)) {
+                            float *p = a.w + (int64_t)k * a.L + l;
+                            float v = tot[mi][ni][i];
+                            if (!kAll && a.accumulate) v += *p;
+                            *p = v;
+                            bsq += (double)v * (double)v;
                         }
                     }
-            };
-            if (k0 + C::kTileK <= a.K && l0 + C::kTileL <= a.L && !a.accumulate) write(std::true_type{});
-            else write(std::false_type{});
-            bsq = wave_sum_f64(bsq);
-            if (tile < a.full) {
-                if (lane == 0) a.tile_big[tile * C::kWaves + wave] = bsq;
-            } else if (lane < C::kMI * C::kNI) {
-                a.tile_big[a.full * C::kWaves + (tile - a.full) * C::kBlocks + wave * (C::kMI * C::kNI) + lane] = lane == 0 ? bsq : 0.0;
-            }
-        } else {
-            float *slot = a.part + (int64_t)at * C::kPart + wave * (C::kPart / C::kWaves) + lane;
-#pragma unroll
-            for (int mi = 0; mi < C::kMI; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < C::kNI; ++ni)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) slot[((mi * C::kNI + ni) * 16 + i) * 64] = tot[mi][ni][i];
+                }
+        };
+        if (k0 + C::kTileK <= a.K && l0 + C::kTileL <= a.L && !a.accumulate) write(std::true_type{});
+        else write(std::false_type{});
+        bsq = wave_sum_f64(bsq);
+        if (tile < a.full) {
+            if (lane == 0) a.tile_big[tile * C::kWaves + wave] = bsq;
+        } else if (lane < C::kMI * C::kNI) {
+            a.tile_big[a.full * C::kWaves + (tile - a.full) * C::kBlocks + wave * (C::kMI * C::kNI) + lane] = lane == 0 ? bsq : 0.0;
         }
+    } else {
+        float *slot = a.part + (int64_t)at * C::kPart + wave * (C::kPart / C::kWaves) + lane;
+#pragma unroll
+        for (int mi = 0; mi < C::kMI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < C::kNI; ++ni)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) slot[((mi * C::kNI + ni) * 16 + i) * 64] = tot[mi][ni][i];
+    }
 #undef WIDE_READ
+#undef WIDE_READ_AND_LOAD
 #undef WIDE_KEEP
 }
 
