@@ -477,11 +477,19 @@ hipError_t launch_fwd_vectors(FwdArgs a, hipStream_t s)
         const int vpt = ceil_div(a.nvec, 64);
         const int64_t want = (N + 3) / 4;
         const dim3 grid((unsigned)(want < 4096 ? want : 4096)), block(256);
+        // bf16 rows ahead as soon as a wave has more than one.  us, without / with: D=768 N=16400 12.8 / 11.7, N=32768 20.5 / 19.0, D=1024
+        // 24.8 / 23.7, D=256 N=65536 18.6 / 17.7; but N=8192 (one row a wave) 7.7 / 7.8, ragged rows (D=1001 N=32768) 26.3 / 27.7,
+        // fp32 D=640 N=8192 9.3 / 9.8, D=512 N=32768 23.6 / 23.6.
+        if constexpr (E == 8 && kWriteY && !kRagged) {
+            if (N > 4 * 4096)
+                return vpt == 1 ? launch(ln_fwd_kernel<T, 1, false, true, false, true>, grid, block, 0, s, a)
+                                : launch(ln_fwd_kernel<T, 2, false, true, false, true>, grid, block, 0, s, a);
+        }
         switch (vpt) {
-            case 1: return launch(ln_fwd_kernel<T, 1, false, kWriteY, kRagged>, grid, block, 0, s, a);
-            case 2: return launch(ln_fwd_kernel<T, 2, false, kWriteY, kRagged>, grid, block, 0, s, a);
-            case 3: return launch(ln_fwd_kernel<T, 3, false, kWriteY, kRagged>, grid, block, 0, s, a);
-            case 4: return launch(ln_fwd_kernel<T, 4, false, kWriteY, kRagged>, grid, block, 0, s, a);
+            case 1: return launch(ln_fwd_kernel<T, 1, false, kWriteY, kRagged, false>, grid, block, 0, s, a);
+            case 2: return launch(ln_fwd_kernel<T, 2, false, kWriteY, kRagged, false>, grid, block, 0, s, a);
+            case 3: return launch(ln_fwd_kernel<T, 3, false, kWriteY, kRagged, false>, grid, block, 0, s, a);
+            case 4: return launch(ln_fwd_kernel<T, 4, false, kWriteY, kRagged, false>, grid, block, 0, s, a);
             default: return hipErrorInvalidValue;
         }
     } else {
@@ -491,11 +499,17 @@ hipError_t launch_fwd_vectors(FwdArgs a, hipStream_t s)
         // against 52.6 with twice as many; D=4096: 92.3 against 95.2), the full 32 for rows of 8 (D=8192: 181 against 190)
         const int64_t cap = waves <= 4 ? 4096 / waves : 4096;
         const dim3 grid((unsigned)(N < cap ? N : cap)), block(64 * waves);
+        // bf16 rows of two waves: ahead where a workgroup has two to four.  us, without / with: D=2048 N=4096 8.9 / 7.8, N=8192
+        // 14.3 / 13.6, D=1536 N=8192 12.1 / 11.3, D=1280 11.7 / 11.0; but D=2048 N=32768 46.6 / 48.6, three waves (D=3072 N=8192)
+        // 20.3 / 21.0, four (D=4096 N=16384) 46.6 / 48.3, and fp32 D=2048 N=8192 24.1 / 25.3.
+        if constexpr (E == 8 && kWriteY && !kRagged) {
+            if (waves == 2 && N > cap && N <= 4 * cap) return launch(ln_fwd_kernel<T, 2, true, true, false, true>, grid, block, 0, s, a);
+        }
         switch (vpt) {
-            case 1: return launch(ln_fwd_kernel<T, 1, true, kWriteY, kRagged>, grid, block, 0, s, a);
-            case 2: return launch(ln_fwd_kernel<T, 2, true, kWriteY, kRagged>, grid, block, 0, s, a);
-            case 3: return launch(ln_fwd_kernel<T, 3, true, kWriteY, kRagged>, grid, block, 0, s, a);
-            case 4: return launch(ln_fwd_kernel<T, 4, true, kWriteY, kRagged>, grid, block, 0, s, a);
+            case 1: return launch(ln_fwd_kernel<T, 1, true, kWriteY, kRagged, false>, grid, block, 0, s, a);
+            case 2: return launch(ln_fwd_kernel<T, 2, true, kWriteY, kRagged, false>, grid, block, 0, s, a);
+            case 3: return launch(ln_fwd_kernel<T, 3, true, kWriteY, kRagged, false>, grid, block, 0, s, a);
+            case 4: return launch(ln_fwd_kernel<T, 4, true, kWriteY, kRagged, false>, grid, block, 0, s, a);
             default: return hipErrorInvalidValue;
         }
     }

@@ -87,6 +87,33 @@ __device__ __forceinline__ void load_gamma_vecs(const void *gamma, int gamma_is_
     }
 }
 
+// gamma and beta (null: zeros) likewise
+template <typename T, int kVpt>
+__device__ __forceinline__ void load_gamma_beta(const void *gamma, const void *beta, int is_f32, const int (&v)[kVpt],
+                                                float (&g)[kVpt][Vec<T>::kElems], float (&b)[kVpt][Vec<T>::kElems])
+{
+    const void *const second = beta ? beta : gamma;
+    if (is_f32) {
+#pragma unroll
+        for (int k = 0; k < kVpt; ++k) {
+            load_gamma_vec<T>(gamma, 1, v[k], g[k]);
+            load_gamma_vec<T>(second, 1, v[k], b[k]);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kVpt; ++k) {
+            load_gamma_vec<T>(gamma, 0, v[k], g[k]);
+            load_gamma_vec<T>(second, 0, v[k], b[k]);
+        }
+    }
+    if (!beta) {
+#pragma unroll
+        for (int k = 0; k < kVpt; ++k)
+#pragma unroll
+            for (int e = 0; e < Vec<T>::kElems; ++e) b[k][e] = 0.f;
+    }
+}
+
 // ... of a row of any width (r: the lane's last vector; `last`: v is that one), zeros behind the row's end.
 template <typename T>
 __device__ __forceinline__ void load_gamma_ragged(const void *gamma, int gamma_is_f32, int v, const Ragged &r, bool last,
@@ -687,9 +714,12 @@ struct FwdArgs {
 // kRagged: rows of any width of at least one vector, at any address (see Ragged).  us, generic kernel / this, bf16: 4000
 // rows of D=1001 11.6 / 5.8 (of 1000, aligned: 5.5), 32768 of 1028 114 / 37, of 1027 104 / 41, 8192 of 3001 59 / 23.
 // gamma and beta come by the vector too: element by element they took as long as the row (11.8 us).
-template <typename T, int kVpt, bool kMulti, bool kWriteY, bool kRagged>
+// kAhead: a row's loads go out before the row in front of it is reduced, and the first row's before gamma and beta.  Taken
+// where it measured faster (launch_fwd_vectors).
+template <typename T, int kVpt, bool kMulti, bool kWriteY, bool kRagged, bool kAhead>
 __global__ void ln_fwd_kernel(FwdArgs a)
 {
+    static_assert(!kAhead || (kWriteY && !kRagged));
     using V = Vec<T>;
     using Raw = typename V::Raw;
     constexpr int E = V::kElems;
@@ -706,8 +736,28 @@ __global__ void ln_fwd_kernel(FwdArgs a)
     }
     constexpr int KL = kVpt - 1;             // only a lane's last vector can be partial or padding
     const Ragged rg = kRagged ? Ragged::of<typename std::conditional<E == 8, uint16_t, float>::type>(vidx[KL], a.D) : Ragged{};
+    const Raw *xv = static_cast<const Raw *>(a.x);
+    Raw *yv = static_cast<Raw *>(a.y);
+    const int64_t first = kMulti ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * nwaves + wave;
+    const int64_t stride = kMulti ? (int64_t)gridDim.x : (int64_t)gridDim.x * nwaves;
+    Raw ahead[kVpt];
+    auto load_ahead = [&](int64_t r) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < kVpt; ++k) {
+            ahead[k] = V::zero();
+            if (ok[k]) ahead[k] = V::load_stream(xv + r * a.nvec + vidx[k]);
+        }
+    };
+    if constexpr (kAhead) {
+        if (first < a.N) load_ahead(first);
+    }
     float gm[kWriteY ? kVpt : 1][E], bt[kWriteY ? kVpt : 1][E];
-    if constexpr (kWriteY) {
+    if constexpr (kAhead) {
+        int v[kVpt];
+#pragma unroll
+        for (int k = 0; k < kVpt; ++k) v[k] = ok[k] ? vidx[k] : 0;
+        load_gamma_beta<T, kVpt>(a.gamma, a.beta, a.gamma_is_f32, v, gm, bt);
+    } else if constexpr (kWriteY) {
 #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             if constexpr (kRagged) {
@@ -729,17 +779,15 @@ __global__ void ln_fwd_kernel(FwdArgs a)
             }
         }
     }
-    const Raw *xv = static_cast<const Raw *>(a.x);
-    Raw *yv = static_cast<Raw *>(a.y);
-    const int64_t first = kMulti ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * nwaves + wave;
-    const int64_t stride = kMulti ? (int64_t)gridDim.x : (int64_t)gridDim.x * nwaves;
     for (int64_t r = first; r < a.N; r += stride) {
         float xf[kVpt][E];
         float s = 0.f;
 #pragma unroll
         for (int k = 0; k < kVpt; ++k) {
             Raw raw = V::zero();
-            if constexpr (kRagged) {
+            if constexpr (kAhead) {
+                raw = ahead[k];
+            } else if constexpr (kRagged) {
                 using P = const __attribute__((address_space(1))) typename element_aligned16<T>::type *;
                 const char *at = static_cast<const char *>(a.x) + r * a.D * (16 / E) + (k < KL ? vidx[k] * 16 : rg.offset);
                 u32x4_t t = (u32x4_t)__builtin_nontemporal_load((P)at);
@@ -750,6 +798,9 @@ __global__ void ln_fwd_kernel(FwdArgs a)
             V::unpack(raw, xf[k]);
 #pragma unroll
             for (int e = 0; e < E; ++e) s += xf[k][e];
+        }
+        if constexpr (kAhead) {
+            if (r + stride < a.N) load_ahead(r + stride);
         }
         s = wave_sum(s);
         if constexpr (kMulti) {
