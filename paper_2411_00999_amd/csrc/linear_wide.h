@@ -264,25 +264,29 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
         for (int st = 1; st < nst; ++st) stage(std::false_type{});
         // example boundary: the wave's part of the squared norm, and the tile into the total.  A tile at a time: all 384
         // accumulators are never in vector registers together (the empty statements say which file a value lives in:
-        // the example's among the accumulation registers, the total's not).
-        float ssq[C::kMI];
+        // the example's among the accumulation registers, the total's not).  The next fragments, read in the shadow of the
+        // MFMAs, have arrived by now; waited for all the same, since here is where they would be moved if registers ran short.
+        asm volatile("s_waitcnt lgkmcnt(0)" : WIDE_KEEP(f0) : : "memory");
+        // Columns beyond the matrix are zeros times x, no number where that is infinite: a lane's part of them is left out.
+        float ssq = 0.f;
 #pragma unroll
-        for (int mi = 0; mi < C::kMI; ++mi) {
-            ssq[mi] = 0.f;
+        for (int ni = 0; ni < C::kNI; ++ni) {
+            float column = 0.f;
 #pragma unroll
-            for (int ni = 0; ni < C::kNI; ++ni) {
+            for (int mi = 0; mi < C::kMI; ++mi) {
                 keep(acc[mi][ni]);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const float v = acc[mi][ni][i];
-                    ssq[mi] = fmaf(v, v, ssq[mi]);
+                    column = fmaf(v, v, column);
                     tot[mi][ni][i] += v;
                     asm volatile("" : "+v"(tot[mi][ni][i]));       // here, not after the branch below
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+            ssq += l0 + (wn * C::kNI + ni) * 32 + (lane & 31) < a.L ? column : 0.f;
         }
-        const float sum = wave_sum((ssq[0] + ssq[1]) + (ssq[2] + ssq[3]));
+        const float sum = wave_sum(ssq);
         if (lane == 0) a.tile_s[((int64_t)b * a.tiles + tile) * C::kWaves + wave] = sum;
     }
     // no load may reach LDS after the workgroup has left it, no read be under way when its registers are used again

@@ -74,3 +74,16 @@ def test_linear_larger_tile_keeps_infinities_to_their_example():
     _, s, _ = binding.linear_pegn(x, g)
     torch.cuda.synchronize()
     assert not bool(torch.isfinite(s[1])) and bool(torch.isfinite(s[[0, 2]]).all())
+
+
+@pytest.mark.parametrize("B,T,K,L", [(2, 1025, 2048, 2560), (2, 1025, 2048, 5120)])
+def test_linear_larger_tile_norm_of_an_infinite_gradient(B, T, K, L):
+    """An infinity in x meets the zeros behind the last tile's 64 columns: outputs that are not there, and not counted."""
+    import torch
+    from paper_2411_00999_amd import binding
+    x, g = _inputs(B, T, K, L)
+    x[1, 1, K - 1] = float("inf")
+    g[1, 1] = g[1, 1].abs() + 1e-4                                         # no zeros, whose product would be no number in truth
+    _, s, big_sq = binding.linear_pegn(x, g)
+    torch.cuda.synchronize()
+    assert bool(torch.isinf(s[1])) and bool(torch.isfinite(s[0])) and bool(torch.isinf(big_sq[0]))
