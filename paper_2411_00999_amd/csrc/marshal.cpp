@@ -157,17 +157,18 @@ ENTRY_POINTS(DEFINE)
 #undef DEFINE
 
 decltype(&::lnpegn_reduce_deferred) p_lnpegn_reduce_deferred;
-// (workspaces: a sequence of tensors, B, T, D, dtype, stream)
+// (workspaces: a collection of tensors, whose number it can tell, B, T, D, the type's number, stream)
 PyObject *py_reduce_deferred(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     if (!expect("reduce_deferred", n, 6)) return nullptr;
     if (!p_lnpegn_reduce_deferred) return PyErr_Format(PyExc_RuntimeError, "reduce_deferred: no library bound");
     return guarded([&]() -> PyObject * {
-        const Owned list(PySequence_Fast(args[0], "workspaces must be a sequence"));
-        std::vector<void *> at((size_t)PySequence_Fast_GET_SIZE(list.o));
-        for (size_t i = 0; i < at.size(); ++i) at[i] = address(PySequence_Fast_GET_ITEM(list.o, (Py_ssize_t)i));
+        if (PyObject_Size(args[0]) < 0) throw Raised{};
+        const Owned list(PySequence_Tuple(args[0]));               // (a tuple: no other thread changes its length)
+        std::vector<void *> at((size_t)PyTuple_GET_SIZE(list.o));
+        for (size_t i = 0; i < at.size(); ++i) at[i] = address(PyTuple_GET_ITEM(list.o, (Py_ssize_t)i));
         const int B = argument<int>(args[1]), T = argument<int>(args[2]), D = argument<int>(args[3]);
-        const lnpegn_dtype dt = element_type(args[4]);
+        const lnpegn_dtype dt = (lnpegn_dtype)argument<int>(args[4]);
         void *stream = stream_handle(args[5]);
         int rc;
         Py_BEGIN_ALLOW_THREADS

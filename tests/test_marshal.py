@@ -81,3 +81,13 @@ def test_a_subclass_is_asked_for_its_address(native):
             return 0                                                       # a null pointer: refused by the library
     x = torch.zeros(8).as_subclass(Sub)
     assert native.ln_fwd_stats(x, torch.zeros(8), torch.zeros(8), 1, 1, 8, binding.F32, 1e-5, _Stream()) == 1
+
+
+def test_deferred_reduction_refuses_what_has_no_length_and_types_that_are_no_number(native):
+    t = torch.zeros(8)
+    for call in (native.reduce_deferred, binding.reduce_deferred):
+        with pytest.raises(TypeError):
+            call((w for w in [t]), 0, 4, 8, binding.F32, _Stream())        # a generator
+        with pytest.raises(TypeError):
+            call([t], 0, 4, 8, t, _Stream())                               # a tensor of the type
+    assert native.reduce_deferred((t,), 0, 4, 8, binding.F32, _Stream()) == 1   # (no rows: refused by the library)
