@@ -98,12 +98,22 @@ def load() -> ctypes.CDLL:
                  "rms_fwd", "rms_bwd_ex", "gns_ema_update", "gns_offline", "gns_linear_accum_steps",
                  "linear_pegn", "embedding_pegn", "embedding_sort_ids", "embedding_pegn_presorted"):
         getattr(lib, name).restype = i
-    from . import _marshal
-    _marshal.bind(path)
+    marshal = _load_marshal(_build.marshal_path())
+    marshal.bind(path)
     global _native
-    _native = _marshal
+    _native = marshal
     _lib = lib
     return lib
+
+
+def _load_marshal(path):
+    """The extension from the file of this Python and this torch."""
+    from importlib import machinery, util
+    name = __package__ + "._marshal"
+    spec = util.spec_from_file_location(name, path, loader=machinery.ExtensionFileLoader(name, path))
+    module = util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
 
 
 def _load_native():

@@ -12,7 +12,6 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblnpegn.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")
 MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
 SOURCES = [os.path.join(CSRC, f) for f in ("lnpegn.hip", "lnpegn_rows_inst.hip", "linear_pegn.hip", "embedding_pegn.hip")]
 HEADERS = [os.path.join(CSRC, h) for h in ("lnpegn_device.h", "lnpegn_rows.h", "lnpegn_finalize.h", "lnpegn_tracker.h",
@@ -35,12 +34,23 @@ HIPCC_FLAGS = [
 ]
 
 
+def marshal_path() -> str:
+    """Where the extension for the Python and the torch that run this belongs.  It unpacks both's objects by their layout, so
+    both are part of its name: another interpreter or another torch over the same tree builds its own."""
+    import sysconfig
+
+    import torch
+    commit = (torch.version.git_version or "")[:8]
+    return os.path.join(HERE, f"_marshal.{sysconfig.get_config_var('SOABI')}.torch-{torch.__version__}.{commit}.so")
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
+    marshal = marshal_path()
+    if not os.path.exists(LIB) or not os.path.exists(marshal):
         return True
     t = os.path.getmtime(LIB)
     return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS) or \
-        any(os.path.getmtime(f) > os.path.getmtime(MARSHAL) for f in (MARSHAL_SOURCE, HEADERS[-1]))
+        any(os.path.getmtime(f) > os.path.getmtime(marshal) for f in (MARSHAL_SOURCE, HEADERS[-1]))
 
 
 def _marshal_command(out: str) -> list:
@@ -54,6 +64,18 @@ def _marshal_command(out: str) -> list:
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
             *("-I" + d for d in (*cpp_extension.include_paths(), sysconfig.get_paths()["include"])),
             MARSHAL_SOURCE, "-o", out, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + lib]
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """Compile the extension alone."""
+    path = marshal_path()
+    tmp = path + f".tmp{os.getpid()}"
+    cmd = _marshal_command(tmp)
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, path)
+    return path
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
@@ -73,15 +95,8 @@ def build(verbose: bool = False, extra_flags=()) -> str:
                 print(" ".join(cmd), flush=True)
             subprocess.run(cmd, check=True)
             return obj
-        def compile_marshal():
-            tmp = MARSHAL + f".tmp{os.getpid()}"
-            cmd = _marshal_command(tmp)
-            if verbose:
-                print(" ".join(cmd), flush=True)
-            subprocess.run(cmd, check=True)
-            os.replace(tmp, MARSHAL)
         with cf.ThreadPoolExecutor(max_workers=min(len(UNITS) + 1, os.cpu_count() or 4)) as ex:
-            marshal = ex.submit(compile_marshal)
+            marshal = ex.submit(build_marshal, verbose)
             objs = list(ex.map(compile_one, UNITS))
             marshal.result()
         tmp = LIB + f".tmp{os.getpid()}"
@@ -96,9 +111,11 @@ def build(verbose: bool = False, extra_flags=()) -> str:
 
 
 def ensure_built() -> str:
-    """Return the library path, building only if it or the extension does not exist yet."""
-    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
+    """Return the library path, building it and the extension only where they do not exist yet."""
+    if not os.path.exists(LIB):
         build()
+    elif not os.path.exists(marshal_path()):
+        build_marshal()
     return LIB
 
 

@@ -1,9 +1,12 @@
 """The extension that marshals arguments to the C ABI, without a device: what it refuses, and that addresses, numbers, types
 and the stream arrive (seen through the entry points' own validation, which launches nothing)."""
+import os
+
 import pytest
 import torch
 
 from paper_2411_00999_amd import binding
+from paper_2411_00999_amd import build as hip_build
 
 
 class _Stream:
@@ -91,3 +94,30 @@ def test_deferred_reduction_refuses_what_has_no_length_and_types_that_are_no_num
         with pytest.raises(TypeError):
             call([t], 0, 4, 8, t, _Stream())                               # a tensor of the type
     assert native.reduce_deferred((t,), 0, 4, 8, binding.F32, _Stream()) == 1   # (no rows: refused by the library)
+
+
+@pytest.mark.parametrize("what", ["torch", "python", "neither"])
+def test_extension_of_another_python_or_torch_is_not_loaded(native, what, monkeypatch):
+    """Beside the library that is there, the extension is built, alone, for the torch and the Python that run."""
+    import sysconfig
+    before, commands = hip_build.marshal_path(), []
+    assert os.path.samefile(native.__file__, before)
+
+    def run(cmd, check):
+        assert check
+        commands.append(cmd)
+        open(cmd[cmd.index("-o") + 1], "w").close()                         # (an empty file in the compiler's place)
+    monkeypatch.setattr(hip_build.subprocess, "run", run)
+    if what == "torch":
+        monkeypatch.setattr(torch, "__version__", "0.0.0+another")
+    if what == "python":
+        monkeypatch.setattr(sysconfig, "get_config_var", lambda name: "cpython-00-another")
+    path = hip_build.marshal_path()
+    try:
+        assert (path == before) == (what == "neither")
+        assert hip_build.ensure_built() == hip_build.LIB
+        assert [hip_build.MARSHAL_SOURCE in c for c in commands] == ([] if what == "neither" else [True])
+        assert os.path.exists(path)
+    finally:
+        if what != "neither":
+            os.unlink(path)
