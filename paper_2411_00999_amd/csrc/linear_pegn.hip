@@ -769,14 +769,20 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, LinKer
         const double pair_us = 0.599 * stages_of(WideCfg::kStageT) + 1.03;
         double us = 0.0;
         int splits = 1, per = B;
-        for (int n = 1; n <= B && (n == 1 || rest * n <= kMaxSlots); ++n) {
-            const int each = (B + n - 1) / n, m = (B + each - 1) / each;
+        // over every number of examples that a workgroup can be left with, by the fewest workgroups that leave it so (some
+        // 2 sqrt(B) of them, 3 rounds at most); none to split where the tiles are whole rounds
+        for (int each = B, m = 1;;) {
             const double t = 6.3 + (double)(full / kCUs) * (B * pair_us + 11.9) + rounds(rest * m, 0.61) * (each * pair_us + 11.9) +
                              (m > 1 ? 0.7 + 0.006 * rest * m : 0.0);
-            if (n > 1 && t >= us) continue;
-            us = t;
-            splits = m;
-            per = each;
+            if (m == 1 || t < us) {
+                us = t;
+                splits = m;
+                per = each;
+            }
+            if (rest == 0 || each == 1) break;
+            m = (B - 1) / (each - 1) + 1;
+            each = (B - 1) / m + 1;
+            if (rest * m > kMaxSlots) break;
         }
         if (us + 1.5 < 0.97 * narrow_us && per * stages_of(WideCfg::kStageT) >= 16) {
             p.wide = true;

@@ -133,3 +133,15 @@ def test_plan_follows_the_tuning_and_rejects_bad_arguments():
     assert lib.lnpegn_plan_query(1, 1, 1, binding.BF16, 1, 1, None, 16) == 1
     out[3] = -5
     assert lib.lnpegn_plan_query(4, 128, 256, binding.F32, 1, 1, out, 3) == 0 and out[3] == -5   # only n_out values
+
+
+@pytest.mark.parametrize("K,L", [(4096, 3072), (256, 192), (768, 3072)])
+def test_linear_planning_takes_no_longer_with_many_examples(K, L):
+    """Host time that each call and each query pays: it grew with B, to 6 ms at a million examples."""
+    import time
+    lib, best = binding.load(), 1.0
+    for _ in range(20):
+        t = time.perf_counter()
+        assert lib.linear_pegn_workspace_bytes(1000000, 64, K, L, binding.BF16) > 0
+        best = min(best, time.perf_counter() - t)
+    assert best < 2e-4
