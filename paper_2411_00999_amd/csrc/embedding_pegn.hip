@@ -1323,18 +1323,19 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     float *bigpart = reinterpret_cast<float *>(ws + p.off_bigpart);
     double *wpart = reinterpret_cast<double *>(ws + p.off_wpart);
     float *runsum = reinterpret_cast<float *>(ws + p.off_runsum);
-    // 1. the ids sorted, and beside the library's own sort the first rows of w' cleared: whole rows that end on a boundary
-    // of 16 bytes, or all of a w' that is no more than that.  Only where the fill is what kernel A waits for: a large w', or few
+    // 1. the ids sorted, and beside the library's own sort the first rows of w' cleared: whole rows that end on the boundary
+    // of a line, or all of a w' that is no more than that.  Only where the fill is what kernel A waits for: a large w', or few
     // rows of g.  (us a call, without / with: B=64 T=512 D=1024 V=32000 fp32, more bytes of g than of w', 78.1 / 78.5; B=16 T=1024
     // D=512 V=32000, 65 MB, 49.0 / 49.6; B=4 T=64 D=128 V=50257 fp32 26.7 / 24.9, B=4 T=256 D=768 43.3 / 40.2.)
     const int esz = dt == LNPEGN_BF16 ? 2 : 4;
     const int64_t row_bytes = (int64_t)D * 4;
+    // rows that are whole lines of 128 bytes, where 64 KB are enough for that
+    const int lines = 32 / (int)((D & -D) < 32 ? (D & -D) : 32), whole = lines * row_bytes <= 2 * kFillMost ? lines : 1;
     int cleared = 0;                                              // rows
     if (ids && p.own_sort && !accumulate && (reinterpret_cast<uintptr_t>(w) & 15u) == 0 && p.n * esz < (int64_t)V * 4 &&
         (V * row_bytes >= 3 * kShadowMost || p.n <= 4096)) {
         const int64_t rows = kShadowMost / row_bytes;
-        const int unit = 4 / (int)((D & -D) < 4 ? (D & -D) : 4);
-        cleared = rows < V ? (int)(rows / unit * unit) : V;
+        cleared = rows < V ? (int)(rows / lines * lines) : V;     // (nor less than 16 bytes)
     }
     const ShadowFill shadow{w, (int64_t)cleared * D, (int)(((int64_t)cleared * row_bytes + kShadowBytes - 1) / kShadowBytes)};
     if (ids && sort_ids(ids, ids_are_int64, p, V, ws, const_cast<uint32_t *>(keys), const_cast<uint32_t *>(vals), shadow, st) != hipSuccess)
@@ -1344,17 +1345,18 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     const bool vec = (reinterpret_cast<uintptr_t>(g) & 15u) == 0 && ((int64_t)D * esz) % 16 == 0 && D % 8 == 0;
     const int64_t chunks = (p.n + kChunk - 1) / kChunk;
     const int runs_x = (int)(chunks < g_emb_run_blocks ? chunks : g_emb_run_blocks), runs_y = (p.ncb + kWavesPerBlock - 1) / kWavesPerBlock;
-    // the rows filled beside kernel A; the rest beside kernel B
+    // The rows filled beside kernel A; the rest beside kernel B.  The shares meet on the boundary of a line: their waves take whole
+    // lines, counted from where a share begins.  (us, shares that meet at any row / this: V=50257 presorted fp32 D=1512 n=1024 80.2 /
+    // 74.0, sorted in the call bf16 D=1688 n=2115 91.9 / 79.8, D=1448 n=406 77.4 / 66.2.)
     const int64_t half = (V - cleared) / 2, late = half < kFillLateBytes / row_bytes ? half : kFillLateBytes / row_bytes;
-    const int fill_end = V - (int)late, fill_a = accumulate ? 0 : fill_end - cleared, fill_b = accumulate ? 0 : (int)late;
-    // Rows to a wave: 8 to 32 KB, so that there are many waves and the search for their ids is hidden, and whole lines of 128
-    // bytes (32 / gcd(D, 32) rows are) where 64 KB are enough for that.
-    const int whole = 32 / (int)((D & -D) < 32 ? (D & -D) : 32);
+    const int meet = (V - (int)late) / whole * whole, fill_end = meet > cleared ? meet : V - (int)late;
+    const int fill_a = accumulate ? 0 : fill_end - cleared, fill_b = accumulate ? 0 : V - fill_end;
+    // Rows to a wave: 8 to 32 KB, so that there are many waves and the search for their ids is hidden, and whole lines.
     auto rows_each = [&](int rows) {
         int64_t bytes = rows * row_bytes / kFillBlocks;
         bytes = bytes < kFillLeast ? kFillLeast : bytes > kFillMost ? kFillMost : bytes;
         int64_t each = bytes / row_bytes > 1 ? bytes / row_bytes : 1;
-        if (whole * row_bytes <= 2 * kFillMost) each = (each + whole - 1) / whole * whole;
+        each = (each + whole - 1) / whole * whole;
         return (int)(each < 64 ? each : 64);
     };
     auto blocks_for = [&](int rows, int each) {
