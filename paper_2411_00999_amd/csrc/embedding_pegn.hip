@@ -33,7 +33,7 @@ constexpr int kWavesPerBlock = 4;
 constexpr int kNormBlocks = 2048;   // workgroups of the ||w'||^2 pass in accumulate mode
 constexpr int kFillBlocks = 16384;  // most workgroups of the zero fill
 constexpr int64_t kFillLeast = 8 << 10, kFillMost = 32 << 10;   // bytes that a wave of it takes at a time
-constexpr int64_t kFillLateBytes = 128 << 20;   // most bytes of it that are left to kernel B
+constexpr int64_t kFillLateBytes = 40 << 20, kFillLateLarge = 128 << 20;   // most bytes of it that are left to kernel B
 
 __global__ __launch_bounds__(256) void emb_prepare_kernel(const void *ids, int ids_i64, uint32_t *keys,
                                                           uint32_t *vals, int64_t n, int V)
@@ -392,9 +392,8 @@ __device__ __forceinline__ uint32_t half_wave_first_not(uint32_t lo, uint32_t le
 // Zero fill of the rows of w' that no id selects (rows begin to end - 1), a part of kernel A's grid and of kernel B's:
 // the rows of ids that occur are written, whole, by the other workgroups, so everything touches different rows and
 // runs side by side.  Kernel A waits for its chains of loads more than for bandwidth and kernel B does little else, so
-// the fill is shared out between the two (half of it, at most 128 MiB, beside kernel B; presorted calls, us, with at most
-// 40 / 96 / 128 / 200 MiB there: B=8 T=1024 D=768 V=50257 37.8 / 35.0 / 35.2 / 34.9, B=16 T=2048 D=2048 118.2 / 112.5 / 110.7 /
-// 111.4, B=8 T=512 D=768 V=60000 fp32 41.2 / 37.9 / 38.2 / 37.8).  A wave takes `rows` neighbouring
+// the fill is shared out between the two: half of it, at most 40 MiB, or of a large w' 128 MiB, beside kernel B
+// (run_embedding).  A wave takes `rows` neighbouring
 // rows (at most 64) and finds their ids in the sorted list, so that no map of the ids is needed before the launch;
 // waves beside each other take rows beside each other, so that together they sweep one moving window of w'.  Absent rows
 // in a row are one stretch of memory: whole lines but at its ends, whatever the width.  (A row at a time, a lane's
@@ -1324,16 +1323,21 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     double *wpart = reinterpret_cast<double *>(ws + p.off_wpart);
     float *runsum = reinterpret_cast<float *>(ws + p.off_runsum);
     // 1. the ids sorted, and beside the library's own sort the first rows of w' cleared: whole rows that end on the boundary
-    // of a line, or all of a w' that is no more than that.  Only where the fill is what kernel A waits for: a large w', or few
-    // rows of g.  (us a call, without / with: B=64 T=512 D=1024 V=32000 fp32, more bytes of g than of w', 78.1 / 78.5; B=16 T=1024
-    // D=512 V=32000, 65 MB, 49.0 / 49.6; B=4 T=64 D=128 V=50257 fp32 26.7 / 24.9, B=4 T=256 D=768 43.3 / 40.2.)
+    // of a line, or all of a w' that is no more than that.
     const int esz = dt == LNPEGN_BF16 ? 2 : 4;
     const int64_t row_bytes = (int64_t)D * 4;
     // rows that are whole lines of 128 bytes, where 64 KB are enough for that
     const int lines = 32 / (int)((D & -D) < 32 ? (D & -D) : 32), whole = lines * row_bytes <= 2 * kFillMost ? lines : 1;
+    const int64_t w_mib = V * row_bytes >> 20;
+    // Only where there is more of it than the kernels behind the sort hide, or so few positions that they hide nothing.  us a call,
+    // without / with: fp32 V=50257 D=488 (94 MiB) n=4096 40.2 / 39.1, V=37197 D=840 (119) n=4096 46.3 / 44.1; bf16 V=50257 D=448 (86) n=8192
+    // 44.0 / 45.3, D=512 (98) n=1024 36.8 / 37.4, D=768 (147) n=8192 50.9 / 49.8, D=640 (123) n=4096 40.6 / 40.3 but n=32768 62.9 / 64.1; V=32000
+    // D=512 (62) n=256 31.9 / 29.3, n=1024 33.4 / 32.9, n=4096 36.4 / 36.9, V=8000 D=768 (23) n=256 27.8 / 26.0, n=4096 35.6 / 35.1, n=32768 59.5 / 59.5;
+    // rows that are no whole lines, V=32000 D=1693 n=1024 84.1 / 79.9, n=16384 126.1 / 126.5.
+    const bool much = w_mib >= (esz == 4 ? 90 : p.n > 16384 ? 144 : 108) && (lines <= 4 || p.n <= 4096);
+    const bool few = p.n <= (w_mib < 32 ? 4096 : w_mib < 64 ? 1024 : 256);
     int cleared = 0;                                              // rows
-    if (ids && p.own_sort && !accumulate && (reinterpret_cast<uintptr_t>(w) & 15u) == 0 && p.n * esz < (int64_t)V * 4 &&
-        (V * row_bytes >= 3 * kShadowMost || p.n <= 4096)) {
+    if (ids && p.own_sort && !accumulate && (reinterpret_cast<uintptr_t>(w) & 15u) == 0 && p.n * esz < (int64_t)V * 4 && (much || few)) {
         const int64_t rows = kShadowMost / row_bytes;
         cleared = rows < V ? (int)(rows / lines * lines) : V;     // (nor less than 16 bytes)
     }
@@ -1348,7 +1352,13 @@ static int run_embedding(const void *ids, int ids_are_int64, const uint32_t *sor
     // The rows filled beside kernel A; the rest beside kernel B.  The shares meet on the boundary of a line: their waves take whole
     // lines, counted from where a share begins.  (us, shares that meet at any row / this: V=50257 presorted fp32 D=1512 n=1024 80.2 /
     // 74.0, sorted in the call bf16 D=1688 n=2115 91.9 / 79.8, D=1448 n=406 77.4 / 66.2.)
-    const int64_t half = (V - cleared) / 2, late = half < kFillLateBytes / row_bytes ? half : kFillLateBytes / row_bytes;
+    // Most of it beside kernel B: 128 MiB, of a w' of which half is well above 40 MiB, the larger the fewer the positions.  us a
+    // presorted call, V=50257, 40 MiB at most / 128: bf16 D=512 (98 MiB) n=4096 39.1 / 39.5, fp32 D=552 (106) n=4096 42.7 / 41.8 but n=256
+    // 35.9 / 36.7, D=768 (147) n=256 42.5 / 42.3, n=8192 54.6 / 50.9, D=2048 n=256 93.3 / 91.6, n=32768 131.6 / 123.1; V=32000 fp32 D=1024 (125) n=256
+    // 39.3 / 40.0, n=1024 41.2 / 40.7.  Not of rows that are whole lines only by eight and more: bf16 D=1001 (192) n=1024 87.4 / 90.8,
+    // V=32000 D=1693 (207) n=16384 125.1 / 128.5.
+    const int64_t late_most = (lines <= 4 && w_mib >= (p.n < 1024 ? 144 : p.n < 4096 ? 112 : 96) ? kFillLateLarge : kFillLateBytes) / row_bytes;
+    const int64_t half = (V - cleared) / 2, late = half < late_most ? half : late_most;
     const int meet = (V - (int)late) / whole * whole, fill_end = meet > cleared ? meet : V - (int)late;
     const int fill_a = accumulate ? 0 : fill_end - cleared, fill_b = accumulate ? 0 : V - fill_end;
     // Rows to a wave: 8 to 32 KB, so that there are many waves and the search for their ids is hidden, and whole lines.
