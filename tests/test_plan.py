@@ -116,6 +116,15 @@ def test_plans_of_the_benchmark_workloads():
         assert got == want, (shape, got, want)
 
 
+@pytest.mark.parametrize("B,T,D,dt,per_example", [
+    (5, 9672, 768, binding.BF16, True), (4, 16000, 568, binding.BF16, True), (4, 16000, 1024, binding.BF16, True),
+    (7, 9111, 768, binding.F32, True), (3, 33333, 768, binding.BF16, False)])
+def test_workgroups_of_eight_row_groups_fill_the_chip(B, T, D, dt, per_example):
+    """Chunks of even length are no reason to leave a quarter of the CUs without one (195 and 200 workgroups of 256 before)."""
+    p = binding.plan_query(B, T, D, dt, per_example)
+    assert p["row_groups"] == 8 and p["chunks"] >= 230
+
+
 def test_plan_follows_the_tuning_and_rejects_bad_arguments():
     import ctypes
     lib = binding.load()
