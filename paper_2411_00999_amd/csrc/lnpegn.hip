@@ -125,6 +125,7 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
     p.R = 4;
     p.max_threads = 256;
     int waves_per_simd = 4;                          // resident waves per SIMD to aim for
+    const bool uneven = pegn && B < kCUs && 20 * (kCUs / B * B) < 17 * kCUs;    // one workgroup a CU does not come out even
     if (p.fast) {
         p.S = vpt_max > 16 / E ? 8 : ceil_div(p.nvec, 64 * vpt_max);   // beyond 16 elements per lane: always eight waves
         p.vpt = ceil_div(p.nvec, 64 * p.S);
@@ -148,7 +149,15 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
         // D=768 27.7 + 8.1 / 27.0 + 7.0, B=8 T=500 D=1001 9.6 + 11.5 / 8.3 + 8.5, B=48 T=256 D=768 14.6 + 8.1 / 14.0 + 6.9, B=100
         // T=24 15.5 / 12.3, fp32 B=16 T=2048 D=1024 68.7 + 15.6 / 68.7 + 11.5; T=24 B=8 11.0 / 11.4; plain B=8 T=1024 D=768
         // 9.8 + 6.2 / 9.1 + 4.6.  Many examples in long tensors, whose chunks come from rounds of workgroups, stay at four.
-        const bool eight = (!pegn || B <= 32 || N <= 16384) && (pegn ? T : N) >= 16;
+        // Nor do those whose examples don't divide the CUs, unless each is one chunk: two workgroups a CU then, which fp32 and ragged
+        // rows take no better than four smaller ones and bf16 rows only if the examples are long enough for as many.  As multiples of the
+        // time with four, deferred calls: fp32 D=1024 B=100 T=60 1.12, B=150 T=50 1.04, B=120 T=60 (even) 0.93, B=100 T=24 0.86; D=768 B=90
+        // T=60 1.10; bf16 D=1001 B=90 T=60 1.15, D=768 1.03, B=100 T=100 0.97.  And fp32 or ragged rows of 48 to 79 examples that
+        // are one chunk are too few: fp32 D=1024 B=64 T=27 1.21, D=768 1.08, bf16 D=1001 1.11.
+        const bool sturdy = E == 8 && !p.ragged;
+        const bool two = uneven && T >= 32 && !(sturdy && T / 16 >= 2 * kCUs / B);
+        const bool thin = pegn && !sturdy && T < 32 && B >= 48 && B < 80;
+        const bool eight = (!pegn || B <= 32 || N <= 16384) && (pegn ? T : N) >= 16 && !two && !thin;
         // (fp32 rows of four waves: two row groups, measured with the per-example sweeps, 288.7 -> 273.8 us)
         // (rows of two waves with lanes left over, D=1280, 1536 or 1600 in bf16, have fewer bytes in flight per
         // wave and take four row groups: D=1280 64.5 -> 52.0 us, D=1536 65.0 -> 55.3; rows of three waves take two:
@@ -205,8 +214,7 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
         p.Tp = T;
         // Eight row groups: where one workgroup per CU does not come out even, two (they fit side by side).  us a call, one / two:
         // bf16 D=768 B=130 T=126 28.0 / 25.8, B=100 T=160 25.8 / 25.4, B=90 T=180 27.1 / 25.2 (B=50 T=300, even, 22.0 / 23.2).
-        const bool uneven = p.R == 8 && B < kCUs && 20 * (kCUs / B * B) < 17 * kCUs;
-        int64_t c = g_chunks_pegn > 0 || !p.fast ? target / B : chunks_per_example(B, T, uneven ? 2 * target : target, p.R);
+        int64_t c = g_chunks_pegn > 0 || !p.fast ? target / B : chunks_per_example(B, T, p.R == 8 && uneven ? 2 * target : target, p.R);
         // Long launches over fp32 rows of 16 elements per lane: several rounds of shorter workgroups, which even
         // out the CUs' unequal progress (measured, us per launch, one round -> this: B=16 T=2048 D=2048
         // 138.3 -> 134.3, B=8 T=4096 D=2048 137.2 -> 134.2, B=16 T=4096 D=2048 280.9 -> 265.9, B=16 T=2048 D=1024

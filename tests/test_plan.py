@@ -125,6 +125,15 @@ def test_workgroups_of_eight_row_groups_fill_the_chip(B, T, D, dt, per_example):
     assert p["row_groups"] == 8 and p["chunks"] >= 230
 
 
+@pytest.mark.parametrize("B,T,D,dt,aligned,groups", [
+    (100, 60, 1024, binding.F32, True, 4), (120, 60, 1024, binding.F32, True, 8), (100, 24, 1024, binding.F32, True, 8),
+    (150, 50, 768, binding.F32, True, 4), (90, 60, 1001, binding.BF16, False, 4), (90, 60, 768, binding.BF16, True, 4),
+    (100, 100, 768, binding.BF16, True, 8), (64, 27, 896, binding.F32, True, 4), (64, 27, 896, binding.BF16, True, 8),
+    (40, 17, 1024, binding.F32, True, 8), (8, 1024, 768, binding.BF16, True, 8)])
+def test_eight_row_groups_only_where_they_come_out_even(B, T, D, dt, aligned, groups):
+    assert binding.plan_query(B, T, D, dt, aligned=aligned)["row_groups"] == groups
+
+
 def test_plan_follows_the_tuning_and_rejects_bad_arguments():
     import ctypes
     lib = binding.load()
