@@ -302,7 +302,15 @@ __device__ __forceinline__ void ln_bwd_rows_body(const RowArgs &a)
         int v[kVpt];
 #pragma unroll
         for (int k = 0; k < kVpt; ++k) v[k] = k < KL ? vidx[k] : v_last;
-        load_gamma_vecs<T, kVpt>(a.gamma, a.gamma_is_f32, v, gm);
+        // Rows of one wave: behind one branch (plain B=8 T=1024 D=768 bf16 13.8 -> 13.6 us).  Of several: behind a branch each,
+        // which rows of two waves with a second one that is mostly empty want (us, one branch / a branch each, bf16 deferred: B=14
+        // T=6099 D=1064 142.0 / 138.6, B=27 T=2238 D=1256 103.1 / 99.3, B=269 T=194 D=1152 171.0 / 166.4; full ones, D=2048, alike).
+        if constexpr (kSync) {
+#pragma unroll
+            for (int k = 0; k < kVpt; ++k) load_gamma_vec<T>(a.gamma, a.gamma_is_f32, v[k], gm[k]);
+        } else {
+            load_gamma_vecs<T, kVpt>(a.gamma, a.gamma_is_f32, v, gm);
+        }
         if (!ok_last) {
 #pragma unroll
             for (int e = 0; e < E; ++e) gm[KL][e] = 0.f;
