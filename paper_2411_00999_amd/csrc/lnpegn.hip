@@ -134,12 +134,13 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
         waves_per_simd = elems > 8 ? 2 : 4;          // measured: more waves of 16-element lanes only add contention
         // Narrow lanes, rows of one wave: half as many workgroups (512) where what the reduction saves is more than the
         // row kernel loses: in short tensors, and in longer ones if the fewer waves still keep as many bytes under way as the memory
-        // wants, with full lanes of one vector or nearly full ones of two.  Multiples of the time with 1024, forward and backward of B=16, N=B*T of
-        // 8000 / 12000 / 24000 / 64000: bf16 D=64 0.95 / 0.97 / 1.06 / 1.11, D=256 0.93 / 0.93 / 1.09 / 1.20, D=448 0.93 / 0.96 / 1.06 / 1.09,
-        // D=512 0.91 / 0.94 / 1.02 / 1.05 (T=2048 0.92), fp32 D=200 0.95 / 0.99 / 1.11 / 1.12, D=256 0.93 / 0.95 / 1.06 / 1.07, D=416
-        // 0.92 / 0.93 / 1.01 / 0.94, D=512 0.91 / 0.91 / 0.98 / 0.97; deferred, B=8: bf16 D=448 0.91 / 0.93 / 1.05 / 1.12, D=512 0.90 / 0.92 / 0.96 / 0.98,
-        // fp32 D=256 0.93 / 0.93 / 0.97 / 0.99; plain, B=100: bf16 D=512 0.91 / 0.94 / 0.97 / 1.00, fp32 D=512 0.89 / 0.90 / 0.97 / 0.99.
-        if (p.S == 1 && elems <= 8 && (!pegn || B <= 32) && N >= 8192 && (N <= 12288 || (p.nvec >= 64 && p.nvec > 48 * p.vpt)))
+        // wants, with lanes of one vector that are (nearly) all full or lanes of two.  Times with 1024 as multiples of those with 512,
+        // N = B*T of 8000 / 12000 / 24000 / 64000, forward and backward, B=16: bf16 D=64 1.06 / 1.03 / 0.94 / 0.90, D=256 1.08 / 1.07 /
+        // 0.91 / 0.83, fp32 D=200 1.05 / 1.01 / 0.90 / 0.90, D=416 1.09 / 1.08 / 0.99 / 1.06, D=512 1.10 / 1.10 / 1.02 / 1.03.  Means of 420 calls of
+        // random B and T, all three forms, N to 20000 / 28000 / 40000 / 64000 / beyond: 49 to 56 vectors 1.05 / 1.01 / 0.99 / 0.98 / 0.97, 57 to 63
+        // 1.03 / 1.03 / 1.02 / 1.01 / 1.01, 64 1.06 / 1.06 / 1.03 / 1.02 / 1.01.
+        if (p.S == 1 && elems <= 8 && (!pegn || B <= 32) && N >= 8192 &&
+            (N <= 12288 || (p.nvec > 48 * p.vpt && (p.nvec >= 57 || N <= 24576))))
             waves_per_simd = 2;
         // launch bound of the instantiation that will run: 256 threads for S = 1, 2, 4; 512 else
         const int max_waves = (elems <= 8 && (p.ragged ? p.S == 1 : p.S <= 2)) ? 4 : 8;
