@@ -343,6 +343,16 @@ int lnpegn_set_tuning(int key, int value);
 int lnpegn_plan_query(int B, int T, int D, lnpegn_dtype dt, int per_example, int aligned, int64_t *out, int n_out);
 
 /*
+ * Testing aid like lnpegn_plan_query, host only: how linear_pegn runs a shape in the workspace that
+ * linear_pegn_workspace_bytes asks for, with x and g on 16-byte boundaries (aligned = 1) or on an element's (0).
+ *    0 scalar kernel (0), matrix-core kernel (1), that with the larger tile (2)       1 output tiles
+ *    2 tiles that a workgroup finishes by itself, whatever 3 (larger tile only)      3 workgroups that share the
+ *      examples of each other tile           4 examples of one of them               5 workspace bytes of this plan
+ */
+#define LINEAR_PEGN_PLAN_FIELDS 6
+int linear_pegn_plan_query(int B, int T, int K, int L, lnpegn_dtype dt, int aligned, int64_t *out, int n_out);
+
+/*
  * Benchmarking aid, one-shot.  The next ln_bwd or ln_bwd_pegn call attaches the two hipEvent_t
  * to the dispatch of its row-streaming kernel (start of execution, end of execution), so that
  * hipEventElapsedTime(start, stop) is that kernel's own duration; then it forgets both.  The

@@ -23,7 +23,7 @@ EXPORTS = ("lnpegn_workspace_bytes", "lnpegn_status_string", "lnpegn_last_hip_er
            "lnpegn_set_profile_events", "lnpegn_stream_probe", "ln_bwd_deferred", "ln_bwd_pegn_deferred", "lnpegn_reduce_deferred",
            "ln_fwd", "ln_bwd_ex", "rms_fwd", "rms_bwd_ex",
            "gns_ema_update", "gns_offline", "gns_linear_accum_steps",
-           "linear_pegn_workspace_bytes", "linear_pegn", "embedding_pegn_workspace_bytes", "embedding_pegn",
+           "linear_pegn_workspace_bytes", "linear_pegn_plan_query", "linear_pegn", "embedding_pegn_workspace_bytes", "embedding_pegn",
            "embedding_sort_ids", "embedding_pegn_presorted")
 PER_EXAMPLE, DEFER, ACCUMULATE = 1, 2, 4
 
@@ -89,10 +89,11 @@ def load() -> ctypes.CDLL:
     lib.gns_estimate.argtypes = [fp, fp, i, i, f, fp, vp]
     lib.lnpegn_set_tuning.argtypes = [i, i]
     lib.lnpegn_plan_query.argtypes = [i, i, i, i, i, i, ctypes.POINTER(ctypes.c_int64), i]
+    lib.linear_pegn_plan_query.argtypes = [i, i, i, i, i, i, ctypes.POINTER(ctypes.c_int64), i]
     lib.lnpegn_set_profile_events.argtypes = [vp, vp]
     lib.lnpegn_stream_probe.argtypes = [vp, vp, vp, sz, i, vp]
     for name in ("ln_fwd_stats", "ln_bwd", "ln_bwd_pegn", "ln_bwd_pegn_static", "gns_estimate", "lnpegn_set_tuning",
-                 "lnpegn_plan_query",
+                 "lnpegn_plan_query", "linear_pegn_plan_query",
                  "lnpegn_set_profile_events", "lnpegn_stream_probe", "ln_bwd_deferred",
                  "ln_bwd_pegn_deferred", "lnpegn_reduce_deferred", "ln_fwd", "ln_bwd_ex",
                  "rms_fwd", "rms_bwd_ex", "gns_ema_update", "gns_offline", "gns_linear_accum_steps",
@@ -297,6 +298,20 @@ def plan_query(B: int, T: int, D: int, dt: int, per_example: bool = True, aligne
     if rc:
         raise LnpegnError("lnpegn_plan_query", rc)
     return dict(zip(PLAN_FIELDS, (int(v) for v in out)))
+
+
+LINEAR_PLAN_FIELDS = ("kernel", "tiles", "whole_tiles", "splits", "examples_per_split", "workspace_bytes")
+LINEAR_KERNELS = ("scalar", "matrix", "matrix_larger_tile")
+
+
+def linear_plan_query(B: int, T: int, K: int, L: int, dt: int, aligned: bool = True) -> dict:
+    """The kernel that linear_pegn takes for a shape and how it shares out the work (host only, no device needed)."""
+    out = (ctypes.c_int64 * len(LINEAR_PLAN_FIELDS))()
+    rc = load().linear_pegn_plan_query(B, T, K, L, dt, 1 if aligned else 0, out, len(LINEAR_PLAN_FIELDS))
+    if rc:
+        raise LnpegnError("linear_pegn_plan_query", rc)
+    plan = dict(zip(LINEAR_PLAN_FIELDS, (int(v) for v in out)))
+    return {**plan, "kernel": LINEAR_KERNELS[plan["kernel"]]}
 
 
 def set_profile_events(start_event, stop_event) -> None:

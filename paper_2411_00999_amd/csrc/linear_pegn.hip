@@ -735,7 +735,7 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, LinKer
         const double position_us = ((tiles16 < 2 ? 0.065 : tiles16 < 16 ? 0.087 : 0.105) + 4e-6 * ((double)K + L) * (bf16 ? 2 : 4)) *
                                    (tiles16 > 2048 ? (double)tiles16 / 2048 : 1.0);
         const double scalar_us = 5.0 + B * (0.42 + 0.0002 * (double)tiles16 + position_us * T);
-        if (ragged && (which == kLinFaster || which == kLinNarrow) && scalar_us < mfma_us) p.mfma = false;
+        if (ragged && which == kLinFaster && scalar_us < mfma_us) p.mfma = false;
     }
     if (!p.mfma) {
         p.tiles_k = (K + 15) / 16;
@@ -826,6 +826,17 @@ size_t linear_pegn_workspace_bytes(int B, int T, int K, int L, lnpegn_dtype dt)
             if (n > most) most = n;
         }
     return most;
+}
+
+int linear_pegn_plan_query(int B, int T, int K, int L, lnpegn_dtype dt, int aligned, int64_t *out, int n_out)
+{
+    if (!lin_shape_ok(B, T, K, L) || !out || n_out < 0) return LNPEGN_EINVAL;
+    if (dt != LNPEGN_F32 && dt != LNPEGN_BF16) return LNPEGN_EUNSUPPORTED;
+    const LinPlan p = make_lin_plan(B, T, K, L, dt, LinAlign{aligned != 0, aligned != 0, true});
+    const int64_t v[LINEAR_PEGN_PLAN_FIELDS] = {p.wide ? 2 : p.mfma ? 1 : 0, (int64_t)p.tiles_k * p.tiles_l, p.full, p.nsplit, p.b_per_split,
+                                                (int64_t)p.bytes};
+    for (int i = 0; i < n_out && i < LINEAR_PEGN_PLAN_FIELDS; ++i) out[i] = v[i];
+    return LNPEGN_OK;
 }
 
 int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq, int B, int T, int K, int L,

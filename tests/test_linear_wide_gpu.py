@@ -1,6 +1,7 @@
 """The linear layer's larger tile at the shapes where it can go wrong: one column of tiles and edges in both directions, examples
-whose last stage is short, whole rounds of tiles beside split ones, one and many splits, accumulation, an infinity that must
-stay in its example, less workspace than it asks for (the smaller tile's).
+whose last stage is short, of one stage and of two, whole rounds of tiles alone and beside split and unsplit ones, one and many
+splits, accumulation, an infinity that must stay in its example, less workspace than it asks for (the smaller tile's).  That the
+larger tile runs, and with which shares, is asserted by the plan.
 
 Reference: the products in fp64 on the device.  Every product is exact in fp32, so an output of n additions is off by at most
 n 2^-24 of the sum of its terms' magnitudes; the norms, sums of squares of such outputs, are held to 1e-5 like those of the
@@ -37,12 +38,25 @@ def _check(x, g, got, w0=None):
     torch.testing.assert_close(got[2].double(), w.square().sum().reshape(1), rtol=1e-5, atol=0)
 
 
-@pytest.mark.parametrize("B,T,K,L", [
-    (2, 1000, 8, 8), (2, 2048, 264, 200), (3, 1025, 768, 584), (4, 601, 1032, 3000), (5, 515, 2056, 2600), (2, 640, 4104, 4000),
-    (3, 545, 4096, 3080), (13, 700, 64, 1000), (1, 3000, 512, 1536)])
-def test_linear_larger_tile(B, T, K, L):
+def _shares(B, T, K, L):
+    """Tiles that a workgroup finishes whatever the splits, other tiles, splits of those."""
+    from paper_2411_00999_amd import binding
+    plan = binding.linear_plan_query(B, T, K, L, binding.BF16)
+    assert plan["kernel"] == "matrix_larger_tile", plan
+    return plan["whole_tiles"], plan["tiles"] - plan["whole_tiles"], plan["splits"]
+
+
+@pytest.mark.parametrize("B,T,K,L,shares", [
+    (2, 1000, 8, 8, (0, 1, 2)), (2, 2048, 264, 200, (0, 4, 2)), (3, 1025, 768, 584, (0, 12, 3)), (4, 601, 1032, 3000, (0, 80, 2)),
+    (5, 515, 2056, 2600, (0, 126, 2)), (2, 640, 4104, 4000, (256, 101, 2)), (3, 545, 4096, 3080, (256, 16, 3)),
+    (13, 700, 64, 1000, (0, 6, 13)), (1, 3000, 1496, 8000, (0, 252, 1)),
+    (6, 100, 5224, 6232, (512, 181, 1)), (8, 33, 4904, 1632, (0, 180, 1)), (40, 64, 776, 3000, (0, 64, 4)),
+    (16, 16, 3072, 4032, (0, 252, 1)), (24, 1, 1936, 6048, (256, 0, 1)), (12, 64, 1928, 6000, (256, 0, 1)),
+    (16, 33, 2048, 6144, (256, 0, 1))])
+def test_linear_larger_tile(B, T, K, L, shares):
     import torch
     from paper_2411_00999_amd import binding
+    assert _shares(B, T, K, L) == shares
     x, g = _inputs(B, T, K, L)
     got = binding.linear_pegn(x, g)
     _check(x, g, got)
@@ -56,6 +70,7 @@ def test_linear_larger_tile(B, T, K, L):
 def test_linear_larger_tile_in_less_workspace(B, T, K, L):
     import torch
     from paper_2411_00999_amd import binding
+    assert _shares(B, T, K, L)[2] == 2
     x, g = _inputs(B, T, K, L)
     need = binding.load().linear_pegn_workspace_bytes(B, T, K, L, binding.BF16)
     for nbytes in (need, need - 1, need // 2, need // 4):
@@ -69,6 +84,7 @@ def test_linear_larger_tile_in_less_workspace(B, T, K, L):
 def test_linear_larger_tile_keeps_infinities_to_their_example():
     import torch
     from paper_2411_00999_amd import binding
+    assert _shares(3, 1025, 768, 584) == (0, 12, 3)
     x, g = _inputs(3, 1025, 768, 584)
     g[1, 1024, 583] = float("inf")                                         # the last row and column of an example
     _, s, _ = binding.linear_pegn(x, g)
@@ -81,6 +97,7 @@ def test_linear_larger_tile_norm_of_an_infinite_gradient(B, T, K, L):
     """An infinity in x meets the zeros behind the last tile's 64 columns: outputs that are not there, and not counted."""
     import torch
     from paper_2411_00999_amd import binding
+    _shares(B, T, K, L)
     x, g = _inputs(B, T, K, L)
     x[1, 1, K - 1] = float("inf")
     g[1, 1] = g[1, 1].abs() + 1e-4                                         # no zeros, whose product would be no number in truth

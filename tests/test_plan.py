@@ -173,3 +173,20 @@ def test_linear_planning_takes_no_longer_with_many_examples(K, L):
         assert lib.linear_pegn_workspace_bytes(1000000, 64, K, L, binding.BF16) > 0
         best = min(best, time.perf_counter() - t)
     assert best < 2e-4
+
+
+def test_linear_plan_query_and_what_it_rejects():
+    import ctypes
+    lib, q = binding.load(), binding.linear_plan_query
+    assert q(16, 2048, 2048, 8192, binding.BF16)["kernel"] == "matrix_larger_tile"
+    assert q(8, 1024, 768, 2304, binding.BF16)["kernel"] == q(8, 1024, 768, 50257, binding.BF16)["kernel"] == "matrix"
+    assert q(16, 2048, 2048, 8192, binding.F32)["kernel"] == q(16, 2048, 2048, 8192, binding.BF16, aligned=False)["kernel"] == "matrix"
+    assert q(1, 8, 257, 300, binding.BF16)["kernel"] == "scalar"
+    for shape in ((16, 2048, 2048, 8192), (6, 100, 5224, 6232), (8, 1024, 768, 50257)):
+        need = lib.linear_pegn_workspace_bytes(*shape, binding.BF16)
+        assert max(q(*shape, binding.BF16, aligned)["workspace_bytes"] for aligned in (False, True)) <= need
+    out = (ctypes.c_int64 * 6)(*[-5] * 6)
+    assert lib.linear_pegn_plan_query(0, 1, 1, 1, binding.BF16, 1, out, 6) == 1
+    assert lib.linear_pegn_plan_query(1, 1, 1, 1, 7, 1, out, 6) == 2
+    assert lib.linear_pegn_plan_query(1, 1, 1, 1, binding.BF16, 1, None, 6) == 1
+    assert lib.linear_pegn_plan_query(2, 1000, 8, 8, binding.BF16, 1, out, 2) == 0 and list(out) == [2, 1, -5, -5, -5, -5]
