@@ -876,7 +876,7 @@ int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq,
         a.tiles_k = p.tiles_k; a.tiles = p.tiles_k * p.tiles_l;
         a.full = p.full; a.splits = p.nsplit; a.per = p.b_per_split;
         a.accumulate = accumulate;
-        if (launch(linear_wide_kernel, dim3(p.full + (a.tiles - p.full) * p.nsplit), dim3(64 * WideCfg::kWaves), 0, st, a) != hipSuccess) return LNPEGN_EHIP;
+        if (launch(accumulate ? linear_wide_kernel<true> : linear_wide_kernel<false>, dim3(p.full + (a.tiles - p.full) * p.nsplit), dim3(64 * WideCfg::kWaves), 0, st, a) != hipSuccess) return LNPEGN_EHIP;
         if (p.nsplit > 1 && launch(linear_wide_sum_kernel, dim3(a.tiles - p.full, WideCfg::kBlocks), dim3(256), 0, st, a) != hipSuccess) return LNPEGN_EHIP;
     } else if (p.mfma) {
         LinArgs a{};

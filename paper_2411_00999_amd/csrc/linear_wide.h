@@ -56,6 +56,9 @@ struct WideFrags {
     wide_u32x2_t a[4][2], b[3][2];
 };
 
+// kAdd: the tiles that a workgroup finishes are added to w (the others by linear_wide_sum_kernel).  A kernel of its own: beside
+// the other form its addresses took registers there (B=1 T=1822 K=640 L=2624, not added to, 38.7 -> 42.6 us).
+template <bool kAdd>
 __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
 {
     using C = WideCfg;
@@ -295,28 +298,46 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
     // ---- write the total
     if (direct) {
         double bsq = 0.0;
-        auto write = [&](auto all_tag) {
-            constexpr bool kAll = decltype(all_tag)::value;    // all outputs lie in the matrix, and nothing is added to
+        // (K and L are multiples of 8: the eight rows that a wave holds in four registers are in the matrix or are not.  With a branch
+        // for every output the edges were 5400 instructions that a wave runs once: B=1 T=1822 K=640 L=2624 38.7 us, so 34.4.)
+        // What is added to is loaded some blocks of 32 x 32 ahead (a load beside each addition, which every store then
+        // waits for: that shape 89 us, so 36.5; B=4 T=97 K=7360 L=11520 730, so 221).
+        constexpr int kTiles = C::kMI * C::kNI, kAhead = 4;
+        auto row = [&](int t, int i) { return (wm * C::kMI + t / C::kNI) * 32 + (i >> 2) * 8 + (i & 3); };
+        auto column = [&](int t) { return (wn * C::kNI + t % C::kNI) * 32; };
+        float *const at_lane = a.w + ((int64_t)(k0 + (lane >> 5) * 4) * a.L + l0 + (lane & 31));
+        auto each = [&](int t, auto body) __attribute__((always_inline)) {
+            if (l0 + column(t) + (lane & 31) < a.L) {
 #pragma unroll
-            for (int mi = 0; mi < C::kMI; ++mi)
+                for (int q = 0; q < 16; q += 4)
+                    if (k0 + row(t, q) < a.K) {
 #pragma unroll
-                for (int ni = 0; ni < C::kNI; ++ni) {
-                    const int l = l0 + (wn * C::kNI + ni) * 32 + (lane & 31);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int k = k0 + (wm * C::kMI + mi) * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-                        if (kAll || (k < a.K && l < a.L)) {
-                            float *p = a.w + (int64_t)k * a.L + l;
-                            float v = tot[mi][ni][i];
-                            if (!kAll && a.accumulate) v += *p;
-                            *p = v;
-                            bsq += (double)v * (double)v;
-                        }
+                        for (int i = q; i < q + 4; ++i) body(i, at_lane + ((int64_t)row(t, i) * a.L + column(t)));
                     }
-                }
+            }
         };
-        if (k0 + C::kTileK <= a.K && l0 + C::kTileL <= a.L && !a.accumulate) write(std::true_type{});
-        else write(std::false_type{});
+        float old[kAhead][16];
+        auto fetch_old = [&](int t) __attribute__((always_inline)) {  // (without branches; from inside the matrix where the block is not)
+            if constexpr (kAdd) {
+                const float *const from = a.w + ((int64_t)((lane >> 5) * 4) * a.L + min(l0 + column(t) + (lane & 31), a.L - 1));
+#pragma unroll
+                for (int i = 0; i < 16; ++i) old[t % kAhead][i] = from[(int64_t)(min(k0 + row(t, i & 12), a.K - 8) + (i & 3)) * a.L];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+#pragma unroll
+        for (int t = 0; t < kAhead - 1; ++t) fetch_old(t);
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) {
+            if (t + kAhead - 1 < kTiles) fetch_old(t + kAhead - 1);
+            each(t, [&](int i, float *p) {
+                float v = tot[t / C::kNI][t % C::kNI][i];
+                if constexpr (kAdd) v += old[t % kAhead][i];
+                *p = v;
+                bsq += (double)v * (double)v;
+            });
+            if constexpr (kAdd) __builtin_amdgcn_sched_barrier(0);
+        }
         bsq = wave_sum_f64(bsq);
         if (tile < a.full) {
             if (lane == 0) a.tile_big[tile * C::kWaves + wave] = bsq;

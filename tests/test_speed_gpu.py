@@ -79,7 +79,7 @@ def test_embedding_of_rows_that_end_inside_a_line():
     assert inside < 1.15 * whole, (inside, whole)
 
 
-def _linear_us(B, T, K, L, dtype):
+def _linear_us(B, T, K, L, dtype, accumulate=False):
     import torch
     from paper_2411_00999_amd import binding
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
@@ -87,7 +87,9 @@ def _linear_us(B, T, K, L, dtype):
     nbytes = max(256, binding.load().linear_pegn_workspace_bytes(B, T, K, L, binding.BF16 if dtype == "bf16" else binding.F32))
     out = dict(w=torch.empty(K, L, device="cuda"), s=torch.empty(B, device="cuda"), big_sq=torch.empty(1, device="cuda"),
                workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
-    return _us(lambda: binding.linear_pegn(x, g, **out), calls=10)
+    if accumulate:
+        out["w"].zero_()
+    return _us(lambda: binding.linear_pegn(x, g, accumulate=accumulate, **out), calls=10)
 
 
 @pytest.mark.parametrize("B,T,K,L,dtype,times", [
@@ -132,3 +134,10 @@ def test_deferred_reduction_of_many_short_examples():
     workgroup sent for every example in vain: 1.7 times)."""
     many, few = _deferred_us(512, 64, 1024, "bf16")[0], _deferred_us(64, 512, 1024, "bf16")[0]
     assert many < 1.45 * few, (many, few)
+
+
+@pytest.mark.parametrize("B,T,K,L", [(1, 1822, 640, 2624), (4, 97, 7360, 11520), (9, 160, 5632, 11136), (1, 2006, 1848, 408)])
+def test_linear_accumulated_by_the_larger_tile(B, T, K, L):
+    """Adding to w costs the reading of it: 1.0 to 1.4 times the call (load by load, each waited for: 2.3 to 4.7 times)."""
+    added, written = _linear_us(B, T, K, L, "bf16", accumulate=True), _linear_us(B, T, K, L, "bf16")
+    assert added < 1.7 * written, (added, written)
