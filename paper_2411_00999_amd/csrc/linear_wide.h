@@ -345,13 +345,16 @@ __global__ __launch_bounds__(256, 1) void linear_wide_kernel(WideArgs a)
             a.tile_big[a.full * C::kWaves + (tile - a.full) * C::kBlocks + wave * (C::kMI * C::kNI) + lane] = lane == 0 ? bsq : 0.0;
         }
     } else {
+        // (the blocks of 32 x 32 that reach into the matrix: of K=8 L=1920 an eighth of 192 KiB)
         float *slot = a.part + (int64_t)at * C::kPart + wave * (C::kPart / C::kWaves) + lane;
 #pragma unroll
         for (int mi = 0; mi < C::kMI; ++mi)
 #pragma unroll
             for (int ni = 0; ni < C::kNI; ++ni)
+                if (k0 + (wm * C::kMI + mi) * 32 < a.K && l0 + (wn * C::kNI + ni) * 32 < a.L) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) slot[((mi * C::kNI + ni) * 16 + i) * 64] = tot[mi][ni][i];
+                    for (int i = 0; i < 16; ++i) slot[((mi * C::kNI + ni) * 16 + i) * 64] = tot[mi][ni][i];
+                }
     }
 #undef WIDE_READ
 #undef WIDE_READ_AND_LOAD
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(256) void linear_wide_sum_kernel(WideArgs a)
     float *p = a.w + (int64_t)k * a.L + l;
     f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
     if (a.accumulate && inside) sum = __builtin_bit_cast(f32x4_t, (u32x4_t)*(Out)p);
-    for (int j = 0; j < a.splits; j += 4) {
+    for (int j = 0; inside && j < a.splits; j += 4) {              // (blocks outside are not in the slots)
         f32x4_t u[4];
 #pragma unroll
         for (int n = 0; n < 4; ++n) u[n] = *reinterpret_cast<const f32x4_t *>(slot + min(j + n, a.splits - 1) * next);

@@ -104,3 +104,14 @@ def test_linear_larger_tile_norm_of_an_infinite_gradient(B, T, K, L):
     _, s, big_sq = binding.linear_pegn(x, g)
     torch.cuda.synchronize()
     assert bool(torch.isinf(s[1])) and bool(torch.isfinite(s[0])) and bool(torch.isinf(big_sq[0]))
+
+
+@pytest.mark.parametrize("B,T,K,L", [(5, 515, 72, 2600), (3, 1025, 768, 584), (13, 700, 64, 1000), (3, 545, 4096, 3080)])
+def test_linear_larger_tile_reads_no_sums_that_it_has_not_written(B, T, K, L):
+    """The parts of a tile behind the matrix are not in the splits' sums; the workspace holds no numbers before the call."""
+    import torch
+    from paper_2411_00999_amd import binding
+    assert _shares(B, T, K, L)[2] > 1
+    x, g = _inputs(B, T, K, L)
+    ws = torch.full((binding.load().linear_pegn_workspace_bytes(B, T, K, L, binding.BF16),), 255, dtype=torch.uint8, device="cuda")
+    _check(x, g, binding.linear_pegn(x, g, workspace=ws))
