@@ -597,7 +597,8 @@ __global__ __launch_bounds__(256) void linear_pegn_generic_kernel(const T *x, co
 
 // w = (accumulate ? w : 0) + sum over splits, in split order; per-block parts of ||w||^2.  Four columns per thread, the loads of
 // eight splits in flight (at any float: the rows of a split begin where they fall).  B=8 T=1024 K=768 L=2304, four splits:
-// 10.9 us a column per thread, 7.0 so (call 55.8 -> 50.1; B=64 L=3072 369 -> 358).
+// 10.9 us a column per thread, 7.0 so (call 55.8 -> 50.1; B=64 L=3072 369 -> 358).  Workgroups of 256 threads, or of one wave (`threads`,
+// make_lin_plan).
 constexpr int kSumEach = 4, kSumThreads = 256;
 __global__ __launch_bounds__(kSumThreads) void linear_sum_splits_kernel(const float *part, float *w, double *blk_big,
                                                                         int64_t n, int nsplit, int accumulate)
@@ -605,7 +606,7 @@ __global__ __launch_bounds__(kSumThreads) void linear_sum_splits_kernel(const fl
     __shared__ double dslots[kSumThreads / 64];
     using In = const __attribute__((address_space(1))) u32x4_at4_t *;
     using Out = __attribute__((address_space(1))) u32x4_at4_t *;
-    const int64_t i = ((int64_t)blockIdx.x * kSumThreads + threadIdx.x) * kSumEach;
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * kSumEach;
     double bsq = 0.0;
     auto add = [&](auto load, auto store, auto &v) {
         v = accumulate ? load(w + i) : v;
@@ -664,6 +665,7 @@ struct LinPlan {
     int full;              // tiles of it that one workgroup finishes, whatever nsplit (of the others)
     int tiles_k, tiles_l, nsplit, b_per_split;
     int nparts;            // rows of the s parts
+    int sum_threads;       // of a workgroup that adds the smaller tile's splits
     int64_t nbig;          // entries of the ||w'||^2 parts
     size_t off_s, off_big, off_part, bytes;
 };
@@ -724,7 +726,16 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, LinKer
             p.nsplit = splits;
         }
         p.nparts = ntiles * Cfg::kWaves;
-        p.nbig = p.nsplit == 1 ? (int64_t)ntiles * Cfg::kWaves : ((int64_t)K * L + kSumThreads * kSumEach - 1) / (kSumThreads * kSumEach);
+        // The splits are added by workgroups of one wave where those of 256 threads would be at most half as many as CUs.  us a
+        // call, 256 threads / 64: B=10 T=268 K=64 L=2048 21.0 / 18.3, B=182 T=95 K=56 L=216 26.4 / 24.1; but, 143 workgroups of 256, B=11 T=81
+        // K=2296 L=64 17.8 / 18.8, B=8 T=1024 K=768 L=2304 45.5 / 46.5, B=22 T=46 K=256 L=9216 32.1 / 34.0.  And where L is 128 or 2048, up to
+        // 2^20 outputs: the product itself, the same code, then takes longer behind sums by larger workgroups (B=91 T=2 K=7808 L=128 34 / 40
+        // of the call's 42.3 / 51.3; the sums and parts of a tile then meet in the caches of other XCDs): B=30 T=100 K=2688 L=128 27.1 /
+        // 25.7, B=17 T=162 K=128 L=2048 24.6 / 21.1, B=3 T=146 K=512 L=2048 21.0 / 17.3; but K=768 L=2048 B=8 T=1024 44.0 / 45.2, and no
+        // such difference at L of 512, 1024, 3072, 4096, 6144, 8192 (0.95 to 1.03).
+        const int64_t outputs = (int64_t)K * L;
+        p.sum_threads = outputs <= (int64_t)kCUs / 2 * kSumThreads * kSumEach || ((L == 128 || L == 2048) && outputs <= 1 << 20) ? 64 : kSumThreads;
+        p.nbig = p.nsplit == 1 ? (int64_t)ntiles * Cfg::kWaves : (outputs + p.sum_threads * kSumEach - 1) / (p.sum_threads * kSumEach);
         // A few short ragged examples cost the matrix-core kernel its start and the scalar one little: the latter runs its
         // outputs side by side, an example and a position after the other.  us, matrix cores / scalar: bf16 B=1 T=8
         // K=257 L=300 14.3 / 6.5, T=100 16.0 / 15.8, T=300 20.5 / 36; B=3 T=8 K=1000 L=499 23 / 11; B=16 T=1 K=129 L=65 20 / 13,
@@ -893,7 +904,7 @@ int linear_pegn(const void *x, const void *g, float *w, float *s, float *big_sq,
         if (e != hipSuccess) return LNPEGN_EHIP;
         if (p.nsplit > 1) {
             const int64_t n = (int64_t)K * L;
-            if (launch(linear_sum_splits_kernel, dim3((unsigned)p.nbig), dim3(kSumThreads), 0, st, part_w, w, part_big, n, p.nsplit, accumulate) != hipSuccess) return LNPEGN_EHIP;
+            if (launch(linear_sum_splits_kernel, dim3((unsigned)p.nbig), dim3(p.sum_threads), 0, st, part_w, w, part_big, n, p.nsplit, accumulate) != hipSuccess) return LNPEGN_EHIP;
         }
     } else {
         const dim3 grid(p.tiles_l, p.tiles_k);
