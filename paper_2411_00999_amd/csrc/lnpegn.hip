@@ -138,9 +138,10 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
         // N = B*T of 8000 / 12000 / 24000 / 64000, forward and backward, B=16: bf16 D=64 1.06 / 1.03 / 0.94 / 0.90, D=256 1.08 / 1.07 /
         // 0.91 / 0.83, fp32 D=200 1.05 / 1.01 / 0.90 / 0.90, D=416 1.09 / 1.08 / 0.99 / 1.06, D=512 1.10 / 1.10 / 1.02 / 1.03.  Means of 420 calls of
         // random B and T, all three forms, N to 20000 / 28000 / 40000 / 64000 / beyond: 49 to 56 vectors 1.05 / 1.01 / 0.99 / 0.98 / 0.97, 57 to 63
-        // 1.03 / 1.03 / 1.02 / 1.01 / 1.01, 64 1.06 / 1.06 / 1.03 / 1.02 / 1.01.
+        // 1.03 / 1.03 / 1.02 / 1.01 / 1.01, 64 1.06 / 1.06 / 1.03 / 1.02 / 1.01.  fp32 rows of 49 to 56, whose lanes do half the work for their
+        // bytes, only to 16384 rows: medians of 431 random calls of up to 32 examples, N to 16384 / 20000 / 24576, 1.02 / 0.97 / 0.94.
         if (p.S == 1 && elems <= 8 && (!pegn || B <= 32) && N >= 8192 &&
-            (N <= 12288 || (p.nvec > 48 * p.vpt && (p.nvec >= 57 || N <= 24576))))
+            (N <= 12288 || (p.nvec > 48 * p.vpt && (p.nvec >= 57 || N <= (E == 8 ? 24576 : 16384)))))
             waves_per_simd = 2;
         // launch bound of the instantiation that will run: 256 threads for S = 1, 2, 4; 512 else
         const int max_waves = (elems <= 8 && (p.ragged ? p.S == 1 : p.S <= 2)) ? 4 : 8;
