@@ -267,6 +267,10 @@ int gns_linear_accum_steps(int64_t tokens_seen, int64_t ramp_tokens, int accum_f
  * (bf16) or 4 (fp32).  Otherwise a few short examples, operands of less than 16 bytes, pointers that split an element,
  * workspaces of a scalar kernel's size, and (aligned or not) K or L beyond some 2^24 are left to that kernel.
  * workspace: linear_pegn_workspace_bytes(...) bytes, 256-byte aligned, caller-owned, contents scratch.  K*L <= 2^31.
+ * It is some KB, and where workgroups share the examples of an output tile also the sums of each: at most 4*K*L bytes a split, or,
+ * for aligned bf16, where the larger tile is the faster one, up to 768 times 192 KiB (B=16 T=2048 K=2048 L=8192: 138.5 MB).  Aligned
+ * bf16 runs in less too, down to what the smaller tile asks for (there 0.3 MB), by that tile: more slowly (1.1 to 1.2
+ * times the time there), and its sums, taken in another order, may differ in their last bits.
  * Enqueued on stream, never synchronises; status codes as above.
  */
 size_t linear_pegn_workspace_bytes(int B, int T, int K, int L, lnpegn_dtype dt);

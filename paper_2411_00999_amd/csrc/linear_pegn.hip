@@ -759,8 +759,10 @@ LinPlan make_lin_plan(int B, int T, int K, int L, int dt, LinAlign align, LinKer
     size_t slots = p.nsplit > 1 ? (size_t)p.nsplit * K * L * sizeof(float) : 0;
     // The larger tile of bf16: whole rounds of 256 workgroups finish a tile each; the examples of the other tiles are split over
     // workgroups.  Taken where it is the faster one by these estimates: the constants are those that fit 180 measured calls of
-    // the smaller tile and 141 of this one (T 64 to 4096, K and L 64 to 8192), within 10 % nine times in ten.  us, smaller / larger
-    // tile: B=16 T=2048 K=2048 L=8192 1047 / 933, L=2048 283 / 283, K=1280 L=5120 466 / 547; B=8 T=1024 K=768 L=50304 667 / 558,
+    // the smaller tile and 141 of this one (T 64 to 4096, K and L 64 to 8192), within 10 % nine times in ten.  They fit calls, not
+    // kernels: of the 704 splits' sums of B=16 T=2048 K=2048 L=8192, 24.8 us by themselves, the price of a split bears 4.9 and the rounds
+    // the rest (call 916 by the estimate, 890 to 910 measured; over 107 drawn calls of 400 to 768 sums 0.97 of it, of none 0.93).  us, smaller /
+    // larger tile: B=16 T=2048 K=2048 L=8192 1047 / 933, L=2048 283 / 283, K=1280 L=5120 466 / 547; B=8 T=1024 K=768 L=50304 667 / 558,
     // L=3072 58.5 / 54.9, L=2304 46.7 / 51.0, K=4096 L=4096 267 / 258; B=64 T=1024 K=768 L=3072 351 / 281; B=32 T=512 K=1536 L=6144
     // 468 / 316; B=3 T=1000 K=1600 L=6400 112 / 71; B=9 T=4096 K=64 L=3840 155 / 82; B=16 T=512 K=1024 L=8192 143 / 159; B=64 T=128
     // K=1024 L=4096 98 / 119.

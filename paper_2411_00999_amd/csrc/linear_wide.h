@@ -3,13 +3,13 @@
 //
 // The kernel with the smaller tile (256 x 128, eight waves of 64 x 64) is bound by LDS: a stage of 64 positions is read by
 // its waves at 108 bytes a clock and written by its direct loads at 64, together the 1980 clocks that a stage takes, for 1024
-// clocks of MFMAs; and by the lines that it fetches.  A wave tile of 128 x 96 reads 27 % less for the same products, and a
+// clocks of MFMAs; and by the lines that it fetches.  A wave tile of 128 x 96 reads 42 % less for the same products, and a
 // tile of 256 x 192 fetches 22 % less; 192 accumulators for the example and 192 for the running total leave room for no more,
 // at four waves with 512 registers each.  One wave to a SIMD has nobody to hide behind, so all that is not an MFMA goes out in
 // their shadow, placed by hand: the next fragments' reads, the next loads and the scalar work for those (all of it
 // between the blocks of MFMAs: B=16 T=2048 K=2048 L=8192 996 us, in their shadow 918).  A stage is 32 positions, 28 KiB, five deep; one
 // barrier a stage.
-// Measured, smaller / larger tile: that shape 1057 / 896 us (1228 TFLOP/s; the library's plain GEMM 1060), B=8 T=1024
+// Measured, smaller / larger tile: that shape 1057 / 896 us (1228 TFLOP/s in a process of its own, 1130 late in a long one; the library's plain GEMM 1060), B=8 T=1024
 // K=768 L=50304 684 / 548, B=64 T=1024 K=768 L=3072 357 / 272.
 // What bounds it: the first shape takes 1.42-1.51 M clocks (smaller tile 1.98-2.11 M), 1.06 M of them MFMAs, at 1.4-1.7 GHz (1.5-1.9): the part
 // limits its power while the matrix cores toggle.

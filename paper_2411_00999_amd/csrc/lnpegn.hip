@@ -97,7 +97,8 @@ int64_t chunks_per_example(int64_t B, int64_t T, int64_t W, int R)
                              : rest == 0 || full >= 3 || (full == 1 && 10 * rest >= 3 * W);
     if (fits) return c0;
     const int64_t c3 = (3 * W + B - 1) / B;         // three rounds
-    return (c3 <= 16 && T / c3 >= (R > 4 ? 4 * R : 16)) ? c3 : c0;    // ... unless that leaves a chunk fewer than 16 rows
+    return (c3 <= 16 && T / c3 >= (R > 4 ? 4 * R : 16)) ? c3 : c0;    // ... unless that leaves a chunk fewer than 16 rows, or four for
+                                                                      // each of more than four row groups
 }
 
 // What the pointers of a call allow: nothing but element accesses, vectors at element addresses, aligned vectors.
