@@ -146,6 +146,7 @@ def test_linear_accumulated_by_the_larger_tile(B, T, K, L):
 
 @pytest.mark.parametrize("B,T,K,L", [(15, 513, 7296, 8), (8, 503, 7488, 64), (3, 695, 16, 3776), (90, 153, 2368, 8)])
 def test_linear_of_narrow_matrices_in_the_larger_tile(B, T, K, L):
-    """Against the smaller tile, which runs in one byte less of workspace (with whole tiles in the splits' sums: 1.1 to 1.2 times)."""
+    """Against the smaller tile, which runs in one byte less of workspace (0.81 to 0.99 times; with whole tiles in the splits' sums
+    1.16 to 1.23)."""
     larger, smaller = _linear_us(B, T, K, L, "bf16"), _linear_us(B, T, K, L, "bf16", less=1)
-    assert larger < 1.03 * smaller, (larger, smaller)
+    assert larger < 1.08 * smaller, (larger, smaller)
