@@ -137,12 +137,13 @@ Plan make_plan(int B, int T, int D, lnpegn_dtype dt, bool pegn, Access access)
         // row kernel loses: in short tensors, and in longer ones if the fewer waves still keep as many bytes under way as the memory
         // wants, with lanes of one vector that are (nearly) all full or lanes of two.  Times with 1024 as multiples of those with 512,
         // N = B*T of 8000 / 12000 / 24000 / 64000, forward and backward, B=16: bf16 D=64 1.06 / 1.03 / 0.94 / 0.90, D=256 1.08 / 1.07 /
-        // 0.91 / 0.83, fp32 D=200 1.05 / 1.01 / 0.90 / 0.90, D=416 1.09 / 1.08 / 0.99 / 1.06, D=512 1.10 / 1.10 / 1.02 / 1.03.  Means of 420 calls of
-        // random B and T, all three forms, N to 20000 / 28000 / 40000 / 64000 / beyond: 49 to 56 vectors 1.05 / 1.01 / 0.99 / 0.98 / 0.97, 57 to 63
-        // 1.03 / 1.03 / 1.02 / 1.01 / 1.01, 64 1.06 / 1.06 / 1.03 / 1.02 / 1.01.  fp32 rows of 49 to 56, whose lanes do half the work for their
-        // bytes, only to 16384 rows: medians of 431 random calls of up to 32 examples, N to 16384 / 20000 / 24576, 1.02 / 0.97 / 0.94.
-        if (p.S == 1 && elems <= 8 && (!pegn || B <= 32) && N >= 8192 &&
-            (N <= 12288 || (p.nvec > 48 * p.vpt && (p.nvec >= 57 || N <= (E == 8 ? 24576 : 16384)))))
+        // 0.91 / 0.83, fp32 D=200 1.05 / 1.01 / 0.90 / 0.90, D=416 1.09 / 1.08 / 0.99 / 1.06, D=512 1.10 / 1.10 / 1.02 / 1.03.  Of one vector
+        // a lane the fewer the rows the less full the lanes, and fp32, whose lanes do half the work for their bytes, less than bf16.  Medians of
+        // 2250 calls of random B up to 32 and T, backward with norms, N to 20000 / 24576 / 32768 / 40000 / 64000 / beyond: bf16 57 to 63
+        // vectors 1.05 / 1.05 / 1.03 / 1.01 / 0.98 / 0.98, fp32 0.99 / 0.99 / 0.98 / 0.98 / 0.97 / 0.95, 49 to 56 0.97 / 0.94 (to 16384 1.02);
+        // 64 vectors, means, 1.06 / 1.06 / 1.03 / 1.03 / 1.02 / 1.01 (bf16 63 beyond 40000 1.06), and bf16 49 to 56 1.05 to 20000, 1.01 to 28000, 0.99 to 40000.
+        const int64_t longest = p.nvec >= (E == 8 ? 63 : 64) ? N : E == 4 ? 16384 : p.nvec >= 57 ? 40960 : 24576;
+        if (p.S == 1 && elems <= 8 && (!pegn || B <= 32) && N >= 8192 && (N <= 12288 || (p.nvec > 48 * p.vpt && N <= longest)))
             waves_per_simd = 2;
         // launch bound of the instantiation that will run: 256 threads for S = 1, 2, 4; 512 else
         const int max_waves = (elems <= 8 && (p.ragged ? p.S == 1 : p.S <= 2)) ? 4 : 8;

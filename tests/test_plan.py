@@ -135,7 +135,7 @@ def test_eight_row_groups_only_where_they_come_out_even(B, T, D, dt, aligned, gr
 
 
 @pytest.mark.parametrize("B,T,D,dt,per_example,chunks", [
-    (429, 204, 200, binding.F32, False, 1024), (16, 2000, 448, binding.BF16, True, 1024), (16, 1500, 448, binding.BF16, True, 512), (16, 4096, 456, binding.BF16, True, 512), (16, 4096, 408, binding.BF16, True, 1024),
+    (429, 204, 200, binding.F32, False, 1024), (16, 2000, 448, binding.BF16, True, 1024), (16, 1500, 448, binding.BF16, True, 512), (16, 2500, 456, binding.BF16, True, 512), (16, 4096, 456, binding.BF16, True, 1024), (16, 4096, 504, binding.BF16, False, 512), (16, 1500, 232, binding.F32, True, 1024), (16, 4096, 408, binding.BF16, True, 1024),
     (16, 768, 448, binding.BF16, True, 512), (16, 2048, 512, binding.BF16, True, 512), (16, 2048, 512, binding.F32, True, 512),
     (64, 256, 448, binding.BF16, True, 1024), (100, 1000, 512, binding.F32, False, 512),
     (10, 1500, 208, binding.F32, True, 512), (11, 2231, 208, binding.F32, True, 1024), (8, 2300, 224, binding.F32, False, 1024)])
